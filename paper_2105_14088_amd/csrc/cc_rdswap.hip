@@ -6,22 +6,15 @@
 // round costs its largest link.  Swapping ranks p and q touches, per round, only the links of p and of q
 // (one link, with unchanged value, when q = p xor 2^k).  The new round cost is therefore
 //     max( link of p re-evaluated, link of q re-evaluated, largest link among all the others ),
-// and "largest among the others" is one of the round's three largest links, found once per sweep.
+// and "largest among the others" is one of the round's three largest links.
 //
 // General kernel: one workgroup per restart, one thread per rank p scanning q = p+1 .. N-1; matrix
 // gathered through L2; 64-bit keys (value << 32 | move id) min-reduced over the workgroup.
-// N = 64 kernel: one wavefront per restart, matrix in LDS (both directed entries of a pair folded into one value),
-// lane p scans partners q = p xor x; two rank differences x with the same top bit share a step (lanes with that bit
-// clear take one, the others the other), so every pair is scored once, in 32 steps.  The node at rank p xor y is
-// fetched once per sweep for all 64 y (ds_swizzle) and the step loop is fully unrolled, so the partner and the round
-// mates of both ends are register selects; the top-3 links of a round come from wave-wide max-reductions over
-// (value << 5 | link index), three rounds at a time.
+// Pruned kernel: one workgroup per restart, any power of two; scores only the swaps that can win.
 #include <type_traits>
-#include <utility>
 
 #include "cc_device.h"
 #include "cc_internal.h"
-#include "cc_wave64.h"
 
 namespace cc {
 using namespace ccd;
@@ -34,10 +27,7 @@ constexpr unsigned long long kNoMove = ~0ull;
 
 // ------------------------------------------------------------------------------------- general kernel
 __global__ void rdswap_general_kernel(const int32_t* __restrict__ c, int N, int32_t* __restrict__ tours,
-                                      int64_t* __restrict__ costs, int32_t* __restrict__ moves,
-                                      const int32_t* __restrict__ skip_if_small) {
-    // when the 16-bit workgroup kernel is launched beside this one, flags[0] = max(c) decides which of the two runs
-    if (skip_if_small && skip_if_small[0] < (1 << 16)) return;
+                                      int64_t* __restrict__ costs, int32_t* __restrict__ moves) {
     extern __shared__ int32_t sm[];
     int32_t* t = sm;                 // [N]
     int32_t* w = sm + N;             // [N] directed cost of each rank in the round being prepared
@@ -147,179 +137,6 @@ __global__ void rdswap_general_kernel(const int32_t* __restrict__ c, int N, int3
     }
 }
 
-// ----------------------------------------------------------------------------------------- N = 64
-using namespace w64;
-
-// lane p <- lane p xor Y for Y < 32 (ds_swizzle in bit mode: no LDS access, no address arithmetic)
-template <int Y>
-__device__ __forceinline__ int from_lane_xor(int v) {
-    if constexpr (Y == 0) return v;
-    else return __builtin_amdgcn_ds_swizzle(v, (Y << 10) | 0x1f);
-}
-// out[y] = the value lane p xor y holds, for every y: own (lower 32 differences) and far (the value of lane p xor 32)
-template <int... Y>
-__device__ __forceinline__ void from_every_lane(int (&out)[kN], int own, int far, std::integer_sequence<int, Y...>) {
-    ((out[Y] = from_lane_xor<(Y & 31)>((Y & 32) ? far : own)), ...);
-}
-
-// Keeps "cond ? a[i] : a[j]" a select between two registers: without it the compiler selects the index instead and
-// the array leaves the register file.
-__device__ __forceinline__ int in_register(int v) {
-    asm("" : "+v"(v));
-    return v;
-}
-
-// One descent.  m: the folded matrix in LDS.  WIDE: totals that need more than 19 bits (entries from 2^16 up), keys
-// of 64 bits.
-template <bool WIDE>
-__device__ __forceinline__ void descend_swaps(const int32_t* m, int lane, int& t, int& cost, int& applied_out) {
-    using K = typename std::conditional<WIDE, unsigned long long, int>::type;
-    const char* mbytes = (const char*)m;
-    auto entry = [&](int byte_offset) { return *(const int32_t*)(mbytes + byte_offset); };   // row << 8 | col << 2
-    const int pair_base = lane * (kN + 1);       // id of the pair {lane, lane xor x}: pair_base ^ x or ^ (x << 6)
-    int applied = 0, cur = 0;
-    for (;;) {
-        // node at rank p xor y, as a column byte offset, for every y: the partners q = p xor x of this sweep and the
-        // round mates of both ends all come from here, by register index
-        const int t2 = t << 2, t8 = t << 8;
-        int tl[kN];
-        from_every_lane(tl, t2, __shfl_xor(t2, 32, kWave), std::make_integer_sequence<int, kN>{});
-        // per round: the best / second-best link value among links other than this lane's, and where the best one is
-        int x1v[6], x2v[6], zk[6], zk_second[6], round_cost[6];
-        int li[6], key[6], k1[6], k2[6], k3[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const int bit = 1 << k;
-            li[k] = ((lane >> (k + 1)) << k) | (lane & (bit - 1));                 // link index, 5 bits
-            key[k] = (entry(t8 | tl[bit]) << 5) | li[k];
-            k1[k] = key[k];
-        }
-        // the three largest links of every round: the rounds are independent, so their reductions run three at a time
-        wave_max3(k1[0], k1[1], k1[2]);
-        wave_max3(k1[3], k1[4], k1[5]);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) k2[k] = (li[k] == (k1[k] & 31)) ? -1 : key[k];
-        wave_max3(k2[0], k2[1], k2[2]);
-        wave_max3(k2[3], k2[4], k2[5]);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) k3[k] = (li[k] == (k1[k] & 31) || li[k] == (k2[k] & 31)) ? -1 : key[k];
-        wave_max3(k3[0], k3[1], k3[2]);
-        wave_max3(k3[3], k3[4], k3[5]);
-        cur = 0;
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const int l1 = k1[k] & 31, l2 = k2[k] & 31;
-            const int a1 = (li[k] == l1) ? k2[k] : k1[k];                          // best link that is not mine
-            const int a2 = (li[k] == l1 || li[k] == l2) ? k3[k] : k2[k];           // second best that is not mine
-            x1v[k] = a1 >> 5;
-            x2v[k] = a2 >> 5;
-            zk[k] = li[k] ^ (a1 & 31);                             // partner's link == that best link  <=>  li(x) == zk
-            zk_second[k] = zk[k] ^ (k ? 1 : 0);                    // the same test for the odd difference of a step
-            round_cost[k] = k1[k] >> 5;
-            cur += round_cost[k];
-        }
-        // Partners by rank difference x = p xor q.  Every pair would be seen from both of its ends; instead two
-        // differences with the same top bit h, x0 = 2j and x1 = 2j + 1, share a step: the lanes whose rank has bit h
-        // clear take x0, the others x1, so the 64 lanes score 64 distinct pairs.  x = 1 has no mate: its step scores
-        // each of its 32 pairs twice (same value, same id).  The loop is unrolled, so every index below is a constant.
-        K best = WIDE ? (K)~0ull : (K)0x7fffffff;
-#pragma unroll
-        for (int j = 0; j < kN / 2; ++j) {
-            const int x0 = j ? 2 * j : 1, x1 = j ? 2 * j + 1 : 1;
-            const int h = 31 - __builtin_clz(x0);
-            const bool second = (lane >> h) & 1;
-            const int tq_second = in_register(tl[x1]);
-            const int tq2 = second ? tq_second : tl[x0];
-            int total = 0;
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                const int bit = 1 << k;
-                if (x0 == bit && x1 == bit) {                      // x = 1 in round 0: every lane swaps with its mate
-                    total += round_cost[k];
-                    continue;
-                }
-                const int qb_second = in_register(tl[x1 ^ bit]);
-                const int qb2 = second ? qb_second : tl[x0 ^ bit];                 // node at rank q xor 2^k
-                const int link_p = entry((tq2 << 6) | tl[bit]);    // rank p now holds t[q]
-                const int link_q = entry(t8 | qb2);                // rank q now holds t[p]
-                // the partner's link index relative to this lane's: x without bit k; x1's differs from x0's in bit 0
-                const int lim0 = ((x0 >> (k + 1)) << k) | (x0 & (bit - 1));
-                const int z = (second && x1 != x0) ? zk_second[k] : zk[k];
-                const int others = (z == lim0) ? x2v[k] : x1v[k];
-                int stage = max(others, max(link_p, link_q));
-                if (x0 == bit) stage = second ? stage : round_cost[k];             // x0 swaps the two ends of a link
-                total += stage;
-            }
-            const int id = pair_base ^ (second ? (x1 << 6) : x0);                  // lower rank * 64 + higher rank
-            const K key = WIDE ? (K)(((unsigned long long)(unsigned)total << 12) | (unsigned)id) : (K)((total << 12) | id);
-            best = key < best ? key : best;
-            // steps are scheduled four at a time: enough gathers in flight, and the live ranges stay within the
-            // register file
-            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-        int total_win, id;
-        if constexpr (WIDE) {
-            const unsigned long long win = wave_min_u64(best);
-            total_win = (int)(win >> 12);
-            id = __builtin_amdgcn_readfirstlane((int)(win & 0xfff));
-        } else {
-            const int win = wave_min(best);
-            total_win = win >> 12;
-            id = win & 0xfff;
-        }
-        if (total_win >= cur) break;
-        const int sp = id >> 6, sq = id & 63;
-        const int a = __builtin_amdgcn_readlane(t, sp), b = __builtin_amdgcn_readlane(t, sq);
-        t = lane == sp ? b : (lane == sq ? a : t);
-        ++applied;
-    }
-    cost = cur;
-    applied_out = applied;
-}
-
-__global__ __launch_bounds__(256) void rdswap_n64_kernel(const int32_t* __restrict__ c, int restarts, uint64_t seed,
-                                                         int generate, int32_t* __restrict__ tours,
-                                                         int64_t* __restrict__ costs, int32_t* __restrict__ moves) {
-    __shared__ __attribute__((aligned(256))) int32_t m[kN * kN];
-    __shared__ int wave_max_entry[4];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    int v[kN * kN / 256];
-#pragma unroll
-    for (int k = 0; k < kN * kN / 256; ++k) v[k] = c[tid + 256 * k];
-    const int64_t r = (int64_t)blockIdx.x * 4 + wv;
-    int t = 0;
-    if (r < restarts)
-        t = generate ? init_tour_in_wave(seed, (uint32_t)r, lane) : clampi(tours[r * kN + lane], 0, kN - 1);
-    int mx = 0;
-#pragma unroll
-    for (int k = 0; k < kN * kN / 256; ++k) {
-        v[k] = clampi(v[k], 0, kCostMax);
-        mx = max(mx, v[k]);
-        m[tid + 256 * k] = v[k];
-    }
-    mx = wave_max(mx);
-    if (lane == 0) wave_max_entry[wv] = mx;
-    __syncthreads();
-    mx = max(max(wave_max_entry[0], wave_max_entry[1]), max(wave_max_entry[2], wave_max_entry[3]));
-    // a link costs the larger of its two directed entries: fold the two into both places once, so that a link is one
-    // gather
-    for_each_pair_64(tid, [&](int lo, int hi) {
-        const int both = max(m[lo * kN + hi], m[hi * kN + lo]);
-        m[lo * kN + hi] = both;
-        m[hi * kN + lo] = both;
-    });
-    __syncthreads();
-    if (r >= restarts) return;
-    int cur, applied;
-    if (mx >= (1 << 16)) descend_swaps<true>(m, lane, t, cur, applied);
-    else descend_swaps<false>(m, lane, t, cur, applied);
-    tours[r * kN + lane] = t;
-    if (lane == 0) {
-        costs[r] = (int64_t)cur;
-        moves[r] = applied;
-    }
-}
-
 // 16-bit matrix with both directed entries of a pair folded into both places, max(c[x][y], c[y][x]): a link is then
 // one gather.  For the sizes whose matrix does not fit LDS; skipped when an entry needs more than 16 bits.
 __global__ __launch_bounds__(256) void fold_to_u16_kernel(const int32_t* __restrict__ c, int n,
@@ -332,410 +149,391 @@ __global__ __launch_bounds__(256) void fold_to_u16_kernel(const int32_t* __restr
     }
 }
 
-// ------------------------------------------------------------------------- N = 128 .. 1024: one workgroup per restart
-// The N = 64 scheme with one thread per rank (SPLIT threads per rank, sharing the rank's steps, where the matrix is
-// in LDS and a restart has a compute unit to itself: one wavefront per SIMD cannot overlap its gathers with its own
-// arithmetic): the order in LDS, the three largest links of a round from workgroup-wide max-reductions, two rank
-// differences per step so that N threads score N distinct pairs.  The matrix is read as folded 16-bit entries:
-// staged and folded in LDS for N = 128, 256 (32 / 128 KiB), gathered through L2 from the folded copy in the
-// workspace for N = 512, 1024 (IN_LDS false).  Needs max(c) < 2^16, otherwise the general kernel runs instead,
-// decided on the device.  Per thread the running minimum is kept over total << log2 N | q (the move id grows with
-// q); the workgroup reduces value << 2 log2 N | move id (value < 2^20).
-template <int LOGN, bool IN_LDS, int SPLIT>
-__global__ __launch_bounds__(SPLIT << LOGN) void rdswap_block_kernel(const int32_t* __restrict__ c,
-                                                                     const uint16_t* __restrict__ folded,
-                                                                     int32_t* __restrict__ tours,
-                                                                     int64_t* __restrict__ costs,
-                                                                     int32_t* __restrict__ moves,
-                                                                     const int32_t* __restrict__ flags) {
-    // SPLIT threads per rank share its steps: several wavefronts per SIMD, whose gathers and arithmetic overlap
-    constexpr int N = 1 << LOGN, THREADS = SPLIT << LOGN, NW = THREADS / 64, LB = LOGN - 1;   // LB: bits of a link index
-    constexpr int kIdBits = 2 * LOGN;
-    constexpr int kStepUnroll = IN_LDS ? 2 : 1;                // two steps in flight where registers allow
-    // 16 wavefronts: the workgroup-wide reductions finish with a wave reduction over the 16 partial results (read as
-    // a chain into registers they cost spills under the 128-register limit of 1024 threads); 8 wavefronts keep the chain
-    constexpr bool kTwoLevel = NW >= 16;
-    if (flags[0] >= (1 << 16)) return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int32_t* tl = (int32_t*)smem;                              // [N] the order
-    uint16_t* m16 = (uint16_t*)(smem + sizeof(int32_t) * N);   // [N * N] (IN_LDS)
-    __shared__ int red_i[2][NW];
-    __shared__ unsigned long long red_k[NW];
-    const int tid = threadIdx.x, p = tid & (N - 1), part = tid >> LOGN, lane = tid & 63, wv = tid >> 6;
-    const int64_t r = blockIdx.x;
-    if (IN_LDS)
-        for (int e = tid; e < N * N; e += THREADS) m16[e] = (uint16_t)clampi(c[e], 0, 0xffff);
-    int t = clampi(tours[r * N + p], 0, N - 1);
-    if (part == 0) tl[p] = t;
-    __syncthreads();
-    if (IN_LDS) {
-        // a link costs the larger of its two directed entries: fold the two into both places once (the threads of
-        // rank p take the pairs {p, p + j}, j = 1 .. N/2; every unordered pair exactly once), so that a link is one
-        // gather
-        for (int j = 1 + part; j <= N / 2; j += SPLIT) {
-            const int b = (p + j) & (N - 1);
-            if (j < N / 2 || p < N / 2) {
-                const uint16_t both = max(m16[p * N + b], m16[b * N + p]);
-                m16[p * N + b] = both;
-                m16[b * N + p] = both;
-            }
-        }
-        __syncthreads();
-    }
-    auto entry = [&](int a, int b) { return IN_LDS ? (int)m16[a * N + b] : (int)folded[a * N + b]; };
-    auto entry_at = [&](unsigned byte_offset) {                // row << (LOGN + 1) | column << 1
-        return (int)*(const uint16_t*)((IN_LDS ? (const char*)m16 : (const char*)folded) + byte_offset);
-    };
-    int parity = 0;
-    auto block_max = [&](int v) {                              // every thread gets the maximum; one barrier per call
-        v = wave_max(v);
-        if (lane == 0) red_i[parity][wv] = v;
-        __syncthreads();
-        int o;
-        if (kTwoLevel) {
-            o = wave_max(red_i[parity][lane & (NW - 1)]);      // second level: one value per lane, no long chain
-        } else {
-            o = red_i[parity][0];
-#pragma unroll
-            for (int k = 1; k < NW; ++k) o = max(o, red_i[parity][k]);
-        }
-        parity ^= 1;
-        return o;
-    };
+// ------------------------------------------------------------------------------------- pruned kernel
+// A round keeps its cost unless the swap touches its largest link, so a swap that lowers the total has to move an
+// end of the largest link of some round: of the N (N-1) / 2 swaps only those with p among the 2 log2 N ends of
+// those links can win (20 of 1024 ranks at N = 1024).  Two bounds cut these further, both taken from the three
+// largest links (values v1 >= v2 >= v3) of every round:
+//   * an end p and any q off every round's two largest links: total >= cur - G(p), G(p) = the sum of v1 - v2 over
+//     the rounds whose largest link is p's.  Ends are scanned in falling order of G while cur - G(p) can still reach
+//     the best total seen (equal totals are scored too: the lowest id wins them), usually one link's two ends.
+//   * an end p and a q on the second largest link of p's round, or two ends: total >= cur - the sum of v1 - the
+//     largest other link over the rounds where p or q touch the largest link; no matrix entry is needed to test it,
+//     and few of the 4 log2 N + 2 log2^2 N pairs pass.
+// The result (value, lowest id) is that of the exhaustive sweep.  Link values live in LDS from sweep to sweep: a swap
+// changes 2 log2 N of them, and a round's three largest are found anew only if one of them changed or was passed.
+//
+// What bounds a sweep is latency (LDS round trips, wave reductions, four or five barriers: about 9000 clocks at N = 256,
+// of which the three largest links take 950, the scans 2450 and the pairs 3450), no longer the gathers of N (N-1) / 2
+// pairs.  Against the exhaustive sweeps before it, matrices of the benchmark's hierarchy: N = 1024, 32 restarts
+// 394 -> 5.4 ms; N = 512, 136 restarts 95.7 -> 4.2 ms; N = 256, 58 restarts 9.4 -> 1.28 ms, 788 restarts
+// 31.7 -> 3.95 ms; N = 128, 600 restarts 4.6 -> 1.0 ms; N = 32, 300 restarts 2.4 -> 0.19 ms; N = 64 the same time.
+//
+// Where entries come from: N <= 128 folded int32 in LDS (64 KiB at 128), N = 256 folded 16-bit in LDS (128 KiB), else
+// the folded 16-bit copy of the workspace through L2, where a scan of p reads only log2 N + 1 rows: the mates' rows in
+// node order (coalesced) and p's own row staged in LDS.  Entries from 2^16 up at N >= 256: the caller's matrix.
 
-    int applied = 0, cur = 0;
-    for (;;) {
-        int pb2[LOGN], x1v[LOGN], x2v[LOGN], zk[LOGN], round_cost[LOGN];
-        cur = 0;
-#pragma unroll
-        for (int k = 0; k < LOGN; ++k) {
-            const int bit = 1 << k;
-            const int pb = tl[p ^ bit];
-            pb2[k] = pb << 1;                                  // the round mate's node as a column byte offset
-            const int lv = entry(t, pb);
-            const int li = ((p >> (k + 1)) << k) | (p & (bit - 1));
-            const int key = (lv << LB) | li;
-            const int k1 = block_max(key);
-            const int k2 = block_max((li == (k1 & (N / 2 - 1))) ? -1 : key);
-            const int k3 = block_max((li == (k1 & (N / 2 - 1)) || li == (k2 & (N / 2 - 1))) ? -1 : key);
-            const int l1 = k1 & (N / 2 - 1), l2 = k2 & (N / 2 - 1);
-            const int a1 = (li == l1) ? k2 : k1;               // best link that is not this rank's
-            const int a2 = (li == l1 || li == l2) ? k3 : k2;   // second best that is not this rank's
-            x1v[k] = a1 >> LB;
-            x2v[k] = a2 >> LB;
-            zk[k] = li ^ (a1 & (N / 2 - 1));                   // partner's link is that best link  <=>  li(x) == zk
-            round_cost[k] = __builtin_amdgcn_readfirstlane(k1 >> LB);
-            cur += round_cost[k];
-        }
-        // Steps grouped by the top bit of the rank difference: within a group a thread keeps its side (x0 = 2j or
-        // x1 = 2j + 1), so the side-dependent link-index test is prepared once per group.  The first step of a group
-        // has x0 = 2^top: there the threads on the x0 side swap with their mate of round `top`, which leaves that
-        // round as it is.  Per thread the move id grows with q, so the running minimum is kept over total << LOGN | q.
-        const int trow = t << (LOGN + 1);
-        int best32 = 0x7fffffff;
-        auto score = [&](int x0, bool second, int secbit, int mate_round) {
-            const int q = p ^ (x0 | secbit);
-            const int q4 = q << 2;
-            const int tqrow = *(const int32_t*)((const char*)tl + q4) << (LOGN + 1);
-            int total = 0;
-#pragma unroll
-            for (int k = 0; k < LOGN; ++k) {
-                const int bit = 1 << k;
-                const int qb = *(const int32_t*)((const char*)tl + (q4 ^ (bit << 2)));     // node at rank q xor 2^k
-                const int link_p = entry_at((unsigned)(tqrow | pb2[k]));           // rank p now holds t[q]
-                const int link_q = entry_at((unsigned)(trow | (qb << 1)));         // rank q now holds t[p]
-                const int lim0 = ((x0 >> (k + 1)) << k) | (x0 & (bit - 1));        // wave-uniform
-                const int others = (zk[k] == lim0) ? x2v[k] : x1v[k];
-                int stage = max(others, max(link_p, link_q));
-                if (k == mate_round) stage = second ? stage : round_cost[k];
-                total += stage;
-            }
-            best32 = min(best32, (total << LOGN) | q);
-        };
-        int side = 0;                                          // the side zk is prepared for
-#pragma unroll 1
-        for (int top = 0; top < LOGN; ++top) {
-            const bool second = top && ((p >> top) & 1);
-            const int secbit = second ? 1 : 0;
-#pragma unroll
-            for (int k = 1; k < LOGN; ++k) zk[k] ^= secbit ^ side;                 // x1's link index is x0's with bit 0 set
-            side = secbit;
-            const int x_first = 1 << top, x_end = 2 << top;
-            if (part == top % SPLIT) score(x_first, second, secbit, top);
-            if (top == 0) continue;                            // the difference 1 has no second step
-#pragma unroll kStepUnroll
-            for (int x0 = x_first + 2 + 2 * part; x0 < x_end; x0 += 2 * SPLIT) score(x0, second, secbit, -1);
-        }
-        unsigned long long best = kNoMove;
-        {
-            const int q = best32 & (N - 1), total = best32 >> LOGN;
-            const int lo = min(p, q), hi = max(p, q);
-            best = ((unsigned long long)(unsigned)total << kIdBits) | (unsigned)(lo * N + hi);
-        }
-        best = wave_min_u64(best);
-        if (lane == 0) red_k[wv] = best;
-        __syncthreads();
-        unsigned long long win;
-        if (kTwoLevel) {
-            win = wave_min_u64(red_k[lane & (NW - 1)]);
-        } else {
-            win = red_k[0];
-#pragma unroll
-            for (int k = 1; k < NW; ++k) win = min(win, red_k[k]);
-        }
-        if ((int)(win >> kIdBits) >= cur) break;
-        const int id = (int)(win & ((1u << kIdBits) - 1u)), sp = id >> LOGN, sq = id & (N - 1);
-        const int a = tl[sp], b = tl[sq];
-        __syncthreads();                                       // everyone has read red_k and the two ranks
-        if (p == sp) { t = b; tl[p] = b; }
-        if (p == sq) { t = a; tl[p] = a; }
-        ++applied;
-        __syncthreads();
+struct LdsWords {                       // folded int32 in LDS
+    const int32_t* m;
+    int log_n;
+    __device__ __forceinline__ int at(int x, int y) const { return m[(x << log_n) | y]; }
+    static constexpr bool kRows = false;
+};
+struct LdsHalves {                      // folded 16-bit in LDS
+    const uint16_t* m;
+    int log_n;
+    __device__ __forceinline__ int at(int x, int y) const { return m[(x << log_n) | y]; }
+    static constexpr bool kRows = false;
+};
+struct GlobalHalves {                   // folded 16-bit copy in the workspace
+    const uint16_t* m;
+    int log_n;
+    __device__ __forceinline__ int at(int x, int y) const { return m[(x << log_n) | y]; }
+    static constexpr bool kRows = true;
+};
+struct GlobalWords {                    // the caller's matrix, folded as it is read
+    const int32_t* m;
+    int log_n;
+    __device__ __forceinline__ int at(int x, int y) const {
+        return max(clampi(m[(x << log_n) | y], 0, kCostMax), clampi(m[(y << log_n) | x], 0, kCostMax));
     }
-    if (part == 0) tours[r * N + p] = t;
-    if (tid == 0) {
-        costs[r] = (int64_t)cur;
-        moves[r] = applied;
-    }
+    static constexpr bool kRows = true;
+};
+
+// LDS words of a workgroup besides the matrix: order, link values, inverse order and rows of two scanned ranks
+constexpr size_t swap_state_words(int log_n, bool rows) {
+    const size_t n = (size_t)1 << log_n;
+    return n + (size_t)log_n * (n / 2) + (rows ? 3 * n : 0);
 }
 
-// ------------------------------------------------------------------ N = 512, 1024: tiles of the folded matrix in LDS
-// One workgroup per restart, one or two threads per rank p (two at N = 512: 1024 threads either way).  The folded
-// 16-bit matrix F (512 KiB / 2 MiB, in the workspace)
-// does not fit LDS, and gathered through L2 a sweep is bound by the misses one compute unit keeps in flight.  Here
-// a sweep goes through the partner ranks q in blocks of QB consecutive ranks B; for a block the workgroup stages
-//   CT[x][j]      = F[x][t[B + j]]                 every row x, the QB columns of the block's nodes
-//   RT[h][j][y]   = F[t[(B + j) xor 2^k]][y]       k = log2 QB + h: the rows of the block's mates in the rounds whose
-//                                                  mate lies outside the block, every column y
-// and every link of every pair (p, q in B) is then an LDS gather: rank p holding t[q] costs, in round k,
-// F[t[q]][t[p xor 2^k]] = CT[t[p xor 2^k]][j]; rank q holding t[p] costs F[t[p]][t[q xor 2^k]], which is
-// CT[t[p]][j xor 2^k] when the mate of q lies in the block and RT[h][j][t[p]] otherwise (F is symmetric).
-// Pairs are split so that every thread scores one pair per step: of two neighbouring partners q0, q0 + 1 a thread
-// takes the one with its own parity when it lies below them and the other one when it lies above (every unordered
-// pair is then scored exactly once, by the thread p for which p + q is even and p < q, or odd and p > q).  Pairs of
-// round mates (q = p xor 2^k), whose round k keeps its cost, are scored apart from the folded copy through L2: 9 or
-// 10 per thread.  Round maxima, keys, reduction and the swap as in the kernel above.
-template <int LOGN, int LOGQ, int SPLIT>
-__global__ __launch_bounds__(SPLIT << LOGN) void rdswap_tiled_kernel(const uint16_t* __restrict__ folded,
-                                                                 int32_t* __restrict__ tours,
-                                                                 int64_t* __restrict__ costs,
-                                                                 int32_t* __restrict__ moves,
-                                                                 const int32_t* __restrict__ flags) {
-    constexpr int N = 1 << LOGN, QB = 1 << LOGQ, NH = LOGN - LOGQ, NT = SPLIT * N, NW = NT / 64, LB = LOGN - 1;
-    static_assert(SPLIT == 1 || SPLIT == 2, "one or two threads per rank");
-    constexpr int kIdBits = 2 * LOGN;
-    constexpr int kInf = 0x7fffffff;
-    // a row of CT takes QB / 2 + 1 words: with QB / 2 the rows of the 64 lanes of a gather would fall into four or
-    // eight LDS banks only
-    constexpr int kCtRowBytes = (QB / 2 + 1) * 4;
-    if (flags[0] >= (1 << 16)) return;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    int32_t* tl = (int32_t*)smem;                                          // [N] the order
-    uint16_t* rt = (uint16_t*)(smem + sizeof(int32_t) * N);                // [NH][QB][N]
-    unsigned char* ct = (unsigned char*)(rt + (size_t)NH * QB * N);        // [N] rows of kCtRowBytes
-    __shared__ int red_i[2][NW];
-    __shared__ unsigned long long red_k[NW];
-    // SPLIT threads per rank p share the rank's steps (part 0 takes the first half of every block of partners): with one
-    // thread per rank at N = 512 a SIMD holds two wavefronts, too few to overlap one's LDS gathers with the other's
-    // arithmetic
-    const int tid = threadIdx.x, p = tid & (N - 1), part = tid >> LOGN, lane = tid & 63, wv = tid >> 6;
-    const int64_t r = blockIdx.x;
-    int t = clampi(tours[r * N + p], 0, N - 1);
-    if (part == 0) tl[p] = t;
+// A link is named by its upper rank (bit k set), a value other than 0; link keys are value << 10 | name, 0 = no link.
+template <int LOGN, int THREADS, class MAT>
+__device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, int32_t* __restrict__ tour,
+                                               int64_t* __restrict__ cost_out, int32_t* __restrict__ moves_out) {
+    constexpr int N = 1 << LOGN, HALF = N / 2, NW = THREADS / 64, M = (HALF + 63) / 64;
+    constexpr int kEnds = 2 * LOGN, kNone = 0x7fffffff;
+    constexpr int kPicks = 2;                          // ends scanned at a time; the waves share them
+    constexpr int kScanThreads = NW > 1 ? THREADS / 2 : 64;
+    __shared__ int top[3][LOGN];                       // keys of every round's three largest links
+    __shared__ int4 gaps[LOGN];                        // {name 1, value 1 - value 2, name 2, value 2 - value 3}
+    __shared__ int4 scan_a[NW][kPicks][LOGN];          // for a scanned end: {largest other link's name, its value, the next value, mate's node}
+    __shared__ int scan_b[NW][kPicks][LOGN];           // value 1
+    __shared__ unsigned dirty_rounds;
+    __shared__ unsigned long long red[3];
+    int32_t* t = state;                                // [N]
+    int32_t* links = t + N;                            // [LOGN][HALF] keys
+    int32_t* pos = links + LOGN * HALF;                // [N] (kRows) rank of a node, -1: none
+    int32_t* rows = pos + N;                           // [kPicks][N] (kRows)
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto sync = [] { if (NW > 1) __syncthreads(); else __builtin_amdgcn_wave_barrier(); };
+    auto upper_of = [](int link, int k) { return ((link >> k) << (k + 1)) | (1 << k) | (link & ((1 << k) - 1)); };
+    auto link_of = [](int p, int k) { return ((p >> (k + 1)) << k) | (p & ((1 << k) - 1)); };
+
+    for (int p = tid; p < N; p += THREADS) {
+        t[p] = clampi(tour[p], 0, N - 1);
+        if (MAT::kRows) pos[p] = -1;
+    }
+    if (tid < 3) red[tid] = ~0ull;
     __syncthreads();
-    int parity = 0;
-    auto block_max = [&](int v) {                              // every thread gets the maximum; one barrier per call
-        v = wave_max(v);
-        if (lane == 0) red_i[parity][wv] = v;
-        __syncthreads();
-        int o;
-        if (NW >= 16) {
-            o = wave_max(red_i[parity][lane & (NW - 1)]);
-        } else {
-            o = red_i[parity][0];
+    if (MAT::kRows)
+        for (int p = tid; p < N; p += THREADS) pos[t[p]] = p;
 #pragma unroll
-            for (int k = 1; k < NW; ++k) o = max(o, red_i[parity][k]);
+    for (int k = 0; k < LOGN; ++k)
+        for (int l = tid; l < HALF; l += THREADS) {
+            const int up = upper_of(l, k);
+            links[k * HALF + l] = (mat.at(t[up ^ (1 << k)], t[up]) << 10) | up;
         }
-        parity ^= 1;
-        return o;
+    __syncthreads();
+
+    int cell = 0;
+    // smallest (hi, lo) over the workgroup; every thread gets it
+    auto block_min = [&](int& hi, int& lo) {
+        int h = wave_min(hi);
+        const unsigned long long at = __ballot(hi == h);
+        int l = __builtin_amdgcn_readlane(lo, (int)__builtin_ctzll(at));
+        if (at & (at - 1)) l = wave_min(hi == h ? lo : kNone);
+        if (NW > 1) {
+            if (lane == 0) atomicMin(&red[cell], ((unsigned long long)(unsigned)h << 32) | (unsigned)l);
+            if (tid == 0) red[cell == 2 ? 0 : cell + 1] = ~0ull;    // last read before the previous barrier
+            __syncthreads();
+            const unsigned long long v = red[cell];
+            h = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+            l = __builtin_amdgcn_readfirstlane((int)(unsigned)v);
+            cell = cell == 2 ? 0 : cell + 1;
+        }
+        hi = h;
+        lo = l;
     };
 
-    int applied = 0, cur = 0;
+    constexpr int kPerWave = (LOGN + NW - 1) / NW;     // rounds whose largest links a wave keeps up to date
+    constexpr int kBatch = kPerWave < 3 ? kPerWave : 3;
+    unsigned dirty = (1u << LOGN) - 1u;
+    int applied = 0, cur = -1;
     for (;;) {
-        // per round: the mate's node, the largest and second largest link that is not this rank's, and the two ranks
-        // (with the round's bit set) of that largest link
-        int pbq[LOGN], x1v[LOGN], x2v[LOGN], a1r[LOGN], round_cost[LOGN];
-        cur = 0;
+        // ---- the three largest links of the rounds that may have new ones
+#pragma unroll 1
+        for (int k0 = wv * kPerWave; k0 < min((wv + 1) * kPerWave, LOGN); k0 += kBatch) {
+            if (!((dirty >> k0) & ((1u << kBatch) - 1u))) continue;
+            int key[kBatch][M], kk[3][3];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j)
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const int l = lane + 64 * m, k = min(k0 + j, LOGN - 1);
+                    key[j][m] = (HALF >= 64 || l < HALF) ? links[k * HALF + l] : 0;
+                }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    int v = 0;
+                    if (j < kBatch)
+#pragma unroll
+                        for (int m = 0; m < M; ++m) {
+                            int& x = key[j < kBatch ? j : 0][m];
+                            if (i > 0 && x == kk[i - 1][j]) x = 0;
+                            v = max(v, x);
+                        }
+                    kk[i][j] = v;
+                }
+                if (kBatch == 1) kk[i][0] = wave_max(kk[i][0]);
+                else wave_max3(kk[i][0], kk[i][1], kk[i][2]);
+            }
+            if (lane == 0) {
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j)
+                    if (k0 + j < LOGN) {
+                        const int k = k0 + j;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) top[i][k] = kk[i][j];
+                        gaps[k] = make_int4(kk[0][j] & 1023, (kk[0][j] >> 10) - (kk[1][j] >> 10), kk[1][j] & 1023,
+                                            (kk[1][j] >> 10) - (kk[2][j] >> 10));
+                    }
+            }
+        }
+        sync();
+        if (cur < 0) cur = wave_sum(lane < LOGN ? top[0][min(lane, LOGN - 1)] >> 10 : 0);
+        // lanes 0 .. 2 LOGN - 1: the ends of the largest links; the next 2 LOGN lanes: those of the second largest
+        const int round = min(lane >> 1, 2 * LOGN - 1);
+        const int name = (&top[0][0])[round] & 1023;
+        const int end_rank = (lane & 1) ? name : name & ~(1 << (round >= LOGN ? round - LOGN : round));
+        int gain = 0, both = 0;                        // G; what moving a second large link of its rounds can add
 #pragma unroll
         for (int k = 0; k < LOGN; ++k) {
-            const int bit = 1 << k;
-            const int pb = tl[p ^ bit];
-            pbq[k] = pb * kCtRowBytes;                         // the mate's node as a row byte offset of CT
-            const int lv = (int)folded[t * N + pb];
-            const int li = ((p >> (k + 1)) << k) | (p & (bit - 1));
-            const int key = (lv << LB) | li;
-            const int k1 = block_max(key);
-            const int k2 = block_max((li == (k1 & (N / 2 - 1))) ? -1 : key);
-            const int k3 = block_max((li == (k1 & (N / 2 - 1)) || li == (k2 & (N / 2 - 1))) ? -1 : key);
-            const int l1 = k1 & (N / 2 - 1), l2 = k2 & (N / 2 - 1);
-            const int a1 = (li == l1) ? k2 : k1;               // best link that is not this rank's
-            const int a2 = (li == l1 || li == l2) ? k3 : k2;   // second best that is not this rank's
-            x1v[k] = a1 >> LB;
-            x2v[k] = a2 >> LB;
-            const int al = a1 & (N / 2 - 1);
-            a1r[k] = (((al >> k) << (k + 1)) | (al & (bit - 1))) | bit;    // link index -> its rank with bit k set
-            round_cost[k] = __builtin_amdgcn_readfirstlane(k1 >> LB);
-            cur += round_cost[k];
+            const int4 g = gaps[k];
+            const int up = end_rank | (1 << k);
+            gain += up == g.x ? g.y : 0;
+            both += (up == g.x || up == g.z) ? g.w : 0;
         }
-        int best_below = kInf, best_above = kInf;              // over partners q < p and q > p: total << LOGN | q
-        // pairs of round mates, scored by the thread whose bit is clear
-#pragma unroll 1
-        for (int km = 0; km < LOGN; ++km) {
-            const int q = p ^ (1 << km);
-            if (q < p || (km & (SPLIT - 1)) != part) continue;
-            const int tq = tl[q];
-            int total = 0;
+        // ---- scans: two ends at a time, in falling order of G, against every rank
+        bool seen = lane >= kEnds;
+        int best_hi = cur, best_id = 0;                // a winner has a total below cur
+        for (;;) {
+            int pick[kPicks];
+            int n = 0;
 #pragma unroll
-            for (int k = 0; k < LOGN; ++k) {
-                const int bit = 1 << k;
-                const int link_p = (int)folded[tq * N + tl[p ^ bit]];
-                const int link_q = (int)folded[t * N + tl[q ^ bit]];
-                const int others = ((q | bit) == a1r[k]) ? x2v[k] : x1v[k];
-                const int stage = max(others, max(link_p, link_q));
-                total += (k == km) ? round_cost[k] : stage;
+            for (int s = 0; s < kPicks; ++s) {
+                const int g = wave_max(seen ? 0 : (gain << 6) | lane);
+                pick[s] = 0;
+                if ((g >> 6) > 0 && cur - (g >> 6) <= best_hi) {
+                    pick[s] = __builtin_amdgcn_readlane(end_rank, g & 63);
+                    seen = seen || end_rank == pick[s];
+                    n = s + 1;
+                }
             }
-            best_above = min(best_above, (total << LOGN) | q);
+            if (n == 0) break;
+            if (MAT::kRows) {
+                for (int i = tid; i < n * N; i += THREADS) rows[i] = mat.at(t[i < N ? pick[0] : pick[1]], i & (N - 1));
+                sync();
+            }
+            int hi = best_hi, id = best_id;
+#pragma unroll
+            for (int s0 = 0; s0 < (NW > 1 ? 1 : kPicks); ++s0) {
+                const int s = NW > 1 ? wv / (NW / 2) : s0;
+                if (s >= n) break;
+                const int p = s ? pick[1] : pick[0];
+                const int tp = __builtin_amdgcn_readfirstlane(t[p]);
+                if (lane < LOGN) {
+                    // round `lane`: its largest link that is not p's, and the value that replaces it when it is q's
+                    const int k1 = top[0][lane], k2 = top[1][lane], k3 = top[2][lane], up = p | (1 << lane);
+                    const bool one = (k1 & 1023) == up, two = (k2 & 1023) == up;
+                    const int first = one ? k2 : k1, second = (one || two) ? k3 : k2;
+                    scan_a[wv][s0][lane] = make_int4(first & 1023, first >> 10, second >> 10, t[p ^ (1 << lane)]);
+                    scan_b[wv][s0][lane] = k1 >> 10;
+                }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+                for (int i = tid & (kScanThreads - 1); i < N; i += kScanThreads) {
+                    const int q = MAT::kRows ? pos[i] : i;         // kRows: i is the node, so that rows are read in order
+                    const int tq = MAT::kRows ? i : t[i];
+                    if (q < 0) continue;
+                    int total = 0;
+#pragma unroll
+                    for (int k = 0; k < LOGN; ++k) {
+                        const int4 w = scan_a[wv][s0][k];
+                        const int v = scan_b[wv][s0][k];
+                        const int tm = t[q ^ (1 << k)];
+                        const int x = mat.at(w.w, tq);
+                        const int y = MAT::kRows ? rows[s * N + tm] : mat.at(tp, tm);
+                        const int up = q | (1 << k);
+                        const int cost = max(up == w.x ? w.z : w.y, max(x, y));
+                        total += up == (p | (1 << k)) ? v : cost;  // the mate: the link stays, and with it the round
+                    }
+                    const int move = min(p, q) * N + max(p, q);
+                    const bool better = q != p && (total < hi || (total == hi && move < id));
+                    hi = better ? total : hi;
+                    id = better ? move : id;
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            block_min(hi, id);
+            best_hi = hi;
+            best_id = id;
         }
-        const int tq2 = t * kCtRowBytes, tc2 = t << 1;
+        // ---- pairs that move two large links at once: an end of a round's largest and one of its second largest link, or
+        // two ends of largest links; pairs with a scanned end are known already
+        const unsigned long long left = __ballot(!seen);
+        if (left) {
+            int hi = best_hi, id = best_id;
+            constexpr int kSameRound = 4 * LOGN, kPairs = kSameRound + kEnds * (kEnds / 2);
 #pragma unroll 1
-        for (int b0 = 0; b0 < N; b0 += QB) {
-            __syncthreads();                                   // the tiles of the previous block are free
-            // all loads of the block first, then the stores: one L2 latency per block
-            // RT: NH * QB rows of N entries, copied 16 bytes at a time; CT: row p, the block's QB columns
-            constexpr int kChunksPerRow = N * 2 / 16, kChunks = NH * QB * kChunksPerRow, kPerThread = kChunks / NT;
-            static_assert(kChunks % NT == 0, "every thread copies the same number of 16-byte pieces");
-            int4 piece[kPerThread];
-#pragma unroll
-            for (int i = 0; i < kPerThread; ++i) {
-                const int ch = tid + i * NT;
-                const int rowi = ch / kChunksPerRow, off = ch % kChunksPerRow;
-                const int h = rowi >> LOGQ, j = rowi & (QB - 1);
-                const int node = tl[(b0 + j) ^ (QB << h)];
-                piece[i] = ((const int4*)(folded + (size_t)node * N))[off];
-            }
-            {
-                // F is symmetric: column t[B + j] is read as row t[B + j], which the threads of a wave read side by side
-                const uint16_t* col = folded + p;
-                constexpr int kWords = QB / 2 / SPLIT;             // words of row p that this thread stages
-                const int j0 = part * kWords;
-                uint32_t w[kWords];
-#pragma unroll
-                for (int j = 0; j < kWords; ++j)
-                    w[j] = (uint32_t)col[(size_t)tl[b0 + 2 * (j0 + j)] * N] |
-                           ((uint32_t)col[(size_t)tl[b0 + 2 * (j0 + j) + 1] * N] << 16);
-#pragma unroll
-                for (int j = 0; j < kWords; ++j) ((uint32_t*)(ct + p * kCtRowBytes))[j0 + j] = w[j];
-            }
-#pragma unroll
-            for (int i = 0; i < kPerThread; ++i) ((int4*)rt)[tid + i * NT] = piece[i];
-            __syncthreads();
-            constexpr int kSteps = QB / 2 / SPLIT;
-#pragma unroll 2
-            for (int ii = 0; ii < kSteps; ++ii) {
-                const int i = part * kSteps + ii;
-                const int q0 = b0 + 2 * i;
-                const bool above = p > q0;                     // p = q0 + 1 takes q0; p = q0 sits this step out
-                const int q = q0 + (((p ^ q0) & 1) ^ (above ? 1 : 0));
-                const int j = q - b0, j2 = j << 1;
-                const int x = p ^ q;
+            for (int i0 = 0; i0 < kPairs; i0 += THREADS) {
+                const int i = i0 + tid, u = max(i - kSameRound, 0);
+                int e1 = u % kEnds, e2 = e1 + 1 + u / kEnds;
+                e2 = e2 >= kEnds ? e2 - kEnds : e2;
+                const bool same = i < kSameRound;
+                e1 = same ? ((i >> 2) << 1) | (i & 1) : e1;
+                e2 = same ? kEnds + (((i >> 2) << 1) | ((i >> 1) & 1)) : e2;
+                const int p = __shfl(end_rank, e1), q = __shfl(end_rank, e2);
+                const int reach = __shfl(gain, e1) + __shfl(gain, e2) + min(__shfl(both, e1), __shfl(both, e2));
+                if (i >= kPairs || !((left >> e1) & 1) || (!same && !((left >> e2) & 1)) || p == q || cur - reach > hi ||
+                    reach == 0)
+                    continue;
+                const int tp = t[p], tq = t[q];
                 int total = 0;
 #pragma unroll
                 for (int k = 0; k < LOGN; ++k) {
-                    const int bit = 1 << k;
-                    const int link_p = (int)*(const uint16_t*)((const char*)ct + (pbq[k] + j2));
-                    int link_q;
-                    if (k < LOGQ) link_q = (int)*(const uint16_t*)((const char*)ct + (tq2 + (j2 ^ (bit << 1))));
-                    else link_q = (int)*(const uint16_t*)((const char*)rt + ((((k - LOGQ) << LOGQ) + j) << (LOGN + 1)) + tc2);
-                    const int others = ((q | bit) == a1r[k]) ? x2v[k] : x1v[k];
-                    total += max(others, max(link_p, link_q));
+                    const int k1 = top[0][k], k2 = top[1][k], k3 = top[2][k], up = p | (1 << k), uq = q | (1 << k);
+                    const bool one = (k1 & 1023) == up || (k1 & 1023) == uq, two = (k2 & 1023) == up || (k2 & 1023) == uq;
+                    const int other = (one ? (two ? k3 : k2) : k1) >> 10;
+                    const int cost = max(other, max(mat.at(tq, t[p ^ (1 << k)]), mat.at(tp, t[q ^ (1 << k)])));
+                    total += up == uq ? k1 >> 10 : cost;
                 }
-                const bool skip = (x & (x - 1)) == 0;          // itself (x = 0) or a round mate (scored above)
-                const int key = skip ? kInf : ((total << LOGN) | q);
-                best_below = min(best_below, above ? key : kInf);
-                best_above = min(best_above, above ? kInf : key);
+                const int move = min(p, q) * N + max(p, q);
+                const bool better = total < hi || (total == hi && move < id);
+                hi = better ? total : hi;
+                id = better ? move : id;
+            }
+            block_min(hi, id);
+            best_hi = hi;
+            best_id = id;
+        }
+        if (best_hi >= cur) break;
+        // ---- the swap: the first wave moves the two nodes and renews the 2 LOGN links they touch
+        const int sp = best_id >> LOGN, sq = best_id & (N - 1);
+        if (wv == 0) {
+            const int a = t[sp], b = t[sq];
+            const int k = min(lane >> 1, LOGN - 1), rank = (lane & 1) ? sq : sp, mate = rank ^ (1 << k);
+            const int tr = (lane & 1) ? a : b;
+            int tm = t[mate];
+            tm = mate == sp ? b : (mate == sq ? a : tm);
+            bool touched = false;
+            if (lane < kEnds) {
+                const int up = rank | (1 << k), key = (mat.at(tr, tm) << 10) | up, l = link_of(rank, k);
+                const int k3 = top[2][k];
+                touched = key > k3 || links[k * HALF + l] >= k3;
+                links[k * HALF + l] = key;
+            }
+            const unsigned long long bits = __ballot(touched);
+            unsigned mask = 0;
+#pragma unroll
+            for (int j = 0; j < LOGN; ++j) mask |= ((bits >> (2 * j)) & 3) ? 1u << j : 0u;
+            if (lane == 0) {
+                t[sp] = b;
+                t[sq] = a;
+                if (MAT::kRows) {
+                    pos[b] = sp;
+                    pos[a] = sq;
+                }
+                dirty_rounds = mask;
             }
         }
-        unsigned long long best = kNoMove;
-        if (best_below != kInf) {
-            const int q = best_below & (N - 1), total = best_below >> LOGN;
-            best = ((unsigned long long)(unsigned)total << kIdBits) | (unsigned)(q * N + p);
-        }
-        if (best_above != kInf) {
-            const int q = best_above & (N - 1), total = best_above >> LOGN;
-            best = min(best, ((unsigned long long)(unsigned)total << kIdBits) | (unsigned)(p * N + q));
-        }
-        best = wave_min_u64(best);
-        if (lane == 0) red_k[wv] = best;
-        __syncthreads();
-        unsigned long long win;
-        if (NW >= 16) {
-            win = wave_min_u64(red_k[lane & (NW - 1)]);
-        } else {
-            win = red_k[0];
-#pragma unroll
-            for (int k = 1; k < NW; ++k) win = min(win, red_k[k]);
-        }
-        if ((int)(win >> kIdBits) >= cur) break;
-        const int id = (int)(win & ((1u << kIdBits) - 1u)), sp = id >> LOGN, sq = id & (N - 1);
-        const int a = tl[sp], b = tl[sq];
-        __syncthreads();                                       // everyone has read red_k and the two ranks
-        if (p == sp) { t = b; if (part == 0) tl[p] = b; }
-        if (p == sq) { t = a; if (part == 0) tl[p] = a; }
         ++applied;
-        __syncthreads();
+        cur = best_hi;
+        sync();
+        dirty = __builtin_amdgcn_readfirstlane(dirty_rounds);
     }
-    if (part == 0) tours[r * N + p] = t;
+    for (int p = tid; p < N; p += THREADS) tour[p] = t[p];
     if (tid == 0) {
-        costs[r] = (int64_t)cur;
-        moves[r] = applied;
+        *cost_out = (int64_t)cur;
+        *moves_out = applied;
     }
 }
 
-template <int LOGN, int LOGQ, int SPLIT>
-static hipError_t rdswap_tiled_launch(const int32_t* c, uint16_t* folded, int restarts, int32_t* tours, int64_t* costs,
-                                      int32_t* moves, const int32_t* flags, hipStream_t s) {
-    constexpr int N = 1 << LOGN, QB = 1 << LOGQ, NH = LOGN - LOGQ;
-    hipError_t e = launch_fold_to_u16(c, N, folded, flags, s);
-    if (e != hipSuccess) return e;
-    const size_t lds = sizeof(int32_t) * N + sizeof(uint16_t) * (size_t)NH * QB * N + (size_t)N * (QB / 2 + 1) * 4;
-    e = hipFuncSetAttribute((const void*)rdswap_tiled_kernel<LOGN, LOGQ, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((rdswap_tiled_kernel<LOGN, LOGQ, SPLIT>), dim3(restarts), dim3(SPLIT * N), lds, s, folded, tours, costs, moves,
-                       flags);
-    return hipGetLastError();
-}
-
-template <int LOGN>
-static hipError_t rdswap_block_launch(const int32_t* c, uint16_t* folded, int restarts, int32_t* tours, int64_t* costs,
-                                      int32_t* moves, const int32_t* flags, hipStream_t s) {
+template <int LOGN, int THREADS>
+__global__ __launch_bounds__(THREADS) void rdswap_pruned_kernel(const int32_t* __restrict__ c,
+                                                                const uint16_t* __restrict__ folded,
+                                                                int32_t* __restrict__ tours, int64_t* __restrict__ costs,
+                                                                int32_t* __restrict__ moves,
+                                                                const int32_t* __restrict__ flags) {
     constexpr int N = 1 << LOGN;
-    constexpr bool kInLds = LOGN <= 8;
-    if (!kInLds) {
-        hipError_t e = launch_fold_to_u16(c, N, folded, flags, s);
-        if (e != hipSuccess) return e;
+    extern __shared__ __attribute__((aligned(16))) int32_t sm[];
+    const int tid = threadIdx.x;
+    const int64_t r = blockIdx.x;
+    int32_t* tour = tours + r * N;
+    if constexpr (LOGN <= 8) {
+        using E = typename std::conditional<LOGN <= 7, int32_t, uint16_t>::type;
+        E* m = (E*)(sm + swap_state_words(LOGN, LOGN == 8));
+        __shared__ int wave_top[THREADS / 64];
+        int mx = 0;
+        for (int e = tid; e < N * N; e += THREADS) {
+            const int v = clampi(c[e], 0, kCostMax);
+            mx = max(mx, v);
+            m[e] = (E)v;
+        }
+        if constexpr (LOGN == 8) {
+            mx = wave_max(mx);
+            if ((tid & 63) == 0) wave_top[tid >> 6] = mx;
+        }
+        __syncthreads();
+        if constexpr (LOGN == 8) {
+            for (int w = 0; w < THREADS / 64; ++w) mx = max(mx, wave_top[w]);
+            if (mx >= (1 << 16)) {
+                descend_pruned<LOGN, THREADS>(GlobalWords{c, LOGN}, sm, tour, costs + r, moves + r);
+                return;
+            }
+        }
+        // a link costs the larger of its two directed entries: fold the two into both places, every unordered pair
+        // once, neighbouring threads on neighbouring columns
+        for (int i = tid; i < N * (N / 2); i += THREADS) {
+            const int x = i & (N - 1), j = 1 + (i >> LOGN), y = (x + j) & (N - 1);
+            if (j < N / 2 || x < N / 2) {
+                const E both = max(m[x * N + y], m[y * N + x]);
+                m[x * N + y] = both;
+                m[y * N + x] = both;
+            }
+        }
+        __syncthreads();
+        if constexpr (LOGN <= 7) descend_pruned<LOGN, THREADS>(LdsWords{m, LOGN}, sm, tour, costs + r, moves + r);
+        else descend_pruned<LOGN, THREADS>(LdsHalves{m, LOGN}, sm, tour, costs + r, moves + r);
+    } else {
+        if (flags[0] < (1 << 16)) descend_pruned<LOGN, THREADS>(GlobalHalves{folded, LOGN}, sm, tour, costs + r, moves + r);
+        else descend_pruned<LOGN, THREADS>(GlobalWords{c, LOGN}, sm, tour, costs + r, moves + r);
     }
-    // matrix in LDS: a workgroup of 1024 threads whatever N (16 wavefronts on the restart's compute unit); through
-    // L2 more wavefronts only queue up behind the same misses (N = 512: 0.57 s with two threads per rank, 0.47 s with one)
-    constexpr int kSplit = kInLds ? 1024 / N : 1;
-    const size_t lds = (kInLds ? sizeof(uint16_t) * N * N : 0) + sizeof(int32_t) * N;
+}
+
+template <int LOGN, int THREADS>
+hipError_t rdswap_pruned_launch(const int32_t* c, const uint16_t* folded, int restarts, int32_t* tours, int64_t* costs,
+                                int32_t* moves, const int32_t* flags, hipStream_t s) {
+    constexpr size_t N = (size_t)1 << LOGN;
+    const size_t lds = swap_state_words(LOGN, LOGN >= 8) * 4 + (LOGN <= 7 ? 4 * N * N : LOGN == 8 ? 2 * N * N : 0);
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)rdswap_block_kernel<LOGN, kInLds, kSplit>,
+        hipError_t e = hipFuncSetAttribute((const void*)rdswap_pruned_kernel<LOGN, THREADS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((rdswap_block_kernel<LOGN, kInLds, kSplit>), dim3(restarts), dim3(N * kSplit), lds, s, c, folded,
-                       tours, costs, moves, flags);
+    hipLaunchKernelGGL((rdswap_pruned_kernel<LOGN, THREADS>), dim3(restarts), dim3(THREADS), lds, s, c, folded, tours, costs,
+                       moves, flags);
     return hipGetLastError();
 }
 
@@ -748,33 +546,36 @@ hipError_t launch_fold_to_u16(const int32_t* c, int N, uint16_t* folded, const i
 
 hipError_t launch_rdswap(const int32_t* c, int N, int restarts, uint64_t seed, bool tours_hold_init, int32_t* tours,
                          int64_t* costs, int32_t* moves, int32_t* flags, uint16_t* mat16, hipStream_t s) {
-    const bool pinned = force_general_path();
-    if (N == 64 && !pinned) {
-        hipLaunchKernelGGL(rdswap_n64_kernel, dim3((restarts + 3) / 4), dim3(256), 0, s, c, restarts, seed,
-                           tours_hold_init ? 0 : 1, tours, costs, moves);
-        return hipGetLastError();
-    }
     if (!tours_hold_init) {
         hipError_t e = launch_init_tours(N, 0, restarts, seed, tours, s);
         if (e != hipSuccess) return e;
     }
-    const int32_t* skip = nullptr;
-    if (!pinned && (N == 128 || N == 256 || N == 512 || N == 1024)) {
-        // 16-bit workgroup kernel when max(c) < 2^16, else the general kernel: both are enqueued and the matrix
-        // maximum, computed on the device, decides which one does the work (no host round trip)
-        hipError_t e = launch_matrix_max(c, N, flags, s);
-        if (e != hipSuccess) return e;
-        e = N == 128   ? rdswap_block_launch<7>(c, mat16, restarts, tours, costs, moves, flags, s)
-            : N == 256 ? rdswap_block_launch<8>(c, mat16, restarts, tours, costs, moves, flags, s)
-            : N == 512 ? rdswap_tiled_launch<9, 4, 2>(c, mat16, restarts, tours, costs, moves, flags, s)
-                       : rdswap_tiled_launch<10, 3, 1>(c, mat16, restarts, tours, costs, moves, flags, s);
-        if (e != hipSuccess) return e;
-        skip = flags;
+    if (force_general_path()) {
+        const int threads = ((N + 63) / 64) * 64;
+        hipLaunchKernelGGL(rdswap_general_kernel, dim3(restarts), dim3(threads), sizeof(int32_t) * 2 * (size_t)N, s, c, N,
+                           tours, costs, moves);
+        return hipGetLastError();
     }
-    const int threads = ((N + 63) / 64) * 64;
-    hipLaunchKernelGGL(rdswap_general_kernel, dim3(restarts), dim3(threads), sizeof(int32_t) * 2 * (size_t)N, s, c, N,
-                       tours, costs, moves, skip);
-    return hipGetLastError();
+    if (N > 256) {
+        hipError_t e = launch_matrix_max(c, N, flags, s);
+        if (e == hipSuccess) e = launch_fold_to_u16(c, N, mat16, flags, s);
+        if (e != hipSuccess) return e;
+    }
+    // Threads per restart, from a sweep over 64 .. 1024 at few and at many restarts: a sweep is a chain of latencies, and
+    // wider workgroups shorten its scans until the barriers cost more than they save (N = 64: 128 and 256 the same at 34
+    // restarts, 128 better at 1024; N = 256: 1.28 ms with 512, 1.54 with 256, 2.3 with 1024, 58 restarts).
+    switch (N) {
+        case 2: return rdswap_pruned_launch<1, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 4: return rdswap_pruned_launch<2, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 8: return rdswap_pruned_launch<3, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 16: return rdswap_pruned_launch<4, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 32: return rdswap_pruned_launch<5, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 64: return rdswap_pruned_launch<6, 128>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 128: return rdswap_pruned_launch<7, 256>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 256: return rdswap_pruned_launch<8, 512>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 512: return rdswap_pruned_launch<9, 512>(c, mat16, restarts, tours, costs, moves, flags, s);
+        default: return rdswap_pruned_launch<10, 512>(c, mat16, restarts, tours, costs, moves, flags, s);
+    }
 }
 
 }  // namespace cc
