@@ -345,18 +345,15 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
         e = launch_2opt_dsum_n64(c, restarts, seed, false, flip, tours, costs, moves, flags, s);
         if (e != hipSuccess) return e;
         e = launch_general_objective(c, N, objective, restarts, tours, costs, moves, flags, flip, s);
-    } else if ((flip || classes == kMoves2opt) && (objective & 1) && (N == 128 || N == 192 || N == 256)) {
-        // max-hop at 128 / 192 / 256: several ranks per lane with a 16-bit LDS matrix when max(c) < 2^16, else the
-        // general kernel (both enqueued, the matrix maximum computed on the device decides)
+    } else if ((flip || classes == kMoves2opt) && (objective & 1) && N >= 4 &&
+               !(objective == 3 && N == 64)) {
+        // only the moves that can win (directed at N = 64: the exhaustive wavefront kernel is still the faster, 62 us
+        // against 130 for 1024 restarts)
         if (!tours_hold_init) {
             e = launch_init_tours(N, 0, restarts, seed, tours, s);
             if (e != hipSuccess) return e;
         }
-        e = launch_matrix_max(c, N, flags, s);
-        if (e != hipSuccess) return e;
-        e = launch_2opt_max_multi(c, N, (objective & 2) != 0, restarts, flip, tours, costs, moves, flags, s);
-        if (e != hipSuccess) return e;
-        e = launch_general_objective(c, N, objective, restarts, tours, costs, moves, flags, flip, s);
+        e = launch_2opt_max_pruned(c, N, (objective & 2) != 0, restarts, flip, tours, costs, moves, s);
     } else if ((flip || classes == kMoves2opt) && objective == 2 && (N == 128 || N == 192 || N == 256)) {
         // directed sum at 128 / 192 / 256: several ranks per lane with a 16-bit LDS matrix when its 32-bit keys hold
         // every partial delta, else the general kernel (both enqueued, the matrix maximum decides)

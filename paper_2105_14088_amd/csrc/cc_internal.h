@@ -84,10 +84,10 @@ hipError_t launch_2opt_sum_flex(const int32_t* c, int N, int restarts, int32_t* 
 hipError_t launch_2opt_sum_multi(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs,
                                  int32_t* moves, const int32_t* flags, hipStream_t s);
 
-// N = 128 / 192 / 256, max-hop objective (directed or not), max(c) < 2^16: one wavefront per restart, 16-bit matrix in
-// LDS (cc_2opt_multi_max.hip).  Same flags convention.  `tours` must hold the initial tours.
-hipError_t launch_2opt_max_multi(const int32_t* c, int N, bool directed, int restarts, bool with_flip, int32_t* tours,
-                                 int64_t* costs, int32_t* moves, const int32_t* flags, hipStream_t s);
+// Max-hop objective (directed or not), any 4 <= N <= 1024 and any entries: one workgroup per restart
+// (cc_2opt_max_pruned.hip).  `tours` must hold the initial tours.
+hipError_t launch_2opt_max_pruned(const int32_t* c, int N, bool directed, int restarts, bool with_flip, int32_t* tours,
+                                  int64_t* costs, int32_t* moves, hipStream_t s);
 
 // N = 128 / 192 / 256, directed ring sum: one wavefront per restart, 16-bit matrix in LDS (cc_2opt_multi_dsum.hip).
 // Runs when flags[0] (the matrix maximum) is below dsum_multi_limit(N), so that its 32-bit keys hold every partial
