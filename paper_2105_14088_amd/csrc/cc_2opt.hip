@@ -385,7 +385,15 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
             e = launch_init_tours(N, 0, restarts, seed, tours, s);
             if (e != hipSuccess) return e;
         }
-        if (objective == 0 && (N == 128 || N == 192 || N == 256)) {
+        // Ring sum: scoring only the moves that can win pays from N = 129 on (N = 140 1.6 to 2.6 times, N = 240 2.2 to 4.7
+        // times, N = 1000 45 times), and from about 1500 restarts on at N = 97 .. 127 (1.2 to 1.7 times).  Below, and at
+        // 192 and 256 between 257 and 1024 restarts (0.7 and 0.96 times), where its restarts have one wavefront each and
+        // that wavefront a SIMD to itself, the exhaustive kernels' shorter sweeps win.
+        const bool pruned = N > 256 || (N > 128 && !((N == 192 || N == 256) && restarts > 256 && restarts <= 1024)) ||
+                            (N > 96 && N < 128 && restarts > 1536);
+        if (objective == 0 && pruned) {
+            e = launch_2opt_sum_pruned(c, N, mat16, restarts, tours, costs, moves, s);
+        } else if (objective == 0 && (N == 128 || N == 192 || N == 256)) {
             // 16-bit LDS matrix path when max(c) < 2^16, else the general kernel: both are enqueued and the
             // matrix maximum, computed on the device, decides which one does the work (no host round trip)
             e = launch_matrix_max(c, N, flags, s);
@@ -397,12 +405,6 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
             e = launch_matrix_max(c, N, flags, s);
             if (e != hipSuccess) return e;
             e = launch_2opt_sum_flex(c, N, restarts, tours, costs, moves, flags, s);
-            if (e != hipSuccess) return e;
-            e = launch_general_objective(c, N, objective, restarts, tours, costs, moves, flags, false, s);
-        } else if (objective == 0 && (N == 512 || N == 1024)) {
-            e = launch_matrix_max(c, N, flags, s);
-            if (e != hipSuccess) return e;
-            e = launch_2opt_sum_n1024(c, N, mat16, restarts, tours, costs, moves, flags, s);
             if (e != hipSuccess) return e;
             e = launch_general_objective(c, N, objective, restarts, tours, costs, moves, flags, false, s);
         } else {

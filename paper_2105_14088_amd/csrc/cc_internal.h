@@ -73,6 +73,10 @@ hipError_t launch_2opt_max_n64(const int32_t* c, int restarts, uint64_t seed, bo
 hipError_t launch_2opt_dsum_n64(const int32_t* c, int restarts, uint64_t seed, bool generate, bool with_flip, int32_t* tours,
                                 int64_t* costs, int32_t* moves, const int32_t* flags, hipStream_t s);
 
+// Ring-sum objective, 65 <= N <= 1024 and any entries (cc_2opt_sum_pruned.hip).  `tours` must hold the initial tours;
+// `room`: 2 N^2 bytes of device memory when N > 256 (the workspace's mat16).
+hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
+                                  int32_t* moves, hipStream_t s);
 // N = 128 / 192 / 256, ring-sum objective, max(c) < 2^16: one wavefront per restart, 16-bit matrix in LDS
 // (cc_2opt_multi.hip).  launch_matrix_max writes max(c) to flags[0]; the kernel returns at once if
 // flags[0] >= 2^16.  `tours` must hold the initial tours.
@@ -95,11 +99,6 @@ hipError_t launch_2opt_max_pruned(const int32_t* c, int N, bool directed, int re
 __host__ __device__ constexpr int dsum_multi_limit(int N) { return (1 << 22) / (N + 2); }
 hipError_t launch_2opt_dsum_multi(const int32_t* c, int N, int restarts, bool with_flip, int32_t* tours, int64_t* costs,
                                   int32_t* moves, const int32_t* flags, hipStream_t s);
-
-// N = 512 or 1024, ring-sum objective, max(c) < 2^16: one workgroup of N/64 waves per restart, matrix rows
-// streamed through LDS (cc_2opt_n1024.hip).  Same flags convention as above.
-hipError_t launch_2opt_sum_n1024(const int32_t* c, int N, uint16_t* c16, int restarts, int32_t* tours, int64_t* costs,
-                                 int32_t* moves, const int32_t* flags, hipStream_t s);
 
 // Pair-swap descent under the halving-doubling model for `restarts` tours (cc_rdswap.hip); same tour
 // convention as launch_2opt.  The best-of-restarts step is launch_best_restart.

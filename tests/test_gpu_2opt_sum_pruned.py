@@ -1,0 +1,46 @@
+"""GPU parity of the pruned ring-sum descents: both launch forms at the edges of their sizes, entries on both sides of
+2^16 (16-bit matrix in LDS or not), ties, rows whose partners outgrow the lists, and orders that are no permutation."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2105_14088_amd as cc
+from gen import COST_MAX, hierarchical_matrix, random_matrix
+from gpu_util import assert_search_equal, dev, gpu_search, say
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
+
+
+@pytest.mark.parametrize("n", [129, 192, 193, 255, 256, 257, 320, 321, 449, 513, 641, 769])
+def test_pruned_ring_sum_equals_the_exhaustive_sweep(n):
+    restarts = 5 if n <= 321 else 2
+    for hi, tag in ((COST_MAX, "entries up to COST_MAX"), (65535, "16-bit entries"), (4, "ties")):
+        say(f"pruned ring sum N={n} {tag} R={restarts}")
+        c = random_matrix(n, 40 + n + hi % 83, symmetric=True, lo=0, hi=hi)
+        assert_search_equal(gpu_search(c, oracle.SUM, restarts, n), oracle.search(c, oracle.SUM, restarts, n))
+
+
+@pytest.mark.parametrize("n,restarts", [(98, 1600), (127, 1601), (130, 700), (192, 1100)])
+def test_one_wavefront_per_restart(n, restarts):
+    for c, tag in ((random_matrix(n, n, symmetric=True, lo=1, hi=70000), "uniform, beyond 2^16"),
+                   (hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n), "racks")):
+        say(f"pruned ring sum N={n} R={restarts} {tag} (every 50th restart and the winner compared)")
+        got = gpu_search(c, oracle.SUM, restarts, 9)
+        for r in range(0, restarts, 50):
+            costs, tours, moves = oracle.restarts(c, oracle.SUM, 9, r, r + 1)
+            assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0]
+            assert np.array_equal(got["tours"][r], tours[0])
+        k = int(np.argmin(got["costs"]))
+        assert got["best_restart"] == k and got["best_cost"] == got["costs"][k]
+
+
+@pytest.mark.parametrize("n", [150, 400])
+def test_orders_that_are_no_permutation_end(n):
+    say(f"pruned ring sum N={n}: orders that are no permutation")
+    rng = np.random.default_rng(5)
+    init = rng.integers(-5, n + 5, size=(3, n)).astype(np.int32)
+    c = random_matrix(n, 18, symmetric=True, lo=0, hi=30)
+    got = gpu_search(c, oracle.SUM, 3, 1, init)
+    clamped = np.clip(init, 0, n - 1)
+    assert (got["costs"] <= [oracle.ring_cost(c, t) for t in clamped]).all()
