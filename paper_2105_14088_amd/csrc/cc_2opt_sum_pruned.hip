@@ -33,110 +33,18 @@
 
 #include "cc_device.h"
 #include "cc_internal.h"
+#include "cc_pruned.h"
 
 namespace cc {
 using namespace ccd;
 
 namespace {
 
-constexpr int kCostMax = (1 << 21) - 1;
-constexpr int kNone = 0x7fffffff;
-constexpr int kBuckets = 128;           // the last one is open: it and everything beyond
-constexpr int kRoom = 512;              // candidates of 64 nodes laid out at a time, N <= 256
-constexpr int kGroupRoom = 1024;        // and above
-constexpr int kPassed = 320;            // candidates whose bracket passed: four times 64 and a rest below 64
-
-__device__ __forceinline__ int bucket_of(int cost) { return (int)(__float_as_uint((float)cost) >> 19); }
-
-__device__ __forceinline__ int wave_prefix_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // row_bcast:31
-    return v;
-}
-// unsigned: 0, what a lane without a source reads, is then the maximum's neutral element and a step is one instruction
-__device__ __forceinline__ unsigned wave_prefix_max(unsigned v) {
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
-    return v;
-}
-__device__ __forceinline__ int lanes_below(unsigned long long mask) {
-    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
-}
-__device__ __forceinline__ int entry(const int32_t* __restrict__ c, int N, int x, int y) {
-    return clampi(c[min(x, y) * N + max(x, y)], 0, kCostMax);
-}
-// Where a descent looks entries up: the caller's matrix, or both triangles as 16-bit entries in LDS.
-struct CallersMatrix {
-    const int32_t* c;
-    int N;
-    __device__ __forceinline__ int operator()(int x, int y) const { return entry(c, N, x, y); }
-};
-struct LdsMatrix {
-    const uint16_t* m;
-    int N;
-    __device__ __forceinline__ int operator()(int x, int y) const { return m[x * N + y]; }
-};
-
-// Makes the list of node x with one wavefront: list[0 .. M): cost << 10 | node, counts[b]: partners up to bucket b (the
-// last one N - 1).  Returns the bucket of the smallest cost; row_max: the largest cost.  hist: kBuckets words of LDS of
-// this wave.  each(y, cost): every entry of the row.
-template <int E, typename COUNT, class EACH>
-__device__ __forceinline__ int make_list(const int32_t* __restrict__ c, int N, int x, int M, uint32_t* list, COUNT* counts,
-                                         int* hist, int lane, int& row_max, EACH each) {
-    int cost[E], low = kNone, high = 0;
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-        const int y = lane + 64 * k;
-        const bool in = y < N && y != x;
-        cost[k] = in ? entry(c, N, x, y) : -1;
-        low = min(low, in ? cost[k] : kNone);
-        high = max(high, cost[k]);
-    }
-    const int base = bucket_of(wave_min(low));
-    row_max = wave_max(high);
-    static_assert(kBuckets == 128, "two buckets per lane");
-    hist[lane] = hist[lane + 64] = 0;
-    __builtin_amdgcn_wave_barrier();
-    int at[E];
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-        at[k] = cost[k] >= 0 ? atomicAdd(&hist[min(bucket_of(cost[k]) - base, kBuckets - 1)], 1) : 0;
-        if (lane + 64 * k < N) each(lane + 64 * k, max(cost[k], 0));
-    }
-    __builtin_amdgcn_wave_barrier();
-    const int here0 = hist[2 * lane], here1 = hist[2 * lane + 1], up_to = wave_prefix_sum(here0 + here1);
-    counts[2 * lane] = (COUNT)(up_to - here1);
-    counts[2 * lane + 1] = (COUNT)up_to;
-    __builtin_amdgcn_wave_barrier();
-    hist[2 * lane] = up_to - here1 - here0;
-    hist[2 * lane + 1] = up_to - here1;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int k = 0; k < E; ++k)
-        if (cost[k] >= 0) {
-            const int i = hist[min(bucket_of(cost[k]) - base, kBuckets - 1)] + at[k];
-            if (i < M) list[i] = ((unsigned)cost[k] << 10) | (unsigned)(lane + 64 * k);
-        }
-    __builtin_amdgcn_wave_barrier();
-    return base;
-}
+using namespace pruned;
 
 // LDS of one restart (WAVES wavefronts): per node {hop into it << 10 | its rank, hop out of it}, the nodes of the ranks
 // -1 .. N, and per wave the laid out candidates' owners and the candidates whose bracket passed.
 __host__ __device__ constexpr size_t order_bytes(int N) { return ((size_t)N * 8 + (size_t)(N + 2) * 2 + 15) & ~(size_t)15; }
-__host__ __device__ constexpr size_t wave_bytes(int room) { return (size_t)room * 2 + kPassed * 4; }
-// LDS the restarts of a workgroup share: lists, counts, bases, matrix
-__host__ __device__ constexpr size_t shared_bytes(int N, int M, int lds_matrix) {
-    return ((size_t)N * (M * 4 + kBuckets + 2 + (lds_matrix ? 2 * N : 0)) + 15) & ~(size_t)15;
-}
 
 // One descent.  The bucket of a node's smallest cost is base0 (one node per lane) or bases[node].  Wave `wv` of the restart owns the nodes 64 * (wv * K + k) + lane.
 template <int WAVES, int K, int ROOM, typename COUNT, class MAT>
@@ -520,54 +428,36 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_sum_pruned_group_kernel(con
 }
 
 template <int K, int WAVES>
-hipError_t launch_lds(const int32_t* c, int N, int M, int lds_matrix, int waves, int restarts, int32_t* tours, int64_t* costs,
+hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, int restarts, int32_t* tours, int64_t* costs,
                       int32_t* moves, hipStream_t s) {
-    const size_t shared = shared_bytes(N, M, lds_matrix);
-    // at least eight wavefronts make the lists
-    const int makers = waves > 8 ? waves : 8;
-    size_t lds = shared + (WAVES > 1 ? order_bytes(N) + WAVES * wave_bytes(kRoom) : (order_bytes(N) + wave_bytes(kRoom)) * (size_t)waves);
-    if (lds < shared + (size_t)makers * kBuckets * 4) lds = shared + (size_t)makers * kBuckets * 4;
     hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<K, WAVES>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.bytes);
     if (e != hipSuccess) return e;
-    const int grid = WAVES > 1 ? restarts : (restarts + waves - 1) / waves;
-    hipLaunchKernelGGL((twoopt_sum_pruned_kernel<K, WAVES>), dim3(grid), dim3(64 * makers), lds, s, c, N, M, lds_matrix, waves,
-                       restarts, tours, costs, moves);
+    const int grid = WAVES > 1 ? restarts : (restarts + plan.waves - 1) / plan.waves;
+    hipLaunchKernelGGL((twoopt_sum_pruned_kernel<K, WAVES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
+                       s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves);
     return hipGetLastError();
 }
 
 template <int K>
 hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                         hipStream_t s) {
-    constexpr size_t kLds = 160 * 1024 - 1024;
-    const int M = N <= 128 ? (N - 1 < 64 ? N - 1 : 64) : 48;
-    const size_t slice = order_bytes(N) + wave_bytes(kRoom);
-    if (K > 1) {
-        // few restarts: K wavefronts for each, as long as all workgroups are resident at once
-        const int lds_matrix = shared_bytes(N, M, 1) + order_bytes(N) + K * wave_bytes(kRoom) <= kLds ? 1 : 0;
-        const size_t each = shared_bytes(N, M, lds_matrix) + order_bytes(N) + K * wave_bytes(kRoom);
-        if (restarts <= 256 * (int)(kLds / each > 2 ? 2 : kLds / each))
-            return launch_lds<1, K>(c, N, M, lds_matrix, K, restarts, tours, costs, moves, s);
-    }
-    // up to 16 restarts share one copy of the lists, but no more than keeps all 256 compute units busy
-    int waves = (restarts + 255) / 256;
-    waves = waves > 16 ? 16 : waves;
-    const int lds_matrix = shared_bytes(N, M, 1) + slice * (size_t)waves <= kLds ? 1 : 0;
-    const int fit = (int)((kLds - shared_bytes(N, M, lds_matrix)) / slice);
-    waves = waves > fit ? fit : waves;
-    return launch_lds<K, 1>(c, N, M, lds_matrix, waves, restarts, tours, costs, moves, s);
+    const LdsPlan plan = lds_plan(N, K, restarts, order_bytes(N));
+    return plan.together ? launch_lds<1, K>(c, N, plan, restarts, tours, costs, moves, s)
+                         : launch_lds<K, 1>(c, N, plan, restarts, tours, costs, moves, s);
 }
 
 template <int WAVES>
 hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                         hipStream_t s) {
-    const int M = group_list(N);
-    uint32_t* lists = (uint32_t*)room;
-    uint16_t* counts = (uint16_t*)(lists + (size_t)N * M);
-    hipLaunchKernelGGL(partner_lists_kernel, dim3((N + 3) / 4), dim3(256), 0, s, c, N, M, lists, counts);
+    int M;
+    const uint32_t* lists;
+    const uint16_t* counts;
+    hipError_t e = launch_partner_lists(c, N, room, M, lists, counts, s);
+    if (e != hipSuccess) return e;
     const size_t lds = order_bytes(N) + WAVES * wave_bytes(kGroupRoom);
-    hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((twoopt_sum_pruned_group_kernel<WAVES>), dim3(restarts), dim3(64 * WAVES), lds, s, c, N, M, lists,
                        counts, tours, costs, moves);
@@ -575,6 +465,15 @@ hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32
 }
 
 }  // namespace
+
+hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
+                                hipStream_t s) {
+    M = group_list(N);
+    lists = (const uint32_t*)room;
+    counts = (const uint16_t*)(lists + (size_t)N * M);
+    hipLaunchKernelGGL(partner_lists_kernel, dim3((N + 3) / 4), dim3(256), 0, s, c, N, M, (uint32_t*)lists, (uint16_t*)counts);
+    return hipGetLastError();
+}
 
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
                                   int32_t* moves, hipStream_t s) {

@@ -45,24 +45,47 @@ __device__ __forceinline__ int add3(int a, int b, int c) {
 // id = i*n + j < n*n reverses ranks i .. j; id = n*n + (variant*n + s)*n + g takes the L ranks s .. s+L-1 out and
 // puts them back, kept or reversed, behind the node of rank g (variant 0: L = 1; 1, 2: L = 2; 3, 4: L = 3; even
 // variants above 0 reverse the segment).
-__device__ __forceinline__ int move_source(int p, int id, int n) {
-    if (id < n * n) {
-        const int i = id / n, j = id - i * n;
-        return (p >= i && p <= j) ? i + j - p : p;
+// MoveSource takes the id apart once for the ranks of a lane.
+struct MoveSource {
+    int first, last, shift;      // ranks first .. last take their nodes from elsewhere
+    int from, to;                // of these, from .. to are the segment (or the reversed span); the others move by shift
+    int a, b;                    // rank of the span -> source a + b * rank
+    __device__ __forceinline__ MoveSource(int id, int n) {
+        if (id < n * n) {
+            const int i = id / n, j = id - i * n;
+            first = from = i;
+            last = to = j;
+            shift = 0;
+            a = i + j;
+            b = -1;
+            return;
+        }
+        const int x = id - n * n;
+        const int row = x / n, g = x - row * n, variant = row / n, s = row - variant * n;
+        const int L = variant == 0 ? 1 : (variant + 3) >> 1;
+        const bool rev = variant != 0 && (variant & 1) == 0;
+        if (g > s) {                               // towards higher ranks: the segment ends at rank g
+            first = s;
+            last = g;
+            from = g - L + 1;
+            to = g;
+            shift = L;
+        } else {                                   // towards lower ranks: it starts behind rank g
+            first = g + 1;
+            last = s + L - 1;
+            from = g + 1;
+            to = g + L;
+            shift = -L;
+        }
+        a = rev ? s + L - 1 + from : s - from;
+        b = rev ? -1 : 1;
     }
-    const int x = id - n * n;
-    const int g = x % n, s = (x / n) % n, variant = x / (n * n);
-    const int L = variant == 0 ? 1 : (variant + 3) >> 1;
-    const bool rev = variant != 0 && (variant & 1) == 0;
-    if (g > s) {                                   // towards higher ranks: the segment ends at rank g
-        if (p >= s && p <= g - L) return p + L;
-        if (p > g - L && p <= g) return rev ? s + L - 1 - (p - (g - L + 1)) : s + (p - (g - L + 1));
-    } else {                                       // towards lower ranks: it starts behind rank g
-        if (p > g && p <= g + L) return rev ? s + L - 1 - (p - (g + 1)) : s + (p - (g + 1));
-        if (p > g + L && p <= s + L - 1) return p - L;
+    __device__ __forceinline__ int operator()(int p) const {
+        const int moved = p >= from && p <= to ? a + b * p : p + shift;
+        return p >= first && p <= last ? moved : p;
     }
-    return p;
-}
+};
+__device__ __forceinline__ int move_source(int p, int id, int n) { return MoveSource(id, n)(p); }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 

@@ -51,7 +51,7 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
 // Descent over segment insertions, with or without the 2-opt moves, ring-sum objective (cc_local.hip).  `tours`
 // must hold the initial tours.
 hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int restarts, int32_t* tours,
-                                   int64_t* costs, int32_t* moves, int32_t* flags, hipStream_t s);
+                                   int64_t* costs, int32_t* moves, int32_t* flags, void* room, hipStream_t s);
 // The same search for N = 64 and max(c) < 2^16, one wavefront per restart (cc_local_n64.hip); returns at once if
 // flags[0] >= 2^16 (flags[0] = matrix maximum, launch_matrix_max).
 // N = 128 / 192 / 256, several ranks per lane, 16-bit matrix in LDS (cc_local_multi.hip); same flags convention.
@@ -77,6 +77,12 @@ hipError_t launch_2opt_dsum_n64(const int32_t* c, int restarts, uint64_t seed, b
 // `room`: 2 N^2 bytes of device memory when N > 256 (the workspace's mat16).
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
                                   int32_t* moves, hipStream_t s);
+// Partner lists of all nodes for N > 256, written into `room` (2 N^2 bytes): M entries per list, where lists and counts lie.
+hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
+                                hipStream_t s);
+// Segment insertions, with or without 2-opt, any 4 <= N <= 1024 (cc_local_pruned.hip); same conventions.
+hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, int restarts, int32_t* tours,
+                               int64_t* costs, int32_t* moves, hipStream_t s);
 // N = 128 / 192 / 256, ring-sum objective, max(c) < 2^16: one wavefront per restart, 16-bit matrix in LDS
 // (cc_2opt_multi.hip).  launch_matrix_max writes max(c) to flags[0]; the kernel returns at once if
 // flags[0] >= 2^16.  `tours` must hold the initial tours.

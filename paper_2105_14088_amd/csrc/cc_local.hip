@@ -168,10 +168,17 @@ hipError_t launch_insertion(const int32_t* c, int N, int restarts, int32_t* tour
 }  // namespace
 
 hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int restarts, int32_t* tours,
-                                   int64_t* costs, int32_t* moves, int32_t* flags, hipStream_t s) {
+                                   int64_t* costs, int32_t* moves, int32_t* flags, void* room, hipStream_t s) {
     const int32_t* skip = nullptr;
+    const bool multi = N == 128 || N == 192 || N == 256;
     if (force_general_path()) {
         // pinned: the kernel below for every size
+    } else if (N >= 9 && N != 64 &&
+               (!multi || (restarts <= 256 && (with_2opt || N > 128)) || (restarts <= 512 && with_2opt && N < 256))) {
+        // only the moves that can win: against the kernel above 1.1 (N = 10) to 3 times (N = 63) to 40 times (N = 1000) as
+        // fast; against the exhaustive wavefront kernels at 128 / 192 / 256 as long as every restart has N / 64 wavefronts to
+        // itself (1.2 to 3 times; beyond that 0.4 to 1)
+        return launch_local_pruned(c, N, with_2opt, room, restarts, tours, costs, moves, s);
     } else if (N == 64) {
         // one wavefront per restart with 32-bit keys when max(c) < 2^16, else the kernel above: both are enqueued
         // and the matrix maximum, computed on the device, decides which of them does the work
@@ -180,7 +187,7 @@ hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int 
         e = launch_local_n64(c, with_2opt, restarts, tours, costs, moves, flags, s);
         if (e != hipSuccess) return e;
         skip = flags;
-    } else if (N == 128 || N == 192 || N == 256) {
+    } else if (multi) {
         hipError_t e = launch_matrix_max(c, N, flags, s);
         if (e != hipSuccess) return e;
         e = launch_local_multi(c, N, with_2opt, restarts, tours, costs, moves, flags, s);

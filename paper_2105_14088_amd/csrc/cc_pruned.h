@@ -1,0 +1,161 @@
+// What the pruned descents (cc_2opt_sum_pruned.hip, cc_local_pruned.hip) share: partner lists by cost, matrix access,
+// wave prefixes.
+#pragma once
+#include "cc_device.h"
+
+namespace cc {
+namespace pruned {
+using namespace ccd;
+
+constexpr int kCostMax = (1 << 21) - 1;
+constexpr int kNone = 0x7fffffff;
+constexpr int kBuckets = 128;           // the last one is open: it and everything beyond
+constexpr int kRoom = 512;              // candidates of 64 nodes laid out at a time, N <= 256
+constexpr int kGroupRoom = 1024;        // and above
+constexpr int kPassed = 320;            // candidates whose bracket passed: four times 64 and a rest below 64
+
+__device__ __forceinline__ int bucket_of(int cost) { return (int)(__float_as_uint((float)cost) >> 19); }
+
+__device__ __forceinline__ int wave_prefix_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // row_bcast:31
+    return v;
+}
+// unsigned: 0, what a lane without a source reads, is then the maximum's neutral element and a step is one instruction
+__device__ __forceinline__ unsigned wave_prefix_max(unsigned v) {
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+__device__ __forceinline__ int lanes_below(unsigned long long mask) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+}
+__device__ __forceinline__ int entry(const int32_t* __restrict__ c, int N, int x, int y) {
+    return clampi(c[min(x, y) * N + max(x, y)], 0, kCostMax);
+}
+// Where a descent looks entries up: the caller's matrix, or both triangles as 16-bit entries in LDS.
+struct CallersMatrix {
+    const int32_t* c;
+    int N;
+    __device__ __forceinline__ int operator()(int x, int y) const { return entry(c, N, x, y); }
+};
+struct LdsMatrix {
+    const uint16_t* m;
+    int N;
+    __device__ __forceinline__ int operator()(int x, int y) const { return m[x * N + y]; }
+};
+
+// Makes the list of node x with one wavefront: list[0 .. M): cost << 10 | node, counts[b]: partners up to bucket b (the
+// last one N - 1).  Returns the bucket of the smallest cost; row_max: the largest cost.  hist: kBuckets words of LDS of
+// this wave.  each(y, cost): every entry of the row.
+template <int E, typename COUNT, class EACH>
+__device__ __forceinline__ int make_list(const int32_t* __restrict__ c, int N, int x, int M, uint32_t* list, COUNT* counts,
+                                         int* hist, int lane, int& row_max, EACH each) {
+    int cost[E], low = kNone, high = 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        const int y = lane + 64 * k;
+        const bool in = y < N && y != x;
+        cost[k] = in ? entry(c, N, x, y) : -1;
+        low = min(low, in ? cost[k] : kNone);
+        high = max(high, cost[k]);
+    }
+    const int base = bucket_of(wave_min(low));
+    row_max = wave_max(high);
+    static_assert(kBuckets == 128, "two buckets per lane");
+    hist[lane] = hist[lane + 64] = 0;
+    __builtin_amdgcn_wave_barrier();
+    int at[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        at[k] = cost[k] >= 0 ? atomicAdd(&hist[min(bucket_of(cost[k]) - base, kBuckets - 1)], 1) : 0;
+        if (lane + 64 * k < N) each(lane + 64 * k, max(cost[k], 0));
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int here0 = hist[2 * lane], here1 = hist[2 * lane + 1], up_to = wave_prefix_sum(here0 + here1);
+    counts[2 * lane] = (COUNT)(up_to - here1);
+    counts[2 * lane + 1] = (COUNT)up_to;
+    __builtin_amdgcn_wave_barrier();
+    hist[2 * lane] = up_to - here1 - here0;
+    hist[2 * lane + 1] = up_to - here1;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < E; ++k)
+        if (cost[k] >= 0) {
+            const int i = hist[min(bucket_of(cost[k]) - base, kBuckets - 1)] + at[k];
+            if (i < M) list[i] = ((unsigned)cost[k] << 10) | (unsigned)(lane + 64 * k);
+        }
+    __builtin_amdgcn_wave_barrier();
+    return base;
+}
+
+// LDS the restarts of a workgroup share (N <= 256): lists, counts, bases, matrix
+__host__ __device__ constexpr size_t shared_bytes(int N, int M, int lds_matrix) {
+    return ((size_t)N * (M * 4 + kBuckets + 2 + (lds_matrix ? 2 * N : 0)) + 15) & ~(size_t)15;
+}
+__host__ __device__ constexpr size_t wave_bytes(int room) { return (size_t)room * 2 + kPassed * 4; }
+
+// How the restarts of a search with N <= 64 K share the chip.
+struct LdsPlan {
+    int waves;              // wavefronts with work per workgroup
+    bool together;          // they share one restart
+    int M, lds_matrix;      // list length, matrix in LDS
+    size_t bytes;           // LDS per workgroup
+};
+// order_bytes: LDS of one restart's order.  Up to 512 restarts, K wavefronts per restart, one or two workgroups per
+// compute unit (a sweep then takes a third to a half of the time that one wavefront needs); beyond that one wavefront per
+// restart, up to 16 around one copy of the lists, but no more than keeps all 256 compute units busy (four workgroups of
+// K wavefronts per unit were slower: their lists are short and made four times).
+// Lists of less than 32 partners would send too many nodes to the scan against every node; beyond 96 they add nothing.
+inline LdsPlan lds_plan(int N, int K, int restarts, size_t order_bytes) {
+    constexpr size_t kLds = 160 * 1024 - 1024;
+    LdsPlan p;
+    const int per_unit = (restarts + 255) / 256;
+    auto longest = [&](size_t room, int lds_matrix) {
+        const size_t fixed = shared_bytes(N, 0, lds_matrix);
+        const int m = room > fixed ? (int)((room - fixed) / ((size_t)N * 4)) : 0;
+        return m < 96 ? m : 96;
+    };
+    auto finish = [&](size_t state) {
+        p.M = p.M < N - 1 ? p.M : N - 1;
+        p.bytes = shared_bytes(N, p.M, p.lds_matrix) + state;
+        // at least eight wavefronts make the lists, with a histogram each
+        const size_t makers = shared_bytes(N, p.M, p.lds_matrix) + (size_t)(p.waves > 8 ? p.waves : 8) * kBuckets * 4;
+        p.bytes = p.bytes < makers ? makers : p.bytes;
+    };
+    if (K > 1 && per_unit <= 2) {
+        const size_t state = order_bytes + K * wave_bytes(kRoom), room = kLds / per_unit - 512 > state ? kLds / per_unit - 512 - state : 0;
+        p.together = true;
+        p.waves = K;
+        for (p.lds_matrix = 1; p.lds_matrix >= 0; --p.lds_matrix) {
+            p.M = longest(room, p.lds_matrix);
+            if (p.M >= (p.lds_matrix ? 64 : 32) || p.M >= N - 1) {
+                finish(state);
+                return p;
+            }
+        }
+    }
+    p.together = false;
+    p.M = N <= 128 ? 64 : 48;
+    p.waves = per_unit < 16 ? per_unit : 16;
+    const size_t slice = order_bytes + wave_bytes(kRoom);
+    p.M = p.M < N - 1 ? p.M : N - 1;
+    p.lds_matrix = shared_bytes(N, p.M, 1) + slice * (size_t)p.waves <= kLds ? 1 : 0;
+    const int fit = (int)((kLds - shared_bytes(N, p.M, p.lds_matrix)) / slice);
+    p.waves = p.waves < fit ? p.waves : fit;
+    const int more = longest(kLds - slice * (size_t)p.waves, p.lds_matrix);
+    p.M = more > p.M ? more : p.M;
+    finish(slice * (size_t)p.waves);
+    return p;
+}
+
+}  // namespace pruned
+}  // namespace cc

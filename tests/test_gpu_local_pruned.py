@@ -1,0 +1,52 @@
+"""GPU parity of the pruned insertion descents, with and without 2-opt, at the edges of their launch shapes: every restart
+with several wavefronts, with one, and a workgroup per restart; ties, entries beyond 2^16, orders that are no
+permutation."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2105_14088_amd as cc
+from gen import COST_MAX, random_matrix
+from gpu_util import dev, say
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
+BOTH, INSERTION = cc.CC_MOVES_2OPT | cc.CC_MOVES_OROPT, cc.CC_MOVES_OROPT
+
+
+def check(c, classes, restarts, seed, sample):
+    b = cc.cc_local_search_ex(dev(c), cc.CC_RING_SUM, classes, restarts, seed)
+    torch.cuda.synchronize()
+    costs, tours, moves = b.restart_costs.cpu().numpy(), b.restart_tours.cpu().numpy(), b.restart_moves.cpu().numpy()
+    for r in sample:
+        oc, ot, om = oracle.local_restarts(c, oracle.SUM, classes, seed, r, r + 1)
+        assert costs[r] == oc[0] and moves[r] == om[0] and np.array_equal(tours[r], ot[0])
+    k = int(np.argmin(costs))
+    assert int(b.best_restart.item()) == k and int(b.best_cost.item()) == costs[k]
+    assert np.array_equal(b.best_perm.cpu().numpy(), tours[k])
+
+
+@pytest.mark.parametrize("n", [9, 10, 63, 65, 127, 129, 193, 255, 256, 257, 321, 385])
+@pytest.mark.parametrize("classes", [BOTH, INSERTION])
+def test_pruned_insertion_equals_the_exhaustive_sweep(n, classes):
+    restarts = 20 if n < 64 else 4 if n < 200 else 2
+    for hi in (COST_MAX, 65535, 3) if n < 256 else (70000, 3):
+        say(f"pruned insertion N={n} classes={classes} entries<={hi} R={restarts}")
+        check(random_matrix(n, 30 + n + hi % 79, symmetric=True, lo=0, hi=hi), classes, restarts, n, range(restarts))
+
+
+@pytest.mark.parametrize("n,restarts", [(33, 3000), (80, 1100), (150, 520), (130, 400)])
+def test_restarts_that_share_a_workgroup(n, restarts):
+    say(f"pruned insertion N={n} R={restarts}: nine restarts and the winner compared")
+    check(random_matrix(n, n, symmetric=True, lo=1, hi=4000), BOTH, restarts, 5, np.linspace(0, restarts - 1, 9).astype(int))
+
+
+@pytest.mark.parametrize("n", [40, 150, 300])
+def test_orders_that_are_no_permutation_end(n):
+    say(f"pruned insertion N={n}: orders that are no permutation")
+    init = np.random.default_rng(6).integers(-5, n + 5, size=(3, n)).astype(np.int32)
+    c = random_matrix(n, 18, symmetric=True, lo=0, hi=30)
+    b = cc.cc_local_search_ex(dev(c), cc.CC_RING_SUM, BOTH, 3, 1, init_tours=dev(init))
+    torch.cuda.synchronize()
+    clamped = np.clip(init, 0, n - 1)
+    assert (b.restart_costs.cpu().numpy() <= [oracle.ring_cost(c, t) for t in clamped]).all()
