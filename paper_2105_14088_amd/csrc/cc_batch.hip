@@ -673,7 +673,7 @@ static hipError_t rd_launch(const int32_t* c, int N, const int32_t* weights, con
     return hipGetLastError();
 }
 
-// N = 128 .. 1024 on a folded 16-bit copy of the matrix, folded[x][y] = max(c[x][y], c[y][x]) (fold_to_u16_kernel): a
+// N = 128, 256 (small batches) on a folded 16-bit copy of the matrix, folded[x][y] = max(c[x][y], c[y][x]) (fold_to_u16_kernel): a
 // link, the two ranks i and i xor 2^k, is one look-up by one lane instead of one per end, so a round is N / 2
 // scattered L2 requests instead of N - and that request rate is what bounds this kernel.  One wave per order, the
 // order parked in LDS; every lane first takes the maximum over its links of every round (all gathers independent),
@@ -821,6 +821,238 @@ __global__ __launch_bounds__(1024) void links_batch_lds16_kernel(const int32_t* 
     }
 }
 
+// N = 512, 1024 with a workspace: a round costs its largest link, so only links among the largest entries have to be
+// looked up exactly.  mark_links_kernel writes one bit per pair of nodes, "the larger direction costs T or more" (128 KiB
+// at N = 1024, which fits LDS; the 16-bit folded matrix, 2 MiB, does not); T is chosen so that about ln(N / 2) of a
+// round's N / 2 links carry the bit, from the same 4096 sampled entries in every workgroup (about where the exact
+// look-ups and the rounds without a marked link, whose links are all looked up, cost the same number of requests).
+// Any T gives the right result, only the time depends on it.  Word (y >> 5) * N + x holds the pairs of x with the
+// nodes y & ~31 .. y | 31.  tops[workgroup] = largest entry seen, for the early end in rd_batch_marked_kernel.
+template <int LOGN>
+__global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restrict__ c, uint32_t* __restrict__ marks,
+                                                          int32_t* __restrict__ tops) {
+    constexpr int N = 1 << LOGN, kSamples = 4096, kMarkedPerRound = LOGN == 10 ? 6 : 5;
+    constexpr int kWanted = kSamples * kMarkedPerRound / (N / 2);               // samples at or above T
+    __shared__ int count[2][16];
+    __shared__ int wave_top[16];
+    const int lane = lane_id(), wv = threadIdx.x >> 6;
+    auto entry = [&](int x, int y) { return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1); };
+    int v[kSamples / 1024];
+#pragma unroll
+    for (int i = 0; i < kSamples / 1024; ++i) {
+        const uint32_t h = (uint32_t)splitmix64_at(0, (uint64_t)(threadIdx.x + 1024 * i + 1));
+        const int x = h & (N - 1), y = (h >> LOGN) & (N - 1);
+        v[i] = entry(x, x == y ? y ^ 1 : y);
+    }
+    int T = 0;                                     // largest value that kWanted samples reach
+    for (int bit = 20; bit >= 0; --bit) {
+        const int t = T | (1 << bit);
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < kSamples / 1024; ++i) n += __popcll(__ballot(v[i] >= t));
+        if (lane == 0) count[bit & 1][wv] = n;
+        __syncthreads();                           // two buffers: the next bit's counts never meet this bit's reads
+        int all = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) all += count[bit & 1][k];
+        if (all >= kWanted) T = t;
+    }
+    const int w = blockIdx.x * 1024 + threadIdx.x, x = w & (N - 1), y0 = (w >> LOGN) * 32;
+    uint32_t bits = 0;
+    int top = 0;
+#pragma unroll 8
+    for (int k = 0; k < 32; ++k) {
+        const int e = entry(x, y0 + k);
+        top = max(top, e);
+        bits |= (uint32_t)(e >= T) << k;
+    }
+    marks[w] = bits;
+    top = wave_max(top);
+    if (lane == 0) wave_top[wv] = top;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < 16; ++k) top = max(top, wave_top[k]);
+        tops[blockIdx.x] = top;
+    }
+}
+
+// Lane l <- lane l xor 2^M of its own `v` (M = 0 .. 3: within a row of 16 lanes).
+template <int M>
+__device__ __forceinline__ unsigned from_lane_xor(unsigned v) {
+    const int s = (int)v;
+    if (M == 0) return (unsigned)__builtin_amdgcn_update_dpp(s, s, 0xB1, 0xf, 0xf, true);          // quad_perm 1,0,3,2
+    if (M == 1) return (unsigned)__builtin_amdgcn_update_dpp(s, s, 0x4E, 0xf, 0xf, true);          // quad_perm 2,3,0,1
+    if (M == 3) return (unsigned)__builtin_amdgcn_update_dpp(s, s, 0x128, 0xf, 0xf, true);         // row_ror:8
+    const int r = __builtin_amdgcn_update_dpp(s, s, 0x141, 0xf, 0xf, true);                        // row_half_mirror: xor 7
+    return (unsigned)__builtin_amdgcn_update_dpp(r, r, 0x1B, 0xf, 0xf, true);                      // quad_perm 3,2,1,0: xor 3
+}
+
+// The two ends of the links of ranks that differ in lane bit M, from two registers of ranks: a lane with the bit clear
+// takes the link of register a, a lane with the bit set that of register b, so the 64 lanes hold 64 different links.
+template <int M>
+__device__ __forceinline__ void lane_links(unsigned a, unsigned b, int lane, unsigned& x, unsigned& y) {
+    if constexpr (M >= 4) {
+        const auto r = M == 4 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
+                              : __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        x = r[0];
+        y = r[1];
+    } else {
+        const bool upper = (lane >> M) & 1;
+        x = upper ? b : a;
+        y = from_lane_xor<M>(upper ? a : b);
+    }
+}
+
+// One order per wave, its ranks in registers: lane l holds ranks 256 q + 4 l + j (register 4 q + j), so rounds 0, 1 and
+// 8, 9 pair registers of a lane and rounds 2 .. 7 pair lanes.  Per link two or three VALU instructions bring the ends
+// together and one LDS look-up (random, which with its bank conflicts is the larger half of the time) tells whether it is
+// marked; the marked ones, about 60 of 5120 at N = 1024, are then looked up exactly in the caller's matrix, each lane
+// taking its own one by one, all rounds mixed, their maxima formed in LDS.  A round without a marked link is looked up
+// whole; one that has reached the matrix maximum is finished, so a matrix of few values ends early.
+// Before: rd_batch_folded_kernel, bound by the L2's request rate.  Both launches together, seeded orders: N = 1024,
+// 65536 orders 1384 -> 162 us (1.7 TB/s of the order stream), 1000 orders 105 -> 32 us; N = 512, 131072 orders
+// 1136 -> 161 us, 1000 orders 27 -> 22 us: faster from the smallest batch on, so nothing else serves these sizes.
+template <int LOGN>
+__global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kernel(
+    const int32_t* __restrict__ c, const uint32_t* __restrict__ marks, const int32_t* __restrict__ tops,
+    const int32_t* __restrict__ weights, const int32_t* __restrict__ perms, int64_t B, int64_t* __restrict__ out) {
+    constexpr int N = 1 << LOGN, RK = N / 64, LM = RK / 2, Q = N / 256;         // ranks, links, quads of ranks per lane
+    constexpr int WAVES = LOGN == 10 ? 15 : 16, WORDS = (LM * LOGN + 31) / 32;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_marked[];
+    uint32_t* lmarks = (uint32_t*)smem_marked;                                              // [N * N / 32]
+    uint16_t* order = (uint16_t*)(smem_marked + N * N / 8) + (threadIdx.x >> 6) * N;        // [WAVES][N]
+    int* worst = (int*)(smem_marked + N * N / 8 + sizeof(uint16_t) * WAVES * N) + (threadIdx.x >> 6) * 16;  // [WAVES][16]
+    const int lane = lane_id(), wv = threadIdx.x >> 6;
+    for (int e = threadIdx.x; e < N * N / 128; e += 64 * WAVES) ((int4*)lmarks)[e] = ((const int4*)marks)[e];
+    int top = 0;
+    for (int k = 0; k < N * N / 32 / 1024; ++k) top = max(top, tops[k]);
+    const long long weight =
+        lane < LOGN ? (weights ? (long long)clampi(weights[lane], 0, kMaxRoundWeight) : 1ll) : 0ll;
+    __syncthreads();
+    auto exact = [&](int x, int y) { return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1); };
+    const bool aligned = ((uintptr_t)perms & 15u) == 0;
+    auto load = [&](int64_t b, int4 (&v)[Q]) {
+        const int32_t* pi = perms + b * N + 4 * lane;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (aligned) v[q] = *(const int4*)(pi + 256 * q);
+            else v[q] = make_int4(pi[256 * q], pi[256 * q + 1], pi[256 * q + 2], pi[256 * q + 3]);
+        }
+    };
+    const int64_t nwaves = (int64_t)gridDim.x * WAVES;
+    int64_t b = (int64_t)blockIdx.x * WAVES + wv;
+    int4 v[Q];
+    if (b < B) load(b, v);
+    for (; b < B; b += nwaves) {
+        unsigned X[RK];                                                          // 4 * node
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            X[4 * q] = (unsigned)clampi(v[q].x, 0, N - 1) << 2;
+            X[4 * q + 1] = (unsigned)clampi(v[q].y, 0, N - 1) << 2;
+            X[4 * q + 2] = (unsigned)clampi(v[q].z, 0, N - 1) << 2;
+            X[4 * q + 3] = (unsigned)clampi(v[q].w, 0, N - 1) << 2;
+            const uint2 four = make_uint2(X[4 * q] | X[4 * q + 1] << 16, X[4 * q + 2] | X[4 * q + 3] << 16);
+            __builtin_memcpy(__builtin_assume_aligned(order + 256 * q + 4 * lane, 8), &four, 8);
+        }
+        if (lane < 16) worst[lane] = -1;
+        if (b + nwaves < B) load(b + nwaves, v);
+        uint32_t hits[WORDS] = {};
+        auto test = [&](int at, unsigned x, unsigned y) {
+            const uint32_t word = *(const uint32_t*)((const char*)lmarks + (((y & ~127u) << (LOGN - 5)) | x));
+            hits[at >> 5] |= ((word >> ((y >> 2) & 31)) & 1u) << (at & 31);
+        };
+#pragma unroll
+        for (int u = 0; u < LM; ++u) {
+            unsigned x, y;
+#pragma unroll
+            for (int k = 0; k < LOGN; ++k) {
+                if (k >= 2 && k < 8) continue;
+                const int bit = k < 2 ? k : k - 6;                               // of the register index
+                const int i = ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));
+                test(k * LM + u, X[i], X[i | (1 << bit)]);
+            }
+            lane_links<0>(X[2 * u], X[2 * u + 1], lane, x, y);
+            test(2 * LM + u, x, y);
+            lane_links<1>(X[2 * u], X[2 * u + 1], lane, x, y);
+            test(3 * LM + u, x, y);
+            lane_links<2>(X[2 * u], X[2 * u + 1], lane, x, y);
+            test(4 * LM + u, x, y);
+            lane_links<3>(X[2 * u], X[2 * u + 1], lane, x, y);
+            test(5 * LM + u, x, y);
+            lane_links<4>(X[2 * u], X[2 * u + 1], lane, x, y);
+            test(6 * LM + u, x, y);
+            lane_links<5>(X[2 * u], X[2 * u + 1], lane, x, y);
+            test(7 * LM + u, x, y);
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t finished = 0;
+        for (;;) {
+            uint32_t any = 0;
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) any |= hits[w];
+            if (__ballot(any != 0) == 0) break;
+            if (any) {
+                int at = 0;
+                bool found = false;
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w) {
+                    if (!found && hits[w]) {
+                        at = 32 * w + __builtin_ctz(hits[w]);
+                        hits[w] &= hits[w] - 1;
+                        found = true;
+                    }
+                }
+                const int k = at / LM, u = at % LM, bit = k < 2 ? k : k - 6;
+                const int i = k >= 2 && k < 8 ? 2 * u + ((lane >> (k - 2)) & 1)
+                                              : ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));
+                const int p = 256 * (i >> 2) + 4 * lane + (i & 3);
+                atomicMax(worst + k, exact(order[p] >> 2, order[p ^ (1 << k)] >> 2));
+            }
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t full = (uint32_t)__ballot(lane < LOGN && *(volatile int*)(worst + (lane & 15)) >= top);
+            if (full != finished) {
+                finished = full;
+#pragma unroll
+                for (int at = 0; at < LM * LOGN; at += LM)
+                    if ((full >> (at / LM)) & 1) hits[at >> 5] &= ~(((1u << LM) - 1) << (at & 31));
+            }
+        }
+        int mine = lane < LOGN ? *(volatile int*)(worst + (lane & 15)) : 0;
+        for (uint32_t missing = (uint32_t)__ballot(mine < 0); missing; missing &= missing - 1) {
+            const int k = __builtin_ctz(missing);
+            int t = 0;
+#pragma unroll
+            for (int u = 0; u < LM; ++u) {
+                const int i = lane + 64 * u, p = ((i >> k) << (k + 1)) | (i & ((1 << k) - 1));
+                t = max(t, exact(order[p] >> 2, order[p | (1 << k)] >> 2));
+            }
+            t = wave_max(t);
+            if (lane == k) mine = t;
+        }
+        const long long total = weights ? wave_sum64(weight * mine) : (long long)wave_sum(mine);
+        __builtin_amdgcn_wave_barrier();   // all look-ups done before the slices are overwritten
+        if (lane == 0) out[b] = total;
+    }
+}
+
+template <int LOGN>
+static hipError_t rd_marked_launch(const int32_t* c, void* room, int32_t* tops, const int32_t* weights,
+                                   const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
+    constexpr int N = 1 << LOGN, WAVES = LOGN == 10 ? 15 : 16;
+    const size_t lds = N * N / 8 + sizeof(uint16_t) * WAVES * N + sizeof(int) * WAVES * 16;
+    hipError_t e = hipFuncSetAttribute((const void*)rd_batch_marked_kernel<LOGN>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mark_links_kernel<LOGN>, dim3(N * N / 32 / 1024), dim3(1024), 0, s, c, (uint32_t*)room, tops);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    int64_t blocks = (B + WAVES - 1) / WAVES;
+    if (blocks > 256) blocks = 256;
+    hipLaunchKernelGGL(rd_batch_marked_kernel<LOGN>, dim3((int)blocks), dim3(64 * WAVES), lds, s, c,
+                       (const uint32_t*)room, tops, weights, perms, B, out);
+    return hipGetLastError();
+}
+
 constexpr int64_t kLdsBatchMinOrders = 32768;      // staging a matrix per compute unit pays from here on
 
 template <int LOGN, bool BCUBE4>
@@ -863,16 +1095,16 @@ hipError_t launch_rd_cost_batch(const int32_t* c, int N, const int32_t* weights,
         if (N == 128) return links_lds16_launch<7, false>(c, weights, perms, B, out, s);
         if (N == 256) return links_lds16_launch<8, false>(c, weights, perms, B, out, s);
     }
+    if (flags && folded && N == 512) return rd_marked_launch<9>(c, folded, flags, weights, perms, B, out, s);
+    if (flags && folded && N == 1024) return rd_marked_launch<10>(c, folded, flags, weights, perms, B, out, s);
     const int32_t* skip = nullptr;
     if (flags && folded) {
         // both kernels are enqueued; the matrix maximum, computed on the device, decides which of them works
         hipError_t e = launch_matrix_max(c, N, flags, s);
         if (e == hipSuccess) e = launch_fold_to_u16(c, N, folded, flags, s);
         if (e == hipSuccess)
-            e = N == 128   ? rd_folded_launch<7>(folded, weights, perms, B, out, flags, s)
-                : N == 256 ? rd_folded_launch<8>(folded, weights, perms, B, out, flags, s)
-                : N == 512 ? rd_folded_launch<9>(folded, weights, perms, B, out, flags, s)
-                           : rd_folded_launch<10>(folded, weights, perms, B, out, flags, s);
+            e = N == 128 ? rd_folded_launch<7>(folded, weights, perms, B, out, flags, s)
+                         : rd_folded_launch<8>(folded, weights, perms, B, out, flags, s);
         if (e != hipSuccess) return e;
         skip = flags;
     }

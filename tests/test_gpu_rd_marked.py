@@ -1,0 +1,55 @@
+"""GPU parity, halving-doubling batch at N = 512 and 1024 with a workspace (marked links): matrices whose marks are many,
+few or none, orders all of whose links are small, and batches that end inside a workgroup's pass."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2105_14088_amd as cc
+from gen import COST_MAX, random_matrix, random_perms
+from gpu_util import dev, gpu_rd, say
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
+
+
+def _matrices(n):
+    rng = np.random.default_rng(n)
+    yield "spread", random_matrix(n, n, symmetric=False, lo=0, hi=COST_MAX)
+    yield "one value", np.where(np.eye(n, dtype=bool), 0, 7).astype(np.int32)
+    yield "zeros", np.zeros((n, n), dtype=np.int32)
+    levels = np.array([5, 40, 41], dtype=np.int32)[rng.choice(3, size=(n, n), p=[0.05, 0.05, 0.9])]
+    np.fill_diagonal(levels, 0)
+    yield "three levels, most at the top", levels
+    rare = random_matrix(n, n + 1, symmetric=True, lo=1, hi=9)
+    rare[3, n - 1] = COST_MAX
+    yield "one large entry, one direction", rare
+    # dear links only between the halves of the nodes: most rounds of the identity order have no marked link
+    half = random_matrix(n, n + 2, symmetric=False, lo=1, hi=500)
+    half[: n // 2, n // 2:] += 10000
+    yield "two islands", half
+
+
+@pytest.mark.parametrize("n", [512, 1024])
+def test_rd_batch_marked_links(n):
+    for name, c in _matrices(n):
+        for b in (1, 16, 241):
+            say(f"rd batch, marked links, N={n} B={b}, {name}")
+            perms = random_perms(n, b, seed=n + b)
+            perms[0] = np.arange(n)
+            assert np.array_equal(gpu_rd(c, perms), oracle.rd_cost_batch(c, perms))
+
+
+@pytest.mark.parametrize("n", [512, 1024])
+def test_rd_batch_marked_links_several_passes_weights_and_unaligned_orders(n):
+    say(f"rd batch, marked links, N={n}: 4111 orders, weighted rounds, order stream 4 bytes off")
+    c = random_matrix(n, 3 * n, symmetric=False, lo=0, hi=COST_MAX)
+    perms = random_perms(n, 4111, seed=n)
+    assert np.array_equal(gpu_rd(c, perms), oracle.rd_cost_batch(c, perms))
+    rounds = n.bit_length() - 1
+    w = np.array([1 << 30, 0] + list(range(3, rounds + 1)), dtype=np.int32)
+    room = torch.empty(200 * n + 1, dtype=torch.int32, device="cuda")
+    view = room[1:].view(200, n)
+    view.copy_(dev(perms[:200]))
+    got = cc.cc_bcube_cost_batch_weighted(dev(c), 2, dev(w), view)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.bcube_cost_weighted_batch(c, 2, w, perms[:200]))
