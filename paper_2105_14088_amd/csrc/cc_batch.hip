@@ -11,6 +11,8 @@
 #include "cc_internal.h"
 #include "cc_wave64.h"
 
+#include <type_traits>
+
 namespace cc {
 using namespace ccd;
 
@@ -170,6 +172,89 @@ __global__ __launch_bounds__(256) void ring_batch_narrow_generic_kernel(const in
     }
 }
 
+// Any N up to kRingRowsMaxN, orders of 1, 2 or 4 bytes per rank: the matrix as 16-bit entries in LDS, sixteen lanes per
+// order (a DPP row), four orders per wave.  A step takes sixteen consecutive ranks of each order, so whatever N and the
+// alignment are the loads of a step are four short runs and those of the next steps lie in the same cache lines; the hop
+// into a lane's rank uses the node of the lane before it (one DPP rotation; lane 0 takes lane 15's node of the step
+// before, in the first step the order's last node).  Eight steps are in flight per wave.  The workgroup finds the matrix
+// maximum while staging; with an entry outside 0 .. 2^16 - 1 it gathers from the caller's matrix through L2 instead.
+// One order per wave through L2 (the generic kernels) runs at the L2's request rate, or for short orders at the cost of
+// its 64-bit reductions.  Measured, generic -> rows: N = 9, 10^6 orders 154 -> 35 us; N = 20, 10^6 orders 150 -> 38 us;
+// N = 100, 100000 orders 33 -> 12 us, 600000 orders 187 -> 46 us (5.3 TB/s of the order stream); N = 180, 300000 orders
+// of two bytes a rank 200 -> 58 us; N = 270, 200000 orders 228 -> 64 us.
+constexpr int kRingRowsMaxN = 280;              // 2 N^2 bytes and the waves' maxima in 160 KiB
+
+template <typename RANK, bool IS_MAX>
+__global__ __launch_bounds__(1024) void ring_batch_rows_kernel(const int32_t* __restrict__ c, int N,
+                                                               const RANK* __restrict__ perms, int64_t B,
+                                                               int64_t* __restrict__ out) {
+    constexpr int U = 8;                        // steps in flight
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_rows[];
+    unsigned* wave_top = (unsigned*)smem_rows;                  // [16]
+    uint16_t* m16 = (uint16_t*)(smem_rows + 64);                // [N * N]
+    const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15;
+    unsigned top = 0;
+    for (int e = threadIdx.x; e < N * N; e += 1024) {
+        const unsigned v = (unsigned)c[e];                      // a negative entry counts as too large
+        top = max(top, v);
+        m16[e] = (uint16_t)v;
+    }
+    top = (unsigned)wave_max((int)min(top, 0x7fffffffu));
+    if (lane == 0) wave_top[wv] = top;
+    __syncthreads();
+    unsigned all_top = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) all_top = max(all_top, wave_top[k]);
+    auto node = [&](RANK r) { return sizeof(RANK) == 4 ? clampi((int)r, 0, N - 1) : min((int)r, N - 1); };
+    // total: all hops of an order in 32 bits when they come from LDS (at most 280 * 65535), in 64 bits otherwise
+    auto score = [&](auto in_lds, auto zero) {
+        using Acc = decltype(zero);
+        const int64_t waves = (int64_t)gridDim.x * 16;
+        for (int64_t w = (int64_t)blockIdx.x * 16 + wv; w * 4 < B; w += waves) {
+            const int64_t b = w * 4 + (lane >> 4);
+            const RANK* pi = perms + (b < B ? b : B - 1) * N;
+            int before = node(pi[N - 1]);                       // of lane 0: the node of the rank before this step's first
+            Acc acc = 0;
+            for (int p0 = 0; p0 < N; p0 += 16 * U) {
+                RANK r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (p0 + 16 * u < N) r[u] = pi[min(p0 + 16 * u + sub, N - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (p0 + 16 * u < N) {
+                        const int x = node(r[u]);
+                        const int rot = __builtin_amdgcn_update_dpp(x, x, 0x121, 0xf, 0xf, true);      // row_ror:1
+                        const int e = x * N + (sub == 0 ? before : rot);
+                        before = rot;
+                        const int hop = in_lds ? (int)m16[e] : c[e];
+                        if (p0 + 16 * u + sub < N) acc = IS_MAX ? max(acc, (Acc)hop) : acc + hop;
+                    }
+                }
+            }
+            if constexpr (sizeof(Acc) == 4) {
+#define CC_ROW_STEP(ctrl)                                                                     \
+    {                                                                                         \
+        const int o = __builtin_amdgcn_update_dpp(acc, acc, ctrl, 0xf, 0xf, true);            \
+        acc = IS_MAX ? max(acc, o) : acc + o;                                                 \
+    }
+                CC_ROW_STEP(0xB1) CC_ROW_STEP(0x4E) CC_ROW_STEP(0x141) CC_ROW_STEP(0x140)
+#undef CC_ROW_STEP
+            } else {
+#pragma unroll
+                for (int m = 8; m >= 1; m >>= 1) {
+                    const Acc o = __shfl_xor(acc, m, kWave);
+                    acc = IS_MAX ? max(acc, o) : acc + o;
+                }
+            }
+            if (sub == 0 && b < B) out[b] = (int64_t)acc;
+        }
+    };
+    if (all_top < (1u << 16)) score(std::true_type{}, 0);
+    else score(std::false_type{}, 0ll);
+}
+
 static int batch_grid(int64_t work_items_per_block_pass, int64_t total) {
     int64_t blocks = (total + work_items_per_block_pass - 1) / work_items_per_block_pass;
     const int64_t cap = 256 * 8;  // 8 workgroups of 4 waves per compute unit
@@ -266,6 +351,27 @@ static hipError_t ring_n256_launch(const int32_t* c, const int32_t* perms, int64
     return hipGetLastError();
 }
 
+template <typename RANK, bool IS_MAX>
+static hipError_t ring_rows_launch(const int32_t* c, int N, const RANK* perms, int64_t B, int64_t* out, hipStream_t s) {
+    const size_t lds = 64 + sizeof(uint16_t) * (size_t)N * N;
+    hipError_t e = hipFuncSetAttribute((const void*)ring_batch_rows_kernel<RANK, IS_MAX>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    const int64_t at_once = lds <= 80 * 1024 ? 512 : 256;       // two workgroups of 16 waves fill a compute unit
+    int64_t blocks = (B + 63) / 64;
+    if (blocks > at_once) blocks = at_once;
+    hipLaunchKernelGGL((ring_batch_rows_kernel<RANK, IS_MAX>), dim3((int)blocks), dim3(1024), lds, s, c, N, perms, B, out);
+    return hipGetLastError();
+}
+
+// Staging N^2 entries per workgroup against L2 gathers: both forms take a call's launch time (7 us) up to about 2^20 hops;
+// beyond that the rows kernel is ahead from 35 N orders (generic / rows at N = 270: 8000 orders 10.9 / 12.8 us, 16000
+// orders 19.5 / 13.1) or 48 N (N = 180: 12000 orders 9.5 / 8.4), at N = 256, whose 1 KiB rows meet in the same memory
+// channels, from 85 N (17000 orders 19.7 / 23.4, 25000 orders 27.7 / 23.5).
+static bool ring_rows_pays(int N, int64_t B) {
+    return N <= kRingRowsMaxN && B * N >= (1 << 20) && B >= (N == 256 ? 96 : 64) * (int64_t)N;
+}
+
 hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const int32_t* perms, int64_t B,
                                   int64_t* out, hipStream_t s) {
     if (B == 0) return hipSuccess;
@@ -283,6 +389,9 @@ hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const in
         if (N == 256 && B >= 32768)
             return is_max ? ring_n256_launch<true>(c, perms, B, out, s) : ring_n256_launch<false>(c, perms, B, out, s);
     }
+    if (ring_rows_pays(N, B))
+        return is_max ? ring_rows_launch<int32_t, true>(c, N, perms, B, out, s)
+                      : ring_rows_launch<int32_t, false>(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_generic_kernel<true>), dim3(grid), dim3(256), 0, s, c, N, perms, B, out);
@@ -317,6 +426,9 @@ hipError_t launch_ring_cost_batch_u8(const int32_t* c, int N, bool is_max, const
             default: break;
         }
     }
+    if (ring_rows_pays(N, B))
+        return is_max ? ring_rows_launch<uint8_t, true>(c, N, perms, B, out, s)
+                      : ring_rows_launch<uint8_t, false>(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_narrow_generic_kernel<uint8_t, true>), dim3(grid), dim3(256), 0, s, c, N, perms, B,
@@ -330,6 +442,9 @@ hipError_t launch_ring_cost_batch_u8(const int32_t* c, int N, bool is_max, const
 hipError_t launch_ring_cost_batch_u16(const int32_t* c, int N, bool is_max, const uint16_t* perms, int64_t B,
                                       int64_t* out, hipStream_t s) {
     if (B == 0) return hipSuccess;
+    if (ring_rows_pays(N, B))
+        return is_max ? ring_rows_launch<uint16_t, true>(c, N, perms, B, out, s)
+                      : ring_rows_launch<uint16_t, false>(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_narrow_generic_kernel<uint16_t, true>), dim3(grid), dim3(256), 0, s, c, N, perms,
