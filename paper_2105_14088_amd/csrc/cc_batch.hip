@@ -372,6 +372,157 @@ static bool ring_rows_pays(int N, int64_t B) {
     return N <= kRingRowsMaxN && B * N >= (1 << 20) && B >= (N == 256 ? 96 : 64) * (int64_t)N;
 }
 
+// Max-hop, 280 < N <= 1024: only hops among the matrix's largest entries have to be looked up exactly.  Every workgroup
+// marks in LDS, one bit per entry (32 KiB at N = 500, 128 KiB at N = 1024), the entries that are T or more; T is chosen
+// from 4096 sampled entries so that about ln N of an order's N hops carry the bit (where the exact look-ups and the orders
+// without a marked hop, which are looked up whole, cost the same).  Any T gives the right result, only the time depends on
+// it.  Sixteen lanes per order as in ring_batch_rows_kernel; a lane notes its marked hops in a 64-bit mask (at most 64
+// steps) and afterwards looks them up one by one, ranks from the order stream (in cache) and entries through L2.  An order
+// that has reached the matrix maximum is finished, so a matrix of few values ends early.
+// The generic kernels ask L2 for every hop and run at its request rate; here what is left is the marking and the order
+// stream.  Generic -> marked: N = 300, 200000 orders 254 -> 79 us; N = 500, 130000 orders 292 -> 89 us, 65000 orders of two
+// bytes a rank 139 -> 82 us; N = 1000, 65000 orders 335 -> 137 us.
+template <typename RANK>
+__global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32_t* __restrict__ c, int N,
+                                                                     const RANK* __restrict__ perms, int64_t B,
+                                                                     int64_t* __restrict__ out, int wanted) {
+    constexpr int U = 16;                                        // steps in flight
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_ring_marks[];
+    int* per_wave = (int*)smem_ring_marks;                       // [2][16]: the waves' estimates of T, their maxima
+    uint32_t* marks = (uint32_t*)(smem_ring_marks + 128);        // bit e of the flat matrix: bit e & 31 of word e >> 5
+    const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15;
+    // every wave takes the wanted-th largest of 256 sampled entries, T is the ninth largest of the sixteen values
+    int v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint64_t h = splitmix64_at(0, (uint64_t)(threadIdx.x + 1024 * i + 1));
+        const int x = (int)(((h & 0xffffffffu) * (uint64_t)N) >> 32), y = (int)(((h >> 32) * (uint64_t)N) >> 32);
+        v[i] = max(c[x * N + (x == y ? (y ? y - 1 : 1) : y)], 0);
+    }
+    int T = 0;
+    for (int seen = 0; seen < wanted;) {
+        T = wave_max(max(max(v[0], v[1]), max(v[2], v[3])));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            seen += __popcll(__ballot(v[i] == T));
+            if (v[i] == T) v[i] = -1;
+        }
+    }
+    if (lane == 0) per_wave[wv] = T;
+    __syncthreads();
+    {
+        const int mine = per_wave[sub];
+        int above = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) above += per_wave[k] > mine || (per_wave[k] == mine && k < sub);
+        T = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)__ballot(above == 8)) - 1);
+    }
+    // 32 runs of 64 entries per wave and pass, all loads in flight; the workgroups start at different places, so that they
+    // do not all ask the same L2 channel at once
+    int top = 0;
+    const int total = N * N, passes = (total + 16 * 2048 - 1) / (16 * 2048);
+    const int first = (int)((int64_t)blockIdx.x * passes / gridDim.x);
+    for (int i = 0; i < passes; ++i) {
+        const int at = ((first + i < passes ? first + i : first + i - passes) * 16 + wv) * 2048;
+        int e[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) e[k] = c[min(at + 64 * k + lane, total - 1)];
+        uint32_t word = 0;
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            const unsigned long long bits = __ballot(e[k] >= T);
+            top = max(top, e[k]);
+            if ((lane >> 1) == k) word = lane & 1 ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+        }
+        if (at + 32 * lane < total) marks[(at >> 5) + lane] = word;
+    }
+    top = wave_max(top);
+    if (lane == 0) per_wave[16 + wv] = top;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) top = max(top, per_wave[16 + k]);
+    auto node = [&](RANK r) { return sizeof(RANK) == 4 ? clampi((int)r, 0, N - 1) : min((int)r, N - 1); };
+    auto row_max = [](int a) {
+        a = max(a, __builtin_amdgcn_update_dpp(a, a, 0xB1, 0xf, 0xf, true));
+        a = max(a, __builtin_amdgcn_update_dpp(a, a, 0x4E, 0xf, 0xf, true));
+        a = max(a, __builtin_amdgcn_update_dpp(a, a, 0x141, 0xf, 0xf, true));
+        return max(a, __builtin_amdgcn_update_dpp(a, a, 0x140, 0xf, 0xf, true));
+    };
+    const int64_t waves = (int64_t)gridDim.x * 16;
+    for (int64_t w = (int64_t)blockIdx.x * 16 + wv; w * 4 < B; w += waves) {
+        const int64_t b = w * 4 + (lane >> 4);
+        const RANK* pi = perms + (b < B ? b : B - 1) * N;
+        auto hop = [&](int p) { return c[node(pi[p]) * N + node(pi[p ? p - 1 : N - 1])]; };
+        int before = node(pi[N - 1]);
+        uint64_t hits = 0;                                       // bit t: the hop into rank 16 t + sub
+        for (int p0 = 0; p0 < N; p0 += 16 * U) {
+            RANK r[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (p0 + 16 * u < N) r[u] = pi[min(p0 + 16 * u + sub, N - 1)];
+            }
+            uint32_t chunk = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (p0 + 16 * u < N) {
+                    const int x = node(r[u]);
+                    const int rot = __builtin_amdgcn_update_dpp(x, x, 0x121, 0xf, 0xf, true);      // row_ror:1
+                    const int y = sub == 0 ? before : rot;
+                    before = rot;
+                    const unsigned e = (unsigned)(x * N + y);
+                    const uint32_t bit = (marks[e >> 5] >> (e & 31)) & 1u;
+                    if (p0 + 16 * u + sub < N) chunk |= bit << u;
+                }
+            }
+            hits |= (uint64_t)chunk << (p0 >> 4);
+        }
+        int best = -1;
+        while (__ballot(hits != 0)) {
+            if (hits) {
+                const int t0 = __ffsll((unsigned long long)hits) - 1;       // two at once: their loads overlap
+                hits &= hits - 1;
+                const int t1 = hits ? __ffsll((unsigned long long)hits) - 1 : t0;
+                hits &= hits - 1;
+                best = max(best, max(hop(16 * t0 + sub), hop(16 * t1 + sub)));
+            }
+            if ((__ballot(best >= top) >> (lane & 48)) & 0xffffu) hits = 0;
+        }
+        best = row_max(best);
+        if (__ballot(best < 0)) {                                // an order without a marked hop: all of them
+            if (best < 0) {
+                best = 0;
+                for (int p0 = sub; p0 < N; p0 += 16 * 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) best = max(best, hop(min(p0 + 16 * u, N - 1)));
+                }
+            }
+            best = row_max(best);
+        }
+        if (sub == 0 && b < B) out[b] = best;
+    }
+}
+
+template <typename RANK>
+static hipError_t ring_max_marked_launch(const int32_t* c, int N, const RANK* perms, int64_t B, int64_t* out,
+                                         hipStream_t s) {
+    const size_t lds = 128 + sizeof(uint32_t) * (((size_t)N * N + 31) / 32);
+    hipError_t e = hipFuncSetAttribute((const void*)ring_batch_max_marked_kernel<RANK>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    int64_t blocks = (B + 63) / 64;
+    if (blocks > 256) blocks = 256;                             // one per compute unit: each reads the whole matrix
+    const int wanted = (256 * 6 + N / 2) / N;                   // of 256 samples: 6 of N, ln N being 5.6 .. 6.9
+    hipLaunchKernelGGL(ring_batch_max_marked_kernel<RANK>, dim3((int)blocks), dim3(1024), lds, s, c, N, perms, B, out,
+                       wanted);
+    return hipGetLastError();
+}
+
+// Marking reads the matrix once per workgroup (N = 300: 12 us, N = 1000: 85 us), as long as the generic kernel takes for
+// about 20000 orders at any of these N (generic / marked: N = 300, 16000 orders 22 / 21 us; N = 700, 20000 orders 65 / 63 us;
+// N = 1000, 16000 orders 85 / 95 us).
+constexpr int64_t kRingMaxMarkedMinOrders = 20480;
+static bool ring_max_marked_pays(int N, int64_t B) { return N > kRingRowsMaxN && B >= kRingMaxMarkedMinOrders; }
+
 hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const int32_t* perms, int64_t B,
                                   int64_t* out, hipStream_t s) {
     if (B == 0) return hipSuccess;
@@ -392,6 +543,7 @@ hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const in
     if (ring_rows_pays(N, B))
         return is_max ? ring_rows_launch<int32_t, true>(c, N, perms, B, out, s)
                       : ring_rows_launch<int32_t, false>(c, N, perms, B, out, s);
+    if (is_max && ring_max_marked_pays(N, B)) return ring_max_marked_launch<int32_t>(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_generic_kernel<true>), dim3(grid), dim3(256), 0, s, c, N, perms, B, out);
@@ -445,6 +597,7 @@ hipError_t launch_ring_cost_batch_u16(const int32_t* c, int N, bool is_max, cons
     if (ring_rows_pays(N, B))
         return is_max ? ring_rows_launch<uint16_t, true>(c, N, perms, B, out, s)
                       : ring_rows_launch<uint16_t, false>(c, N, perms, B, out, s);
+    if (is_max && ring_max_marked_pays(N, B)) return ring_max_marked_launch<uint16_t>(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_narrow_generic_kernel<uint16_t, true>), dim3(grid), dim3(256), 0, s, c, N, perms,
