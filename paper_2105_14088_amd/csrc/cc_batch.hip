@@ -181,7 +181,9 @@ __global__ __launch_bounds__(256) void ring_batch_narrow_generic_kernel(const in
 // One order per wave through L2 (the generic kernels) runs at the L2's request rate, or for short orders at the cost of
 // its 64-bit reductions.  Measured, generic -> rows: N = 9, 10^6 orders 154 -> 35 us; N = 20, 10^6 orders 150 -> 38 us;
 // N = 100, 100000 orders 33 -> 12 us, 600000 orders 187 -> 46 us (5.3 TB/s of the order stream); N = 180, 300000 orders
-// of two bytes a rank 200 -> 58 us; N = 270, 200000 orders 228 -> 64 us.
+// of two bytes a rank 200 -> 39 us; N = 270, 200000 orders 228 -> 64 us.
+// The ranks in flight are held as int whatever their type: as 16-bit values each was masked, and so waited for, in the
+// conditional block of its own load (58 us for the two-byte case; 82 instead of 55 us in ring_batch_max_marked_kernel).
 constexpr int kRingRowsMaxN = 280;              // 2 N^2 bytes and the waves' maxima in 160 KiB
 
 template <typename RANK, bool IS_MAX>
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(1024) void ring_batch_rows_kernel(const int32_t* __
     unsigned all_top = 0;
 #pragma unroll
     for (int k = 0; k < 16; ++k) all_top = max(all_top, wave_top[k]);
-    auto node = [&](RANK r) { return sizeof(RANK) == 4 ? clampi((int)r, 0, N - 1) : min((int)r, N - 1); };
+    auto node = [&](int r) { return sizeof(RANK) == 4 ? clampi(r, 0, N - 1) : min(r, N - 1); };
     // total: all hops of an order in 32 bits when they come from LDS (at most 280 * 65535), in 64 bits otherwise
     auto score = [&](auto in_lds, auto zero) {
         using Acc = decltype(zero);
@@ -216,10 +218,10 @@ __global__ __launch_bounds__(1024) void ring_batch_rows_kernel(const int32_t* __
             int before = node(pi[N - 1]);                       // of lane 0: the node of the rank before this step's first
             Acc acc = 0;
             for (int p0 = 0; p0 < N; p0 += 16 * U) {
-                RANK r[U];
+                int r[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (p0 + 16 * u < N) r[u] = pi[min(p0 + 16 * u + sub, N - 1)];
+                    if (p0 + 16 * u < N) r[u] = (int)pi[min(p0 + 16 * u + sub, N - 1)];
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -381,7 +383,7 @@ static bool ring_rows_pays(int N, int64_t B) {
 // that has reached the matrix maximum is finished, so a matrix of few values ends early.
 // The generic kernels ask L2 for every hop and run at its request rate; here what is left is the marking and the order
 // stream.  Generic -> marked: N = 300, 200000 orders 254 -> 79 us; N = 500, 130000 orders 292 -> 89 us, 65000 orders of two
-// bytes a rank 139 -> 82 us; N = 1000, 65000 orders 335 -> 137 us.
+// bytes a rank 139 -> 55 us; N = 1000, 65000 orders 335 -> 137 us.
 template <typename RANK>
 __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32_t* __restrict__ c, int N,
                                                                      const RANK* __restrict__ perms, int64_t B,
@@ -441,7 +443,7 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; ++k) top = max(top, per_wave[16 + k]);
-    auto node = [&](RANK r) { return sizeof(RANK) == 4 ? clampi((int)r, 0, N - 1) : min((int)r, N - 1); };
+    auto node = [&](int r) { return sizeof(RANK) == 4 ? clampi(r, 0, N - 1) : min(r, N - 1); };
     auto row_max = [](int a) {
         a = max(a, __builtin_amdgcn_update_dpp(a, a, 0xB1, 0xf, 0xf, true));
         a = max(a, __builtin_amdgcn_update_dpp(a, a, 0x4E, 0xf, 0xf, true));
@@ -456,10 +458,10 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
         int before = node(pi[N - 1]);
         uint64_t hits = 0;                                       // bit t: the hop into rank 16 t + sub
         for (int p0 = 0; p0 < N; p0 += 16 * U) {
-            RANK r[U];
+            int r[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                if (p0 + 16 * u < N) r[u] = pi[min(p0 + 16 * u + sub, N - 1)];
+                if (p0 + 16 * u < N) r[u] = (int)pi[min(p0 + 16 * u + sub, N - 1)];
             }
             uint32_t chunk = 0;
 #pragma unroll
