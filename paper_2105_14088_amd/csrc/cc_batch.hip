@@ -1701,6 +1701,130 @@ __global__ __launch_bounds__(256) void dbt_batch_n64_kernel(const int32_t* __res
     }
 }
 
+// Small and middling N: sixteen lanes per order, four orders per wave, the matrix as 16-bit entries in LDS.  The tree's
+// shape does not depend on the order: a rank's place in it is a heap slot (root 1, children 2h and 2h + 1; every level
+// but the last is full), found once per workgroup.  An order is staged by slot, each word the nodes of the slot's rank
+// in the first and in the second tree, so a slot's parent is slot h >> 1 and a level is one pass over consecutive slots:
+// two words, one edge per tree, the parent's path costs plus those edges.  N - 1 edges per tree are looked up instead of
+// the whole path of every rank.  Slots of the last level without a rank keep the mark ~0.  A workgroup that meets an
+// entry outside 0 .. 2^16 - 1 while staging gathers from the caller's matrix through L2.
+// Issue-bound: the four top levels are a pass of at most 16 lanes each, and a form with four passes of a level in flight
+// was slower for its extra instructions (N = 100, 100000 orders 40 us).  Before (every rank walks its whole path, for
+// N > 64 through L2) -> this kernel: N = 100, 100000 orders 103 -> 33 us, 600000 orders 624 -> 149 us; N = 65, 300000 orders
+// 291 -> 55 us; N = 50, 300000 orders 119 -> 39 us; N = 20, 10^6 orders 326 -> 90 us; N = 200, 100000 orders 223 -> 80 us.
+__global__ __launch_bounds__(1024) void dbt_batch_rows_kernel(const int32_t* __restrict__ c, int N, int levels,
+                                                              const int32_t* __restrict__ perms, int64_t B,
+                                                              int64_t* __restrict__ out) {
+    constexpr int U = 4;                                                        // staging steps in flight
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_dbt[];
+    const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15, waves = blockDim.x >> 6;
+    const int slots = 1 << levels;
+    unsigned* wave_top = (unsigned*)smem_dbt;                                   // [16]
+    uint16_t* slot_of = (uint16_t*)(smem_dbt + 64);                             // [N]
+    uint16_t* m16 = slot_of + ((N + 7) & ~7);                                   // [N * N]
+    uint32_t* nodes = (uint32_t*)(m16 + ((N * N + 7) & ~7)) + wv * 4 * slots + (lane >> 4) * slots;   // [waves][4][slots]
+    int2* cost = (int2*)((uint32_t*)(m16 + ((N * N + 7) & ~7)) + waves * 4 * slots) + wv * 2 * slots +
+                 (lane >> 4) * (slots / 2);                                     // [waves][4][slots / 2]
+    unsigned top = 0;
+    for (int e = threadIdx.x; e < N * N; e += blockDim.x) {
+        const unsigned v = (unsigned)c[e];                                      // a negative entry counts as too large
+        top = max(top, v);
+        m16[e] = (uint16_t)v;
+    }
+    for (int p = threadIdx.x; p < N; p += blockDim.x) {
+        int lo = 0, hi = N - 1, m = (N - 1) >> 1, h = 1;
+        for (int depth = 0; depth < 11 && m != p; ++depth) {
+            if (p < m) hi = m - 1;
+            else lo = m + 1;
+            h = 2 * h + (p > m);
+            m = (lo + hi) >> 1;
+        }
+        slot_of[p] = (uint16_t)h;
+    }
+    for (int h = sub; h < slots; h += 16) nodes[h] = ~0u;
+    if (sub == 0) cost[1] = make_int2(0, 0);
+    top = (unsigned)wave_max((int)min(top, 0x7fffffffu));
+    if (lane == 0) wave_top[wv] = top;
+    __syncthreads();
+    for (int k = 0; k < waves; ++k) top = max(top, wave_top[k]);
+    auto score = [&](auto in_lds) {
+        const int64_t nwaves = (int64_t)gridDim.x * waves;
+        for (int64_t w = (int64_t)blockIdx.x * waves + wv; w * 4 < B; w += nwaves) {
+            const int64_t b = w * 4 + (lane >> 4);
+            const int32_t* pi = perms + (b < B ? b : B - 1) * N;
+            for (int p0 = sub; p0 < N + sub; p0 += 16 * U) {
+                int x[U], y[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int p = min(p0 + 16 * u, N - 1);
+                    x[u] = pi[p];
+                    y[u] = pi[p + 1 < N ? p + 1 : 0];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (p0 + 16 * u < N)
+                        nodes[slot_of[p0 + 16 * u]] =
+                            (unsigned)clampi(x[u], 0, N - 1) | (unsigned)clampi(y[u], 0, N - 1) << 16;
+            }
+            __builtin_amdgcn_wave_barrier();
+            int worst = 0;
+            for (int d = 1; d < levels; ++d) {
+                for (int h0 = 1 << d; h0 < 2 << d; h0 += 16) {
+                    const int h = h0 + sub;
+                    const uint32_t own = h < 2 << d ? nodes[h] : ~0u, parent = nodes[(h >> 1) & (slots - 1)];
+                    if (own != ~0u) {
+                        const unsigned e0 = __umul24(parent & 0xffffu, N) + (own & 0xffffu);
+                        const unsigned e1 = __umul24(parent >> 16, N) + (own >> 16);
+                        int2 k = cost[h >> 1];
+                        k.x += in_lds ? (int)m16[e0] : c[e0];
+                        k.y += in_lds ? (int)m16[e1] : c[e1];
+                        worst = max(worst, max(k.x, k.y));
+                        if (d < levels - 1) cost[h] = k;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0xB1, 0xf, 0xf, true));
+            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0x4E, 0xf, 0xf, true));
+            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0x141, 0xf, 0xf, true));
+            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0x140, 0xf, 0xf, true));
+            if (sub == 0 && b < B) out[b] = worst;
+        }
+    };
+    if (top < (1u << 16)) score(std::true_type{});
+    else score(std::false_type{});
+}
+
+constexpr int kDbtRowsMinWaves = 4;
+
+static int dbt_levels(int N) { return 32 - __builtin_clz((unsigned)N); }
+static size_t dbt_rows_fixed_bytes(int N) { return 64 + 2 * (size_t)((N + 7) & ~7) + 2 * (((size_t)N * N + 7) & ~(size_t)7); }
+// waves of a workgroup: what the LDS beside the matrix holds, 8 bytes per slot and order
+static int dbt_rows_waves(int N) {
+    const size_t fixed = dbt_rows_fixed_bytes(N), slice = (size_t)32 << dbt_levels(N), all = 160 * 1024;
+    if (fixed + slice > all) return 0;
+    const size_t fit = (all - fixed) / slice;
+    return fit < 16 ? (int)fit : 16;
+}
+
+static hipError_t dbt_rows_launch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
+    const int waves = dbt_rows_waves(N), levels = dbt_levels(N);
+    const size_t lds = dbt_rows_fixed_bytes(N) + waves * ((size_t)32 << levels);
+    hipError_t e = hipFuncSetAttribute((const void*)dbt_batch_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       160 * 1024);
+    if (e != hipSuccess) return e;
+    const int64_t at_once = 256 * (2 * lds <= 160 * 1024 ? 2 : 1);
+    int64_t blocks = (B + 4 * waves - 1) / (4 * waves);
+    if (blocks > at_once) blocks = at_once;
+    hipLaunchKernelGGL(dbt_batch_rows_kernel, dim3((int)blocks), dim3(64 * waves), lds, s, c, N, levels, perms, B, out);
+    return hipGetLastError();
+}
+
+// Up to about 2^20 ranks a call takes its launch time either way, or the staging shows (generic / rows: N = 128, 4000 orders
+// 7.6 / 9.9 us; N = 200, 4000 orders 14.3 / 15.8); above, rows is ahead (N = 128, 16000 orders 18.4 / 14.5; N = 245, where
+// four waves fit beside the matrix, 100000 orders 229 / 168).
+static bool dbt_rows_pays(int N, int64_t B) { return dbt_rows_waves(N) >= kDbtRowsMinWaves && B * N >= (1 << 20); }
+
 hipError_t launch_dbt_cost_batch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out,
                                  hipStream_t s) {
     if (B == 0) return hipSuccess;
@@ -1709,6 +1833,8 @@ hipError_t launch_dbt_cost_batch(const int32_t* c, int N, const int32_t* perms, 
         hipLaunchKernelGGL(dbt_lanes64_kernel, dim3(batch_grid(4 * 64, B)), dim3(256), 0, s, c, (const int4*)perms, B, out);
     } else if (N == 64) {
         hipLaunchKernelGGL(dbt_batch_n64_kernel, dim3(grid), dim3(256), 0, s, c, perms, B, out);
+    } else if (dbt_rows_pays(N, B)) {
+        return dbt_rows_launch(c, N, perms, B, out, s);
     } else if (N <= 64) {
         const size_t lds = sizeof(int32_t) * (size_t)(4 * N + N * N);
         hipLaunchKernelGGL((dbt_batch_kernel<true>), dim3(grid), dim3(256), lds, s, c, N, perms, B, out);
