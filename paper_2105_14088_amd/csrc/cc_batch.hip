@@ -996,7 +996,7 @@ __global__ __launch_bounds__(256) void rd_batch_folded_kernel(const uint16_t* __
 }
 
 // N = 128, 256 for large batches, matrix in LDS: a 1024-thread workgroup per compute unit stages the matrix as 16-bit
-// entries, folds the two directions of every pair into both places (as rdswap_block_kernel does) and then scores one
+// entries, folds the two directions of every pair into both places (every unordered pair once) and then scores one
 // order per wave as rd_batch_folded_kernel / bcube_b4_folded_kernel do, with LDS gathers instead of L2 requests.
 // The workgroup finds the matrix maximum while staging; with an entry outside 0 .. 2^16 - 1 its links are scored from
 // the caller's matrix through L2 (both directions per link).  BCUBE4: base-4 BCube rounds instead of halving-doubling.
