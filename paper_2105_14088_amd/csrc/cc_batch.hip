@@ -6,7 +6,8 @@
 // vector loads in flight per wave; each lane gathers its four hops from LDS and the N/4 lanes of an
 // order are combined with a butterfly.  The stream is read exactly once, so the kernel is bound by
 // HBM bandwidth (4N bytes in + 8 bytes out per order).
-// Other N: one wave per order, hops gathered from the L2-resident matrix.
+// Other N up to 280, large batches: 16-bit matrix in LDS, sixteen lanes per order; max-hop above: marked entries in LDS.
+// The rest: one wave per order, hops gathered from the L2-resident matrix.
 #include "cc_device.h"
 #include "cc_internal.h"
 #include "cc_wave64.h"
@@ -825,47 +826,6 @@ __global__ __launch_bounds__(256) void dbt_lanes64_kernel(const int32_t* __restr
     }
 }
 
-// N = 32 or 64 with the matrix in LDS: the rounds are unrolled, so the partner look-ups and the gathers of all rounds are
-// in flight together and the rounds' maxima are reduced three at a time; the next order is requested before the
-// current one is scored.
-template <int LOGN>
-__global__ __launch_bounds__(256) void rd_batch_small_kernel(const int32_t* __restrict__ c,
-                                                             const int32_t* __restrict__ weights,
-                                                             const int32_t* __restrict__ perms, int64_t B,
-                                                             int64_t* __restrict__ out) {
-    constexpr int N = 1 << LOGN;
-    __shared__ int32_t m[N * N];
-    __shared__ int32_t order_all[4][N];
-    for (int e = threadIdx.x; e < N * N; e += 256) m[e] = c[e];
-    __syncthreads();
-    int32_t* order = order_all[threadIdx.x >> 6];
-    const int lane = lane_id();
-    const bool live = lane < N;
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
-    long long w[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) w[k] = (k < LOGN && weights) ? (long long)clampi(weights[k], 0, kMaxRoundWeight) : 1ll;
-    int next = (wave < B && live) ? perms[wave * N + lane] : 0;
-    for (int64_t b = wave; b < B; b += nwaves) {
-        const int a = clampi(next, 0, N - 1);
-        const int64_t bn = b + nwaves;
-        next = (bn < B && live) ? perms[bn * N + lane] : 0;
-        if (live) order[lane] = a;
-        __builtin_amdgcn_wave_barrier();
-        int v[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) v[k] = (k < LOGN && live) ? m[a * N + order[lane ^ (1 << k)]] : 0;
-        __builtin_amdgcn_wave_barrier();   // all partner look-ups done before the slice is overwritten
-        wave_max3(v[0], v[1], v[2]);
-        wave_max3(v[3], v[4], v[5]);
-        long long total = 0;
-#pragma unroll
-        for (int k = 0; k < LOGN; ++k) total += w[k] * v[k];
-        if (lane == 0) out[b] = total;
-    }
-}
-
 // N = 64: a round costs the largest of its 32 links and a link costs the larger of its two directed entries, so the
 // kernel folds the two entries of every pair into both places while staging (max(c[x][y], c[y][x])) and then scores
 // links, not ranks: the 6 x 32 links of an order are three gathers per lane (lanes 0..31 one round, lanes 32..63 the
@@ -917,14 +877,6 @@ __global__ __launch_bounds__(256) void rd_batch_links64_kernel(const int32_t* __
             total += w[2 * j] * __builtin_amdgcn_readlane(v[j], 31) + w[2 * j + 1] * __builtin_amdgcn_readlane(v[j], 63);
         if (lane == 0) out[b] = total;
     }
-}
-
-template <int LOGN>
-static hipError_t rd_small_launch(const int32_t* c, const int32_t* weights, const int32_t* perms, int64_t B,
-                                  int64_t* out, hipStream_t s) {
-    const int grid = batch_grid(4, B);
-    hipLaunchKernelGGL(rd_batch_small_kernel<LOGN>, dim3(grid), dim3(256), 0, s, c, weights, perms, B, out);
-    return hipGetLastError();
 }
 
 template <int NM>
@@ -1323,6 +1275,72 @@ static hipError_t rd_marked_launch(const int32_t* c, void* room, int32_t* tops, 
     return hipGetLastError();
 }
 
+// N = 4 .. 32, halving-doubling and base-4 BCube (4, 16): one order per LANE.  A lane loads its own order (16 N bytes of
+// consecutive cache lines per four lanes at N = 16; all of every line is used), the folded matrix, both directions of a
+// pair in one entry, is in LDS, and with all loops unrolled the ends of a link are registers: per link one address, one
+// LDS look-up and half a maximum, nothing is reduced across lanes.  Bound by the order stream and the launch.  One wave per
+// order, as before, left lanes idle and paid for reductions; 10^6 orders: halving-doubling N = 8 150 -> 8 us, N = 16
+// 184 -> 14 us (4.9 TB/s), N = 32 176 -> 26 us (5.3 TB/s), BCube N = 16 295 -> 14 us; 1000 orders the launch's 7.4 us.
+template <int LOGN, bool BCUBE4>
+__global__ __launch_bounds__(256) void rounds_batch_small_kernel(const int32_t* __restrict__ c,
+                                                                 const int32_t* __restrict__ weights,
+                                                                 const int32_t* __restrict__ perms, int64_t B,
+                                                                 int64_t* __restrict__ out) {
+    constexpr int N = 1 << LOGN, ROUNDS = BCUBE4 ? LOGN / 2 : LOGN;
+    __shared__ int32_t m[N * N];
+    for (int e = threadIdx.x; e < N * N; e += 256) {
+        const int x = e >> LOGN, y = e & (N - 1);
+        m[e] = max(c[e], c[y * N + x]);
+    }
+    __syncthreads();
+    long long w[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) w[r] = weights ? (long long)clampi(weights[r], 0, kMaxRoundWeight) : 1ll;
+    const bool aligned = ((uintptr_t)perms & 15u) == 0;
+    for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < B; b += (int64_t)gridDim.x * 256) {
+        int t[N];
+        const int32_t* pi = perms + b * N;
+        if (aligned) {
+#pragma unroll
+            for (int q = 0; q < N / 4; ++q) {
+                const int4 v = ((const int4*)pi)[q];
+                t[4 * q] = v.x;
+                t[4 * q + 1] = v.y;
+                t[4 * q + 2] = v.z;
+                t[4 * q + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int p = 0; p < N; ++p) t[p] = pi[p];
+        }
+#pragma unroll
+        for (int p = 0; p < N; ++p) t[p] = clampi(t[p], 0, N - 1);
+        long long total = 0;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            int worst = 0;
+#pragma unroll
+            for (int p = 0; p < N; ++p) {
+                const int step = BCUBE4 ? 1 << (2 * r) : 1 << r;
+#pragma unroll
+                for (int d = 1; d < (BCUBE4 ? 4 : 2); ++d)                 // peers above p in digit r
+                    if ((p / step) % (BCUBE4 ? 4 : 2) + d < (BCUBE4 ? 4 : 2))
+                        worst = max(worst, m[(t[p] << LOGN) | t[p + d * step]]);
+            }
+            total += w[r] * worst;
+        }
+        out[b] = total;
+    }
+}
+
+template <int LOGN, bool BCUBE4>
+static hipError_t rounds_small_launch(const int32_t* c, const int32_t* weights, const int32_t* perms, int64_t B,
+                                      int64_t* out, hipStream_t s) {
+    hipLaunchKernelGGL((rounds_batch_small_kernel<LOGN, BCUBE4>), dim3(batch_grid(256, B)), dim3(256), 0, s, c, weights, perms,
+                       B, out);
+    return hipGetLastError();
+}
+
 constexpr int64_t kLdsBatchMinOrders = 32768;      // staging a matrix per compute unit pays from here on
 
 template <int LOGN, bool BCUBE4>
@@ -1359,7 +1377,10 @@ hipError_t launch_rd_cost_batch(const int32_t* c, int N, const int32_t* weights,
             hipLaunchKernelGGL(rd_batch_links64_kernel, dim3(batch_grid(4, B)), dim3(256), 0, s, c, weights, perms, B, out);
         return hipGetLastError();
     }
-    if (N == 32) return rd_small_launch<5>(c, weights, perms, B, out, s);
+    if (N == 4) return rounds_small_launch<2, false>(c, weights, perms, B, out, s);
+    if (N == 8) return rounds_small_launch<3, false>(c, weights, perms, B, out, s);
+    if (N == 16) return rounds_small_launch<4, false>(c, weights, perms, B, out, s);
+    if (N == 32) return rounds_small_launch<5, false>(c, weights, perms, B, out, s);
     if (N <= 64) return rd_launch<1>(c, N, weights, perms, B, out, nullptr, s);
     if (B >= kLdsBatchMinOrders) {
         if (N == 128) return links_lds16_launch<7, false>(c, weights, perms, B, out, s);
@@ -1569,6 +1590,8 @@ hipError_t launch_bcube_cost_batch(const int32_t* c, int N, int base, const int3
             hipLaunchKernelGGL(bcube_batch_b4n64_kernel, dim3(batch_grid(4, B)), dim3(256), 0, s, c, weights, perms, B, out);
         return hipGetLastError();
     }
+    if (base == 4 && N == 4) return rounds_small_launch<2, true>(c, weights, perms, B, out, s);
+    if (base == 4 && N == 16) return rounds_small_launch<4, true>(c, weights, perms, B, out, s);
     if (base == 4 && N == 256 && B >= kLdsBatchMinOrders) return links_lds16_launch<8, true>(c, weights, perms, B, out, s);
     const int32_t* skip = nullptr;
     if (flags && folded && base == 4 && (N == 256 || N == 1024)) {
