@@ -19,6 +19,28 @@ using namespace ccd;
 
 constexpr int kMaxRoundWeight = 1 << 30;   // round weights are clamped to [0, 2^30]: weight * cost stays below 2^51
 
+// A threshold that about `wanted` of 256 entries reach, from 4096 sampled ones, four per thread of a 1024-thread workgroup:
+// every wave takes the wanted-th largest of its 256, the result is the ninth largest of the sixteen values.  `v` are not
+// negative; per_wave: 16 words of LDS.  (A bit-by-bit search over all 4096, a barrier per bit, took 10 us longer.)
+__device__ __forceinline__ int sampled_threshold(int (&v)[4], int wanted, int* per_wave) {
+    int T = 0;
+    for (int seen = 0; seen < wanted;) {
+        T = wave_max(max(max(v[0], v[1]), max(v[2], v[3])));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            seen += __popcll(__ballot(v[i] == T));
+            if (v[i] == T) v[i] = -1;
+        }
+    }
+    if (lane_id() == 0) per_wave[threadIdx.x >> 6] = T;
+    __syncthreads();
+    const int sub = lane_id() & 15, mine = per_wave[sub];
+    int above = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) above += per_wave[k] > mine || (per_wave[k] == mine && k < sub);
+    return __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)__ballot(above == 8)) - 1);
+}
+
 // ------------------------------------------------------------------------------------------ ring
 template <int N, bool IS_MAX>
 __global__ __launch_bounds__(256) void ring_batch_lds_kernel(const int32_t* __restrict__ c,
@@ -394,7 +416,6 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
     int* per_wave = (int*)smem_ring_marks;                       // [2][16]: the waves' estimates of T, their maxima
     uint32_t* marks = (uint32_t*)(smem_ring_marks + 128);        // bit e of the flat matrix: bit e & 31 of word e >> 5
     const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15;
-    // every wave takes the wanted-th largest of 256 sampled entries, T is the ninth largest of the sixteen values
     int v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -402,24 +423,7 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
         const int x = (int)(((h & 0xffffffffu) * (uint64_t)N) >> 32), y = (int)(((h >> 32) * (uint64_t)N) >> 32);
         v[i] = max(c[x * N + (x == y ? (y ? y - 1 : 1) : y)], 0);
     }
-    int T = 0;
-    for (int seen = 0; seen < wanted;) {
-        T = wave_max(max(max(v[0], v[1]), max(v[2], v[3])));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            seen += __popcll(__ballot(v[i] == T));
-            if (v[i] == T) v[i] = -1;
-        }
-    }
-    if (lane == 0) per_wave[wv] = T;
-    __syncthreads();
-    {
-        const int mine = per_wave[sub];
-        int above = 0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) above += per_wave[k] > mine || (per_wave[k] == mine && k < sub);
-        T = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)__ballot(above == 8)) - 1);
-    }
+    const int T = sampled_threshold(v, wanted, per_wave);
     // 32 runs of 64 entries per wave and pass, all loads in flight; the workgroups start at different places, so that they
     // do not all ask the same L2 channel at once
     int top = 0;
@@ -1049,46 +1053,43 @@ __global__ __launch_bounds__(1024) void links_batch_lds16_kernel(const int32_t* 
 // round's N / 2 links carry the bit, from the same 4096 sampled entries in every workgroup (about where the exact
 // look-ups and the rounds without a marked link, whose links are all looked up, cost the same number of requests).
 // Any T gives the right result, only the time depends on it.  Word (y >> 5) * N + x holds the pairs of x with the
-// nodes y & ~31 .. y | 31.  tops[workgroup] = largest entry seen, for the early end in rd_batch_marked_kernel.
+// nodes y & ~31 .. y | 31 (the folded matrix is symmetric, so a ballot over x gives the words of y).  tops[workgroup] =
+// largest entry seen, for the early end in rd_batch_marked_kernel.
+// Behind the marks (N^2 / 8 bytes) the folded entries themselves, 16 bits each, lower triangle with diagonal by rows
+// (N (N + 1) bytes, both within the workspace's 2 N^2): an exact look-up is then one request; used when all fit 16 bits.
+constexpr int kMarkBlocks = 64;                    // tops: 64 words, the flags part of the workspace
+
 template <int LOGN>
 __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restrict__ c, uint32_t* __restrict__ marks,
                                                           int32_t* __restrict__ tops) {
-    constexpr int N = 1 << LOGN, kSamples = 4096, kMarkedPerRound = LOGN == 10 ? 6 : 5;
-    constexpr int kWanted = kSamples * kMarkedPerRound / (N / 2);               // samples at or above T
-    __shared__ int count[2][16];
-    __shared__ int wave_top[16];
+    constexpr int N = 1 << LOGN, kWanted = LOGN == 10 ? 3 : 5;                  // of 256 samples: 6 or 5 of N / 2
+    constexpr int kRows = N * N / 64 / (16 * kMarkBlocks);                      // rows of 64 entries per wave
+    uint16_t* folded = (uint16_t*)(marks + N * N / 32);
+    __shared__ int per_wave[16], wave_top[16];
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     auto entry = [&](int x, int y) { return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1); };
-    int v[kSamples / 1024];
+    int v[4];
 #pragma unroll
-    for (int i = 0; i < kSamples / 1024; ++i) {
+    for (int i = 0; i < 4; ++i) {
         const uint32_t h = (uint32_t)splitmix64_at(0, (uint64_t)(threadIdx.x + 1024 * i + 1));
         const int x = h & (N - 1), y = (h >> LOGN) & (N - 1);
         v[i] = entry(x, x == y ? y ^ 1 : y);
     }
-    int T = 0;                                     // largest value that kWanted samples reach
-    for (int bit = 20; bit >= 0; --bit) {
-        const int t = T | (1 << bit);
-        int n = 0;
+    // a wave takes 64 consecutive x and kRows consecutive y, so both directions come from few cache lines
+    const int w = blockIdx.x * 16 + wv, x0 = (w & (N / 64 - 1)) * 64, y0 = (w / (N / 64)) * kRows;
+    int e[kRows];
 #pragma unroll
-        for (int i = 0; i < kSamples / 1024; ++i) n += __popcll(__ballot(v[i] >= t));
-        if (lane == 0) count[bit & 1][wv] = n;
-        __syncthreads();                           // two buffers: the next bit's counts never meet this bit's reads
-        int all = 0;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) all += count[bit & 1][k];
-        if (all >= kWanted) T = t;
-    }
-    const int w = blockIdx.x * 1024 + threadIdx.x, x = w & (N - 1), y0 = (w >> LOGN) * 32;
-    uint32_t bits = 0;
+    for (int k = 0; k < kRows; ++k) e[k] = entry(x0 + lane, y0 + k);
+    const int T = sampled_threshold(v, kWanted, per_wave);
     int top = 0;
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) {
-        const int e = entry(x, y0 + k);
-        top = max(top, e);
-        bits |= (uint32_t)(e >= T) << k;
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = y0 + k;
+        const unsigned long long bits = __ballot(e[k] >= T);
+        top = max(top, e[k]);
+        if (lane < 2) marks[((x0 >> 5) + lane) * N + y] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+        if (x0 + lane <= y) folded[y * (y + 1) / 2 + x0 + lane] = (uint16_t)e[k];
     }
-    marks[w] = bits;
     top = wave_max(top);
     if (lane == 0) wave_top[wv] = top;
     __syncthreads();
@@ -1131,9 +1132,10 @@ __device__ __forceinline__ void lane_links(unsigned a, unsigned b, int lane, uns
 // marked; the marked ones, about 60 of 5120 at N = 1024, are then looked up exactly in the caller's matrix, each lane
 // taking its own one by one, all rounds mixed, their maxima formed in LDS.  A round without a marked link is looked up
 // whole; one that has reached the matrix maximum is finished, so a matrix of few values ends early.
-// Before: rd_batch_folded_kernel, bound by the L2's request rate.  Both launches together, seeded orders: N = 1024,
-// 65536 orders 1384 -> 162 us (1.7 TB/s of the order stream), 1000 orders 105 -> 32 us; N = 512, 131072 orders
-// 1136 -> 161 us, 1000 orders 27 -> 22 us: faster from the smallest batch on, so nothing else serves these sizes.
+// Before: the folded 16-bit matrix through L2, bound by its request rate.  Both launches together, seeded orders: N = 1024,
+// 65536 orders 1384 -> 146 us (1.9 TB/s of the order stream), 1000 orders 104 -> 28 us; N = 512, 131072 orders
+// 1136 -> 147 us, 1000 orders 27 -> 17 us.  Orders without any marked link, every link looked up: N = 1024, 65536 orders
+// 1213 -> 1227 us, N = 512 458 -> 455 us.  So nothing else serves these sizes.
 template <int LOGN>
 __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kernel(
     const int32_t* __restrict__ c, const uint32_t* __restrict__ marks, const int32_t* __restrict__ tops,
@@ -1147,11 +1149,19 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     for (int e = threadIdx.x; e < N * N / 128; e += 64 * WAVES) ((int4*)lmarks)[e] = ((const int4*)marks)[e];
     int top = 0;
-    for (int k = 0; k < N * N / 32 / 1024; ++k) top = max(top, tops[k]);
+    for (int k = 0; k < kMarkBlocks; ++k) top = max(top, tops[k]);
     const long long weight =
         lane < LOGN ? (weights ? (long long)clampi(weights[lane], 0, kMaxRoundWeight) : 1ll) : 0ll;
     __syncthreads();
-    auto exact = [&](int x, int y) { return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1); };
+    const uint16_t* folded = (const uint16_t*)(marks + N * N / 32);
+    const bool halves = top < (1 << 16);
+    auto exact = [&](int x, int y) {
+        if (halves) {
+            const int hi = max(x, y), lo = min(x, y);
+            return (int)folded[hi * (hi + 1) / 2 + lo];
+        }
+        return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1);
+    };
     const bool aligned = ((uintptr_t)perms & 15u) == 0;
     auto load = [&](int64_t b, int4 (&v)[Q]) {
         const int32_t* pi = perms + b * N + 4 * lane;
@@ -1265,7 +1275,7 @@ static hipError_t rd_marked_launch(const int32_t* c, void* room, int32_t* tops, 
     hipError_t e = hipFuncSetAttribute((const void*)rd_batch_marked_kernel<LOGN>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mark_links_kernel<LOGN>, dim3(N * N / 32 / 1024), dim3(1024), 0, s, c, (uint32_t*)room, tops);
+    hipLaunchKernelGGL(mark_links_kernel<LOGN>, dim3(kMarkBlocks), dim3(1024), 0, s, c, (uint32_t*)room, tops);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     int64_t blocks = (B + WAVES - 1) / WAVES;
