@@ -399,14 +399,16 @@ static bool ring_rows_pays(int N, int64_t B) {
 
 // Max-hop, 280 < N <= 1024: only hops among the matrix's largest entries have to be looked up exactly.  Every workgroup
 // marks in LDS, one bit per entry (32 KiB at N = 500, 128 KiB at N = 1024), the entries that are T or more; T is chosen
-// from 4096 sampled entries so that about ln N of an order's N hops carry the bit (where the exact look-ups and the orders
+// from 4096 sampled hops of the batch's orders so that about ln N of an order's N hops carry the bit (where the exact look-ups and the orders
 // without a marked hop, which are looked up whole, cost the same).  Any T gives the right result, only the time depends on
 // it.  Sixteen lanes per order as in ring_batch_rows_kernel; a lane notes its marked hops in a 64-bit mask (at most 64
 // steps) and afterwards looks them up one by one, ranks from the order stream (in cache) and entries through L2.  An order
 // that has reached the matrix maximum is finished, so a matrix of few values ends early.
 // The generic kernels ask L2 for every hop and run at its request rate; here what is left is the marking and the order
-// stream.  Generic -> marked: N = 300, 200000 orders 254 -> 79 us; N = 500, 130000 orders 292 -> 89 us, 65000 orders of two
-// bytes a rank 139 -> 55 us; N = 1000, 65000 orders 335 -> 137 us.
+// stream.  Generic -> marked, seeded orders: N = 300, 200000 orders 255 -> 87 us; N = 500, 65000 orders 144 -> 65 us, of two
+// bytes a rank 140 -> 58 us; N = 1000, 65000 orders 335 -> 134 us.  Orders of small hops only: N = 500, 65000 orders
+// 113 -> 57 us (a threshold from the matrix's entries instead was 3 to 7 us cheaper on seeded orders, but marks none of
+// these).
 template <typename RANK>
 __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32_t* __restrict__ c, int N,
                                                                      const RANK* __restrict__ perms, int64_t B,
@@ -416,12 +418,14 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
     int* per_wave = (int*)smem_ring_marks;                       // [2][16]: the waves' estimates of T, their maxima
     uint32_t* marks = (uint32_t*)(smem_ring_marks + 128);        // bit e of the flat matrix: bit e & 31 of word e >> 5
     const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15;
+    auto node = [&](int r) { return sizeof(RANK) == 4 ? clampi(r, 0, N - 1) : min(r, N - 1); };
     int v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint64_t h = splitmix64_at(0, (uint64_t)(threadIdx.x + 1024 * i + 1));
-        const int x = (int)(((h & 0xffffffffu) * (uint64_t)N) >> 32), y = (int)(((h >> 32) * (uint64_t)N) >> 32);
-        v[i] = max(c[x * N + (x == y ? (y ? y - 1 : 1) : y)], 0);
+        const int p = (int)(((h & 0xffffffffu) * (uint64_t)N) >> 32);
+        const RANK* pi = perms + (int64_t)__umul64hi(h, (uint64_t)B) * N;
+        v[i] = max(c[node(pi[p]) * N + node(pi[p ? p - 1 : N - 1])], 0);
     }
     const int T = sampled_threshold(v, wanted, per_wave);
     // 32 runs of 64 entries per wave and pass, all loads in flight; the workgroups start at different places, so that they
@@ -448,7 +452,6 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; ++k) top = max(top, per_wave[16 + k]);
-    auto node = [&](int r) { return sizeof(RANK) == 4 ? clampi(r, 0, N - 1) : min(r, N - 1); };
     auto row_max = [](int a) {
         a = max(a, __builtin_amdgcn_update_dpp(a, a, 0xB1, 0xf, 0xf, true));
         a = max(a, __builtin_amdgcn_update_dpp(a, a, 0x4E, 0xf, 0xf, true));
@@ -524,10 +527,9 @@ static hipError_t ring_max_marked_launch(const int32_t* c, int N, const RANK* pe
     return hipGetLastError();
 }
 
-// Marking reads the matrix once per workgroup (N = 300: 12 us, N = 1000: 85 us), as long as the generic kernel takes for
-// about 20000 orders at any of these N (generic / marked: N = 300, 16000 orders 22 / 21 us; N = 700, 20000 orders 65 / 63 us;
-// N = 1000, 16000 orders 85 / 95 us).
-constexpr int64_t kRingMaxMarkedMinOrders = 20480;
+// The threshold and the marking, once per workgroup, take about as long as the generic kernel takes for 21000 (N = 1000) to
+// 25000 orders (N = 300; generic / marked: N = 300, 20480 orders 26 / 31 us; N = 1000, 20480 orders 106 / 111 us).
+constexpr int64_t kRingMaxMarkedMinOrders = 28672;
 static bool ring_max_marked_pays(int N, int64_t B) { return N > kRingRowsMaxN && B >= kRingMaxMarkedMinOrders; }
 
 hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const int32_t* perms, int64_t B,

@@ -28,7 +28,7 @@ def _matrices(n):
 
 @pytest.mark.parametrize("n", [281, 319, 320, 321, 500, 512, 1000, 1023, 1024])
 def test_ring_batch_max_marked(n):
-    b = 20480 + 5                                      # just above the smallest batch that takes this kernel
+    b = 28672 + 5                                      # just above the smallest batch that takes this kernel
     perms = random_perms(n, b, seed=n)
     perms[0] = np.arange(n)
     perms[1] = np.roll(np.arange(n), 3)[::-1]
