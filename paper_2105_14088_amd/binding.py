@@ -128,12 +128,17 @@ def _dev(t: Optional[torch.Tensor], dtype, name: str) -> Optional[int]:
 
 
 # The current stream's handle without a torch.cuda.Stream object around it (0.2 us instead of 3 us, measured; a small
-# batch call takes about 6 us in all).
-_current_device, _current_raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+# batch call takes about 6 us in all).  Both names are private to torch: where one is missing, the public call is made.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream) -> int:
-    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_device is None or _current_raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(_current_device())
 
 
 def _new(shape, dtype, device, stream=None) -> torch.Tensor:
