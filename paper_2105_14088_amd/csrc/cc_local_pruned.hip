@@ -87,7 +87,14 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
 #pragma unroll
     for (int k = 0; k < K; ++k) good = good && (tid + THREADS * k >= N || rank_of(info[t0[k]]) == tid + THREADS * k);
     bool search = __ballot(!good) == 0;
-    if (WAVES > 1) search = __syncthreads_and(search) != 0;
+    if (WAVES > 1) {
+        // over the wavefronts of this restart alone: the workgroup's others have ended, which a plain barrier allows and a
+        // workgroup-wide reduction of the library need not
+        if (lane == 0) red[parity][wv] = search ? 1u : 0u;
+        __syncthreads();
+        search = __ballot(red[parity][min(lane, WAVES - 1)] == 0) == 0;
+        parity ^= 1;
+    }
 
     // the move a lane remembers: a pair and how it is used.  Use: length of the segment x ends (0: a 2-opt move) << 2 |
     // x is its last rank << 1 | y stands behind the gap (2-opt: the edges before x and y).  At first the nearest partner

@@ -44,3 +44,20 @@ def test_orders_that_are_no_permutation_end(n):
     got = gpu_search(c, oracle.SUM, 3, 1, init)
     clamped = np.clip(init, 0, n - 1)
     assert (got["costs"] <= [oracle.ring_cost(c, t) for t in clamped]).all()
+
+
+@pytest.mark.parametrize("n", [130, 192, 256, 400, 1024])
+def test_a_node_twice_in_one_wavefronts_ranks_leaves_the_order_alone(n):
+    """Only one wavefront of the restart sees the repeated node; all of them have to stop, while the next restart's search."""
+    restarts = min((n + 63) // 64, 6) + 1
+    init = np.stack([np.random.default_rng(r).permutation(n) for r in range(restarts)]).astype(np.int32)
+    for r in range(restarts - 1):
+        last = min(64 * (r + 1), n) - 1
+        init[r, 64 * r] = init[r, last]              # 64 r and last are ranks of wavefront r
+    say(f"pruned ring sum N={n}: a node twice among one wavefront's ranks")
+    c = random_matrix(n, 19, symmetric=True, lo=0, hi=3000)
+    got = gpu_search(c, oracle.SUM, restarts, 1, init)
+    assert np.array_equal(got["tours"][:-1], init[:-1]) and not got["moves"][:-1].any()
+    assert np.array_equal(got["costs"][:-1], [oracle.ring_cost(c, t) for t in init[:-1]])
+    costs, tours, moves = oracle.restarts(c, oracle.SUM, 1, 0, 1, init=init[-1:])
+    assert got["costs"][-1] == costs[0] and got["moves"][-1] == moves[0] and np.array_equal(got["tours"][-1], tours[0])

@@ -50,3 +50,21 @@ def test_orders_that_are_no_permutation_end(n):
     torch.cuda.synchronize()
     clamped = np.clip(init, 0, n - 1)
     assert (b.restart_costs.cpu().numpy() <= [oracle.ring_cost(c, t) for t in clamped]).all()
+
+
+@pytest.mark.parametrize("n", [150, 256, 400])
+def test_a_node_twice_in_one_wavefronts_ranks_leaves_the_order_alone(n):
+    """Only one wavefront of the restart sees the repeated node; all of them have to stop, while the next restart's search."""
+    restarts = min((n + 63) // 64, 6) + 1
+    init = np.stack([np.random.default_rng(r).permutation(n) for r in range(restarts)]).astype(np.int32)
+    for r in range(restarts - 1):
+        init[r, 64 * r] = init[r, min(64 * (r + 1), n) - 1]        # both are ranks of wavefront r
+    say(f"pruned insertion N={n}: a node twice among one wavefront's ranks")
+    c = random_matrix(n, 19, symmetric=True, lo=0, hi=3000)
+    b = cc.cc_local_search_ex(dev(c), cc.CC_RING_SUM, BOTH, restarts, 1, init_tours=dev(init))
+    torch.cuda.synchronize()
+    costs, tours, moves = b.restart_costs.cpu().numpy(), b.restart_tours.cpu().numpy(), b.restart_moves.cpu().numpy()
+    assert np.array_equal(tours[:-1], init[:-1]) and not moves[:-1].any()
+    assert np.array_equal(costs[:-1], [oracle.ring_cost(c, t) for t in init[:-1]])
+    oc, ot, om = oracle.local_restarts(c, oracle.SUM, BOTH, 1, 0, 1, init=init[-1:])
+    assert costs[-1] == oc[0] and moves[-1] == om[0] and np.array_equal(tours[-1], ot[0])
