@@ -12,8 +12,8 @@
 // N = 256) where the exhaustive sweep has N (N-3) / 2 moves.  Equal values are looked at too (<=, not <), so the winner
 // (value, lowest id) is the exhaustive sweep's.
 //
-// Lists: the partners of a node in buckets of cost (eight per octave, from the row's smallest entry on: the top bits of
-// the cost as a float), with the number of partners up to each bucket: how far a threshold reaches is one look-up, and
+// Lists: the partners of a node in buckets of cost (16, 8 or 4 per octave, as the spread of the row asks: the top bits of
+// 2 cost + 1 as a float), with the number of partners up to each bucket: how far a threshold reaches is one look-up, and
 // order inside a bucket does not matter.  A list holds the nearest M partners; a node whose threshold reaches further,
 // or whose candidates exceed the room for them, is scanned against every node instead.
 //   * N <= 256: lists in LDS, made by the workgroup itself; up to 256 (N <= 192: mostly 512) restarts one workgroup of a
@@ -46,10 +46,11 @@ using namespace pruned;
 // -1 .. N, and per wave the laid out candidates' owners and the candidates whose bracket passed.
 __host__ __device__ constexpr size_t order_bytes(int N) { return ((size_t)N * 8 + (size_t)(N + 2) * 2 + 15) & ~(size_t)15; }
 
-// One descent.  The bucket of a node's smallest cost is base0 (one node per lane) or bases[node].  Wave `wv` of the restart owns the nodes 64 * (wv * K + k) + lane.
+// One descent.  A node's scale (of its buckets) is scale0 (one node per lane) or scales[node].  Wave `wv` of the restart
+// owns the nodes 64 * (wv * K + k) + lane.
 template <int WAVES, int K, int ROOM, typename COUNT, class MAT>
 __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __restrict__ lists, int M,
-                                        const COUNT* __restrict__ counts, int base0, const uint16_t* bases, unsigned char* order_mem,
+                                        const COUNT* __restrict__ counts, int scale0, const uint16_t* scales, unsigned char* order_mem,
                                         unsigned char* wave_mem, unsigned long long (*red)[WAVES], int wv, int lane,
                                         int32_t* __restrict__ tour, int64_t* __restrict__ cost_out,
                                         int32_t* __restrict__ moves_out) {
@@ -158,7 +159,8 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             r_value = sweep_best;
         }
         group_min();
-        const int D = hi;
+        // only a move that lowers the cost is wanted: its value is -1 or less
+        const int D = min(hi, -1);
         int n_passed = 0;
         // scores the n passed candidates from `from` on; a lane's candidate may stand on both sides
         auto score = [&](int from, int n) {
@@ -215,8 +217,8 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             const int x_first = 64 * (wv * K + k), x = x_first + lane;
             const uint2 ix = info[min(x, N - 1)];
             const int reach = max(hop_in(ix), hop_out(ix)) + (D >> 1);
-            const int b = K == 1 ? base0 : (int)bases[min(x, N - 1)];
-            const int bucket = bucket_of(max(reach, 0)) - b;
+            const int scale = K == 1 ? scale0 : (int)scales[min(x, N - 1)];
+            const int bucket = bucket_of(max(reach, 0), scale);
             int count = (int)counts[(size_t)min(x, N - 1) * kBuckets + max(0, min(bucket, kBuckets - 2))];
             count = bucket >= kBuckets - 1 ? N - 1 : count;
             count = x < N && reach >= 0 && bucket >= 0 ? count : 0;
@@ -362,8 +364,8 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
     __shared__ unsigned long long red[2][WAVES];
     uint32_t* lists = (uint32_t*)smem;                         // [N][M]
     unsigned char* counts = smem + (size_t)N * M * 4;          // [N][kBuckets]
-    uint16_t* bases = (uint16_t*)(counts + (size_t)N * kBuckets);      // [N]
-    uint16_t* m16 = bases + N;                                 // [N][N]
+    uint16_t* scales = (uint16_t*)(counts + (size_t)N * kBuckets);     // [N]
+    uint16_t* m16 = scales + N;                                 // [N][N]
     unsigned char* rest = smem + shared_bytes(N, M, lds_matrix);
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     {
@@ -373,11 +375,11 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
         int high = 0;
         for (int x = wv; x < N; x += nw) {
             int row_max;
-            const int b = make_list<(WAVES > 1 ? WAVES : K)>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
+            const int scale = make_list<(WAVES > 1 ? WAVES : K)>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
                                                              hist, lane, row_max, [&](int y, int cost) {
                                                                  if (lds_matrix) m16[x * N + y] = (uint16_t)cost;
                                                              });
-            if (lane == 0) bases[x] = (uint16_t)b;
+            if (lane == 0) scales[x] = (uint16_t)scale;
             high = max(high, row_max);
         }
         if (lane == 0) largest[wv] = high;
@@ -392,12 +394,12 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
     const int mine = WAVES > 1 ? 0 : wv, part = WAVES > 1 ? wv : 0;
     unsigned char* order_mem = rest + (size_t)mine * (order_bytes(N) + wave_bytes(kRoom));
     unsigned char* wave_mem = order_mem + order_bytes(N) + (size_t)part * wave_bytes(kRoom);
-    const int base0 = (int)bases[min(64 * part + lane, N - 1)];
+    const int scale0 = (int)scales[min(64 * part + lane, N - 1)];
     if (in_lds)
-        descend<WAVES, K, kRoom>(LdsMatrix{m16, N}, N, lists, M, counts, base0, bases, order_mem, wave_mem, red, part, lane,
+        descend<WAVES, K, kRoom>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, red, part, lane,
                           tours + r * N, costs + r, moves + r);
     else
-        descend<WAVES, K, kRoom>(CallersMatrix{c, N}, N, lists, M, counts, base0, bases, order_mem, wave_mem, red, part, lane,
+        descend<WAVES, K, kRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, red, part, lane,
                           tours + r * N, costs + r, moves + r);
 }
 
@@ -412,9 +414,9 @@ __global__ __launch_bounds__(256) void partner_lists_kernel(const int32_t* __res
     if (x >= N) return;
     uint16_t* mine = counts + (size_t)x * kBuckets;
     int high;
-    const int b = N <= 512 ? make_list<8>(c, N, x, M, lists + (size_t)x * M, mine, hist[wv], lane, high, [](int, int) {})
+    const int scale = N <= 512 ? make_list<8>(c, N, x, M, lists + (size_t)x * M, mine, hist[wv], lane, high, [](int, int) {})
                            : make_list<16>(c, N, x, M, lists + (size_t)x * M, mine, hist[wv], lane, high, [](int, int) {});
-    if (lane == 63) mine[kBuckets - 1] = (uint16_t)b;          // the open bucket's count is N - 1: the base has its place
+    if (lane == 63) mine[kBuckets - 1] = (uint16_t)scale;      // the last bucket's count is N - 1: the scale has its place
 }
 
 template <int WAVES>
@@ -428,8 +430,8 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_sum_pruned_group_kernel(con
     __shared__ unsigned long long red[2][WAVES];
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
-    const int base = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
-    descend<WAVES, 1, kGroupRoom>(CallersMatrix{c, N}, N, lists, M, counts, base, nullptr, smem,
+    const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
+    descend<WAVES, 1, kGroupRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
                                   smem + order_bytes(N) + wv * wave_bytes(kGroupRoom), red, wv, lane, tours + r * N, costs + r,
                                   moves + r);
 }

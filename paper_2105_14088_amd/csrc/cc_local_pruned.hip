@@ -40,7 +40,7 @@ __host__ __device__ constexpr size_t local_order_bytes(int N) {
 
 template <int WAVES, int K, int ROOM, bool WITH_2OPT, typename COUNT, class MAT>
 __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __restrict__ lists, int M,
-                                        const COUNT* __restrict__ counts, int base0, const uint16_t* bases,
+                                        const COUNT* __restrict__ counts, int scale0, const uint16_t* scales,
                                         unsigned char* order_mem, unsigned char* wave_mem,
                                         unsigned long long (*red)[WAVES], int wv, int lane, int32_t* __restrict__ tour,
                                         int64_t* __restrict__ cost_out, int32_t* __restrict__ moves_out) {
@@ -192,7 +192,8 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
         }
         group_min();                                           // its barrier also covers `value`
         if (WAVES == 1) __builtin_amdgcn_wave_barrier();
-        const int D = hi;
+        // only a move that lowers the cost is wanted: its value is -1 or less
+        const int D = min(hi, -1);
         int n_passed = 0;
         // scores n passed pairs in all their roles
         auto score = [&](int from, int n) {
@@ -289,8 +290,8 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             const int x_first = 64 * (wv * K + k), x = x_first + lane;
             const int2 vx = value[min(x, N - 1)];
             const int reach = max(vx.x, vx.y) + (D >> 1);
-            const int b = K == 1 ? base0 : (int)bases[min(x, N - 1)];
-            const int bucket = bucket_of(max(reach, 0)) - b;
+            const int scale = K == 1 ? scale0 : (int)scales[min(x, N - 1)];
+            const int bucket = bucket_of(max(reach, 0), scale);
             int count = (int)counts[(size_t)min(x, N - 1) * kBuckets + max(0, min(bucket, kBuckets - 2))];
             count = bucket >= kBuckets - 1 ? N - 1 : count;
             count = x < N && reach >= 0 && bucket >= 0 ? count : 0;
@@ -436,8 +437,8 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
     __shared__ unsigned long long red[2][WAVES];
     uint32_t* lists = (uint32_t*)smem;                         // [N][M]
     unsigned char* counts = smem + (size_t)N * M * 4;          // [N][kBuckets]
-    uint16_t* bases = (uint16_t*)(counts + (size_t)N * kBuckets);      // [N]
-    uint16_t* m16 = bases + N;                                 // [N][N]
+    uint16_t* scales = (uint16_t*)(counts + (size_t)N * kBuckets);      // [N]
+    uint16_t* m16 = scales + N;                                 // [N][N]
     unsigned char* rest = smem + shared_bytes(N, M, lds_matrix);
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     {
@@ -445,11 +446,11 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
         int high = 0;
         for (int x = wv; x < N; x += nw) {
             int row_max;
-            const int b = make_list<(WAVES > 1 ? WAVES : K)>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
+            const int scale = make_list<(WAVES > 1 ? WAVES : K)>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
                                                              hist, lane, row_max, [&](int y, int cost) {
                                                                  if (lds_matrix) m16[x * N + y] = (uint16_t)cost;
                                                              });
-            if (lane == 0) bases[x] = (uint16_t)b;
+            if (lane == 0) scales[x] = (uint16_t)scale;
             high = max(high, row_max);
         }
         if (lane == 0) largest[wv] = high;
@@ -464,12 +465,12 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
     const int mine = WAVES > 1 ? 0 : wv, part = WAVES > 1 ? wv : 0;
     unsigned char* order_mem = rest + (size_t)mine * (local_order_bytes(N) + wave_bytes(kRoom));
     unsigned char* wave_mem = order_mem + local_order_bytes(N) + (size_t)part * wave_bytes(kRoom);
-    const int base0 = (int)bases[min(64 * part + lane, N - 1)];
+    const int scale0 = (int)scales[min(64 * part + lane, N - 1)];
     if (in_lds)
-        descend<WAVES, K, kRoom, WITH_2OPT>(LdsMatrix{m16, N}, N, lists, M, counts, base0, bases, order_mem, wave_mem, red, part,
+        descend<WAVES, K, kRoom, WITH_2OPT>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, red, part,
                                             lane, tours + r * N, costs + r, moves + r);
     else
-        descend<WAVES, K, kRoom, WITH_2OPT>(CallersMatrix{c, N}, N, lists, M, counts, base0, bases, order_mem, wave_mem, red,
+        descend<WAVES, K, kRoom, WITH_2OPT>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, red,
                                             part, lane, tours + r * N, costs + r, moves + r);
 }
 
@@ -485,8 +486,8 @@ __global__ __launch_bounds__(64 * WAVES) void local_pruned_group_kernel(const in
     __shared__ unsigned long long red[2][WAVES];
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
-    const int base = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
-    descend<WAVES, 1, kGroupRoom, WITH_2OPT>(CallersMatrix{c, N}, N, lists, M, counts, base, nullptr, smem,
+    const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
+    descend<WAVES, 1, kGroupRoom, WITH_2OPT>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
                                              smem + local_order_bytes(N) + wv * wave_bytes(kGroupRoom), red, wv, lane,
                                              tours + r * N, costs + r, moves + r);
 }

@@ -9,12 +9,26 @@ using namespace ccd;
 
 constexpr int kCostMax = (1 << 21) - 1;
 constexpr int kNone = 0x7fffffff;
-constexpr int kBuckets = 128;           // the last one is open: it and everything beyond
+constexpr int kBuckets = 128;           // of cost per node; the last one holds no partner
 constexpr int kRoom = 512;              // candidates of 64 nodes laid out at a time, N <= 256
 constexpr int kGroupRoom = 1024;        // and above
 constexpr int kPassed = 320;            // candidates whose bracket passed: four times 64 and a rest below 64
 
-__device__ __forceinline__ int bucket_of(int cost) { return (int)(__float_as_uint((float)cost) >> 19); }
+// A cost on a logarithmic scale, 0 included: the bits of 2 cost + 1 as a float, its exponent from 0 on.
+__device__ __forceinline__ unsigned key_of(int cost) { return __float_as_uint((float)(2 * cost + 1)) - (127u << 23); }
+// The buckets of a node: 16, 8 or 4 per octave, the most with which its row's smallest to largest cost (22 octaves at most)
+// fit.  Kept as first bucket | step << 12.  Sixteen per octave of the cost itself from the smallest on, everything beyond
+// 8 octaves in the last, sent every node with one partner at cost 0 to the scan against every node: ring sum, one such
+// partner per node, N = 256, 4096 restarts 79 ms, now 4.8; N = 512, 768 restarts 145 ms, now 6.2; N = 1000, 32 restarts 222 ms,
+// now 10.5.
+__device__ __forceinline__ int scale_of(int lowest, int highest) {
+    const unsigned low = key_of(lowest), high = key_of(highest);
+    int step = 0;
+    while ((high >> (19 + step)) - (low >> (19 + step)) > kBuckets - 2) ++step;
+    return (int)(low >> (19 + step)) | (step << 12);
+}
+// negative: below the row's smallest cost
+__device__ __forceinline__ int bucket_of(int cost, int scale) { return (int)(key_of(cost) >> (19 + (scale >> 12))) - (scale & 4095); }
 
 __device__ __forceinline__ int wave_prefix_sum(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1
@@ -54,7 +68,7 @@ struct LdsMatrix {
 };
 
 // Makes the list of node x with one wavefront: list[0 .. M): cost << 10 | node, counts[b]: partners up to bucket b (the
-// last one N - 1).  Returns the bucket of the smallest cost; row_max: the largest cost.  hist: kBuckets words of LDS of
+// last one N - 1).  Returns the node's scale; row_max: the largest cost.  hist: kBuckets words of LDS of
 // this wave.  each(y, cost): every entry of the row.
 template <int E, typename COUNT, class EACH>
 __device__ __forceinline__ int make_list(const int32_t* __restrict__ c, int N, int x, int M, uint32_t* list, COUNT* counts,
@@ -68,15 +82,15 @@ __device__ __forceinline__ int make_list(const int32_t* __restrict__ c, int N, i
         low = min(low, in ? cost[k] : kNone);
         high = max(high, cost[k]);
     }
-    const int base = bucket_of(wave_min(low));
     row_max = wave_max(high);
+    const int scale = scale_of(wave_min(low), row_max);
     static_assert(kBuckets == 128, "two buckets per lane");
     hist[lane] = hist[lane + 64] = 0;
     __builtin_amdgcn_wave_barrier();
     int at[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-        at[k] = cost[k] >= 0 ? atomicAdd(&hist[min(bucket_of(cost[k]) - base, kBuckets - 1)], 1) : 0;
+        at[k] = cost[k] >= 0 ? atomicAdd(&hist[bucket_of(cost[k], scale)], 1) : 0;
         if (lane + 64 * k < N) each(lane + 64 * k, max(cost[k], 0));
     }
     __builtin_amdgcn_wave_barrier();
@@ -90,14 +104,14 @@ __device__ __forceinline__ int make_list(const int32_t* __restrict__ c, int N, i
 #pragma unroll
     for (int k = 0; k < E; ++k)
         if (cost[k] >= 0) {
-            const int i = hist[min(bucket_of(cost[k]) - base, kBuckets - 1)] + at[k];
+            const int i = hist[bucket_of(cost[k], scale)] + at[k];
             if (i < M) list[i] = ((unsigned)cost[k] << 10) | (unsigned)(lane + 64 * k);
         }
     __builtin_amdgcn_wave_barrier();
-    return base;
+    return scale;
 }
 
-// LDS the restarts of a workgroup share (N <= 256): lists, counts, bases, matrix
+// LDS the restarts of a workgroup share (N <= 256): lists, counts, scales, matrix
 __host__ __device__ constexpr size_t shared_bytes(int N, int M, int lds_matrix) {
     return ((size_t)N * (M * 4 + kBuckets + 2 + (lds_matrix ? 2 * N : 0)) + 15) & ~(size_t)15;
 }

@@ -61,3 +61,54 @@ def test_a_node_twice_in_one_wavefronts_ranks_leaves_the_order_alone(n):
     assert np.array_equal(got["costs"][:-1], [oracle.ring_cost(c, t) for t in init[:-1]])
     costs, tours, moves = oracle.restarts(c, oracle.SUM, 1, 0, 1, init=init[-1:])
     assert got["costs"][-1] == costs[0] and got["moves"][-1] == moves[0] and np.array_equal(got["tours"][-1], tours[0])
+
+
+def _seconds(c, restarts, buffers):
+    best = float("inf")
+    for _ in range(3):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        cc.cc_2opt_search_ex(c, oracle.SUM, restarts, 5, buffers=buffers)
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end))
+    return best
+
+
+def _racks(n):
+    return hierarchical_matrix(n, (4, 32), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n)
+
+
+def _one_zero_each(n):
+    c, a = _racks(n), np.random.default_rng(n).permutation(n)
+    c[a[0:n - 1:2], a[1::2]] = c[a[1::2], a[0:n - 1:2]] = 0
+    return c
+
+
+def _wide(n):
+    u = np.triu(np.exp(np.random.default_rng(n).uniform(0, 14.5, (n, n))).astype(np.int32), 1)
+    u = np.where(u < 3, 0, u)
+    return (u + u.T).astype(np.int32)
+
+
+@pytest.mark.parametrize("n,restarts", [(130, 3), (191, 700), (256, 3), (300, 2)])
+@pytest.mark.parametrize("make", [_one_zero_each, lambda n: _racks(n) // 100, _wide], ids=["one zero each", "coarse", "wide"])
+def test_zeros_and_wide_spreads(n, restarts, make):
+    say(f"pruned ring sum N={n} R={restarts}: costs from 0 on")
+    c = make(n).astype(np.int32)
+    got = gpu_search(c, oracle.SUM, restarts, 3)
+    for r in range(0, restarts, 100):
+        costs, tours, moves = oracle.restarts(c, oracle.SUM, 3, r, r + 1)
+        assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0] and np.array_equal(got["tours"][r], tours[0])
+    if restarts < 10:
+        assert_search_equal(got, oracle.search(c, oracle.SUM, restarts, 3))
+
+
+def test_a_partner_at_cost_zero_does_not_switch_the_lists_off():
+    """With one partner at cost 0 per node the search takes about the time it takes without (12 times while the buckets of
+    cost covered 8 octaves from the smallest one on)."""
+    n, restarts = 512, 32
+    say(f"pruned ring sum N={n} R={restarts}: time with a zero per node")
+    buffers = cc.SearchBuffers(n, oracle.SUM, restarts, "cuda")
+    plain, zeros = (dev(c) for c in (_racks(n), _one_zero_each(n)))
+    assert _seconds(zeros, restarts, buffers) < 3 * _seconds(plain, restarts, buffers)
