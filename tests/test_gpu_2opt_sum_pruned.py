@@ -91,10 +91,19 @@ def _wide(n):
     return (u + u.T).astype(np.int32)
 
 
+def _zones(n, count=2, near=1, far=10):
+    """Equal costs inside a zone, equal ones across."""
+    zone = np.random.default_rng(n).permutation(n) * count // n
+    c = np.where(zone[:, None] == zone[None, :], near, far)
+    return np.where(np.eye(n, dtype=bool), 0, c).astype(np.int32)
+
+
 @pytest.mark.parametrize("n,restarts", [(130, 3), (191, 700), (256, 3), (300, 2)])
-@pytest.mark.parametrize("make", [_one_zero_each, lambda n: _racks(n) // 100, _wide], ids=["one zero each", "coarse", "wide"])
-def test_zeros_and_wide_spreads(n, restarts, make):
-    say(f"pruned ring sum N={n} R={restarts}: costs from 0 on")
+@pytest.mark.parametrize("make", [_one_zero_each, lambda n: _racks(n) // 100, _wide, _zones, lambda n: _zones(n, 5, 2, 5),
+                                  lambda n: _zones(n, 16, 3, 4), lambda n: _zones(n, 1, 7)],
+                         ids=["one zero each", "coarse", "wide", "two zones", "five zones", "sixteen zones", "all equal"])
+def test_zeros_and_wide_spreads_and_ties(n, restarts, make):
+    say(f"pruned ring sum N={n} R={restarts}: zeros, spreads, ties")
     c = make(n).astype(np.int32)
     got = gpu_search(c, oracle.SUM, restarts, 3)
     for r in range(0, restarts, 100):
@@ -112,3 +121,13 @@ def test_a_partner_at_cost_zero_does_not_switch_the_lists_off():
     buffers = cc.SearchBuffers(n, oracle.SUM, restarts, "cuda")
     plain, zeros = (dev(c) for c in (_racks(n), _one_zero_each(n)))
     assert _seconds(zeros, restarts, buffers) < 3 * _seconds(plain, restarts, buffers)
+
+
+def test_ties_do_not_bring_all_moves_back():
+    """Two zones of equal costs take less time than racks of costs that all differ (6 times as long while every node looked
+    for the moves that only equal the known one)."""
+    n, restarts = 512, 768
+    say(f"pruned ring sum N={n} R={restarts}: time with two zones of equal costs")
+    buffers = cc.SearchBuffers(n, oracle.SUM, restarts, "cuda")
+    plain, zones = (dev(c) for c in (_racks(n), _zones(n)))
+    assert _seconds(zones, restarts, buffers) < 1.5 * _seconds(plain, restarts, buffers)
