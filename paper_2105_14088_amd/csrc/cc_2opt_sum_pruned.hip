@@ -364,7 +364,10 @@ template <int K, int WAVES>
 __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* __restrict__ c, int N, int M, int lds_matrix,
                                                                  int waves, int restarts, int32_t* __restrict__ tours,
                                                                  int64_t* __restrict__ costs,
-                                                                 int32_t* __restrict__ moves) {
+                                                                 int32_t* __restrict__ moves,
+                                                                 const int32_t* __restrict__ skip_if_small) {
+    // when the exhaustive 16-bit kernel is launched beside this one, the matrix maximum decides which of them runs
+    if (skip_if_small && skip_if_small[0] < (1 << 16)) return;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int largest[16];
     __shared__ unsigned long long red[2][WAVES];
@@ -444,22 +447,22 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_sum_pruned_group_kernel(con
 
 template <int K, int WAVES>
 hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, int restarts, int32_t* tours, int64_t* costs,
-                      int32_t* moves, hipStream_t s) {
+                      int32_t* moves, const int32_t* skip_if_small, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<K, WAVES>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.bytes);
     if (e != hipSuccess) return e;
     const int grid = WAVES > 1 ? restarts : (restarts + plan.waves - 1) / plan.waves;
     hipLaunchKernelGGL((twoopt_sum_pruned_kernel<K, WAVES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
-                       s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves);
+                       s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves, skip_if_small);
     return hipGetLastError();
 }
 
 template <int K>
 hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
-                        hipStream_t s) {
+                        const int32_t* skip_if_small, hipStream_t s) {
     const LdsPlan plan = lds_plan(N, K, restarts, order_bytes(N));
-    return plan.together ? launch_lds<1, K>(c, N, plan, restarts, tours, costs, moves, s)
-                         : launch_lds<K, 1>(c, N, plan, restarts, tours, costs, moves, s);
+    return plan.together ? launch_lds<1, K>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s)
+                         : launch_lds<K, 1>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
 }
 
 template <int WAVES>
@@ -491,10 +494,10 @@ hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, con
 }
 
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
-                                  int32_t* moves, hipStream_t s) {
-    if (N <= 128) return launch_waves<2>(c, N, restarts, tours, costs, moves, s);
-    if (N <= 192) return launch_waves<3>(c, N, restarts, tours, costs, moves, s);
-    if (N <= 256) return launch_waves<4>(c, N, restarts, tours, costs, moves, s);
+                                  int32_t* moves, const int32_t* skip_if_small, hipStream_t s) {
+    if (N <= 128) return launch_waves<2>(c, N, restarts, tours, costs, moves, skip_if_small, s);
+    if (N <= 192) return launch_waves<3>(c, N, restarts, tours, costs, moves, skip_if_small, s);
+    if (N <= 256) return launch_waves<4>(c, N, restarts, tours, costs, moves, skip_if_small, s);
     if (N <= 320) return launch_group<5>(c, N, room, restarts, tours, costs, moves, s);
     if (N <= 384) return launch_group<6>(c, N, room, restarts, tours, costs, moves, s);
     if (N <= 448) return launch_group<7>(c, N, room, restarts, tours, costs, moves, s);

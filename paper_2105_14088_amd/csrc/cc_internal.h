@@ -74,9 +74,10 @@ hipError_t launch_2opt_dsum_n64(const int32_t* c, int restarts, uint64_t seed, b
                                 int64_t* costs, int32_t* moves, const int32_t* flags, hipStream_t s);
 
 // Ring-sum objective, 65 <= N <= 1024 and any entries (cc_2opt_sum_pruned.hip).  `tours` must hold the initial tours;
-// `room`: 2 N^2 bytes of device memory when N > 256 (the workspace's mat16).
+// `room`: 2 N^2 bytes of device memory when N > 256 (the workspace's mat16).  With skip_if_small (N <= 256) it returns at
+// once if skip_if_small[0], the matrix maximum, is below 2^16.
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
-                                  int32_t* moves, hipStream_t s);
+                                  int32_t* moves, const int32_t* skip_if_small, hipStream_t s);
 // Partner lists of all nodes for N > 256, written into `room` (2 N^2 bytes): M entries per list, where lists and counts lie.
 hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
                                 hipStream_t s);

@@ -131,3 +131,18 @@ def test_ties_do_not_bring_all_moves_back():
     buffers = cc.SearchBuffers(n, oracle.SUM, restarts, "cuda")
     plain, zones = (dev(c) for c in (_racks(n), _zones(n)))
     assert _seconds(zones, restarts, buffers) < 1.5 * _seconds(plain, restarts, buffers)
+
+
+@pytest.mark.parametrize("n,restarts", [(97, 3), (99, 2047), (100, 1537), (128, 2), (128, 300), (192, 257), (192, 3073), (256, 257), (256, 1537)])
+@pytest.mark.parametrize("hi", [65535, 65536])
+def test_sizes_with_an_exhaustive_kernel_of_16_bit_entries(n, restarts, hi):
+    """Either side of 2^16, where the two kernels that are enqueued take turns, and of the lines between them."""
+    say(f"ring sum N={n} R={restarts} entries<={hi}")
+    c = random_matrix(n, n, symmetric=True, lo=0, hi=hi)
+    c[0, n - 1] = c[n - 1, 0] = hi
+    got = gpu_search(c, oracle.SUM, restarts, 9)
+    for r in np.linspace(0, restarts - 1, 5).astype(int):
+        costs, tours, moves = oracle.restarts(c, oracle.SUM, 9, int(r), int(r) + 1)
+        assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0] and np.array_equal(got["tours"][r], tours[0])
+    k = int(np.argmin(got["costs"]))
+    assert got["best_restart"] == k and got["best_cost"] == got["costs"][k]
