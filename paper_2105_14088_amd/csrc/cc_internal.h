@@ -82,8 +82,16 @@ hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int resta
 hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
                                 hipStream_t s);
 // Segment insertions, with or without 2-opt, any 4 <= N <= 1024 (cc_local_pruned.hip); same conventions.
-hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, int restarts, int32_t* tours,
-                               int64_t* costs, int32_t* moves, hipStream_t s);
+// With `flags` set an exhaustive kernel is enqueued behind it, and the matrix decides which of them does the work: the other
+// one when more than `most` of the N (N - 1) costs are about the smallest of their row (and, for to_16bit, all are below
+// 2^16).  flags[0] then lets it run: below 2^16 for to_16bit, otherwise 2^16 or above.
+struct TieHandover {
+    int32_t* flags;
+    int most;
+    bool to_16bit;
+};
+hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, const TieHandover& ties, int restarts,
+                               int32_t* tours, int64_t* costs, int32_t* moves, hipStream_t s);
 // N = 128 / 192 / 256, ring-sum objective, max(c) < 2^16: one wavefront per restart, 16-bit matrix in LDS
 // (cc_2opt_multi.hip).  launch_matrix_max writes max(c) to flags[0]; the kernel returns at once if
 // flags[0] >= 2^16.  `tours` must hold the initial tours.

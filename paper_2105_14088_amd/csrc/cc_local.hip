@@ -177,8 +177,18 @@ hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int 
                (!multi || (restarts <= 256 && (with_2opt || N > 128)) || (restarts <= 512 && with_2opt && N < 256))) {
         // only the moves that can win: against the kernel above 1.1 (N = 10) to 3 times (N = 63) to 40 times (N = 1000) as
         // fast; against the exhaustive wavefront kernels at 128 / 192 / 256 as long as every restart has N / 64 wavefronts to
-        // itself (1.2 to 3 times; beyond that 0.4 to 1)
-        return launch_local_pruned(c, N, with_2opt, room, restarts, tours, costs, moves, s);
+        // itself (1.2 to 3 times; beyond that 0.4 to 1).  From N = 65 on the matrix has a say: with many partners at a row's
+        // smallest cost most pairs pass their brackets, and the other kernel is the faster.  Where the lines lie: zones of equal
+        // costs, 1 inside and 10 across, 2-opt and insertion, this kernel against the other one: N = 192, 256 restarts, 2 / 8 / 16
+        // zones 5.2 against 1.2 ms, 2.3 / 1.7, 1.8 / 2.1; N = 128, 64 restarts, 16 zones equal; N = 150, 512 restarts, 2 / 3
+        // zones 6.1 against 4.0 ms, 3.9 / 4.3; insertion alone, 3 / 4 zones 3.6 against 2.6, 3.1 / 3.0.
+        const int all = N * (N - 1);
+        const int most = N == 128 ? all / 24 : multi ? all / 12 : with_2opt ? all / 5 * 2 : all / 10 * 3;
+        const TieHandover ties{N > 64 ? flags : nullptr, most, multi};
+        hipError_t e = launch_local_pruned(c, N, with_2opt, room, ties, restarts, tours, costs, moves, s);
+        if (e != hipSuccess || !ties.flags) return e;
+        if (multi) return launch_local_multi(c, N, with_2opt, restarts, tours, costs, moves, flags, s);
+        skip = flags;
     } else if (N == 64) {
         // one wavefront per restart with 32-bit keys when max(c) < 2^16, else the kernel above: both are enqueued
         // and the matrix maximum, computed on the device, decides which of them does the work

@@ -426,14 +426,24 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
     }
 }
 
+// Whether the kernel behind this one does the work (see TieHandover).  Where many partners cost the same, most pairs pass
+// their brackets in one role or another, and scoring them costs more than the exhaustive sweeps.
+__device__ __forceinline__ bool hand_over(const TieHandover& ties, int tied, int highest) {
+    if (!ties.flags) return false;
+    const bool hand = tied > ties.most && (!ties.to_16bit || highest < (1 << 16));
+    if (blockIdx.x == 0 && threadIdx.x == 0) ties.flags[0] = hand == ties.to_16bit ? 0 : 1 << 16;
+    return hand;
+}
+
 // N <= 64 K, as twoopt_sum_pruned_kernel: lists (and the matrix) in LDS, for `waves` restarts of one wavefront each or
 // (WAVES > 1) one restart of WAVES wavefronts.
 template <int K, int WAVES, bool WITH_2OPT>
 __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __restrict__ c, int N, int M, int lds_matrix,
-                                                            int waves, int restarts, int32_t* __restrict__ tours,
-                                                            int64_t* __restrict__ costs, int32_t* __restrict__ moves) {
+                                                            int waves, TieHandover ties, int restarts,
+                                                            int32_t* __restrict__ tours, int64_t* __restrict__ costs,
+                                                            int32_t* __restrict__ moves) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ int largest[16];
+    __shared__ int largest[16], tied[16];
     __shared__ unsigned long long red[2][WAVES];
     uint32_t* lists = (uint32_t*)smem;                         // [N][M]
     unsigned char* counts = smem + (size_t)N * M * 4;          // [N][kBuckets]
@@ -443,7 +453,7 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     {
         int* hist = (int*)rest + kBuckets * wv;                // where the restarts' state comes later
-        int high = 0;
+        int high = 0, tied_here = 0;
         for (int x = wv; x < N; x += nw) {
             int row_max;
             const int scale = make_list<(WAVES > 1 ? WAVES : K)>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
@@ -452,14 +462,23 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
                                                              });
             if (lane == 0) scales[x] = (uint16_t)scale;
             high = max(high, row_max);
+            tied_here += counts[(size_t)x * kBuckets];
         }
-        if (lane == 0) largest[wv] = high;
+        if (lane == 0) {
+            largest[wv] = high;
+            tied[wv] = tied_here;
+        }
     }
     __syncthreads();
+    int high = 0, tied_in_all = 0;
+    for (int w = 0; w < nw; ++w) {
+        high = max(high, largest[w]);
+        tied_in_all += tied[w];
+    }
+    high = __builtin_amdgcn_readfirstlane(high);
+    if (hand_over(ties, __builtin_amdgcn_readfirstlane(tied_in_all), high)) return;
     if (wv >= waves) return;                                   // barriers below wait for the remaining wavefronts only
-    int high = 0;
-    for (int w = 0; w < nw; ++w) high = max(high, largest[w]);
-    const bool in_lds = lds_matrix && __builtin_amdgcn_readfirstlane(high) < (1 << 16);
+    const bool in_lds = lds_matrix && high < (1 << 16);
     const int64_t r = WAVES > 1 ? blockIdx.x : (int64_t)blockIdx.x * waves + wv;
     if (r >= restarts) return;
     const int mine = WAVES > 1 ? 0 : wv, part = WAVES > 1 ? wv : 0;
@@ -479,13 +498,22 @@ template <int WAVES, bool WITH_2OPT>
 __global__ __launch_bounds__(64 * WAVES) void local_pruned_group_kernel(const int32_t* __restrict__ c, int N, int M,
                                                                         const uint32_t* __restrict__ lists,
                                                                         const uint16_t* __restrict__ counts,
-                                                                        int32_t* __restrict__ tours,
+                                                                        TieHandover ties, int32_t* __restrict__ tours,
                                                                         int64_t* __restrict__ costs,
                                                                         int32_t* __restrict__ moves) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned long long red[2][WAVES];
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
+    {
+        const int x = threadIdx.x;
+        const int tied = wave_sum(x < N ? (int)counts[(size_t)x * kBuckets] : 0);
+        if (lane == 0) red[0][wv] = (unsigned long long)tied;
+        __syncthreads();
+        int tied_in_all = 0;
+        for (int w = 0; w < WAVES; ++w) tied_in_all += (int)red[0][w];
+        if (hand_over(ties, __builtin_amdgcn_readfirstlane(tied_in_all), 0)) return;
+    }
     const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
     descend<WAVES, 1, kGroupRoom, WITH_2OPT>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
                                              smem + local_order_bytes(N) + wv * wave_bytes(kGroupRoom), red, wv, lane,
@@ -493,28 +521,28 @@ __global__ __launch_bounds__(64 * WAVES) void local_pruned_group_kernel(const in
 }
 
 template <int K, int WAVES, bool WITH_2OPT>
-hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, int restarts, int32_t* tours, int64_t* costs,
-                      int32_t* moves, hipStream_t s) {
+hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, const TieHandover& ties, int restarts, int32_t* tours,
+                      int64_t* costs, int32_t* moves, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)local_pruned_kernel<K, WAVES, WITH_2OPT>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.bytes);
     if (e != hipSuccess) return e;
     const int grid = WAVES > 1 ? restarts : (restarts + plan.waves - 1) / plan.waves;
     hipLaunchKernelGGL((local_pruned_kernel<K, WAVES, WITH_2OPT>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)),
-                       plan.bytes, s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves);
+                       plan.bytes, s, c, N, plan.M, plan.lds_matrix, plan.waves, ties, restarts, tours, costs, moves);
     return hipGetLastError();
 }
 
 template <int K, bool WITH_2OPT>
-hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
+hipError_t launch_waves(const int32_t* c, int N, const TieHandover& ties, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                         hipStream_t s) {
     const LdsPlan plan = lds_plan(N, K, restarts, local_order_bytes(N));
     if constexpr (K > 1)
-        if (plan.together) return launch_lds<1, K, WITH_2OPT>(c, N, plan, restarts, tours, costs, moves, s);
-    return launch_lds<K, 1, WITH_2OPT>(c, N, plan, restarts, tours, costs, moves, s);
+        if (plan.together) return launch_lds<1, K, WITH_2OPT>(c, N, plan, ties, restarts, tours, costs, moves, s);
+    return launch_lds<K, 1, WITH_2OPT>(c, N, plan, ties, restarts, tours, costs, moves, s);
 }
 
 template <int WAVES, bool WITH_2OPT>
-hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
+hipError_t launch_group(const int32_t* c, int N, void* room, const TieHandover& ties, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                         hipStream_t s) {
     int M;
     const uint32_t* lists;
@@ -526,30 +554,30 @@ hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((local_pruned_group_kernel<WAVES, WITH_2OPT>), dim3(restarts), dim3(64 * WAVES), lds, s, c, N, M, lists,
-                       counts, tours, costs, moves);
+                       counts, ties, tours, costs, moves);
     return hipGetLastError();
 }
 
 template <bool WITH_2OPT>
-hipError_t launch(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
+hipError_t launch(const int32_t* c, int N, void* room, const TieHandover& ties, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                   hipStream_t s) {
-    if (N <= 64) return launch_waves<1, WITH_2OPT>(c, N, restarts, tours, costs, moves, s);
-    if (N <= 128) return launch_waves<2, WITH_2OPT>(c, N, restarts, tours, costs, moves, s);
-    if (N <= 192) return launch_waves<3, WITH_2OPT>(c, N, restarts, tours, costs, moves, s);
-    if (N <= 256) return launch_waves<4, WITH_2OPT>(c, N, restarts, tours, costs, moves, s);
-    if (N <= 320) return launch_group<5, WITH_2OPT>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 384) return launch_group<6, WITH_2OPT>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 512) return launch_group<8, WITH_2OPT>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 768) return launch_group<12, WITH_2OPT>(c, N, room, restarts, tours, costs, moves, s);
-    return launch_group<16, WITH_2OPT>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 64) return launch_waves<1, WITH_2OPT>(c, N, ties, restarts, tours, costs, moves, s);
+    if (N <= 128) return launch_waves<2, WITH_2OPT>(c, N, ties, restarts, tours, costs, moves, s);
+    if (N <= 192) return launch_waves<3, WITH_2OPT>(c, N, ties, restarts, tours, costs, moves, s);
+    if (N <= 256) return launch_waves<4, WITH_2OPT>(c, N, ties, restarts, tours, costs, moves, s);
+    if (N <= 320) return launch_group<5, WITH_2OPT>(c, N, room, ties, restarts, tours, costs, moves, s);
+    if (N <= 384) return launch_group<6, WITH_2OPT>(c, N, room, ties, restarts, tours, costs, moves, s);
+    if (N <= 512) return launch_group<8, WITH_2OPT>(c, N, room, ties, restarts, tours, costs, moves, s);
+    if (N <= 768) return launch_group<12, WITH_2OPT>(c, N, room, ties, restarts, tours, costs, moves, s);
+    return launch_group<16, WITH_2OPT>(c, N, room, ties, restarts, tours, costs, moves, s);
 }
 
 }  // namespace
 
-hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, int restarts, int32_t* tours,
-                               int64_t* costs, int32_t* moves, hipStream_t s) {
-    return with_2opt ? launch<true>(c, N, room, restarts, tours, costs, moves, s)
-                     : launch<false>(c, N, room, restarts, tours, costs, moves, s);
+hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, const TieHandover& ties, int restarts,
+                               int32_t* tours, int64_t* costs, int32_t* moves, hipStream_t s) {
+    return with_2opt ? launch<true>(c, N, room, ties, restarts, tours, costs, moves, s)
+                     : launch<false>(c, N, room, ties, restarts, tours, costs, moves, s);
 }
 
 }  // namespace cc

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import paper_2105_14088_amd as cc
-from gen import COST_MAX, random_matrix
+from gen import COST_MAX, hierarchical_matrix, random_matrix
 from gpu_util import dev, say
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
@@ -68,3 +68,40 @@ def test_a_node_twice_in_one_wavefronts_ranks_leaves_the_order_alone(n):
     assert np.array_equal(costs[:-1], [oracle.ring_cost(c, t) for t in init[:-1]])
     oc, ot, om = oracle.local_restarts(c, oracle.SUM, BOTH, 1, 0, 1, init=init[-1:])
     assert costs[-1] == oc[0] and moves[-1] == om[0] and np.array_equal(tours[-1], ot[0])
+
+
+def _zones(n, count, near=1, far=10):
+    """Equal costs inside a zone, equal ones across."""
+    zone = np.random.default_rng(n).permutation(n) * count // n
+    c = np.where(zone[:, None] == zone[None, :], near, far)
+    return np.where(np.eye(n, dtype=bool), 0, c).astype(np.int32)
+
+
+@pytest.mark.parametrize("n", [64, 65, 96, 128, 150, 192, 256, 257, 400])
+@pytest.mark.parametrize("classes", [BOTH, INSERTION])
+def test_few_values_go_to_the_exhaustive_kernel(n, classes):
+    """Either side of the lines: one zone of equal costs to thirty, with entries below 2^16 and beyond."""
+    restarts = 3 if n < 200 else 2
+    for count, near, far in ((1, 5, 5), (2, 1, 10), (2, 9000, 90000), (3, 1, 10), (4, 2, 3), (8, 1, 10), (30, 0, 10)):
+        say(f"insertion N={n} classes={classes} {count} zones {near}/{far} R={restarts}")
+        check(_zones(n, count, near, far), classes, restarts, n, range(restarts))
+
+
+def test_ties_do_not_score_every_pair():
+    """Two zones of equal costs take less time than costs that all differ (2.7 times as long in the pruned kernel)."""
+    n, restarts = 192, 256
+    say(f"insertion N={n} R={restarts}: time with two zones of equal costs")
+    buffers = cc.SearchBuffers(n, oracle.SUM, restarts, "cuda")
+
+    def seconds(c):
+        c, best = dev(c), float("inf")
+        for _ in range(3):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            cc.cc_local_search_ex(c, oracle.SUM, BOTH, restarts, 5, buffers=buffers)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end))
+        return best
+
+    assert seconds(_zones(n, 2)) < 1.3 * seconds(hierarchical_matrix(n, (4, 32), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n))
