@@ -378,7 +378,7 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
             e = launch_general_objective(c, N, objective, restarts, tours, costs, moves, nullptr, true, s);
     } else if (N == 64 && objective == 0) {
         e = launch_2opt_sum_n64(c, restarts, seed, !tours_hold_init, tours, costs, moves, s);
-    } else if (N == 64 && (objective & 1)) {
+    } else if (N == 64 && objective == 3) {
         e = launch_2opt_max_n64(c, restarts, seed, !tours_hold_init, false, tours, costs, moves, s);
     } else {
         if (!tours_hold_init) {

@@ -12,7 +12,8 @@
 // their move ids are ordered; after the sweep each rank converts its best partner to the move id and
 // (delta, id) is min-reduced lexicographically over the wave.
 // Keys are delta << 8 | rank in 32 bits (|delta| < 2^22 always fits); the 16-bit matrix needs
-// max(c) < 2^16, otherwise the general kernel runs instead (decided on the device, see launch code).
+// max(c) < 2^16, otherwise the pruned kernel (N <= 96: the general one) runs instead (decided on the device, see the
+// launch code).
 #include "cc_device.h"
 #include "cc_internal.h"
 
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void twoopt_sum_multi_kernel(
     constexpr int N = 64 * K;
     constexpr int H = N / 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (flags[0] >= (1 << 16)) return;            // 16-bit staging impossible: the general kernel handles it
+    if (flags[0] >= (1 << 16)) return;            // 16-bit staging impossible: the kernel enqueued behind this one does the work
     uint16_t* mat = (uint16_t*)smem;                                   // [N][N]
     int32_t* scratch_all = (int32_t*)(smem + (size_t)N * N * 2);       // kWavesPerGroup x N
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -218,8 +219,8 @@ __global__ __launch_bounds__(64 * kWavesPerGroup) void twoopt_sum_multi_kernel(
     }
 }
 
-// ------------------------------------------------------------------------------------ any N <= 256
-// Ring-sum descent for the sizes the kernels above do not cover (N not a multiple of 64).  One wavefront per
+// ------------------------------------------------------------------------------------ other N < 128
+// Ring-sum descent for the sizes below 128 that are no multiple of 64.  One wavefront per
 // restart, rank a = lane + 64 m in slot m (slots past N idle), 16-bit matrix in LDS.  Without N = 64 K the partner
 // data cannot travel round the wave by lane rotates, so it sits in LDS: the wave's slice holds the order T[N] and,
 // twice over so that a + d never wraps, the pairs P[x] = (column byte offset of t[x mod N],
@@ -233,7 +234,7 @@ __global__ void twoopt_sum_flex_kernel(const int32_t* __restrict__ c, int N, int
                                        int64_t* __restrict__ costs, int32_t* __restrict__ moves,
                                        const int32_t* __restrict__ flags) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    if (flags[0] >= (1 << 16)) return;            // 16-bit staging impossible: the general kernel handles it
+    if (flags[0] >= (1 << 16)) return;            // 16-bit staging impossible: the kernel enqueued behind this one does the work
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, waves = blockDim.x >> 6;
     uint16_t* mat = (uint16_t*)smem;                                           // [N][N]
     const size_t slice_bytes = flex_slice_bytes(N);                            // P: 16 N, then T: 4 N (padded)
@@ -380,9 +381,7 @@ static hipError_t launch_flex_k(const int32_t* c, int N, int restarts, int32_t* 
                                 const int32_t* flags, hipStream_t s) {
     const size_t mat_bytes = ((size_t)N * N * 2 + 15) & ~(size_t)15;
     const size_t slice = flex_slice_bytes(N);
-    const int fit = (int)((160 * 1024 - 512 - mat_bytes) / slice);
-    if (fit < 1) return hipErrorInvalidValue;
-    const int waves = waves_per_group(restarts, fit < kWavesPerGroup ? fit : kWavesPerGroup);
+    const int waves = waves_per_group(restarts, kWavesPerGroup);
     const size_t lds = mat_bytes + (size_t)waves * slice;
     hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_flex_kernel<K>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -393,13 +392,11 @@ static hipError_t launch_flex_k(const int32_t* c, int N, int restarts, int32_t* 
     return hipGetLastError();
 }
 
-// Any 4 <= N <= 256.  Tours must already hold the initial orders, flags[0] the matrix maximum.
+// Any 4 <= N < 128.  Tours must already hold the initial orders, flags[0] the matrix maximum.
 hipError_t launch_2opt_sum_flex(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                                 const int32_t* flags, hipStream_t s) {
     if (N <= 64) return launch_flex_k<1>(c, N, restarts, tours, costs, moves, flags, s);
-    if (N <= 128) return launch_flex_k<2>(c, N, restarts, tours, costs, moves, flags, s);
-    if (N <= 192) return launch_flex_k<3>(c, N, restarts, tours, costs, moves, flags, s);
-    return launch_flex_k<4>(c, N, restarts, tours, costs, moves, flags, s);
+    return launch_flex_k<2>(c, N, restarts, tours, costs, moves, flags, s);
 }
 
 }  // namespace cc

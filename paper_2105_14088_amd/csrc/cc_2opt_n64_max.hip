@@ -1,7 +1,5 @@
 // 2-opt descent for N = 64 under the bottleneck (max-hop) objective, directed: one wavefront per
-// restart, one ring rank per lane, the cost matrix staged once per workgroup in LDS.  Also serves the
-// undirected max objective (on a symmetric matrix both walking directions of a move cost the same and
-// the lower id, orientation 0, wins, which is exactly the undirected trajectory).
+// restart, one ring rank per lane, the cost matrix staged once per workgroup in LDS.
 //
 // Cyclic-diagonal sweep as in cc_2opt_n64.hip.  Exchanging ring edges a and b = a + d (edge p joins
 // ranks p-1 and p) cuts the ring into S1 = ranks a..b-1 and S2 = ranks b..a-1 and rejoins them with one
