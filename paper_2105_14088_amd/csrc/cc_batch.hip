@@ -1856,9 +1856,15 @@ static hipError_t dbt_rows_launch(const int32_t* c, int N, const int32_t* perms,
 }
 
 // Up to about 2^20 ranks a call takes its launch time either way, or the staging shows (generic / rows: N = 128, 4000 orders
-// 7.6 / 9.9 us; N = 200, 4000 orders 14.3 / 15.8); above, rows is ahead (N = 128, 16000 orders 18.4 / 14.5; N = 245, where
-// four waves fit beside the matrix, 100000 orders 229 / 168).
-static bool dbt_rows_pays(int N, int64_t B) { return dbt_rows_waves(N) >= kDbtRowsMinWaves && B * N >= (1 << 20); }
+// 7.6 / 9.9 us, 16000 orders 18.4 / 14.5; N = 200, 4000 orders 14.3 / 15.8, 16000 orders 34.8 / 21.7).  The fewer waves fit
+// beside the matrix, the longer the staging and the slower the orders: N = 220 (8 waves), 8000 orders 19.4 / 19.1; N = 236 (6),
+// 8000 orders 19.8 / 30.0, 16000 orders 36.4 / 35.6; N = 245 (5), 30000 orders 69 / 72, 50000 orders 117 / 112; N = 255 (4), 50000
+// orders 119 / 144, 100000 orders 230 / 214.
+static bool dbt_rows_pays(int N, int64_t B) {
+    const int waves = dbt_rows_waves(N);
+    const int64_t ranks = waves >= 10 ? 1 << 20 : waves >= 8 ? 3 << 19 : waves >= 6 ? 1 << 22 : waves == 5 ? 3 << 22 : 6 << 22;
+    return waves >= kDbtRowsMinWaves && B * N >= ranks;
+}
 
 hipError_t launch_dbt_cost_batch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out,
                                  hipStream_t s) {
