@@ -528,7 +528,9 @@ static hipError_t ring_max_marked_launch(const int32_t* c, int N, const RANK* pe
 }
 
 // The threshold and the marking, once per workgroup, take about as long as the generic kernel takes for 21000 (N = 1000) to
-// 25000 orders (N = 300; generic / marked: N = 300, 20480 orders 26 / 31 us; N = 1000, 20480 orders 106 / 111 us).
+// 25000 orders (N = 300; generic / marked: N = 300, 20480 orders 26 / 31 us; N = 1000, 20480 orders 106 / 111 us).  Orders that
+// differ in a few ranks ask for the same few entries, which the caches hold: for them the lines meet later (N = 300, 30000
+// orders 26 / 32 us, 100000 orders 88 / 62; N = 1000, 30000 orders 97 / 109; seeded orders there 41 / 34, 130 / 59, 154 / 113).
 constexpr int64_t kRingMaxMarkedMinOrders = 28672;
 static bool ring_max_marked_pays(int N, int64_t B) { return N > kRingRowsMaxN && B >= kRingMaxMarkedMinOrders; }
 

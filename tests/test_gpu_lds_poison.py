@@ -55,6 +55,36 @@ def test_batches_with_poisoned_lds(n):
             assert np.array_equal(got.cpu().numpy(), oracle.bcube_cost_batch(c, 4, ph))
 
 
+# Batches large enough for the kernels that keep the matrix as 16-bit entries, or marks of it, in LDS.
+@pytest.mark.parametrize("n,count", [(20, 53000), (100, 12000), (270, 18000), (300, 28672), (1000, 28700)])
+@pytest.mark.parametrize("hi", [60000, 70000])
+def test_large_ring_batches_with_poisoned_lds(n, count, hi):
+    c = random_matrix(n, 5 + n, symmetric=False, lo=0, hi=hi)
+    perms = _orders(n, count, 11)
+    ph = perms.cpu().numpy()
+    calls = [(cc.cc_ring_cost_batch, perms), (cc.cc_ring_cost_batch_u16, perms.to(torch.int16))]
+    if n <= 256:
+        calls.append((cc.cc_ring_cost_batch_u8, perms.to(torch.uint8)))
+    for obj in (0, 1):
+        want = oracle.ring_cost_batch(c, ph, obj)
+        for call, ranks in calls:
+            say(f"poisoned LDS: {call.__name__} N={n} orders={count} objective={obj} entries<={hi}")
+            got = call(dev(c), ranks, obj)
+            torch.cuda.synchronize()
+            assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,count", [(20, 53000), (100, 12000), (255, 98700)])
+@pytest.mark.parametrize("hi", [60000, 70000])
+def test_large_tree_batches_with_poisoned_lds(n, count, hi):
+    c = random_matrix(n, 5 + n, symmetric=False, lo=0, hi=hi)
+    perms = _orders(n, count, 11)
+    say(f"poisoned LDS: double binary trees N={n} orders={count} entries<={hi}")
+    got = cc.cc_dbt_cost_batch(dev(c), perms)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.dbt_cost_batch(c, perms.cpu().numpy()))
+
+
 @pytest.mark.parametrize("n,restarts", [(64, 9), (100, 5), (128, 5), (192, 4), (256, 18), (300, 2), (512, 2), (1024, 1)])
 @pytest.mark.parametrize("hi", [3000, 70000])
 def test_2opt_with_poisoned_lds(n, restarts, hi):
