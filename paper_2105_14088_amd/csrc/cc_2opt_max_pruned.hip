@@ -15,9 +15,11 @@
 // One workgroup per restart; order and hops in LDS, carried through the moves; rows of the matrix through L2.  A sweep
 // is a chain of latencies (two or three wave reductions, two LDS round trips, one gather, the move; about 7000 clocks
 // directed at N = 100, of which the pairs around e are 2500): no matrix staging, so any number of workgroups share a
-// compute unit.  Against the exhaustive kernels: undirected N = 50, 1197 restarts 587 -> 60 us, N = 256, 1024 restarts
-// 1456 -> 160 us, N = 700, 100 restarts 21 -> 0.27 ms; directed N = 100, 1000 restarts 2272 -> 208 us, N = 256, 1024
-// restarts 2656 -> 560 us, N = 350, 316 restarts 20.4 -> 0.83 ms, N = 1023, 41 restarts 141 -> 2.7 ms.
+// compute unit.  Whole searches, against the exhaustive kernels: undirected N = 50, 1197 restarts 587 -> 60 us, N = 256, 1024
+// restarts 1456 -> 160 us, N = 700, 100 restarts 21 -> 0.26 ms; directed, inverse bandwidths that are eight times as small
+// inside a rack, N = 100, 1000 restarts 2272 -> 205 us, N = 256, 1024 restarts 2656 -> 551 us, N = 350, 316 restarts
+// 20.4 -> 0.81 ms, N = 1023, 41 restarts 141 -> 2.8 ms; directed on a symmetric matrix, N = 256, 1024 restarts 2350 -> 252 us
+// (fewer sweeps).
 #include "cc_device.h"
 #include "cc_internal.h"
 #include "cc_wave64.h"
@@ -549,8 +551,9 @@ hipError_t launch(const int32_t* c, int N, bool directed, int restarts, bool wit
 
 hipError_t launch_2opt_max_pruned(const int32_t* c, int N, bool directed, int restarts, bool with_flip, int32_t* tours,
                                   int64_t* costs, int32_t* moves, hipStream_t s) {
-    // Wider workgroups shorten a sweep's phases until their barriers cost more: directed N = 100 243 us with 128 threads,
-    // 275 with 64; N = 256, 1024 restarts 600 us with 256, 700 with 128, 980 with 64.
+    // Wider workgroups shorten a sweep's phases until their barriers cost more.  The directed searches of the head of this
+    // file: N = 100, 1000 restarts 205 us with 128 threads, 261 with 64; N = 256, 1024 restarts 551 us with 256, 684 with
+    // 128, 1040 with 64.
     if (N <= 64) return launch<64, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
     if (N <= 128) {
         if (directed) return launch<128, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);

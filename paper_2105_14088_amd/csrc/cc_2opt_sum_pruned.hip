@@ -26,9 +26,10 @@
 //
 // What bounds it: instruction issue, about 60 instructions per 64 candidates and 180 per 64 scored ones, and with 16
 // wavefronts per restart the barriers (N = 1000: 17000 clocks a sweep, 6000 of them brackets, 4000 waiting for the
-// slowest wavefront).  Measured against the exhaustive kernels: N = 1000, 128 restarts 494 -> 11 ms; N = 583, 47 restarts
-// 112 -> 4.7 ms; N = 345, 2140 restarts 239 -> 7.5 ms; N = 1024, 256 restarts 57.9 -> 12 ms (the row-streaming kernel);
-// N = 512, 768 restarts 19.2 -> 6.2 ms; N = 240, 1024 restarts 7.1 -> 3.2 ms; N = 256, 4096 restarts 7.8 -> 5.3 ms.
+// slowest wavefront).  Costs of few values or from 0 on take no longer than others (see cc_pruned.h and where D is known).  Measured against the exhaustive kernels: N = 1000, 128 restarts 494 -> 11 ms; N = 583, 47 restarts
+// 112 -> 4.6 ms; N = 345, 2140 restarts 239 -> 7.5 ms; N = 1024, 256 restarts 57.9 -> 12 ms (a kernel that streamed the
+// matrix through LDS row by row, gone since); N = 512, 768 restarts 19.2 -> 6.1 ms; N = 240, 1024 restarts 7.1 -> 3.4 ms;
+// N = 256, 4096 restarts 7.8 -> 5.2 ms.
 #include <type_traits>
 
 #include "cc_device.h"

@@ -16,8 +16,9 @@
 // What bounds it: instruction issue and look-up latency; scoring 64 pairs in all roles is about 650 instructions (4000
 // clocks alone on a SIMD; 10000 while every move waited for its own look-ups), one or two of these per 64 nodes and sweep.
 // Against the general kernel (cc_local.hip), 2-opt and insertion: N = 32, 1024 restarts 381 -> 174 us; N = 100, 512 restarts
-// 4.9 -> 0.89 ms; N = 150, 512 restarts 13.1 -> 1.6 ms; N = 292, 228 restarts 53 -> 4.5 ms; N = 1000, 20 restarts 1371 -> 33 ms;
-// against the exhaustive multi-rank kernel at N = 256, 250 restarts 9.6 -> 3.2 ms.
+// 4.9 -> 0.99 ms; N = 150, 512 restarts 13.1 -> 1.6 ms; N = 292, 228 restarts 53 -> 5.0 ms; N = 1000, 20 restarts 1371 -> 33 ms;
+// against the exhaustive multi-rank kernel at N = 256, 250 restarts 9.6 -> 3.0 ms.  Matrices of few values are handed over to
+// those kernels (hand_over).
 #include <type_traits>
 
 #include "cc_device.h"
