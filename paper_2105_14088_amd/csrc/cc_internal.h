@@ -52,9 +52,9 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
 // must hold the initial tours.
 hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int restarts, int32_t* tours,
                                    int64_t* costs, int32_t* moves, int32_t* flags, void* room, hipStream_t s);
-// The same search for N = 64 and max(c) < 2^16, one wavefront per restart (cc_local_n64.hip); returns at once if
-// flags[0] >= 2^16 (flags[0] = matrix maximum, launch_matrix_max).
-// N = 128 / 192 / 256, several ranks per lane, 16-bit matrix in LDS (cc_local_multi.hip); same flags convention.
+// The same search for N = 64 (cc_local_n64.hip, below) and for N = 128 / 192 / 256, several ranks per lane, 16-bit matrix in
+// LDS (cc_local_multi.hip): max(c) < 2^16, one wavefront per restart; they return at once if flags[0] >= 2^16 (flags[0]: the
+// matrix maximum, launch_matrix_max, or what launch_local_pruned left there).
 hipError_t launch_local_multi(const int32_t* c, int N, bool with_2opt, int restarts, int32_t* tours, int64_t* costs,
                               int32_t* moves, const int32_t* flags, hipStream_t s);
 hipError_t launch_local_n64(const int32_t* c, bool with_2opt, int restarts, int32_t* tours, int64_t* costs,
