@@ -7,12 +7,17 @@
 // current order at once; the wave then commits the FIRST accepted one (ballot + find-first-set), and
 // the steps after it are proposed again in the next round against the new order.  The result is the
 // sequential chain bit for bit; a round advances 1 .. 64 steps, most of them when the chain is cold.
-// What a step draws does not depend on the order: its two ring edges and the acceptance threshold E(u).  The wave
-// therefore draws 64 steps at a time, one per lane (counter-based generator), into a ring of 128 entries in LDS,
-// and a round only reads its entry back; steps that are proposed again after a commit cost no second draw.
+// What a step draws does not depend on the order: its two ring edges and the largest cost increase it accepts.  The wave
+// draws 64 steps at a time, one per lane (counter-based generator), and keeps two such blocks in registers: lane l
+// evaluates the next step that is l modulo 64, so that a step proposed again after a commit costs no second draw and a round
+// no look-up of its draws.
 // Per round a lane then gathers four ranks of the order and four matrix entries (LDS for N <= 128, else through
-// L2) and tests acceptance in 64-bit integer arithmetic.  The committed reversal is done by the whole wave, one
-// pair of ranks per lane.
+// L2).  The committed reversal is done by the whole wave.
+//
+// What bounds it: with a wavefront per SIMD (1024 chains) the instructions and LDS round trips of a round (N <= 64: fifty
+// instructions and three round trips, 530 clocks), one round per commit, and a seventh of the time the draws.  Draws in a ring in LDS, a
+// 64-bit division per step -> now, 20000 steps: 1024 chains N = 64 755 -> 515 us, N = 33 1214 -> 606 us (order in LDS before), N = 100
+// 1616 -> 1108 us, N = 256 1630 -> 1092 us, N = 1024 4.6 -> 4.3 ms (entries through L2); 8192 chains N = 64 2.00 -> 1.65 ms.
 #include "cc_device.h"
 #include "cc_internal.h"
 #include "cc_wave64.h"
@@ -24,7 +29,6 @@ namespace {
 
 constexpr int kCostMax = (1 << 21) - 1;
 constexpr int kDrawBase = 1024;       // low counter words below this belong to the initial shuffles
-constexpr int kDrawRing = 128;        // steps whose draws a wave keeps in LDS (two blocks of 64)
 
 // all LDS traffic of the wave issued so far is complete and visible to every lane, and the compiler keeps
 // LDS accesses on their side of this point
@@ -47,6 +51,128 @@ __device__ __forceinline__ int largest_accepted_increase(long long step, long lo
     return (int)((num * E) / (4096ull * (unsigned long long)(steps > 0 ? steps : 1)));       // below 22 * 2^21
 }
 
+// What the steps of a chain draw, 64 consecutive steps at a time (one per lane).
+struct RingDraws {
+    uint64_t state;              // generator state of this lane's next step
+    long long num, num_step;     // its temperature times steps, and by how much that changes in 64 steps
+    double per_unit;
+    unsigned long long unit;     // 4096 * steps
+    long long left;              // steps not drawn yet
+    int N, lane;
+
+    __device__ __forceinline__ RingDraws(uint64_t seed, int64_t r, int n, long long steps, int t_start, int t_end)
+        : num((long long)t_start * (steps - lane_id()) + (long long)t_end * lane_id()),
+          num_step(64 * ((long long)t_end - t_start)), unit(4096ull * (unsigned long long)(steps > 0 ? steps : 1)), left(steps), N(n),
+          lane(lane_id()) {
+        state = seed + ((((uint64_t)(uint32_t)r << 32) | (uint32_t)(kDrawBase + lane)) + 1u) * 0x9E3779B97F4A7C15ull;
+        per_unit = 1.0 / (double)unit;
+    }
+    // edges a and b of this lane's step; most: the largest cost increase it accepts, below every increase past the last step.
+    // The acceptance rule of cc.h, "delta * 4096 * steps <= (t_start * (steps - s) + t_end * s) * E(u)", is delta <= floor(right
+    // side / (4096 * steps)), delta being an integer, and a non-positive delta passes as well (the right side is never
+    // negative).  The quotient is below 22 * 2^21, so the product with the reciprocal is off by one at most, which the
+    // remainder tells (a 64-bit division is three times as many instructions: a fifth of the whole kernel at N = 64).
+    __device__ __forceinline__ void next(int& a, int& b, int& most) {
+        uint64_t z = state;
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        const uint64_t w = z ^ (z >> 31);
+        a = (int)(((uint32_t)(w >> 43) * (uint32_t)N) >> 21);
+        const int d = 2 + (int)((((uint32_t)(w >> 22) & 0x1FFFFFu) * (uint32_t)(N - 3)) >> 21);
+        b = a + d;
+        b = b >= N ? b - N : b;
+        const int u = (int)((uint32_t)w & 0x3FFFFFu) + 1;
+        const int e = 31 - __clz(u), mant = u - (1 << e);
+        const int frac = e >= 12 ? (mant >> (e - 12)) : (mant << (12 - e));
+        const unsigned E = (unsigned)(22 * 4096 - (e * 4096 + frac));
+        const unsigned long long product = (unsigned long long)num * E;
+        unsigned q = (unsigned)((double)num * (double)E * per_unit);
+        const long long rest = (long long)(product - unit * q);
+        q += rest < 0 ? -1 : rest >= (long long)unit ? 1 : 0;
+        most = lane < left ? (int)q : (int)0x80000000;
+        state += 64ull * 0x9E3779B97F4A7C15ull;
+        num += num_step;
+        left -= 64;
+    }
+};
+
+// One chain of any N >= 4, the order in LDS: t[-1 .. N-1], t[-1] = t[N-1]; bt [N]: the best order so far.  ONE: a reversal is
+// at most 64 exchanges (N <= 128).
+template <bool ONE, class MAT>
+__device__ __forceinline__ void ring_chain(const MAT M, int N, int64_t r, long long steps, int t_start, int t_end, uint64_t seed,
+                                           int32_t* t, int32_t* bt, long long& cur, long long& best, int& acc) {
+    const int lane = lane_id();
+    RingDraws draws(seed, r, N, steps, t_start, t_end);
+    auto draw = [&](int& ab, int& most) {
+        int a, b;
+        draws.next(a, b, most);
+        ab = a | (b << 16);
+    };
+    // lane l: the step of this block in the lanes from `at` on, of the next block below
+    int ab, most, ab_next, most_next, at = 0;
+    draw(ab, most);
+    draw(ab_next, most_next);
+    auto commit = [&](int delta, int k) {
+        const int abk = __builtin_amdgcn_readlane(ab, k), dk = __builtin_amdgcn_readlane(delta, k);
+        const int ak = abk & 0xffff, bk = abk >> 16;
+        const int lo = min(ak, bk), hi = max(ak, bk);
+        const int i = lo ? lo : hi, j = lo ? hi - 1 : N - 1;
+        wave_lds_sync();                               // every lane has read the order before it changes
+        const int half = (j - i + 1) >> 1;
+        for (int x = lane; x < half; x += kWave) {
+            const int p = i + x, q = j - x;
+            const int vp = t[p], vq = t[q];
+            t[p] = vq;
+            t[q] = vp;
+            if (q == N - 1) t[-1] = vp;
+            if (ONE) break;
+        }
+        wave_lds_sync();
+        cur += dk;
+        ++acc;
+        if (cur < best) {
+            best = cur;
+            for (int p = lane; p < N; p += kWave) bt[p] = t[p];
+        }
+        ab = lane <= k ? ab_next : ab;
+        most = lane <= k ? most_next : most;
+        at = k + 1;
+    };
+    for (long long block = 0; block < steps; block += kWave) {
+        // rounds until this block is through
+        unsigned long long mask;
+        int delta;
+        bool more;
+        do {
+            const int a = ab & 0xffff, b = ab >> 16;
+            const int ta = t[a], tap = t[a - 1], tb = t[b], tbp = t[b - 1];
+            delta = (M(tap, tbp) + M(ta, tb)) - (M(ta, tap) + M(tb, tbp));
+            mask = __ballot(delta <= most);
+            const unsigned long long ahead = mask >> at;
+            more = ahead != 0ull;
+            if (more) {
+                commit(delta, at + __builtin_ctzll(ahead));
+                more = at < kWave;
+            }
+        } while (more);
+        if (at == kWave) {
+            at = 0;
+            draw(ab_next, most_next);
+            continue;
+        }
+        // the rest of the block is rejected, and of the next one the steps before its first accepted
+        ab = lane >= at ? ab_next : ab;
+        most = lane >= at ? most_next : most;
+        draw(ab_next, most_next);
+        if (mask == 0ull) {
+            ab = lane < at ? ab_next : ab;
+            most = lane < at ? most_next : most;
+        } else if (block + kWave < steps) {
+            commit(delta, __builtin_ctzll(mask));
+        }
+    }
+}
+
 // MAT: where the matrix is read from - 0 through L2, 1 staged in LDS as int32 (N <= 128), 2 staged in LDS as 16-bit
 // entries (N <= 256) when every entry is in 0 .. 2^16 - 1 (found while staging), else through L2.
 template <int MAT>
@@ -56,20 +182,16 @@ __global__ __launch_bounds__(256) void sa_ring_kernel(const int32_t* __restrict_
                                                       int32_t* __restrict__ accepted) {
     extern __shared__ __attribute__((aligned(16))) int32_t sm[];
     const int lane = lane_id(), wv = threadIdx.x >> 6;
-    int32_t* draws = sm + wv * 2 * kDrawRing;            // per step: edges a | b << 16, threshold E
-    int32_t* t = sm + 8 * kDrawRing + wv * 2 * N;        // current order
+    int32_t* t = sm + wv * (2 * N + 1) + 1;              // current order, from rank -1 on
     int32_t* bt = t + N;                                 // best order so far
-    const int32_t* mat = c;
-    const uint16_t* m16 = nullptr;
+    int32_t* staged = sm + 4 * (2 * N + 1);
     bool narrow = false;                                 // MAT == 2: the 16-bit copy holds the matrix
     if (MAT == 1) {
-        int32_t* m = sm + 8 * kDrawRing + 8 * N;
-        for (int e = threadIdx.x; e < N * N; e += 256) m[e] = clampi(c[e], 0, kCostMax);
+        for (int e = threadIdx.x; e < N * N; e += 256) staged[e] = clampi(c[e], 0, kCostMax);
         __syncthreads();
-        mat = m;
     }
     if (MAT == 2) {
-        uint16_t* m = (uint16_t*)(sm + 8 * kDrawRing + 8 * N);
+        uint16_t* m = (uint16_t*)staged;
         __shared__ unsigned wave_top[4];
         unsigned top = 0;
         for (int e = threadIdx.x; e < N * N; e += 256) {
@@ -81,88 +203,28 @@ __global__ __launch_bounds__(256) void sa_ring_kernel(const int32_t* __restrict_
         if (lane == 0) wave_top[wv] = top;
         __syncthreads();
         narrow = max(max(wave_top[0], wave_top[1]), max(wave_top[2], wave_top[3])) < (1u << 16);
-        m16 = m;
     }
     const int64_t r = (int64_t)blockIdx.x * 4 + wv;
     if (r >= chains) return;
-    auto M = [&](int x, int y) {
-        if (MAT == 1) return mat[x * N + y];
-        if (MAT == 2 && narrow) return (int)m16[x * N + y];
-        return clampi(c[x * N + y], 0, kCostMax);
-    };
-
     for (int p = lane; p < N; p += kWave) {
         const int v = clampi(tours[r * N + p], 0, N - 1);
         t[p] = v;
         bt[p] = v;
+        if (p == N - 1) t[-1] = v;
     }
     wave_lds_sync();
-    long long cur = 0;
-    for (int p = lane; p < N; p += kWave) cur += M(t[p], t[p ? p - 1 : N - 1]);
-    cur = wave_sum64(cur);
-    long long best = cur;
+    long long best = 0;
     int acc = 0;
-
-    if (N >= 4) {
-        const uint64_t chain_hi = (uint64_t)(uint32_t)r << 32;
-        // draws of the 64 steps first .. first + 63, one per lane, into their ring entries
-        auto draw_block = [&](long long first) {
-            const long long step = first + lane;
-            const uint64_t w = splitmix64_at(seed, (chain_hi | (uint32_t)(kDrawBase + (uint32_t)step)) + 1u);
-            const int a = (int)(((uint32_t)(w >> 43) * (uint32_t)N) >> 21);
-            const int d = 2 + (int)((((uint32_t)(w >> 22) & 0x1FFFFFu) * (uint32_t)(N - 3)) >> 21);
-            int b = a + d;
-            b = b >= N ? b - N : b;
-            const int u = (int)((uint32_t)w & 0x3FFFFFu) + 1;
-            const int slot = (int)step & (kDrawRing - 1);
-            *(int2*)(draws + 2 * slot) = make_int2(a | (b << 16), largest_accepted_increase(step, steps, t_start, t_end, u));
-        };
-        draw_block(0);
-        draw_block(kWave);
-        long long drawn = 2 * kWave;          // steps [drawn - 128, drawn) are in the ring
-        wave_lds_sync();
-        long long s = 0;
-        while (s < steps) {
-            if (s + kWave > drawn) {          // the round reaches past the ring: the older half makes room
-                draw_block(drawn);
-                drawn += kWave;
-                wave_lds_sync();
-            }
-            const long long step = s + lane;
-            const bool active = step < steps;
-            const int2 drawn_step = *(const int2*)(draws + 2 * ((int)step & (kDrawRing - 1)));
-            const int a = drawn_step.x & 0xffff, b = drawn_step.x >> 16;
-            const int ap = a ? a - 1 : N - 1, bp = b ? b - 1 : N - 1;
-            const int ta = t[a], tap = t[ap], tb = t[b], tbp = t[bp];
-            const int delta = M(tap, tbp) + M(ta, tb) - M(ta, tap) - M(tb, tbp);
-            const bool accept = active && delta <= drawn_step.y;
-            const unsigned long long mask = __ballot(accept);
-            if (mask == 0ull) {
-                s += kWave;
-                continue;
-            }
-            const int k = __ffsll((long long)mask) - 1;
-            const int ak = __shfl(a, k, kWave), bk = __shfl(b, k, kWave), dk = __shfl(delta, k, kWave);
-            const int lo = min(ak, bk), hi = max(ak, bk);
-            const int i = lo ? lo : hi, j = lo ? hi - 1 : N - 1;
-            wave_lds_sync();                       // every lane has read the order before it changes
-            const int half = (j - i + 1) >> 1;
-            for (int x = lane; x < half; x += kWave) {
-                const int p = i + x, q = j - x;
-                const int vp = t[p], vq = t[q];
-                t[p] = vq;
-                t[q] = vp;
-            }
-            wave_lds_sync();
-            cur += dk;
-            ++acc;
-            if (cur < best) {
-                best = cur;
-                for (int p = lane; p < N; p += kWave) bt[p] = t[p];
-            }
-            s += k + 1;
-        }
-    }
+    auto run = [&](auto M) {
+        long long cur = 0;
+        for (int p = lane; p < N; p += kWave) cur += M(t[p], t[p - 1]);
+        cur = wave_sum64(cur);
+        best = cur;
+        if (N >= 4) ring_chain<MAT == 1>(M, N, r, steps, t_start, t_end, seed, t, bt, cur, best, acc);
+    };
+    if (MAT == 1) run([=](int x, int y) { return staged[x * N + y]; });
+    else if (MAT == 2 && narrow) run([=](int x, int y) { return (int)((const uint16_t*)staged)[x * N + y]; });
+    else run([=](int x, int y) { return clampi(c[x * N + y], 0, kCostMax); });
     wave_lds_sync();
     for (int p = lane; p < N; p += kWave) tours[r * N + p] = bt[p];
     if (lane == 0) {
@@ -486,84 +548,90 @@ static hipError_t sa_rd_launch(const int32_t* c, int chains, long long steps, in
     return hipGetLastError();
 }
 
-// N = 64: the chain of sa_ring_kernel with the order in one VGPR (lane = rank).  The four ranks a proposal needs are
-// lane permutes, the committed proposal is read by a scalar lane index, the reversal is one lane permute, the best
-// order a register copy: no order in LDS, so no write-read synchronisation within a round.  Draws as in
-// sa_ring_kernel (a ring of 128 steps in LDS, 64 drawn at a time).
-__global__ __launch_bounds__(256) void sa_ring_n64_kernel(const int32_t* __restrict__ c, int chains, long long steps,
-                                                          int t_start, int t_end, uint64_t seed,
+// 4 <= N <= 64: the same chain with the order in one VGPR (lane = rank, lane 63 the last rank once more as the one before rank
+// 0): the ranks a proposal needs are lane permutes, the reversal is one, the best order a register copy.  A drawn step
+// is one word (edges a, b and the ranks i .. j it reverses, each times 4: lane permutes read bits 2 .. 7 of an address), the
+// order holds nodes times 4, the matrix has rows of 64 words, so that an address is one shift-and-or.
+__global__ __launch_bounds__(256) void sa_ring_n64_kernel(const int32_t* __restrict__ c, int N, int chains,
+                                                          long long steps, int t_start, int t_end, uint64_t seed,
                                                           int32_t* __restrict__ tours, int64_t* __restrict__ costs,
                                                           int32_t* __restrict__ accepted) {
-    constexpr int N = 64;
-    __shared__ int32_t m[N * N];
-    __shared__ __attribute__((aligned(16))) int32_t draws_all[4][2 * kDrawRing];
+    __shared__ int32_t m[64 * 64];
     const int lane = lane_id(), wv = threadIdx.x >> 6;
-    for (int e = threadIdx.x; e < N * N; e += 256) m[e] = clampi(c[e], 0, kCostMax);
+    for (int e = threadIdx.x; e < N * 64; e += 256) m[e] = clampi(c[(e >> 6) * N + min(e & 63, N - 1)], 0, kCostMax);
     __syncthreads();
     const int64_t r = (int64_t)blockIdx.x * 4 + wv;
     if (r >= chains) return;
-    int32_t* draws = draws_all[wv];
     const char* mbytes = (const char*)m;
-    auto M = [&](int x, int y) { return *(const int32_t*)(mbytes + ((x << 8) | (y << 2))); };
-    auto node_at = [&](int rank, int order) { return __builtin_amdgcn_ds_bpermute(rank << 2, order); };
+    auto M = [&](int x4, int y4) { return *(const int32_t*)(mbytes + ((x4 << 6) | y4)); };
+    auto node_at = [&](int address, int order) { return __builtin_amdgcn_ds_bpermute(address, order); };
 
-    int t = clampi(tours[r * N + lane], 0, N - 1);
+    const int rank4 = (lane == 63 ? N - 1 : min(lane, N - 1)) << 2;
+    int t = clampi(tours[r * N + (rank4 >> 2)], 0, N - 1) << 2;
     int bt = t;
-    long long cur = wave_sum64((long long)M(t, __builtin_amdgcn_update_dpp(t, t, 0x13C, 0xf, 0xf, true)));
-    long long best = cur;
-    int acc = 0;
-    const uint64_t chain_hi = (uint64_t)(uint32_t)r << 32;
-    auto draw_block = [&](long long first) {
-        const long long step = first + lane;
-        const uint64_t w = splitmix64_at(seed, (chain_hi | (uint32_t)(kDrawBase + (uint32_t)step)) + 1u);
-        const int a = (int)(((uint32_t)(w >> 43) * (uint32_t)N) >> 21);
-        const int d = 2 + (int)((((uint32_t)(w >> 22) & 0x1FFFFFu) * (uint32_t)(N - 3)) >> 21);
-        const int b = (a + d) & (N - 1);
-        const int u = (int)((uint32_t)w & 0x3FFFFFu) + 1;
-        const int slot = (int)step & (kDrawRing - 1);
-        *(int2*)(draws + 2 * slot) = make_int2(a | (b << 16), largest_accepted_increase(step, steps, t_start, t_end, u));
+    const int before = node_at((lane << 2) + 252, t);
+    int cur = wave_sum(lane < N ? M(t, before) : 0);     // at most 64 entries below 2^21
+    int best = cur, acc = 0;
+    RingDraws draws(seed, r, N, steps, t_start, t_end);
+    auto draw = [&](int& step, int& most) {
+        int a, b;
+        draws.next(a, b, most);
+        const int lo = min(a, b), hi = max(a, b);
+        const int i = lo ? lo : hi, j = lo ? hi - 1 : N - 1;
+        step = (a | (b << 8) | (i << 16) | (j << 24)) << 2;
     };
-    draw_block(0);
-    draw_block(kWave);
-    long long drawn = 2 * kWave;              // steps [drawn - 128, drawn) are in the ring
-    wave_lds_sync();
-    long long s = 0;
-    while (s < steps) {
-        if (s + kWave > drawn) {              // the round reaches past the ring: the older half makes room
-            draw_block(drawn);
-            drawn += kWave;
-            wave_lds_sync();
-        }
-        const long long step = s + lane;
-        const bool active = step < steps;
-        const int2 drawn_step = *(const int2*)(draws + 2 * ((int)step & (kDrawRing - 1)));
-        const int a = drawn_step.x & 0xffff, b = drawn_step.x >> 16;
-        const int ap = (a + N - 1) & (N - 1), bp = (b + N - 1) & (N - 1);
-        const int ta = node_at(a, t), tap = node_at(ap, t), tb = node_at(b, t), tbp = node_at(bp, t);
-        const int delta = M(tap, tbp) + M(ta, tb) - M(ta, tap) - M(tb, tbp);
-        const bool accept = active && delta <= drawn_step.y;
-        const unsigned long long mask = __ballot(accept);
-        if (mask == 0ull) {
-            s += kWave;
+    int step, most, step_next, most_next, at = 0;        // as in ring_chain
+    draw(step, most);
+    draw(step_next, most_next);
+    auto commit = [&](int delta, int k) {
+        const unsigned taken = (unsigned)__builtin_amdgcn_readlane(step, k);
+        const int i4 = (int)((taken >> 16) & 255u), j4 = (int)(taken >> 24);
+        const int behind = rank4 - i4;
+        t = node_at((unsigned)behind <= (unsigned)(j4 - i4) ? j4 - behind : rank4, t);      // ranks i .. j reversed
+        cur += __builtin_amdgcn_readlane(delta, k);
+        ++acc;
+        step = lane <= k ? step_next : step;
+        most = lane <= k ? most_next : most;
+        at = k + 1;
+        bt = cur < best ? t : bt;
+        best = min(best, cur);
+    };
+    for (int block = 0; block < (int)steps; block += kWave) {        // steps <= 2^24
+        // rounds until this block is through
+        unsigned long long mask;
+        int delta;
+        bool more;
+        do {
+            const int step_b = (int)((unsigned)step >> 8);
+            const int ta = node_at(step, t), tap = node_at(step + 252, t), tb = node_at(step_b, t), tbp = node_at(step_b + 252, t);
+            delta = (M(tap, tbp) + M(ta, tb)) - (M(ta, tap) + M(tb, tbp));
+            mask = __ballot(delta <= most);
+            const unsigned long long ahead = mask >> at;
+            more = ahead != 0ull;
+            if (more) {
+                commit(delta, at + __builtin_ctzll(ahead));
+                more = at < kWave;
+            }
+        } while (more);
+        if (at == kWave) {
+            at = 0;
+            draw(step_next, most_next);
             continue;
         }
-        const int k = __ffsll((long long)mask) - 1;
-        const int abk = __builtin_amdgcn_readlane(drawn_step.x, k), dk = __builtin_amdgcn_readlane(delta, k);
-        const int ak = abk & 0xffff, bk = abk >> 16;
-        const int lo = min(ak, bk), hi = max(ak, bk);
-        const int i = lo ? lo : hi, j = lo ? hi - 1 : N - 1;
-        t = node_at((lane >= i && lane <= j) ? i + j - lane : lane, t);      // ranks i .. j reversed
-        cur += dk;
-        ++acc;
-        if (cur < best) {
-            best = cur;
-            bt = t;
+        // the rest of the block is rejected, and of the next one the steps before its first accepted
+        step = lane >= at ? step_next : step;
+        most = lane >= at ? most_next : most;
+        draw(step_next, most_next);
+        if (mask == 0ull) {
+            step = lane < at ? step_next : step;
+            most = lane < at ? most_next : most;
+        } else if (block + kWave < (int)steps) {
+            commit(delta, __builtin_ctzll(mask));
         }
-        s += k + 1;
     }
-    tours[r * N + lane] = bt;
+    if (lane < N) tours[r * N + lane] = bt >> 2;
     if (lane == 0) {
-        costs[r] = best;
+        costs[r] = (int64_t)best;
         accepted[r] = acc;
     }
 }
@@ -577,11 +645,11 @@ hipError_t launch_sa_ring(const int32_t* c, int N, int chains, long long steps, 
         if (e != hipSuccess) return e;
     }
     const int grid = (chains + 3) / 4;
-    if (N == 64) {
-        hipLaunchKernelGGL(sa_ring_n64_kernel, dim3(grid), dim3(256), 0, s, c, chains, steps, t_start, t_end, seed, tours,
+    if (N >= 4 && N <= 64) {
+        hipLaunchKernelGGL(sa_ring_n64_kernel, dim3(grid), dim3(256), 0, s, c, N, chains, steps, t_start, t_end, seed, tours,
                            costs, accepted);
     } else if (N <= 128) {
-        const size_t lds = sizeof(int32_t) * ((size_t)8 * kDrawRing + (size_t)8 * N + (size_t)N * N);
+        const size_t lds = sizeof(int32_t) * ((size_t)4 * (2 * N + 1) + (size_t)N * N);
         if (lds > 48 * 1024) {
             hipError_t e = hipFuncSetAttribute((const void*)sa_ring_kernel<1>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -590,14 +658,14 @@ hipError_t launch_sa_ring(const int32_t* c, int N, int chains, long long steps, 
         hipLaunchKernelGGL((sa_ring_kernel<1>), dim3(grid), dim3(256), lds, s, c, N, chains, steps, t_start, t_end,
                            seed, tours, costs, accepted);
     } else if (N <= 256) {
-        const size_t lds = sizeof(int32_t) * ((size_t)8 * kDrawRing + (size_t)8 * N) + sizeof(uint16_t) * (size_t)N * N;
+        const size_t lds = sizeof(int32_t) * (size_t)4 * (2 * N + 1) + sizeof(uint16_t) * (size_t)N * N;
         hipError_t e = hipFuncSetAttribute((const void*)sa_ring_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((sa_ring_kernel<2>), dim3(grid), dim3(256), lds, s, c, N, chains, steps, t_start, t_end, seed,
                            tours, costs, accepted);
     } else {
-        const size_t lds = sizeof(int32_t) * ((size_t)8 * kDrawRing + (size_t)8 * N);
+        const size_t lds = sizeof(int32_t) * (size_t)4 * (2 * N + 1);
         hipLaunchKernelGGL((sa_ring_kernel<0>), dim3(grid), dim3(256), lds, s, c, N, chains, steps, t_start, t_end,
                            seed, tours, costs, accepted);
     }
