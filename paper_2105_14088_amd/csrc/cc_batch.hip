@@ -41,6 +41,29 @@ __device__ __forceinline__ int sampled_threshold(int (&v)[4], int wanted, int* p
     return __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)__ballot(above == 8)) - 1);
 }
 
+// four ranks of an order, aligned as a rank is
+typedef int ranks4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// The caller's matrix into LDS, by all threads of the workgroup, sixteen loads of each in flight; returns the thread's share
+// of the largest entry (a negative one counts as too large).  16 bits: what is too large for them is staged as 0xffff.
+template <typename ENTRY>
+__device__ __forceinline__ unsigned stage_matrix(const int32_t* __restrict__ c, int entries, ENTRY* staged) {
+    constexpr int U = 16;
+    unsigned top = 0;
+    const int threads = blockDim.x;
+    for (int e0 = threadIdx.x; e0 < entries; e0 += U * threads) {
+        unsigned v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = (unsigned)c[min(e0 + u * threads, entries - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            top = max(top, v[u]);
+            if (e0 + u * threads < entries) staged[e0 + u * threads] = (ENTRY)(sizeof(ENTRY) == 2 ? min(v[u], 0xffffu) : v[u]);
+        }
+    }
+    return top;
+}
+
 // ------------------------------------------------------------------------------------------ ring
 template <int N, bool IS_MAX>
 __global__ __launch_bounds__(256) void ring_batch_lds_kernel(const int32_t* __restrict__ c,
@@ -797,18 +820,19 @@ __global__ __launch_bounds__(256) void bcube_b4_lanes64_kernel(const int32_t* __
     }
 }
 
-// Double binary tree: the tree over positions LO .. HI hangs below a parent whose node and path cost are given; the
-// costliest root-to-leaf path is the largest path cost met.  SHIFT: tree position p holds rank (p + SHIFT) mod 64.
-template <int LO, int HI, int SHIFT>
-__device__ __forceinline__ void dbt_walk_64(const char* mbytes, const unsigned (&node4)[64], unsigned parent4, int cost,
+// Double binary tree over N ranks in registers: the tree over positions LO .. HI hangs below a parent whose node and path cost are
+// given; the costliest root-to-leaf path is the largest path cost met.  SHIFT: tree position p holds rank (p + SHIFT) mod N.  Nodes
+// times 4, rows of 64 words.
+template <int LO, int HI, int SHIFT, int N>
+__device__ __forceinline__ void dbt_walk_64(const char* mbytes, const unsigned (&node4)[N], unsigned parent4, int cost,
                                             bool has_parent, int& worst) {
     if constexpr (LO <= HI) {
         constexpr int M = (LO + HI) / 2;
-        const unsigned here = node4[(M + SHIFT) & 63];
+        const unsigned here = node4[(M + SHIFT) % N];
         const int mine = has_parent ? cost + *(const int32_t*)(mbytes + ((parent4 << 6) | here)) : 0;
         worst = max(worst, mine);
-        dbt_walk_64<LO, M - 1, SHIFT>(mbytes, node4, here, mine, true, worst);
-        dbt_walk_64<M + 1, HI, SHIFT>(mbytes, node4, here, mine, true, worst);
+        dbt_walk_64<LO, M - 1, SHIFT, N>(mbytes, node4, here, mine, true, worst);
+        dbt_walk_64<M + 1, HI, SHIFT, N>(mbytes, node4, here, mine, true, worst);
     }
 }
 
@@ -828,8 +852,8 @@ __global__ __launch_bounds__(256) void dbt_lanes64_kernel(const int32_t* __restr
         unsigned node4[N];
         load_order_per_lane(perms4, b0, B, tile_all[wv], lane, node4);
         int worst = 0;
-        dbt_walk_64<0, N - 1, 0>(mbytes, node4, 0u, 0, false, worst);
-        dbt_walk_64<0, N - 1, 1>(mbytes, node4, 0u, 0, false, worst);
+        dbt_walk_64<0, N - 1, 0, N>(mbytes, node4, 0u, 0, false, worst);
+        dbt_walk_64<0, N - 1, 1, N>(mbytes, node4, 0u, 0, false, worst);
         if (b0 + lane < B) out[b0 + lane] = worst;
     }
 }
@@ -1632,46 +1656,93 @@ hipError_t launch_bcube_cost_batch(const int32_t* c, int N, int base, const int3
 // --------------------------------------------------------------------- double-binary-tree cost model
 // Section 4.1, equation C_dbt: the ranks form an in-order binary tree whose subtree roots are the middle
 // ranks of their ranges; a tree costs its most expensive root-to-leaf path; the second tree has the same
-// shape one position further along the order; the result is the larger of the two.  Every lane walks from
-// the root to its own position (a binary search, at most 10 hops), adding c[parent][child] per hop; the
-// largest path over the wave is the tree's cost.
-template <bool LDS_MATRIX>
+// shape one position further along the order; the result is the larger of the two.
+//
+// Any N, one wave per order, entries through L2: each half wave takes one tree, each lane the path to one of the 32 subtrees
+// below the fifth level and then that subtree, REST levels below its root (N < 2^(6 + REST)).  Which ranks these are does not
+// depend on the order: their places in LDS are found once.  (5 + 2^(REST + 1) - 1) look-ups per lane for 2 (N - 1) edges; what
+// bounds it is the rate of scattered requests to the L2 (about 3e11 a second).  Every rank walking its whole path -> this kernel: N = 1000,
+// 65000 orders 851 -> 544 us, 1000 orders 72 -> 13 us; N = 500, 65000 orders 338 -> 244 us; N = 300, 16000 orders 51 -> 38 us.
+template <int REST>
 __global__ __launch_bounds__(256) void dbt_batch_kernel(const int32_t* __restrict__ c, int N,
                                                         const int32_t* __restrict__ perms, int64_t B,
                                                         int64_t* __restrict__ out) {
+    constexpr int SUB = (2 << REST) - 1;                   // places of a subtree, heap order: 0; 1, 2; 3 .. 6; ..
+    constexpr int CHUNKS = REST < 5 ? 1 << REST : 16;      // 64 ranks each
     extern __shared__ int32_t sm[];
-    int32_t* order = sm + (threadIdx.x >> 6) * N;
-    const int32_t* mat = c;
-    if (LDS_MATRIX) {
-        int32_t* m = sm + 4 * N;
-        for (int e = threadIdx.x; e < N * N; e += 256) m[e] = c[e];
-        __syncthreads();
-        mat = m;
+    const int lane = lane_id(), shift = lane >> 5;
+    int32_t* order = sm + (threadIdx.x >> 6) * (N + N / 32 + 1);
+    // one word left out behind every 32: the places of a level lie N / 32 ranks apart
+    auto place = [](int rank) { return rank + (rank >> 5); };
+    auto rank_at = [&](int position) { return position + shift >= N ? position + shift - N : position + shift; };
+    int path[6], sub[SUB];
+    bool on_path[6], in_sub[SUB];
+    int first[SUB], last[SUB];
+    {
+        int lo = 0, hi = N - 1;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int mid = (lo + hi) >> 1;
+            on_path[k] = lo <= hi;
+            path[k] = place(rank_at(on_path[k] ? mid : 0));
+            if (k == 5) {
+                first[0] = lo;
+                last[0] = hi;
+            } else {
+                const bool right = (lane >> (4 - k)) & 1;
+                lo = right ? mid + 1 : lo;
+                hi = right ? hi : mid - 1;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < SUB; ++h) {
+            if (h) {
+                const int up = (h - 1) >> 1, mid = (first[up] + last[up]) >> 1;
+                const bool there = first[up] <= last[up];
+                first[h] = there ? ((h & 1) ? first[up] : mid + 1) : 1;
+                last[h] = there ? ((h & 1) ? mid - 1 : last[up]) : 0;
+            }
+            in_sub[h] = first[h] <= last[h];
+            sub[h] = place(rank_at(in_sub[h] ? (first[h] + last[h]) >> 1 : 0));
+        }
     }
-    const int lane = lane_id();
     const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
+    int next[CHUNKS];
+    auto request = [&](int64_t b) {
+        const int32_t* pi = perms + (b < B ? b : B - 1) * N;
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u) next[u] = pi[min(lane + 64 * u, N - 1)];
+    };
+    request(wave);
     for (int64_t b = wave; b < B; b += nwaves) {
-        const int32_t* pi = perms + b * N;
-        for (int p = lane; p < N; p += kWave) order[p] = clampi(pi[p], 0, N - 1);
+#pragma unroll
+        for (int u = 0; u < CHUNKS; ++u)
+            if (lane + 64 * u < N) order[place(lane + 64 * u)] = clampi(next[u], 0, N - 1);
+        request(b + nwaves);
         __builtin_amdgcn_wave_barrier();
-        int worst = 0;
-        for (int shift = 0; shift < 2; ++shift) {
-            for (int p = lane; p < N; p += kWave) {
-                int lo = 0, hi = N - 1, m = (N - 1) >> 1, acc = 0;
-                int at = m + shift;
-                int prev = order[at >= N ? at - N : at];
-                for (int depth = 0; depth < 11 && m != p; ++depth) {
-                    if (p < m) hi = m - 1;
-                    else lo = m + 1;
-                    m = (lo + hi) >> 1;
-                    at = m + shift;
-                    const int cur = order[at >= N ? at - N : at];
-                    acc += mat[prev * N + cur];
-                    prev = cur;
-                }
-                worst = max(worst, acc);
-            }
+        int node[6], below[SUB], cost[SUB];
+        int way = 0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) node[k] = order[path[k]];
+#pragma unroll
+        for (int h = 1; h < SUB; ++h) below[h] = order[sub[h]];
+        below[0] = node[5];
+        int edge[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) edge[k] = c[REST > 0 || on_path[k + 1] ? (unsigned)(node[k] * N + node[k + 1]) : 0u];
+        // every level but the last is full; where a place is empty all lanes ask for the same entry
+#pragma unroll
+        for (int h = 1; h < SUB; ++h)
+            cost[h] = c[h < (SUB >> 1) || in_sub[h] ? (unsigned)(below[(h - 1) >> 1] * N + below[h]) : 0u];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) way += REST > 0 || on_path[k + 1] ? edge[k] : 0;
+        cost[0] = way;
+        int worst = way;
+#pragma unroll
+        for (int h = 1; h < SUB; ++h) {
+            cost[h] = cost[(h - 1) >> 1] + (h < (SUB >> 1) || in_sub[h] ? cost[h] : 0);
+            worst = max(worst, cost[h]);
         }
         const int total = wave_max(worst);
         __builtin_amdgcn_wave_barrier();
@@ -1679,211 +1750,332 @@ __global__ __launch_bounds__(256) void dbt_batch_kernel(const int32_t* __restric
     }
 }
 
-// N = 64: the tree's shape does not depend on the order, so every lane (tree position) finds its parent once, by
-// the same binary search, and the positions 2 and 4 levels up by two look-ups.  Per order a lane gathers the one
-// edge into its position for each of the two trees; path costs are then sums over ancestors, formed by pointer
-// jumping in three lane-permute steps (the root's edge is 0 and it is its own ancestor, so chains that have reached
-// the root add nothing).
-__global__ __launch_bounds__(256) void dbt_batch_n64_kernel(const int32_t* __restrict__ c,
-                                                            const int32_t* __restrict__ perms, int64_t B,
-                                                            int64_t* __restrict__ out) {
-    constexpr int N = 64;
-    __shared__ int32_t m[N * N];
-    __shared__ int32_t order_all[4][N];
-    for (int e = threadIdx.x; e < N * N; e += 256) m[e] = c[e];
-    const int lane = lane_id();
-    int32_t* order = order_all[threadIdx.x >> 6];
-    // parent of tree position `lane`
-    int parent = lane;
-    {
-        int lo = 0, hi = N - 1, mid = (N - 1) >> 1;
-        for (int depth = 0; depth < 7 && mid != lane; ++depth) {
-            parent = mid;
-            if (lane < mid) hi = mid - 1;
-            else lo = mid + 1;
-            mid = (lo + hi) >> 1;
-        }
-    }
-    const bool is_root = parent == lane;
-    order[lane] = parent;                                  // borrowed for the ancestor look-ups
-    __builtin_amdgcn_wave_barrier();
-    const int up2 = order[parent];
-    const int up4 = order[order[up2]];
-    __builtin_amdgcn_wave_barrier();
-    __syncthreads();                                       // the matrix is staged
-    const int from1 = parent << 2, from2 = up2 << 2, from4 = up4 << 2;
-    const int parent_shifted = (parent + 1) & (N - 1);     // second tree: position q holds rank q + 1
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
-    int next = wave < B ? perms[wave * N + lane] : 0;
-    for (int64_t b = wave; b < B; b += nwaves) {
-        const int a = clampi(next, 0, N - 1);
-        const int64_t bn = b + nwaves;
-        next = bn < B ? perms[bn * N + lane] : 0;
-        order[lane] = a;
-        __builtin_amdgcn_wave_barrier();
-        // node at tree position `lane` of the second tree: the next lane's (cyclic over the 64 lanes)
-        const int a_shifted = __builtin_amdgcn_update_dpp(a, a, 0x134, 0xf, 0xf, true);
-        int cost0 = is_root ? 0 : m[order[parent] * N + a];
-        int cost1 = is_root ? 0 : m[order[parent_shifted] * N + a_shifted];
-        __builtin_amdgcn_wave_barrier();                   // all look-ups done before the slice is overwritten
-        cost0 += __builtin_amdgcn_ds_bpermute(from1, cost0);
-        cost1 += __builtin_amdgcn_ds_bpermute(from1, cost1);
-        cost0 += __builtin_amdgcn_ds_bpermute(from2, cost0);
-        cost1 += __builtin_amdgcn_ds_bpermute(from2, cost1);
-        cost0 += __builtin_amdgcn_ds_bpermute(from4, cost0);
-        cost1 += __builtin_amdgcn_ds_bpermute(from4, cost1);
-        const int total = wave_max(max(cost0, cost1));
-        if (lane == 0) out[b] = total;
-    }
-}
-
-// Small and middling N: sixteen lanes per order, four orders per wave, the matrix as 16-bit entries in LDS.  The tree's
-// shape does not depend on the order: a rank's place in it is a heap slot (root 1, children 2h and 2h + 1; every level
-// but the last is full), found once per workgroup.  An order is staged by slot, each word the nodes of the slot's rank
-// in the first and in the second tree, so a slot's parent is slot h >> 1 and a level is one pass over consecutive slots:
-// two words, one edge per tree, the parent's path costs plus those edges.  N - 1 edges per tree are looked up instead of
-// the whole path of every rank.  Slots of the last level without a rank keep the mark ~0.  A workgroup that meets an
-// entry outside 0 .. 2^16 - 1 while staging gathers from the caller's matrix through L2.
-// Issue-bound: the four top levels are a pass of at most 16 lanes each, and a form with four passes of a level in flight
-// was slower for its extra instructions (N = 100, 100000 orders 40 us).  Before (every rank walks its whole path, for
-// N > 64 through L2) -> this kernel: N = 100, 100000 orders 103 -> 33 us, 600000 orders 624 -> 149 us; N = 65, 300000 orders
-// 291 -> 55 us; N = 50, 300000 orders 119 -> 39 us; N = 20, 10^6 orders 326 -> 90 us; N = 200, 100000 orders 223 -> 80 us.
-__global__ __launch_bounds__(1024) void dbt_batch_rows_kernel(const int32_t* __restrict__ c, int N, int levels,
-                                                              const int32_t* __restrict__ perms, int64_t B,
-                                                              int64_t* __restrict__ out) {
-    constexpr int U = 4;                                                        // staging steps in flight
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_dbt[];
-    const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15, waves = blockDim.x >> 6;
-    const int slots = 1 << levels;
-    unsigned* wave_top = (unsigned*)smem_dbt;                                   // [16]
-    uint16_t* slot_of = (uint16_t*)(smem_dbt + 64);                             // [N]
-    uint16_t* m16 = slot_of + ((N + 7) & ~7);                                   // [N * N]
-    uint32_t* nodes = (uint32_t*)(m16 + ((N * N + 7) & ~7)) + wv * 4 * slots + (lane >> 4) * slots;   // [waves][4][slots]
-    int2* cost = (int2*)((uint32_t*)(m16 + ((N * N + 7) & ~7)) + waves * 4 * slots) + wv * 2 * slots +
-                 (lane >> 4) * (slots / 2);                                     // [waves][4][slots / 2]
-    unsigned top = 0;
-    for (int e = threadIdx.x; e < N * N; e += blockDim.x) {
-        const unsigned v = (unsigned)c[e];                                      // a negative entry counts as too large
-        top = max(top, v);
-        m16[e] = (uint16_t)v;
-    }
-    for (int p = threadIdx.x; p < N; p += blockDim.x) {
-        int lo = 0, hi = N - 1, m = (N - 1) >> 1, h = 1;
-        for (int depth = 0; depth < 11 && m != p; ++depth) {
-            if (p < m) hi = m - 1;
-            else lo = m + 1;
-            h = 2 * h + (p > m);
-            m = (lo + hi) >> 1;
-        }
-        slot_of[p] = (uint16_t)h;
-    }
-    for (int h = sub; h < slots; h += 16) nodes[h] = ~0u;
-    if (sub == 0) cost[1] = make_int2(0, 0);
-    top = (unsigned)wave_max((int)min(top, 0x7fffffffu));
-    if (lane == 0) wave_top[wv] = top;
-    __syncthreads();
-    for (int k = 0; k < waves; ++k) top = max(top, wave_top[k]);
-    auto score = [&](auto in_lds) {
-        const int64_t nwaves = (int64_t)gridDim.x * waves;
-        for (int64_t w = (int64_t)blockIdx.x * waves + wv; w * 4 < B; w += nwaves) {
-            const int64_t b = w * 4 + (lane >> 4);
-            const int32_t* pi = perms + (b < B ? b : B - 1) * N;
-            for (int p0 = sub; p0 < N + sub; p0 += 16 * U) {
-                int x[U], y[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int p = min(p0 + 16 * u, N - 1);
-                    x[u] = pi[p];
-                    y[u] = pi[p + 1 < N ? p + 1 : 0];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (p0 + 16 * u < N)
-                        nodes[slot_of[p0 + 16 * u]] =
-                            (unsigned)clampi(x[u], 0, N - 1) | (unsigned)clampi(y[u], 0, N - 1) << 16;
-            }
-            __builtin_amdgcn_wave_barrier();
-            int worst = 0;
-            for (int d = 1; d < levels; ++d) {
-                for (int h0 = 1 << d; h0 < 2 << d; h0 += 16) {
-                    const int h = h0 + sub;
-                    const uint32_t own = h < 2 << d ? nodes[h] : ~0u, parent = nodes[(h >> 1) & (slots - 1)];
-                    if (own != ~0u) {
-                        const unsigned e0 = __umul24(parent & 0xffffu, N) + (own & 0xffffu);
-                        const unsigned e1 = __umul24(parent >> 16, N) + (own >> 16);
-                        int2 k = cost[h >> 1];
-                        k.x += in_lds ? (int)m16[e0] : c[e0];
-                        k.y += in_lds ? (int)m16[e1] : c[e1];
-                        worst = max(worst, max(k.x, k.y));
-                        if (d < levels - 1) cost[h] = k;
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0xB1, 0xf, 0xf, true));
-            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0x4E, 0xf, 0xf, true));
-            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0x141, 0xf, 0xf, true));
-            worst = max(worst, __builtin_amdgcn_update_dpp(worst, worst, 0x140, 0xf, 0xf, true));
-            if (sub == 0 && b < B) out[b] = worst;
-        }
-    };
-    if (top < (1u << 16)) score(std::true_type{});
-    else score(std::false_type{});
-}
-
-constexpr int kDbtRowsMinWaves = 4;
-
-static int dbt_levels(int N) { return 32 - __builtin_clz((unsigned)N); }
-static size_t dbt_rows_fixed_bytes(int N) { return 64 + 2 * (size_t)((N + 7) & ~7) + 2 * (((size_t)N * N + 7) & ~(size_t)7); }
-// waves of a workgroup: what the LDS beside the matrix holds, 8 bytes per slot and order
-static int dbt_rows_waves(int N) {
-    const size_t fixed = dbt_rows_fixed_bytes(N), slice = (size_t)32 << dbt_levels(N), all = 160 * 1024;
-    if (fixed + slice > all) return 0;
-    const size_t fit = (all - fixed) / slice;
-    return fit < 16 ? (int)fit : 16;
-}
-
-static hipError_t dbt_rows_launch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
-    const int waves = dbt_rows_waves(N), levels = dbt_levels(N);
-    const size_t lds = dbt_rows_fixed_bytes(N) + waves * ((size_t)32 << levels);
-    hipError_t e = hipFuncSetAttribute((const void*)dbt_batch_rows_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       160 * 1024);
-    if (e != hipSuccess) return e;
-    const int64_t at_once = 256 * (2 * lds <= 160 * 1024 ? 2 : 1);
-    int64_t blocks = (B + 4 * waves - 1) / (4 * waves);
-    if (blocks > at_once) blocks = at_once;
-    hipLaunchKernelGGL(dbt_batch_rows_kernel, dim3((int)blocks), dim3(64 * waves), lds, s, c, N, levels, perms, B, out);
+template <int REST>
+static hipError_t dbt_launch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
+    const size_t lds = sizeof(int32_t) * 4 * (size_t)(N + N / 32 + 1);
+    hipLaunchKernelGGL(dbt_batch_kernel<REST>, dim3(batch_grid(4, B)), dim3(256), lds, s, c, N, perms, B, out);
     return hipGetLastError();
 }
 
-// Up to about 2^20 ranks a call takes its launch time either way, or the staging shows (generic / rows: N = 128, 4000 orders
-// 7.6 / 9.9 us, 16000 orders 18.4 / 14.5; N = 200, 4000 orders 14.3 / 15.8, 16000 orders 34.8 / 21.7).  The fewer waves fit
-// beside the matrix, the longer the staging and the slower the orders: N = 220 (8 waves), 8000 orders 19.4 / 19.1; N = 236 (6),
-// 8000 orders 19.8 / 30.0, 16000 orders 36.4 / 35.6; N = 245 (5), 30000 orders 69 / 72, 50000 orders 117 / 112; N = 255 (4), 50000
-// orders 119 / 144, 100000 orders 230 / 214.
-static bool dbt_rows_pays(int N, int64_t B) {
-    const int waves = dbt_rows_waves(N);
-    const int64_t ranks = waves >= 10 ? 1 << 20 : waves >= 8 ? 3 << 19 : waves >= 6 ? 1 << 22 : waves == 5 ? 3 << 22 : 6 << 22;
-    return waves >= kDbtRowsMinWaves && B * N >= ranks;
+// Large batches of 8 <= N <= 255: one order per lane, the matrix in LDS, 64 orders at a time as bytes beside it
+// (a tile: by rank, so that the lanes of a wave read one rank of all orders from consecutive bytes).  All lanes walk
+// the tree together: where a rank range begins and ends is scalar arithmetic, and every edge is looked up once per tree.  A tile belongs
+// to as many waves as make eight bottom subtrees each (K of them in all): every wave stages its part of the orders and walks
+// its part of both trees, the next tile's ranks on their way meanwhile.  The bottom subtrees are of two or three ranks
+// (AT_MOST 3: N >= 3 K) or of one or two: three or two look-ups per tree, of which the one that not every subtree has is masked.
+// What bounds it: LDS look-ups (two bytes and two entries per rank) and, up to some 100000 orders, the latency of one or two tiles per
+// wave.  Level by level with sixteen lanes per order, top levels nearly empty -> here: N = 100, 100000 orders 33.3 -> 18.5 us, 300000
+// orders 80 -> 38 us; N = 50, 10^6 orders 120 -> 58 us; N = 8, 10^6 orders 78 -> 10 us; N = 255 (few waves beside the
+// matrix), 100000 orders 212 -> 40 us; N = 200, 300000 orders 202 -> 73 us.  Only matrices without an entry below 65535 are slower at
+// N = 193 .. 230 (100000 orders, N = 200 148 -> 187 us: all look-ups through L2, with half the wavefronts).  One wave per tile: N = 255,
+// 100000 orders 127 us; two workgroups of eight waves per unit: N = 100, 50000 orders 11.2 instead of 9.4 us.
+constexpr int kDbtRow = 68;                     // bytes per rank: 64 orders, and a bank further from rank to rank
+
+// MIXED: the staged entry 0xffff stands for one in the caller's matrix
+template <typename ENTRY, bool MIXED>
+struct DbtTile {
+    const ENTRY* mat;
+    const int32_t* callers;
+    const unsigned char* tile;                  // byte `lane` of rank 0 is this lane's
+    int N, lane;
+    __device__ __forceinline__ unsigned node(int rank) const { return tile[rank * kDbtRow + lane]; }
+    // of the second tree's positions the last one holds rank 0
+    __device__ __forceinline__ unsigned next_node(int rank) const { return node(rank >= N ? rank - N : rank); }
+    // rows in bytes
+    __device__ __forceinline__ unsigned row_of(unsigned x) const { return __umul24(x, (unsigned)(sizeof(ENTRY) * N)); }
+    __device__ __forceinline__ int edge(unsigned from_row, unsigned to) const {
+        const unsigned at = from_row + (unsigned)sizeof(ENTRY) * to;
+        const int entry = *(const ENTRY*)((const char*)mat + at);
+        if (!MIXED) return entry;
+        const bool large = entry == 0xffff;
+        const int callers_entry = callers[large ? at / (unsigned)sizeof(ENTRY) : 0u];
+        return large ? callers_entry : entry;
+    }
+};
+
+// A bottom subtree: of three ranks the middle one is the root, of two the lower.  nodes[]: (AT_MOST 3) its lowest rank, then
+// for either the root and the two ranks above it.
+template <int AT_MOST>
+struct DbtBottom {
+    unsigned lowest, nodes[3];
+    int more;                                   // 1: as many ranks as there may be
+    int edges[AT_MOST == 3 ? 6 : 4];
+
+    template <class TILE>
+    __device__ __forceinline__ void read_nodes(const TILE& t, int lo, int hi) {
+        more = hi - lo - (AT_MOST - 2);
+        const int root = AT_MOST == 3 ? lo + more : lo;
+        lowest = AT_MOST == 3 ? t.node(lo) : 0;
+        nodes[0] = t.node(root);
+        nodes[1] = AT_MOST == 3 ? t.node(root + 1) : t.next_node(root + 1);
+        nodes[2] = t.next_node(root + 2);
+    }
+    // p0, p1: rows of the node above in either tree
+    template <class TILE>
+    __device__ __forceinline__ void read_edges(const TILE& t, unsigned p0, unsigned p1) {
+        const unsigned r0 = t.row_of(nodes[0]), r1 = t.row_of(nodes[1]);
+        edges[0] = t.edge(p0, nodes[0]);
+        edges[1] = t.edge(p1, nodes[1]);
+        edges[2] = t.edge(r0, nodes[1]);
+        edges[3] = t.edge(r1, nodes[2]);
+        if constexpr (AT_MOST == 3) {
+            edges[4] = t.edge(r0, lowest);
+            edges[5] = t.edge(r1, nodes[0]);
+        }
+    }
+    __device__ __forceinline__ int costliest(int k0, int k1) const {
+        if constexpr (AT_MOST == 3)
+            return max(k0 + edges[0] + max(edges[2], edges[4] & -more), k1 + edges[1] + max(edges[3], edges[5] & -more));
+        else
+            return max(k0 + edges[0] + (edges[2] & -more), k1 + edges[1] + (edges[3] & -more));
+    }
+};
+
+// The tree of positions lo .. hi, LEFT levels above the bottom subtrees, below the node of row p0 (p1 in the second tree; root:
+// below none).  Two levels above the bottom ones it is read as a whole, all nodes and then all entries in flight together.
+template <int LEFT, int AT_MOST, class TILE>
+__device__ __forceinline__ void dbt_descend(TILE& t, int lo, int hi, bool root, unsigned p0, unsigned p1, int k0, int k1, int& worst) {
+    const int mid = (lo + hi) >> 1;
+    const unsigned x0 = t.node(mid), x1 = t.node(mid + 1), x0_row = t.row_of(x0), x1_row = t.row_of(x1);
+    if constexpr (LEFT > 2) {
+        k0 += root ? 0 : t.edge(p0, x0);
+        k1 += root ? 0 : t.edge(p1, x1);
+        dbt_descend<LEFT - 1, AT_MOST>(t, lo, mid - 1, false, x0_row, x1_row, k0, k1, worst);
+        dbt_descend<LEFT - 1, AT_MOST>(t, mid + 1, hi, false, x0_row, x1_row, k0, k1, worst);
+    } else {
+        unsigned y0[2], y1[2];
+        DbtBottom<AT_MOST> bottom[4];
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int from = side ? mid + 1 : lo, to = side ? hi : mid - 1, m = (from + to) >> 1;
+            y0[side] = t.node(m);
+            y1[side] = t.node(m + 1);
+            bottom[2 * side].read_nodes(t, from, m - 1);
+            bottom[2 * side + 1].read_nodes(t, m + 1, to);
+        }
+        const int e0 = root ? 0 : t.edge(p0, x0), e1 = root ? 0 : t.edge(p1, x1);
+        int f0[2], f1[2];
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            f0[side] = t.edge(x0_row, y0[side]);
+            f1[side] = t.edge(x1_row, y1[side]);
+            const unsigned y0_row = t.row_of(y0[side]), y1_row = t.row_of(y1[side]);
+            bottom[2 * side].read_edges(t, y0_row, y1_row);
+            bottom[2 * side + 1].read_edges(t, y0_row, y1_row);
+        }
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int m0 = k0 + e0 + f0[side], m1 = k1 + e1 + f1[side];
+            worst = max(worst, max(bottom[2 * side].costliest(m0, m1), bottom[2 * side + 1].costliest(m0, m1)));
+        }
+        // the next look-ups wait for this group's: the compiler would have all of them in flight and spill
+        asm volatile("" : "+v"(t.lane), "+v"(worst));
+    }
+}
+
+// PARTS: waves per tile
+__host__ __device__ constexpr int dbt_parts(int K) { return K <= 8 ? 1 : K / 8; }
+
+// ENTRY: 32 bits where the matrix has room as such, 16 above
+template <int K, int AT_MOST, bool QUADS, typename ENTRY>
+__global__ __launch_bounds__(1024) void dbt_batch_lanes_kernel(const int32_t* __restrict__ c, int N, int tiles,
+                                                               const int32_t* __restrict__ perms, int64_t B,
+                                                               int64_t* __restrict__ out) {
+    constexpr int PARTS = dbt_parts(K), LEVELS = 31 - __builtin_clz((unsigned)K), SPLIT = 31 - __builtin_clz((unsigned)PARTS);
+    constexpr int U = K / PARTS;                                        // loads of a wave for a tile: N <= 4 K - 1
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_lanes[];
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wv % PARTS, slot = wv / PARTS;
+    unsigned* wave_top = (unsigned*)smem_lanes;                         // [16]
+    int* costliest = (int*)(smem_lanes + 64) + 64 * slot;               // [tiles][64]
+    ENTRY* staged = (ENTRY*)(smem_lanes + 64 + 256 * tiles);            // [N * N]
+    unsigned char* tile = (unsigned char*)(staged + ((N * N + 7) & ~7)) + slot * N * kDbtRow;
+    const int64_t elements = B * N, stride = (int64_t)gridDim.x * tiles;
+    ranks4 v[U];
+    // this wave's part of 64 orders, which lie one after the other; past the batch's end whatever is there
+    auto request = [&](int64_t task) {
+        const int64_t first = task * 64 * N + 256 * part + 4 * lane;
+        if (QUADS || (task + 1) * 64 <= B) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *(const ranks4*)(perms + min(first + 256 * PARTS * u, elements - 4));
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[u][j] = perms[min(first + 256 * PARTS * u + j, elements - 1)];
+        }
+    };
+    if (slot < tiles) request((int64_t)blockIdx.x * tiles + slot);
+    unsigned top = stage_matrix(c, N * N, staged);
+    top = (unsigned)wave_max((int)min(top, 0x7fffffffu));
+    if (lane == 0) wave_top[wv] = top;
+    if (PARTS > 1 && part == 0 && slot < tiles) costliest[lane] = 0;
+    __syncthreads();
+    if (slot >= tiles) return;                                          // they staged only; later barriers wait for the others
+    for (int k = 0; k < (int)blockDim.x >> 6; ++k) top = max(top, wave_top[k]);
+    // where this wave's first four ranks are (order and rank), and how far on those of its next load
+    const int first = 256 * part + 4 * lane, first_o = first / N, first_p = first - first_o * N;
+    const int step_o = 256 * PARTS / N, step_p = 256 * PARTS - step_o * N;
+    auto score = [&](auto mixed) {
+        for (int64_t base = (int64_t)blockIdx.x * tiles; base * 64 < B; base += stride) {
+            const int64_t task = base + slot;
+            int p = first_p, o = first_o;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (4 * (u * PARTS + part) < N) {
+                    // the four's first byte, and, where the next order begins among them, what the later ones are counted from;
+                    // past the 64 orders (the last load, N no multiple of 4): the byte behind a rank's 64
+                    int to = p * kDbtRow + o, to_next = to - N * kDbtRow + 1;
+                    if (!QUADS) {
+                        to = o < 64 ? to : 64;
+                        to_next = o < 63 ? to_next : 64;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        tile[(QUADS || p + j < N ? to : to_next) + j * kDbtRow] = (unsigned char)clampi(v[u][j], 0, N - 1);
+                    p += step_p;
+                    o += step_o;
+                    if (p >= N) {
+                        p -= N;
+                        ++o;
+                    }
+                }
+            }
+            if (PARTS > 1) __syncthreads();
+            else __builtin_amdgcn_wave_barrier();
+            request(task + stride);
+            // ---- both trees of every lane's order; new to the compiler in every round: it would keep the addresses of all ranks in
+            // registers, more than there are
+            DbtTile<ENTRY, decltype(mixed)::value> t{staged, c, tile, N, lane};
+            int worst = 0, lo = 0, hi = N - 1, k0 = 0, k1 = 0;
+            unsigned p0 = 0, p1 = 0;
+            asm volatile("" : "+v"(t.lane), "+s"(hi));
+#pragma unroll
+            for (int k = 0; k < SPLIT; ++k) {
+                const int mid = (lo + hi) >> 1;
+                const unsigned x0 = t.node(mid), x1 = t.node(mid + 1);
+                if (k) {
+                    k0 += t.edge(p0, x0);
+                    k1 += t.edge(p1, x1);
+                }
+                p0 = t.row_of(x0);
+                p1 = t.row_of(x1);
+                const bool right = (part >> (SPLIT - 1 - k)) & 1;
+                lo = right ? mid + 1 : lo;
+                hi = right ? hi : mid - 1;
+            }
+            dbt_descend<LEVELS - SPLIT, AT_MOST>(t, lo, hi, SPLIT == 0, p0, p1, k0, k1, worst);
+            const int64_t b = task * 64 + lane;
+            if (PARTS > 1) {
+                atomicMax(&costliest[lane], worst);
+                __syncthreads();
+                if (part == 0) {
+                    if (b < B) out[b] = costliest[lane];
+                    costliest[lane] = 0;
+                }
+            } else {
+                if (b < B) out[b] = worst;
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    };
+    if (sizeof(ENTRY) == 4 || __builtin_amdgcn_readfirstlane(top) < 0xffffu) score(std::false_type{});
+    else score(std::true_type{});
+}
+
+// N < 8: one order per lane in registers, the matrix in LDS.  10^6 orders of N = 7: 7.7 us (a wave per order 130, sixteen lanes 65).
+template <int N>
+__global__ __launch_bounds__(256) void dbt_batch_tiny_kernel(const int32_t* __restrict__ c, const int32_t* __restrict__ perms,
+                                                             int64_t B, int64_t* __restrict__ out) {
+    __shared__ int32_t m[N * 64];
+    for (int e = threadIdx.x; e < N * N; e += 256) m[e / N * 64 + e % N] = c[e];
+    __syncthreads();
+    for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < B; b += (int64_t)gridDim.x * 256) {
+        unsigned node4[N];
+#pragma unroll
+        for (int p = 0; p < N; ++p) node4[p] = (unsigned)clampi(perms[b * N + p], 0, N - 1) << 2;
+        int worst = 0;
+        dbt_walk_64<0, N - 1, 0, N>((const char*)m, node4, 0u, 0, false, worst);
+        dbt_walk_64<0, N - 1, 1, N>((const char*)m, node4, 0u, 0, false, worst);
+        out[b] = worst;
+    }
+}
+
+template <int N>
+static hipError_t dbt_tiny_launch(const int32_t* c, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
+    hipLaunchKernelGGL(dbt_batch_tiny_kernel<N>, dim3(batch_grid(256, B)), dim3(256), 0, s, c, perms, B, out);
+    return hipGetLastError();
+}
+
+static size_t dbt_lanes_bytes(int N, int entry, int tiles) {
+    return 64 + 256 * (size_t)tiles + (size_t)entry * ((N * N + 7) & ~7) + (size_t)tiles * N * kDbtRow;
+}
+
+template <int K, int AT_MOST>
+static hipError_t dbt_lanes_launch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
+    constexpr size_t kLds = 160 * 1024;
+    const int64_t tasks = (B + 63) / 64;
+    int64_t tiles = 16 / dbt_parts(K);
+    const int entry = dbt_lanes_bytes(N, 4, (int)tiles) <= kLds ? 4 : 2;
+    while (tiles > 1 && dbt_lanes_bytes(N, entry, (int)tiles) > kLds) --tiles;
+    const int64_t per_round = 256 * tiles;
+    // few orders: on as many compute units as there are; many: as many at a time as make the rounds equally long
+    const int64_t rounds = (tasks + per_round - 1) / per_round;
+    if (rounds == 1 && tasks < 256 * tiles) tiles = (tasks + 255) / 256;
+    const bool quads = (N & 3) == 0 && ((uintptr_t)perms & 15u) == 0;
+    auto kernel = quads ? dbt_batch_lanes_kernel<K, AT_MOST, true, int32_t> : dbt_batch_lanes_kernel<K, AT_MOST, false, int32_t>;
+    if constexpr (K == 64)
+        if (entry == 2) kernel = quads ? dbt_batch_lanes_kernel<K, AT_MOST, true, uint16_t> : dbt_batch_lanes_kernel<K, AT_MOST, false, uint16_t>;
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = (tasks + tiles * rounds - 1) / (tiles * rounds);
+    hipLaunchKernelGGL(kernel, dim3((int)blocks), dim3(1024), dbt_lanes_bytes(N, entry, (int)tiles), s, c, N, (int)tiles, perms, B, out);
+    return hipGetLastError();
+}
+
+static hipError_t dbt_lanes(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
+    if (N < 12) return dbt_lanes_launch<4, 2>(c, N, perms, B, out, s);
+    if (N < 16) return dbt_lanes_launch<4, 3>(c, N, perms, B, out, s);
+    if (N < 24) return dbt_lanes_launch<8, 2>(c, N, perms, B, out, s);
+    if (N < 32) return dbt_lanes_launch<8, 3>(c, N, perms, B, out, s);
+    if (N < 48) return dbt_lanes_launch<16, 2>(c, N, perms, B, out, s);
+    if (N < 64) return dbt_lanes_launch<16, 3>(c, N, perms, B, out, s);
+    if (N < 96) return dbt_lanes_launch<32, 2>(c, N, perms, B, out, s);
+    if (N < 128) return dbt_lanes_launch<32, 3>(c, N, perms, B, out, s);
+    if (N < 192) return dbt_lanes_launch<64, 2>(c, N, perms, B, out, s);
+    return dbt_lanes_launch<64, 3>(c, N, perms, B, out, s);
+}
+
+// One order per wave is the faster until its waves take several orders each or the L2 has enough requests to bound it; the matrix in
+// LDS has its staging to bring in (through L2 / from LDS: N = 8, 32000 orders 7.4 / 7.4 us, 65000 orders 10.7 / 7.2; N = 50, 16000
+// orders 7.0 / 7.2, 32000 8.3 / 7.4; N = 100, 8000 orders 6.9 / 7.0, 16000 8.3 / 7.0; N = 150, 4000 orders 6.7 / 9.0, 8000 9.9 / 8.6;
+// N = 255, 4000 orders 10.3 / 12.7, 8000 17.4 / 12.0).
+static bool dbt_lanes_pay(int N, int64_t B) {
+    return N < 256 && (B >= 40000 || B * N >= (N > 192 ? 5 << 18 : 1 << 20));
 }
 
 hipError_t launch_dbt_cost_batch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out,
                                  hipStream_t s) {
     if (B == 0) return hipSuccess;
-    const int grid = batch_grid(4, B);
     if (N == 64 && ((uintptr_t)perms & 15u) == 0) {
         hipLaunchKernelGGL(dbt_lanes64_kernel, dim3(batch_grid(4 * 64, B)), dim3(256), 0, s, c, (const int4*)perms, B, out);
-    } else if (N == 64) {
-        hipLaunchKernelGGL(dbt_batch_n64_kernel, dim3(grid), dim3(256), 0, s, c, perms, B, out);
-    } else if (dbt_rows_pays(N, B)) {
-        return dbt_rows_launch(c, N, perms, B, out, s);
-    } else if (N <= 64) {
-        const size_t lds = sizeof(int32_t) * (size_t)(4 * N + N * N);
-        hipLaunchKernelGGL((dbt_batch_kernel<true>), dim3(grid), dim3(256), lds, s, c, N, perms, B, out);
+    } else if (N < 8) {
+        switch (N) {
+            case 2: return dbt_tiny_launch<2>(c, perms, B, out, s);
+            case 3: return dbt_tiny_launch<3>(c, perms, B, out, s);
+            case 4: return dbt_tiny_launch<4>(c, perms, B, out, s);
+            case 5: return dbt_tiny_launch<5>(c, perms, B, out, s);
+            case 6: return dbt_tiny_launch<6>(c, perms, B, out, s);
+            default: return dbt_tiny_launch<7>(c, perms, B, out, s);
+        }
+    } else if (dbt_lanes_pay(N, B)) {
+        return dbt_lanes(c, N, perms, B, out, s);
     } else {
-        const size_t lds = sizeof(int32_t) * (size_t)(4 * N);
-        hipLaunchKernelGGL((dbt_batch_kernel<false>), dim3(grid), dim3(256), lds, s, c, N, perms, B, out);
+        if (N < 64) return dbt_launch<0>(c, N, perms, B, out, s);
+        if (N < 128) return dbt_launch<1>(c, N, perms, B, out, s);
+        if (N < 256) return dbt_launch<2>(c, N, perms, B, out, s);
+        if (N < 512) return dbt_launch<3>(c, N, perms, B, out, s);
+        if (N < 1024) return dbt_launch<4>(c, N, perms, B, out, s);
+        return dbt_launch<5>(c, N, perms, B, out, s);
     }
     return hipGetLastError();
 }
