@@ -16,20 +16,22 @@
 // 2 cost + 1 as a float), with the number of partners up to each bucket: how far a threshold reaches is one look-up, and
 // order inside a bucket does not matter.  A list holds the nearest M partners; a node whose threshold reaches further,
 // or whose candidates exceed the room for them, is scanned against every node instead.
-//   * N <= 256: lists in LDS, made by the workgroup itself; up to 256 (N <= 192: mostly 512) restarts one workgroup of a
-//     wavefront per 64 nodes each, beyond that up to 16 restarts of one wavefront each around one copy of the lists.
-//   * N > 256: one workgroup per restart, a wavefront per 64 nodes, lists in the workspace (M = (N - 128) / 2), made by a
-//     kernel of their own.
+//   * N <= 256: lists in LDS, made by the workgroup itself; up to 256 (N <= 192: mostly 512) restarts one workgroup of eight
+//     (four) wavefronts each, beyond that up to 16 restarts of one wavefront each around one copy of the lists.
+//   * N > 256: one workgroup per restart, lists in the workspace (M = (N - 128) / 2), made by a kernel of their own.
 // The candidates of 64 nodes are laid out end to end (prefix sum of their counts) and taken 64 at a time, up to four
 // times 64 with their look-ups in flight together; those whose bracket passes are collected in LDS and scored 64 at a
-// time.
+// time.  The wavefronts of one restart take the 64s of all nodes in turn (the nodes of one wavefront have two or three times the
+// candidates of another's, and the passed ones lie together), so there may be more wavefronts than nodes / 64.
 //
-// What bounds it: instruction issue, about 60 instructions per 64 candidates and 180 per 64 scored ones, and with 16
-// wavefronts per restart the barriers (N = 1000: 17000 clocks a sweep, 6000 of them brackets, 4000 waiting for the
-// slowest wavefront).  Costs of few values or from 0 on take no longer than others (see cc_pruned.h and where D is known).  Measured against the exhaustive kernels: N = 1000, 128 restarts 494 -> 11 ms; N = 583, 47 restarts
-// 112 -> 4.6 ms; N = 345, 2140 restarts 239 -> 7.5 ms; N = 1024, 256 restarts 57.9 -> 12 ms (a kernel that streamed the
-// matrix through LDS row by row, gone since); N = 512, 768 restarts 19.2 -> 6.1 ms; N = 240, 1024 restarts 7.1 -> 3.4 ms;
-// N = 256, 4096 restarts 7.8 -> 5.2 ms.
+// What bounds it: instruction issue (with 16 wavefronts, N = 1000, about 740 vector instructions per wavefront and sweep, 70 % of the
+// SIMDs' rate), and with few wavefronts the latency of each one's own.  Exhaustive kernels -> this one: N = 1000, 128 restarts 494 ->
+// 10.6 ms; N = 583, 47 restarts 112 -> 4.4 ms; N = 345, 2140 restarts 239 -> 7.4 ms; N = 1024, 256 restarts 57.9 -> 11.3 ms; N = 512, 768
+// restarts 19.2 -> 5.6 ms; N = 256, 4096 restarts 7.8 -> 5.2 ms.  Every wavefront its own nodes' candidates, one per 64 nodes -> shared,
+// more wavefronts: N = 1000, 128 restarts 11.5 -> 10.6 ms, N = 700, 100 restarts 6.4 -> 5.5, N = 400, 64 restarts 2.77 -> 2.23, N = 300,
+// 250 restarts 1.89 -> 1.53, N = 200, 256 restarts 1.24 -> 0.96, N = 150, 500 restarts 0.88 -> 0.70.  Slower were: two or four nodes per lane
+// and half or a quarter of the wavefronts (N = 1000 13.2, 21.2 ms); a D of each wavefront's own without the barrier (N = 1000 10.4 ms, but
+// two zones of equal costs, N = 1024, 64 restarts 2.9 -> 5.3 ms: fewer equal moves are ruled out).
 #include <type_traits>
 
 #include "cc_device.h"
@@ -47,28 +49,50 @@ using namespace pruned;
 // -1 .. N, and per wave the laid out candidates' owners and the candidates whose bracket passed.
 __host__ __device__ constexpr size_t order_bytes(int N) { return ((size_t)N * 8 + (size_t)(N + 2) * 2 + 15) & ~(size_t)15; }
 
+// Several waves per restart: besides, where each node's candidates begin.
+__host__ __device__ constexpr size_t group_order_bytes(int N) { return order_bytes(N) + (((size_t)N * 2 + 15) & ~(size_t)15); }
+constexpr int kGroupAtOnce = 3;         // times 64 candidates
+constexpr int kGroupPassed = 64 * (kGroupAtOnce + 1);
+__host__ __device__ constexpr size_t group_wave_bytes(int room) { return (size_t)room * 2 + kGroupPassed * 8; }
+
+// What the waves of one restart tell each other
+template <int WAVES>
+struct GroupWords {
+    unsigned long long key[4];              // of the best move, used in turn: value, id, wave
+    uint2 hops[2][WAVES];                   // the hops each wave's best move makes
+    int laid_out[WAVES];                    // candidates
+    int word[WAVES];
+};
+
 // One descent.  A node's scale (of its buckets) is scale0 (one node per lane) or scales[node].  Wave `wv` of the restart
 // owns the nodes 64 * (wv * K + k) + lane.
 template <int WAVES, int K, int ROOM, typename COUNT, class MAT>
 __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __restrict__ lists, int M,
                                         const COUNT* __restrict__ counts, int scale0, const uint16_t* scales, unsigned char* order_mem,
-                                        unsigned char* wave_mem, unsigned long long (*red)[WAVES], int wv, int lane,
+                                        unsigned char* wave_mem, GroupWords<WAVES>* group, int wv, int lane,
                                         int32_t* __restrict__ tour, int64_t* __restrict__ cost_out,
                                         int32_t* __restrict__ moves_out) {
     constexpr int THREADS = 64 * WAVES;
+    // The waves of a restart share the candidates of all its nodes, and what a look-up through L2 has brought is kept: a passed
+    // candidate's entry of the list, the hops that the best move makes.
+    constexpr bool GROUP = WAVES > 1;
+    static_assert(!GROUP || K == 1, "a group's wave owns 64 nodes at most");
     uint2* info = (uint2*)order_mem;                           // [N] by node
     uint16_t* t = (uint16_t*)(info + N) + 1;                   // t[-1] = t[N-1], t[N] = t[0]
     uint16_t* owner = (uint16_t*)wave_mem;                     // [ROOM] stamp << 6 | lane
     // [kPassed] x | place << 10 | sides << 21; place: in the list of x, or M + y for a node scanned against every node
     uint32_t* passed = (uint32_t*)(wave_mem + ROOM * 2);
+    uint2* passed_entries = (uint2*)passed;                    // GROUP: [kGroupPassed] x | sides << 21, cost << 10 | y
+    uint16_t* starts = (uint16_t*)(order_mem + order_bytes(N));                    // GROUP: [N] place of a node's first candidate
     const int tid = wv * 64 + lane;
+    auto list_entry = [&](unsigned at) { return *(const uint32_t*)((const char*)lists + at * 4u); };
     auto sync = [] { if (WAVES > 1) __syncthreads(); else __builtin_amdgcn_wave_barrier(); };
     auto hop_in = [](uint2 w) { return (int)(w.x >> 10); };
     auto hop_out = [](uint2 w) { return (int)w.y; };
     auto rank_of = [](uint2 w) { return (int)(w.x & 1023u); };
 
     // ---- order, hops, ranks
-    int t0[K], applied = 0, parity = 0;
+    int t0[K], applied = 0, turn = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int p = tid + THREADS * k;
@@ -99,67 +123,85 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
 #pragma unroll
     for (int k = 0; k < K; ++k) good = good && (tid + THREADS * k >= N || rank_of(info[t0[k]]) == tid + THREADS * k);
     bool search = __ballot(!good) == 0;
-    if (WAVES > 1) {
+    // the candidate a lane remembers from an earlier sweep; at first the nearest partner of its first node
+    int rx = min(64 * wv * K + lane, N - 1);
+    const uint32_t nearest = lists[(size_t)rx * M];
+    int ry = (int)(nearest & 1023u), r_cost = (int)(nearest >> 10);
+    int r_value = 0;                                           // what it was worth
+    if (GROUP) {
         // over the wavefronts of this restart alone: the workgroup's others have ended, which a plain barrier allows and a
         // workgroup-wide reduction of the library need not
-        if (lane == 0) red[parity][wv] = search ? 1u : 0u;
+        if (lane == 0) group->word[wv] = search ? 1 : 0;
+        if (tid < 4) group->key[tid] = ~0ull;
         __syncthreads();
-        search = __ballot(red[parity][min(lane, WAVES - 1)] == 0) == 0;
-        parity ^= 1;
+        search = __ballot(group->word[min(lane, WAVES - 1)] == 0) == 0;
     }
-
-    // the candidate a lane remembers from an earlier sweep; at first the nearest partner of its first node
-    int rx = min(64 * wv * K + lane, N - 1), ry = (int)(lists[(size_t)rx * M] & 1023u);
-    int r_value = 0;                                           // what it was worth
     unsigned stamp = 0;
+    int last_start = 0;
     while (search) {
         int hi = 0, lo = -1;                                   // best move so far; none: 0 and an id nothing undercuts
         int sweep_best = kNone;                                // this lane's own best of the sweep, for rx and ry
-        // edges a and b exchanged
-        auto take = [&](int delta, int a, int b) {
+        int first_hop = 0, after_hop = 0;                      // GROUP: the hops into the reversed ranks and behind them
+        // edges a and b exchanged; the new hops before and behind what lies between them
+        auto take = [&](int delta, int a, int b, int before, int behind) {
             a = a >= N ? a - N : a;
             b = b >= N ? b - N : b;
             const int p = min(a, b), q = max(a, b);
-            const int id = p ? p * N + q - 1 : q * N + N - 1;
+            const int id = (int)__umul24((unsigned)(p ? p : q), (unsigned)N) + (p ? q : N) - 1;
             const bool better = delta < hi || (delta == hi && id < lo);
             hi = better ? delta : hi;
             lo = better ? id : lo;
+            if (GROUP) {
+                first_hop = better ? before : first_hop;
+                after_hop = better ? behind : after_hop;
+            }
         };
-        auto group_min = [&] {
-            int h = wave_min(hi);
+        // the best move of all lanes
+        auto group_best = [&] {
+            const int h = wave_min(hi);
             const unsigned long long at = __ballot(hi == h);
-            int l = __builtin_amdgcn_readlane(lo, (int)__builtin_ctzll(at));
-            if (at & (at - 1)) l = wave_min(hi == h ? lo : kNone);
-            if (WAVES > 1) {
-                if (lane == 0) red[parity][wv] = ((unsigned long long)(unsigned)(h + (1 << 30)) << 32) | (unsigned)l;
-                __syncthreads();
-                const unsigned long long v = red[parity][min(lane, WAVES - 1)];
-                const int vh = (int)(v >> 32) - (1 << 30), vl = (int)(unsigned)v;
-                h = wave_min(vh);
-                const unsigned long long who = __ballot(vh == h);
-                l = __builtin_amdgcn_readlane(vl, (int)__builtin_ctzll(who));
-                if (who & (who - 1)) l = wave_min(vh == h ? vl : kNone);
-                parity ^= 1;
+            int holder = (int)__builtin_ctzll(at), l = __builtin_amdgcn_readlane(lo, holder);
+            if (at & (at - 1)) {
+                l = wave_min(hi == h ? lo : kNone);
+                holder = (int)__builtin_ctzll(__ballot(hi == h && lo == l));
             }
             hi = h;
             lo = l;
+            if (GROUP) {
+                first_hop = __builtin_amdgcn_readlane(first_hop, holder);
+                after_hop = __builtin_amdgcn_readlane(after_hop, holder);
+                if (lane == 0) {
+                    group->hops[turn & 1][wv] = make_uint2((unsigned)first_hop, (unsigned)after_hop);
+                    atomicMin(&group->key[turn & 3], ((unsigned long long)(unsigned)(hi + (1 << 30)) << 24) |
+                                                         (unsigned)((lo & 0xfffff) << 4) | (unsigned)wv);
+                    group->key[(turn + 2) & 3] = ~0ull;          // read by all before the last barrier, used again after the next
+                }
+                __syncthreads();
+                const unsigned long long key = group->key[turn & 3];
+                const uint2 hops = group->hops[turn & 1][(int)key & 15];
+                hi = __builtin_amdgcn_readfirstlane((int)(key >> 24)) - (1 << 30);
+                lo = hi < 0 ? __builtin_amdgcn_readfirstlane((int)((unsigned)key >> 4 & 0xfffffu)) : -1;
+                first_hop = (int)hops.x;
+                after_hop = (int)hops.y;
+                ++turn;
+            }
         };
         // ---- D from the remembered candidates, on both sides (a reversal turns one into the other)
         {
             const bool worth = r_value <= 0;
             const uint2 ix = info[rx], iy = info[ry];
             const int p = rank_of(ix), q = rank_of(iy), d = p < q ? q - p : p - q;
-            const int cxy = mat(worth ? rx : 1, worth ? ry : 0);
+            const int cxy = GROUP ? r_cost : mat(worth ? rx : 1, worth ? ry : 0);
             const int cp = mat(worth ? t[p + 1] : 1, worth ? t[q + 1] : 0), cm = mat(worth ? t[p - 1] : 1, worth ? t[q - 1] : 0);
             if (worth && d >= 2 && d <= N - 2) {
                 const int behind = cxy + cp - hop_out(ix) - hop_out(iy), before = cxy + cm - hop_in(ix) - hop_in(iy);
-                take(behind, p + 1, q + 1);
-                take(before, p, q);
+                take(behind, p + 1, q + 1, cxy, cp);
+                take(before, p, q, cm, cxy);
                 sweep_best = min(behind, before);
             }
             r_value = sweep_best;
         }
-        group_min();
+        group_best();
         // only a move that lowers the cost is wanted: its value is -1 or less
         const int D = min(hi, -1);
         // A move of value D has one bracket below D / 2, or two of D / 2.  In the second case both new edges cost
@@ -171,37 +213,58 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
         // scores the n passed candidates from `from` on; a lane's candidate may stand on both sides
         auto score = [&](int from, int n) {
             const bool live = lane < n;
-            const uint32_t w = passed[from + (live ? lane : 0)];
-            const int x = (int)(w & 1023u), place = (int)((w >> 10) & 2047u), sides = (int)(w >> 21);
-            const bool listed = place < M;
-            const uint32_t e = lists[(size_t)x * M + (listed ? place : 0)];
-            const int y = listed ? (int)(e & 1023u) : place - M;
-            int cost = (int)(e >> 10);
-            if (__ballot(!listed)) cost = listed ? cost : mat(x, y);
+            int x, y, sides, cost;
+            if (GROUP) {
+                const uint2 w = passed_entries[from + (live ? lane : 0)];
+                x = (int)(w.x & 1023u);
+                sides = (int)(w.x >> 21);
+                y = (int)(w.y & 1023u);
+                cost = (int)(w.y >> 10);
+            } else {
+                const uint32_t w = passed[from + (live ? lane : 0)];
+                const int place = (int)((w >> 10) & 2047u);
+                x = (int)(w & 1023u);
+                sides = (int)(w >> 21);
+                const bool listed = place < M;
+                const uint32_t e = list_entry(__umul24((unsigned)x, (unsigned)M) + (unsigned)(listed ? place : 0));
+                y = listed ? (int)(e & 1023u) : place - M;
+                cost = (int)(e >> 10);
+                if (__ballot(!listed)) cost = listed ? cost : mat(x, y);
+            }
             const uint2 ix = info[x], iy = info[y];
             const int p = rank_of(ix), q = rank_of(iy), d = p < q ? q - p : p - q;
             const bool fits = live && d >= 2 && d <= N - 2;
             auto side = [&](bool out) {
                 const int a = out ? p + 1 : p, b = out ? q + 1 : q;
-                const int delta = cost + mat(t[out ? p + 1 : p - 1], t[out ? q + 1 : q - 1]) -
-                                  (out ? hop_out(ix) + hop_out(iy) : hop_in(ix) + hop_in(iy));
+                const int other = mat(t[out ? p + 1 : p - 1], t[out ? q + 1 : q - 1]);
+                const int delta = cost + other - (out ? hop_out(ix) + hop_out(iy) : hop_in(ix) + hop_in(iy));
                 if (fits) {
-                    take(delta, a, b);
+                    take(delta, a, b, out ? cost : other, out ? other : cost);
                     if (delta < sweep_best) {
                         sweep_best = delta;
                         r_value = delta;
                         rx = x;
                         ry = y;
+                        r_cost = cost;
                     }
                 }
             };
             side(sides & 1);
             if (__ballot(live && sides == 3)) side(sides != 3);        // the other side of those; of the others, any
         };
-        // side bits: 1 the edges behind x and y, 2 those before
-        auto pass = [&](int sides, int x, int place) {
-            const unsigned long long mask = __ballot(sides != 0);
-            if (sides) passed[n_passed + lanes_below(mask)] = (unsigned)x | ((unsigned)place << 10) | ((unsigned)sides << 21);
+        // Notes the pair x, y of cost e >> 10 if a bracket of it passes; the node with the longer removed edge looks at it.  Side bits: 1
+        // the edges behind x and y, 2 those before; place: where the list has y (GROUP: unused).  No branches but the store:
+        // with one per condition a candidate took half as many instructions again.
+        auto look = [&](bool live, uint2 ix, uint2 iy, uint32_t e, int x, int place) {
+            const int ox = hop_out(ix), oy = hop_out(iy), nx = hop_in(ix), ny = hop_in(iy), least = (int)((e >> 9) & ~1u) - D;
+            const bool out = live & (ox >= oy) & (ox + oy >= least), in = live & (nx >= ny) & (nx + ny >= least);
+            const unsigned long long mask = __ballot(out | in);
+            if (out | in) {
+                const unsigned at = (unsigned)(n_passed + lanes_below(mask));
+                const unsigned who = (unsigned)x | (out ? 1u << 21 : 0u) | (in ? 2u << 21 : 0u);
+                if (GROUP) passed_entries[at] = make_uint2(who, e);
+                else passed[at] = who | ((unsigned)place << 10);
+            }
             n_passed += __popcll(mask);
         };
         auto flush = [&] {
@@ -212,109 +275,166 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             }
             __builtin_amdgcn_wave_barrier();
         };
-        // the node with the longer removed edge looks at the pair
-        auto sides_of = [&](uint2 ix, uint2 iy, int twice) {
-            const int ox = hop_out(ix), oy = hop_out(iy), nx = hop_in(ix), ny = hop_in(iy);
-            return (ox >= oy && twice - oy <= ox + D ? 1 : 0) | (nx >= ny && twice - ny <= nx + D ? 2 : 0);
-        };
-#pragma unroll 1
-        for (int k = 0; k < K; ++k) {
-            // ---- how far the thresholds of 64 nodes reach; their candidates end to end
-            const int x_first = 64 * (wv * K + k), x = x_first + lane;
+        // ---- how far the threshold of node x (one per lane) reaches; the candidates of the 64 nodes end to end from place `from` on.
+        // Returns where they end; all: x is scanned against every node instead, its partners are beyond the list or the room.
+        auto lay_out = [&](int x, int scale, int from, unsigned mark, bool& all) {
             const uint2 ix = info[min(x, N - 1)];
-            const bool equals = (unsigned)(rank_of(ix) * N) <= (unsigned)lo;      // lo is -1 where no move is known
+            const bool equals = __umul24((unsigned)rank_of(ix), (unsigned)N) <= (unsigned)lo;      // lo is -1 where no move is known
             const int reach = max(hop_in(ix), hop_out(ix)) + ((equals ? D : D - 1) >> 1);
-            const int scale = K == 1 ? scale0 : (int)scales[min(x, N - 1)];
             const int bucket = bucket_of(max(reach, 0), scale);
-            int count = (int)counts[(size_t)min(x, N - 1) * kBuckets + max(0, min(bucket, kBuckets - 2))];
+            int count = (int)*(const COUNT*)((const char*)counts + (unsigned)sizeof(COUNT) * (unsigned)(min(x, N - 1) * kBuckets + max(0, min(bucket, kBuckets - 2))));
             count = bucket >= kBuckets - 1 ? N - 1 : count;
             count = x < N && reach >= 0 && bucket >= 0 ? count : 0;
-            bool all = count > M;                              // beyond the list: scanned against every node below
+            all = count > M;
             count = all ? 0 : count;
-            int end = wave_prefix_sum(count);
+            int end = from + wave_prefix_sum(count);
             int total = __builtin_amdgcn_readlane(end, 63);
             if (total > ROOM) {
                 const bool out = end > ROOM;
                 all = all || (out && count > 0);
                 count = out ? 0 : count;
-                total = wave_max(out ? 0 : end);
+                total = wave_max(out ? from : end);
             }
             const int start = end - count;
+            if (count > 0) {
+                owner[start] = (uint16_t)mark;
+                for (int i = (start | 63) + 1; i < start + count; i += 64) owner[i] = (uint16_t)mark;     // every 64 start anew
+            }
+            if (GROUP && x < N) starts[x] = (uint16_t)start;
+            last_start = start;
+            return total;
+        };
+        auto next_stamp = [&] {
             if (++stamp == 1024) {
                 stamp = 1;
                 for (int i = lane; i < ROOM; i += 64) owner[i] = 0;
                 __builtin_amdgcn_wave_barrier();
             }
-            if (count > 0) {
-                const uint16_t mark = (uint16_t)((stamp << 6) | (unsigned)lane);
-                owner[start] = mark;
-                for (int i = (start | 63) + 1; i < start + count; i += 64) owner[i] = mark;     // every 64 start anew
-            }
-            __builtin_amdgcn_wave_barrier();
-            // ---- brackets, U times 64 candidates with their LDS and list reads in flight together
-            auto brackets = [&](auto u_const, int i0) {
-                constexpr int U = decltype(u_const)::value;
-                unsigned src[U];
-                int from[U];
-                uint2 jx[U], jy[U];
-                uint32_t e[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) src[u] = owner[i0 + 64 * u + lane];
-                // marks of earlier layouts are smaller than this one's, and the first of the 64 is always marked
-#pragma unroll
-                for (int u = 0; u < U; ++u) src[u] = wave_prefix_max(src[u]) & 63u;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    from[u] = __builtin_amdgcn_ds_bpermute((int)(src[u] << 2), start);
-                    jx[u] = info[min(x_first + (int)src[u], N - 1)];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = i0 + 64 * u + lane;
-                    e[u] = lists[(size_t)((x_first + (int)src[u]) * M + i - from[u]) * (i < total ? 1 : 0)];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) jy[u] = info[e[u] & 1023u];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = i0 + 64 * u + lane;
-                    const int sides = sides_of(jx[u], jy[u], 2 * (int)(e[u] >> 10));
-                    pass(i < total ? sides : 0, x_first + (int)src[u], i - from[u]);
-                }
-            };
-            for (int i0 = 0; i0 < total; i0 += 256) {
-                if (total - i0 > 128) brackets(std::integral_constant<int, 4>{}, i0);
-                else if (total - i0 > 64) brackets(std::integral_constant<int, 2>{}, i0);
-                else brackets(std::integral_constant<int, 1>{}, i0);
-                flush();
-            }
-            // ---- nodes scanned against every node
+        };
+        auto scan_all = [&](bool all, int x_first) {
             unsigned long long rest = __ballot(all);
             while (rest) {
                 const int nx = x_first + (int)__builtin_ctzll(rest);
                 rest &= rest - 1;
                 const uint2 jx = info[nx];
-                for (int y0 = 0; y0 < N; y0 += 256) {
-                    int cost[4];
+                constexpr int U = GROUP ? kGroupAtOnce : 4;
+                for (int y0 = 0; y0 < N; y0 += 64 * U) {
+                    int cost[U];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) cost[u] = mat(nx, min(y0 + 64 * u + lane, N - 1));
+                    for (int u = 0; u < U; ++u) cost[u] = mat(nx, min(y0 + 64 * u + lane, N - 1));
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < U; ++u) {
                         const int y = y0 + 64 * u + lane;
-                        pass(y < N ? sides_of(jx, info[min(y, N - 1)], 2 * cost[u]) : 0, nx, M + y);
+                        look(y < N, jx, info[min(y, N - 1)], ((unsigned)cost[u] << 10) | (unsigned)y, nx, M + y);
                     }
                     flush();
                 }
             }
+        };
+        if constexpr (GROUP) {
+            // ---- an equal share of all nodes' candidates for every wave, 64 at a time
+            bool all;
+            next_stamp();
+            const int total = lay_out(64 * wv + lane, scale0, 0, stamp * 64 + (unsigned)lane, all);
+            if (lane == 0) group->laid_out[wv] = total;
+            __syncthreads();
+            const int laid_out = lane < WAVES ? group->laid_out[lane] : 0;
+            const int upto = wave_prefix_sum((laid_out + 63) >> 6);          // of the waves up to this lane's
+            const int blocks = __builtin_amdgcn_readlane(upto, 63);
+            auto brackets = [&](auto u_const, int g0) {
+                constexpr int U = decltype(u_const)::value;
+                unsigned src[U];
+                int from[U], place[U], first[U], live[U];
+                uint2 jx[U], jy[U];
+                uint32_t e[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int g = g0 + WAVES * u, w = __popcll(__ballot(upto <= g));         // whose candidates these are
+                    const int i0 = 64 * (g - (w ? __builtin_amdgcn_readlane(upto, w - 1) : 0));
+                    first[u] = 64 * w;
+                    live[u] = __builtin_amdgcn_readlane(laid_out, w) - i0;
+                    place[u] = i0 + lane;
+                    src[u] = ((const uint16_t*)(wave_mem + (w - wv) * (int)group_wave_bytes(ROOM)))[place[u]];
+                }
+                // marks of earlier layouts are smaller than this one's, and the first of the 64 is always marked
+#pragma unroll
+                for (int u = 0; u < U; ++u) src[u] = min((unsigned)first[u] + (wave_prefix_max(src[u]) & 63u), (unsigned)N - 1);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    from[u] = starts[src[u]];
+                    jx[u] = info[src[u]];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) e[u] = list_entry(lane < live[u] ? __umul24(src[u], (unsigned)M) + (unsigned)(place[u] - from[u]) : 0u);
+#pragma unroll
+                for (int u = 0; u < U; ++u) jy[u] = info[e[u] & 1023u];
+#pragma unroll
+                for (int u = 0; u < U; ++u) look(lane < live[u], jx[u], jy[u], e[u], (int)src[u], 0);
+            };
+            // one after the other in turn: the candidates of a node that most is scored of lie side by side
+            for (int g = wv; g < blocks; g += kGroupAtOnce * WAVES) {
+                if (blocks - g > 2 * WAVES) brackets(std::integral_constant<int, 3>{}, g);
+                else if (blocks - g > WAVES) brackets(std::integral_constant<int, 2>{}, g);
+                else brackets(std::integral_constant<int, 1>{}, g);
+                flush();
+            }
+            scan_all(all, 64 * wv);
+        } else {
+#pragma unroll 1
+            for (int k = 0; k < K; ++k) {
+                const int x_first = 64 * (wv * K + k);
+                bool all;
+                next_stamp();
+                const int total = lay_out(x_first + lane, K == 1 ? scale0 : (int)scales[min(x_first + lane, N - 1)], 0,
+                                          stamp * 64 + (unsigned)lane, all);
+                const int start = last_start;
+                __builtin_amdgcn_wave_barrier();
+                // ---- brackets, U times 64 candidates with their LDS and list reads in flight together
+                auto brackets = [&](auto u_const, int i0) {
+                    constexpr int U = decltype(u_const)::value;
+                    unsigned src[U];
+                    int from[U];
+                    uint2 jx[U], jy[U];
+                    uint32_t e[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) src[u] = owner[i0 + 64 * u + lane];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) src[u] = wave_prefix_max(src[u]) & 63u;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        from[u] = __builtin_amdgcn_ds_bpermute((int)(src[u] << 2), start);
+                        jx[u] = info[min(x_first + (int)src[u], N - 1)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = i0 + 64 * u + lane;
+                        e[u] = list_entry(i < total ? __umul24((unsigned)x_first + src[u], (unsigned)M) + (unsigned)(i - from[u]) : 0u);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) jy[u] = info[e[u] & 1023u];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = i0 + 64 * u + lane;
+                        look(i < total, jx[u], jy[u], e[u], x_first + (int)src[u], i - from[u]);
+                    }
+                };
+                for (int i0 = 0; i0 < total; i0 += 256) {
+                    if (total - i0 > 128) brackets(std::integral_constant<int, 4>{}, i0);
+                    else if (total - i0 > 64) brackets(std::integral_constant<int, 2>{}, i0);
+                    else brackets(std::integral_constant<int, 1>{}, i0);
+                    flush();
+                }
+                scan_all(all, x_first);
+            }
         }
         __builtin_amdgcn_wave_barrier();
         if (n_passed) score(0, n_passed);
-        group_min();
+        group_best();
         if (hi >= 0) break;
         // ---- reverse ranks mi .. mj: the nodes inside swap the hops in and out, two hops are new
         const int mi = lo / N, mj = lo - mi * N;
         const int n_before = t[mi - 1], n_first = t[mi], n_last = t[mj], n_after = t[mj + 1];
-        const int h_first = mat(n_before, n_last), h_after = mat(n_first, n_after);
+        const int h_first = GROUP ? first_hop : mat(n_before, n_last), h_after = GROUP ? after_hop : mat(n_first, n_after);
         int node[K];
         uint2 w[K];
 #pragma unroll
@@ -344,11 +464,12 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
     }
     // ---- results
     sum = wave_sum(sum);
-    if (WAVES > 1) {
-        if (lane == 0) red[parity][wv] = (unsigned long long)(unsigned)sum;
+    if (GROUP) {
+        __syncthreads();
+        if (lane == 0) group->word[wv] = sum;
         __syncthreads();
         sum = 0;
-        for (int i = 0; i < WAVES; ++i) sum += (int)red[parity][i];
+        for (int i = 0; i < WAVES; ++i) sum += group->word[i];
     }
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -361,17 +482,18 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
 
 // N <= 64 K: a workgroup holds the lists in LDS (and the matrix as 16-bit entries when lds_matrix is set and its entries
 // allow) for `waves` restarts of one wavefront each, or (WAVES > 1) for one restart of WAVES wavefronts.
-template <int K, int WAVES>
+template <int E, int WAVES>
 __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* __restrict__ c, int N, int M, int lds_matrix,
                                                                  int waves, int restarts, int32_t* __restrict__ tours,
                                                                  int64_t* __restrict__ costs,
                                                                  int32_t* __restrict__ moves,
                                                                  const int32_t* __restrict__ skip_if_small) {
+    constexpr int K = WAVES > 1 ? 1 : E;                        // nodes per lane
     // when the exhaustive 16-bit kernel is launched beside this one, the matrix maximum decides which of them runs
     if (skip_if_small && skip_if_small[0] < (1 << 16)) return;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int largest[16];
-    __shared__ unsigned long long red[2][WAVES];
+    __shared__ GroupWords<WAVES> group;
     uint32_t* lists = (uint32_t*)smem;                         // [N][M]
     unsigned char* counts = smem + (size_t)N * M * 4;          // [N][kBuckets]
     uint16_t* scales = (uint16_t*)(counts + (size_t)N * kBuckets);     // [N]
@@ -385,7 +507,7 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
         int high = 0;
         for (int x = wv; x < N; x += nw) {
             int row_max;
-            const int scale = make_list<(WAVES > 1 ? WAVES : K)>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
+            const int scale = make_list<E>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets,
                                                              hist, lane, row_max, [&](int y, int cost) {
                                                                  if (lds_matrix) m16[x * N + y] = (uint16_t)cost;
                                                              });
@@ -403,13 +525,14 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
     if (r >= restarts) return;
     const int mine = WAVES > 1 ? 0 : wv, part = WAVES > 1 ? wv : 0;
     unsigned char* order_mem = rest + (size_t)mine * (order_bytes(N) + wave_bytes(kRoom));
-    unsigned char* wave_mem = order_mem + order_bytes(N) + (size_t)part * wave_bytes(kRoom);
+    unsigned char* wave_mem = WAVES > 1 ? order_mem + group_order_bytes(N) + (size_t)part * group_wave_bytes(kRoom)
+                                        : order_mem + order_bytes(N);
     const int scale0 = (int)scales[min(64 * part + lane, N - 1)];
     if (in_lds)
-        descend<WAVES, K, kRoom>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, red, part, lane,
+        descend<WAVES, K, kRoom>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
                           tours + r * N, costs + r, moves + r);
     else
-        descend<WAVES, K, kRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, red, part, lane,
+        descend<WAVES, K, kRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
                           tours + r * N, costs + r, moves + r);
 }
 
@@ -429,41 +552,49 @@ __global__ __launch_bounds__(256) void partner_lists_kernel(const int32_t* __res
     if (lane == 63) mine[kBuckets - 1] = (uint16_t)scale;      // the last bucket's count is N - 1: the scale has its place
 }
 
+// More than 80 scalar registers leave room for fewer wavefronts than the vector registers do (N = 1024, 512 restarts, two
+// workgroups per unit: 84 of them 22.0 ms, 78 17.2).
 template <int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void twoopt_sum_pruned_group_kernel(const int32_t* __restrict__ c, int N, int M,
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(80))) void twoopt_sum_pruned_group_kernel(const int32_t* __restrict__ c, int N, int M,
                                                                              const uint32_t* __restrict__ lists,
                                                                              const uint16_t* __restrict__ counts,
                                                                              int32_t* __restrict__ tours,
                                                                              int64_t* __restrict__ costs,
                                                                              int32_t* __restrict__ moves) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ unsigned long long red[2][WAVES];
+    __shared__ GroupWords<WAVES> group;
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
     const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
     descend<WAVES, 1, kGroupRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
-                                  smem + order_bytes(N) + wv * wave_bytes(kGroupRoom), red, wv, lane, tours + r * N, costs + r,
+                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom), &group, wv, lane, tours + r * N, costs + r,
                                   moves + r);
 }
 
-template <int K, int WAVES>
+template <int E, int WAVES>
 hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, int restarts, int32_t* tours, int64_t* costs,
                       int32_t* moves, const int32_t* skip_if_small, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<K, WAVES>,
+    hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<E, WAVES>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.bytes);
     if (e != hipSuccess) return e;
     const int grid = WAVES > 1 ? restarts : (restarts + plan.waves - 1) / plan.waves;
-    hipLaunchKernelGGL((twoopt_sum_pruned_kernel<K, WAVES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
+    hipLaunchKernelGGL((twoopt_sum_pruned_kernel<E, WAVES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
                        s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves, skip_if_small);
     return hipGetLastError();
 }
 
-template <int K>
+template <int E>
 hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                         const int32_t* skip_if_small, hipStream_t s) {
-    const LdsPlan plan = lds_plan(N, K, restarts, order_bytes(N));
-    return plan.together ? launch_lds<1, K>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s)
-                         : launch_lds<K, 1>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    // A wave's own instructions bound a sweep, so more of them than the 64 nodes each would need are the faster as long as the unit has
+    // room (4 / 8 / 12 / 16 waves: N = 150, 200 restarts 612 / 579 / 610 / 650 us; N = 256, 200 restarts 1526 / 1335 / 1319 / 1550; two
+    // restarts per unit: N = 150, 500 restarts 696 / 723 / 876 / 1230).
+    constexpr int kOne = 8, kTwo = 4;
+    const int group = restarts <= 256 ? kOne : kTwo;
+    const LdsPlan plan = lds_plan(N, E, restarts, order_bytes(N), group, group_order_bytes(N) + group * group_wave_bytes(kRoom));
+    if (!plan.together) return launch_lds<E, 1>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    return group == kOne ? launch_lds<E, kOne>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s)
+                         : launch_lds<E, kTwo>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
 }
 
 template <int WAVES>
@@ -474,7 +605,7 @@ hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32
     const uint16_t* counts;
     hipError_t e = launch_partner_lists(c, N, room, M, lists, counts, s);
     if (e != hipSuccess) return e;
-    const size_t lds = order_bytes(N) + WAVES * wave_bytes(kGroupRoom);
+    const size_t lds = group_order_bytes(N) + WAVES * group_wave_bytes(kGroupRoom);
     e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -499,6 +630,14 @@ hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int resta
     if (N <= 128) return launch_waves<2>(c, N, restarts, tours, costs, moves, skip_if_small, s);
     if (N <= 192) return launch_waves<3>(c, N, restarts, tours, costs, moves, skip_if_small, s);
     if (N <= 256) return launch_waves<4>(c, N, restarts, tours, costs, moves, skip_if_small, s);
+    // at least a wave per 64 nodes; more where the compute units have room for them (a wave per 64 nodes / 8 / 12 / 16 waves: N = 300, 250
+    // restarts 1782 / 1590 / 1534 / 1620 us, 500 restarts 1982 / 1867 / 2022 / 2300, 1000 restarts 2523 / 3219 / 3786; N = 512, 250
+    // restarts 3621 / - / 3340 / 3330, 500 restarts 4431 / - / 4605 / 4900)
+    if (restarts <= 256) {
+        if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, s);
+    } else if (restarts <= 512) {
+        if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, s);
+    }
     if (N <= 320) return launch_group<5>(c, N, room, restarts, tours, costs, moves, s);
     if (N <= 384) return launch_group<6>(c, N, room, restarts, tours, costs, moves, s);
     if (N <= 448) return launch_group<7>(c, N, room, restarts, tours, costs, moves, s);

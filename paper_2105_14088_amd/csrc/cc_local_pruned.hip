@@ -536,7 +536,7 @@ hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, const TieHan
 template <int K, bool WITH_2OPT>
 hipError_t launch_waves(const int32_t* c, int N, const TieHandover& ties, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                         hipStream_t s) {
-    const LdsPlan plan = lds_plan(N, K, restarts, local_order_bytes(N));
+    const LdsPlan plan = lds_plan(N, K, restarts, local_order_bytes(N), K, local_order_bytes(N) + K * wave_bytes(kRoom));
     if constexpr (K > 1)
         if (plan.together) return launch_lds<1, K, WITH_2OPT>(c, N, plan, ties, restarts, tours, costs, moves, s);
     return launch_lds<K, 1, WITH_2OPT>(c, N, plan, ties, restarts, tours, costs, moves, s);

@@ -53,7 +53,9 @@ __device__ __forceinline__ int lanes_below(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
 }
 __device__ __forceinline__ int entry(const int32_t* __restrict__ c, int N, int x, int y) {
-    return clampi(c[min(x, y) * N + max(x, y)], 0, kCostMax);
+    // 24-bit products and 32-bit offsets: a full-rate multiply, one address register
+    const unsigned at = __umul24((unsigned)min(x, y), (unsigned)N) + (unsigned)max(x, y);
+    return clampi(*(const int32_t*)((const char*)c + at * 4u), 0, kCostMax);
 }
 // Where a descent looks entries up: the caller's matrix, or both triangles as 16-bit entries in LDS.
 struct CallersMatrix {
@@ -64,7 +66,7 @@ struct CallersMatrix {
 struct LdsMatrix {
     const uint16_t* m;
     int N;
-    __device__ __forceinline__ int operator()(int x, int y) const { return m[x * N + y]; }
+    __device__ __forceinline__ int operator()(int x, int y) const { return m[__umul24((unsigned)x, (unsigned)N) + (unsigned)y]; }
 };
 
 // Makes the list of node x with one wavefront: list[0 .. M): cost << 10 | node, counts[b]: partners up to bucket b (the
@@ -129,7 +131,8 @@ struct LdsPlan {
 // restart, up to 16 around one copy of the lists, but no more than keeps all 256 compute units busy (four workgroups of
 // K wavefronts per unit were slower: their lists are short and made four times).
 // Lists of less than 32 partners would send too many nodes to the scan against every node; beyond 96 they add nothing.
-inline LdsPlan lds_plan(int N, int K, int restarts, size_t order_bytes) {
+// group_waves: wavefronts that share a restart, with group_state bytes of LDS.
+inline LdsPlan lds_plan(int N, int K, int restarts, size_t order_bytes, int group_waves, size_t group_state) {
     constexpr size_t kLds = 160 * 1024 - 1024;
     LdsPlan p;
     const int per_unit = (restarts + 255) / 256;
@@ -146,9 +149,9 @@ inline LdsPlan lds_plan(int N, int K, int restarts, size_t order_bytes) {
         p.bytes = p.bytes < makers ? makers : p.bytes;
     };
     if (K > 1 && per_unit <= 2) {
-        const size_t state = order_bytes + K * wave_bytes(kRoom), room = kLds / per_unit - 512 > state ? kLds / per_unit - 512 - state : 0;
+        const size_t state = group_state, room = kLds / per_unit - 1024 > state ? kLds / per_unit - 1024 - state : 0;
         p.together = true;
-        p.waves = K;
+        p.waves = group_waves;
         for (p.lds_matrix = 1; p.lds_matrix >= 0; --p.lds_matrix) {
             p.M = longest(room, p.lds_matrix);
             if (p.M >= (p.lds_matrix ? 64 : 32) || p.M >= N - 1) {

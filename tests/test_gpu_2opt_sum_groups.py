@@ -1,0 +1,28 @@
+"""GPU parity of the pruned ring-sum descents with more wavefronts per restart than their nodes ask for: every number of wavefronts
+per restart the launches choose, entries on both sides of 2^16, ties, costs of two values."""
+import numpy as np
+import pytest
+
+import oracle
+from gen import hierarchical_matrix, random_matrix
+from gpu_util import gpu_search, say
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
+
+
+@pytest.mark.parametrize("n,restarts", [(129, 3), (129, 300), (192, 256), (192, 257), (193, 3), (256, 256), (257, 3), (257, 257), (257, 513),
+                                        (448, 257), (512, 513), (513, 257), (768, 2), (769, 2)])
+def test_every_number_of_wavefronts(n, restarts):
+    zones = np.where(np.random.default_rng(n).integers(0, 2, n)[:, None] == np.random.default_rng(n).integers(0, 2, n)[None, :], 100, 1000)
+    np.fill_diagonal(zones, 0)
+    for c, tag in ((hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n), "racks"),
+                   (random_matrix(n, n, symmetric=True, lo=0, hi=4), "ties"), (zones.astype(np.int32), "two zones"),
+                   (random_matrix(n, n, symmetric=True, lo=1, hi=1 << 20), "beyond 2^16")):
+        say(f"pruned ring sum groups N={n} R={restarts} {tag}")
+        got = gpu_search(c, oracle.SUM, restarts, 21)
+        k = int(np.argmin(got["costs"]))
+        assert got["best_restart"] == k and got["best_cost"] == got["costs"][k]
+        for r in {0, restarts // 2, restarts - 1}:
+            costs, tours, moves = oracle.restarts(c, oracle.SUM, 21, r, r + 1)
+            assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0]
+            assert np.array_equal(got["tours"][r], tours[0])
