@@ -590,10 +590,10 @@ hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, i
     // room (4 / 8 / 12 / 16 waves: N = 150, 200 restarts 612 / 579 / 610 / 650 us; N = 256, 200 restarts 1526 / 1335 / 1319 / 1550; two
     // restarts per unit: N = 150, 500 restarts 696 / 723 / 876 / 1230).
     constexpr int kOne = 8, kTwo = 4;
-    const int group = restarts <= 256 ? kOne : kTwo;
-    const LdsPlan plan = lds_plan(N, E, restarts, order_bytes(N), group, group_order_bytes(N) + group * group_wave_bytes(kRoom));
+    auto state = [&](int waves) { return group_order_bytes(N) + waves * group_wave_bytes(kRoom); };
+    const LdsPlan plan = lds_plan(N, restarts, order_bytes(N), Groups{2, false, {kOne, kTwo}, {state(kOne), state(kTwo)}});
     if (!plan.together) return launch_lds<E, 1>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
-    return group == kOne ? launch_lds<E, kOne>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s)
+    return plan.waves == kOne ? launch_lds<E, kOne>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s)
                          : launch_lds<E, kTwo>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
 }
 

@@ -174,17 +174,21 @@ hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int 
     if (force_general_path()) {
         // pinned: the kernel below for every size
     } else if (N >= 9 && N != 64 &&
-               (!multi || (restarts <= 256 && (with_2opt || N > 128)) || (restarts <= 512 && with_2opt && N < 256))) {
-        // only the moves that can win: against the kernel above 1.1 (N = 10) to 3 times (N = 63) to 40 times (N = 1000) as
-        // fast; against the exhaustive wavefront kernels at 128 / 192 / 256 as long as every restart has N / 64 wavefronts to
-        // itself (1.2 to 3 times; beyond that 0.4 to 1).  From N = 65 on the matrix has a say: with many partners at a row's
-        // smallest cost most pairs pass their brackets, and the other kernel is the faster.  Where the lines lie: zones of equal
-        // costs, 1 inside and 10 across, 2-opt and insertion, this kernel against the other one: N = 192, 256 restarts, 2 / 8 / 16
-        // zones 5.2 against 1.2 ms, 2.3 / 1.7, 1.8 / 2.1; N = 128, 64 restarts, 16 zones equal; N = 150, 512 restarts, 2 / 3
-        // zones 6.1 against 4.0 ms, 3.9 / 4.3; insertion alone, 3 / 4 zones 3.6 against 2.6, 3.1 / 3.0.
+               (!multi || restarts <= 256 || (restarts <= 512 && (with_2opt || N < 256)))) {
+        // only the moves that can win: against the kernel above 1.1 (N = 10) to 3 times (N = 63) to 50 times (N = 1000) as
+        // fast; against the exhaustive wavefront kernels at 128 / 192 / 256 as long as every restart has several wavefronts to
+        // itself (N = 128, 512 restarts 1.6 -> 0.9 ms, insertion alone 1.6 -> 1.26; N = 256, 512 restarts 9.7 -> 4.0; insertion
+        // alone 9.0 and 8.8, and with 16 zones of equal costs 4.4 and 5.3).  From N = 65 on the matrix has a say: with many partners
+        // at a row's smallest cost most pairs pass their brackets, and the other kernel can be the faster.  Where the lines lie, in
+        // zones of equal costs, 100 inside and 1000 across, this kernel against the other one.  2-opt and insertion, up to 512
+        // restarts: always this one, two zones, N = 100, 512 restarts 0.74 against 1.54 ms, N = 240 9.1 / 10.5, N = 400 40.1 / 40.8; above
+        // as before, N = 240, 1024 restarts 16.9 / 16.2.  Insertion alone, up to 512 restarts: three zones N = 100 0.52 / 1.18 ms, N = 240
+        // 6.8 / 6.6, two zones N = 200 5.7 / 4.2.  N = 128, 192, 256: up to 256 restarts 8 zones 0.59 / 0.71, 1.33 / 1.72, 2.97 / 3.88 ms,
+        // 4 zones 0.79 / 0.60, 1.64 / 1.41, 3.30 / 3.31; 512 restarts, 12 zones 0.66 / 0.83, 2.02 / 1.9, 5.24 / 4.52.
         const int all = N * (N - 1);
-        const int most = N == 128 ? all / 24 : multi ? all / 12 : with_2opt ? all / 5 * 2 : all / 10 * 3;
-        const TieHandover ties{N > 64 ? flags : nullptr, most, multi};
+        const int most = multi ? all / (restarts <= 256 ? 7 : N == 128 ? 9 : 12)
+                         : with_2opt ? (restarts <= 512 ? all : all / 5 * 2) : restarts <= 512 ? all / 5 * 2 : all / 10 * 3;
+        const TieHandover ties{N > 64 && most < all ? flags : nullptr, most, multi};
         hipError_t e = launch_local_pruned(c, N, with_2opt, room, ties, restarts, tours, costs, moves, s);
         if (e != hipSuccess || !ties.flags) return e;
         if (multi) return launch_local_multi(c, N, with_2opt, restarts, tours, costs, moves, flags, s);

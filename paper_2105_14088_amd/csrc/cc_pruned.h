@@ -59,14 +59,38 @@ __device__ __forceinline__ int entry(const int32_t* __restrict__ c, int N, int x
 }
 // Where a descent looks entries up: the caller's matrix, or both triangles as 16-bit entries in LDS.
 struct CallersMatrix {
+    static constexpr bool kScattered = true;                    // a cache line per lane that reads
     const int32_t* c;
     int N;
     __device__ __forceinline__ int operator()(int x, int y) const { return entry(c, N, x, y); }
+    __device__ __forceinline__ int row(int x) const { return x; }
+    // for several look-ups at once: what is read, and then the cost
+    __device__ __forceinline__ int raw(bool ok, int row, int y) const {
+        const unsigned at = __umul24((unsigned)min(row, y), (unsigned)N) + (unsigned)max(row, y);
+        return *(const int32_t*)((const char*)c + (ok ? at : 0u) * 4u);
+    }
+    __device__ __forceinline__ int cost(int raw) const { return clampi(raw, 0, kCostMax); }
 };
 struct LdsMatrix {
+    static constexpr bool kScattered = false;
     const uint16_t* m;
     int N;
     __device__ __forceinline__ int operator()(int x, int y) const { return m[__umul24((unsigned)x, (unsigned)N) + (unsigned)y]; }
+    __device__ __forceinline__ const uint16_t* row(int x) const { return m + __umul24((unsigned)x, (unsigned)N); }
+    __device__ __forceinline__ int raw(bool, const uint16_t* row, int y) const { return row[(unsigned)y]; }
+    __device__ __forceinline__ int cost(int raw) const { return raw; }
+};
+// the lower triangle with the diagonal, row by row: row x begins at (x x + x) / 2
+struct LdsTriangle {
+    static constexpr bool kScattered = false;
+    const uint16_t* m;
+    __device__ __forceinline__ int operator()(int x, int y) const {
+        const unsigned high = (unsigned)max(x, y), low = (unsigned)min(x, y);
+        return *(const uint16_t*)((const char*)m + (__umul24(high, high) + high) + 2u * low);
+    }
+    __device__ __forceinline__ int row(int x) const { return x; }
+    __device__ __forceinline__ int raw(bool, int row, int y) const { return (*this)(row, y); }
+    __device__ __forceinline__ int cost(int raw) const { return raw; }
 };
 
 // Makes the list of node x with one wavefront: list[0 .. M): cost << 10 | node, counts[b]: partners up to bucket b (the
@@ -115,24 +139,30 @@ __device__ __forceinline__ int make_list(const int32_t* __restrict__ c, int N, i
 
 // LDS the restarts of a workgroup share (N <= 256): lists, counts, scales, matrix
 __host__ __device__ constexpr size_t shared_bytes(int N, int M, int lds_matrix) {
-    return ((size_t)N * (M * 4 + kBuckets + 2 + (lds_matrix ? 2 * N : 0)) + 15) & ~(size_t)15;
+    return ((size_t)N * (M * 4 + kBuckets + 2 + (lds_matrix ? lds_matrix > 1 ? N + 1 : 2 * N : 0)) + 15) & ~(size_t)15;
 }
 __host__ __device__ constexpr size_t wave_bytes(int room) { return (size_t)room * 2 + kPassed * 4; }
 
-// How the restarts of a search with N <= 64 K share the chip.
+// How the restarts of a search with N <= 256 share the chip.
 struct LdsPlan {
     int waves;              // wavefronts with work per workgroup
     bool together;          // they share one restart
-    int M, lds_matrix;      // list length, matrix in LDS
+    int M, lds_matrix;      // list length; matrix in LDS, 2: one triangle of it
     size_t bytes;           // LDS per workgroup
 };
-// order_bytes: LDS of one restart's order.  Up to 512 restarts, K wavefronts per restart, one or two workgroups per
-// compute unit (a sweep then takes a third to a half of the time that one wavefront needs); beyond that one wavefront per
-// restart, up to 16 around one copy of the lists, but no more than keeps all 256 compute units busy (four workgroups of
-// K wavefronts per unit were slower: their lists are short and made four times).
+// Wavefronts that share a restart.
+struct Groups {
+    int most_per_unit;      // restarts per compute unit up to which they do, 0: never
+    bool triangle;          // the kernel can read one
+    int waves[2];           // with one and with two workgroups per unit at a time
+    size_t state[2];        // bytes of LDS they need then
+};
+// order_bytes: LDS of one restart's order.  Few restarts: a group of wavefronts each, one or two workgroups per compute unit at a
+// time (a sweep then takes a fifth to a half of the time that one wavefront needs; four workgroups per unit at a time were slower:
+// their lists are short and made four times).  Many: one wavefront per restart, up to 16 around one copy of the lists, but no more
+// than keeps all 256 compute units busy.
 // Lists of less than 32 partners would send too many nodes to the scan against every node; beyond 96 they add nothing.
-// group_waves: wavefronts that share a restart, with group_state bytes of LDS.
-inline LdsPlan lds_plan(int N, int K, int restarts, size_t order_bytes, int group_waves, size_t group_state) {
+inline LdsPlan lds_plan(int N, int restarts, size_t order_bytes, const Groups& groups) {
     constexpr size_t kLds = 160 * 1024 - 1024;
     LdsPlan p;
     const int per_unit = (restarts + 255) / 256;
@@ -148,18 +178,21 @@ inline LdsPlan lds_plan(int N, int K, int restarts, size_t order_bytes, int grou
         const size_t makers = shared_bytes(N, p.M, p.lds_matrix) + (size_t)(p.waves > 8 ? p.waves : 8) * kBuckets * 4;
         p.bytes = p.bytes < makers ? makers : p.bytes;
     };
-    if (K > 1 && per_unit <= 2) {
-        const size_t state = group_state, room = kLds / per_unit - 1024 > state ? kLds / per_unit - 1024 - state : 0;
-        p.together = true;
-        p.waves = group_waves;
-        for (p.lds_matrix = 1; p.lds_matrix >= 0; --p.lds_matrix) {
-            p.M = longest(room, p.lds_matrix);
-            if (p.M >= (p.lds_matrix ? 64 : 32) || p.M >= N - 1) {
-                finish(state);
-                return p;
+    if (per_unit <= groups.most_per_unit)
+        for (int at_a_time = per_unit > 1 ? 2 : 1; at_a_time >= 1; --at_a_time) {
+            const size_t state = groups.state[at_a_time - 1], all = kLds / at_a_time - 1024, room = all > state ? all - state : 0;
+            p.together = true;
+            p.waves = groups.waves[at_a_time - 1];
+            const int forms[3] = {1, groups.triangle ? 2 : 0, 0};
+            for (int form : forms) {
+                p.lds_matrix = form;
+                p.M = longest(room, form);
+                if (p.M >= (form == 1 ? 64 : 32) || p.M >= N - 1) {
+                    finish(state);
+                    return p;
+                }
             }
         }
-    }
     p.together = false;
     p.M = N <= 128 ? 64 : 48;
     p.waves = per_unit < 16 ? per_unit : 16;

@@ -1,0 +1,32 @@
+"""GPU parity of the pruned insertion descents: every number of wavefronts per restart that the launches choose, on both sides of the
+sizes and restart counts where it changes; the matrix in LDS, as a triangle and in memory; ties, zones of equal costs (more
+candidates than one round scores), entries beyond 2^16."""
+import numpy as np
+import pytest
+
+from gen import hierarchical_matrix, random_matrix
+from gpu_util import say
+from test_gpu_local_pruned import BOTH, INSERTION, check
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
+
+
+def zones(n, k):
+    z = np.random.default_rng(n + k).integers(0, k, n)
+    c = np.where(z[:, None] == z[None, :], 100, 1000)
+    np.fill_diagonal(c, 0)
+    return c.astype(np.int32)
+
+
+@pytest.mark.parametrize("n,restarts", [(32, 40), (33, 40), (48, 512), (48, 513), (65, 3), (65, 257), (100, 1024), (100, 1025), (128, 256), (128, 512),
+                                        (129, 3), (150, 257), (161, 300), (192, 300), (193, 3), (255, 300), (256, 3), (256, 300),
+                                        (257, 3), (257, 257), (512, 257), (513, 2), (513, 257), (1000, 1)])
+def test_every_number_of_wavefronts(n, restarts):
+    for c, tag in ((hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n), "racks"),
+                   (random_matrix(n, n, symmetric=True, lo=0, hi=4), "ties"), (zones(n, 2), "two zones"), (zones(n, 9), "nine zones"),
+                   (random_matrix(n, n, symmetric=True, lo=1, hi=1 << 20), "beyond 2^16")):
+        if n > 512 and tag != "racks":
+            continue
+        for classes in (BOTH, INSERTION) if n < 512 else (BOTH,):
+            say(f"pruned insertion groups N={n} R={restarts} {tag} classes={classes}")
+            check(c, classes, restarts, 21, sorted({0, restarts - 1}))
