@@ -163,11 +163,13 @@ __global__ __launch_bounds__(256) void fold_to_u16_kernel(const int32_t* __restr
 // The result (value, lowest id) is that of the exhaustive sweep.  Link values live in LDS from sweep to sweep: a swap
 // changes 2 log2 N of them, and a round's three largest are found anew only if one of them changed or was passed.
 //
-// What bounds a sweep is latency (LDS round trips, wave reductions, four or five barriers: about 9000 clocks at N = 256,
-// of which the three largest links take 950, the scans 2450 and the pairs 3450), no longer the gathers of N (N-1) / 2
-// pairs.  Against the exhaustive sweeps before it, matrices of the benchmark's hierarchy: N = 1024, 32 restarts
-// 394 -> 5.4 ms; N = 512, 136 restarts 95.7 -> 4.2 ms; N = 256, 58 restarts 9.4 -> 1.28 ms, 788 restarts
-// 31.7 -> 3.95 ms; N = 128, 600 restarts 4.6 -> 1.0 ms; N = 32, 300 restarts 2.4 -> 0.19 ms; N = 64 the same time.
+// What bounds a sweep is latency: LDS round trips, wave reductions, two barriers.  N = 256, 9000 clocks: the three largest links 900,
+// which ends to scan 1300, the scans 1900 each, 1.6 a sweep, the pairs 2950 beside the first of them, the swap 650; every wave renews
+// the links of the rounds whose largest it keeps, and the order has a second copy for the swap, so that no barrier stands between.
+// (11200 with the pairs behind the scans, one wave for the swap and five barriers: 256 restarts 1.27 ms, now 1.01.)  Against the
+// exhaustive sweeps before it, matrices of the benchmark's hierarchy: N = 1024, 32 restarts 394 -> 3.3 ms; N = 512, 136 restarts
+// 95.7 -> 3.1 ms; N = 256, 58 restarts 9.4 -> 0.98 ms, 788 restarts 31.7 -> 3.0 ms; N = 128, 600 restarts 4.6 -> 0.75 ms; N = 32, 300
+// restarts 2.4 -> 0.09 ms.
 //
 // Where entries come from: N <= 128 folded int32 in LDS (64 KiB at 128), N = 256 folded 16-bit in LDS (128 KiB), else
 // the folded 16-bit copy of the workspace through L2, where a scan of p reads only log2 N + 1 rows: the mates' rows in
@@ -200,43 +202,58 @@ struct GlobalWords {                    // the caller's matrix, folded as it is 
     static constexpr bool kRows = true;
 };
 
-// LDS words of a workgroup besides the matrix: order, link values, inverse order and rows of two scanned ranks
+// LDS words of a workgroup besides the matrix: order, link values, inverse order (the two orders twice) and rows of two scanned
+// ranks
 constexpr size_t swap_state_words(int log_n, bool rows) {
     const size_t n = (size_t)1 << log_n;
-    return n + (size_t)log_n * (n / 2) + (rows ? 3 * n : 0);
+    return 2 * n + (size_t)log_n * (n / 2) + (rows ? 4 * n : 0);
+}
+
+// Read before any of them is used: left alone, each is waited for before the next is asked for.
+template <int K>
+__device__ __forceinline__ void in_flight(int (&x)[K], int (&y)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) asm volatile("" : "+v"(x[k]), "+v"(y[k]));
 }
 
 // A link is named by its upper rank (bit k set), a value other than 0; link keys are value << 10 | name, 0 = no link.
-template <int LOGN, int THREADS, class MAT>
+// SCAN threads scan, PAIRS more look at the pairs meanwhile (0: the same, afterwards); every wave keeps some rounds' links.
+template <int LOGN, int SCAN, int PAIRS, class MAT>
 __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, int32_t* __restrict__ tour,
                                                int64_t* __restrict__ cost_out, int32_t* __restrict__ moves_out) {
-    constexpr int N = 1 << LOGN, HALF = N / 2, NW = THREADS / 64, M = (HALF + 63) / 64;
+    constexpr int THREADS = SCAN + PAIRS, N = 1 << LOGN, HALF = N / 2, NW = THREADS / 64, SW = SCAN / 64, M = (HALF + 63) / 64;
     constexpr int kEnds = 2 * LOGN, kNone = 0x7fffffff;
     constexpr int kPicks = 2;                          // ends scanned at a time; the waves share them
-    constexpr int kScanThreads = NW > 1 ? THREADS / 2 : 64;
+    constexpr int kScanThreads = SW > 1 ? SCAN / 2 : 64;
+    constexpr int kPairThreads = PAIRS ? PAIRS : THREADS, kPairs = 4 * LOGN + kEnds * (kEnds / 2);
+    constexpr int kPairLanes = 2 * kPairs <= kPairThreads ? 2 : 1;     // that share a pair's rounds
+    static_assert((SW > 1) == (NW > 1), "one wavefront for everything, or a scanned end for half of them");
     __shared__ int top[3][LOGN];                       // keys of every round's three largest links
     __shared__ int4 gaps[LOGN];                        // {name 1, value 1 - value 2, name 2, value 2 - value 3}
-    __shared__ int4 scan_a[NW][kPicks][LOGN];          // for a scanned end: {largest other link's name, its value, the next value, mate's node}
-    __shared__ int scan_b[NW][kPicks][LOGN];           // value 1
-    __shared__ unsigned dirty_rounds;
+    __shared__ int4 scan_a[SW][kPicks][LOGN];          // for a scanned end: {largest other link's name, its value, the next value, mate's node}
+    __shared__ int scan_b[SW][kPicks][LOGN];           // value 1
     __shared__ unsigned long long red[3];
-    int32_t* t = state;                                // [N]
-    int32_t* links = t + N;                            // [LOGN][HALF] keys
-    int32_t* pos = links + LOGN * HALF;                // [N] (kRows) rank of a node, -1: none
-    int32_t* rows = pos + N;                           // [kPicks][N] (kRows)
+    // the order, and what it becomes while every wave still reads the nodes that move; it is a swap behind
+    int32_t *t = state, *t_next = t + N;               // [N]
+    int32_t* links = t_next + N;                       // [LOGN][HALF] keys
+    int32_t *pos = links + LOGN * HALF, *pos_next = pos + N;           // [N] (kRows) rank of a node, -1: none
+    int32_t* rows = pos_next + N;                      // [kPicks][N] (kRows)
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto sync = [] { if (NW > 1) __syncthreads(); else __builtin_amdgcn_wave_barrier(); };
     auto upper_of = [](int link, int k) { return ((link >> k) << (k + 1)) | (1 << k) | (link & ((1 << k) - 1)); };
     auto link_of = [](int p, int k) { return ((p >> (k + 1)) << k) | (p & ((1 << k) - 1)); };
 
     for (int p = tid; p < N; p += THREADS) {
-        t[p] = clampi(tour[p], 0, N - 1);
+        t[p] = t_next[p] = clampi(tour[p], 0, N - 1);
         if (MAT::kRows) pos[p] = -1;
     }
     if (tid < 3) red[tid] = ~0ull;
     __syncthreads();
-    if (MAT::kRows)
+    if (MAT::kRows) {
         for (int p = tid; p < N; p += THREADS) pos[t[p]] = p;
+        __syncthreads();
+        for (int p = tid; p < N; p += THREADS) pos_next[p] = pos[p];
+    }
 #pragma unroll
     for (int k = 0; k < LOGN; ++k)
         for (int l = tid; l < HALF; l += THREADS) {
@@ -267,8 +284,8 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
 
     constexpr int kPerWave = (LOGN + NW - 1) / NW;     // rounds whose largest links a wave keeps up to date
     constexpr int kBatch = kPerWave < 3 ? kPerWave : 3;
-    unsigned dirty = (1u << LOGN) - 1u;
-    int applied = 0, cur = -1;
+    unsigned dirty = (1u << LOGN) - 1u;                // of this wave's rounds
+    int applied = 0, cur = -1, last_p = 0, last_q = 0, last_a = t[0], last_b = t[0];
     for (;;) {
         // ---- the three largest links of the rounds that may have new ones
 #pragma unroll 1
@@ -328,9 +345,10 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
         // ---- scans: two ends at a time, in falling order of G, against every rank
         bool seen = lane >= kEnds;
         int best_hi = cur, best_id = 0;                // a winner has a total below cur
-        for (;;) {
-            int pick[kPicks];
+        for (bool first = true;; first = false) {
+            int pick[kPicks] = {};
             int n = 0;
+            if (__ballot(!seen && gain > 0 && cur - gain <= best_hi))
 #pragma unroll
             for (int s = 0; s < kPicks; ++s) {
                 const int g = wave_max(seen ? 0 : (gain << 6) | lane);
@@ -341,16 +359,17 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
                     n = s + 1;
                 }
             }
-            if (n == 0) break;
-            if (MAT::kRows) {
+            const unsigned long long left = first ? __ballot(!seen) : 0;
+            if (n == 0 && !left) break;
+            if (MAT::kRows && n) {
                 for (int i = tid; i < n * N; i += THREADS) rows[i] = mat.at(t[i < N ? pick[0] : pick[1]], i & (N - 1));
                 sync();
             }
             int hi = best_hi, id = best_id;
 #pragma unroll
             for (int s0 = 0; s0 < (NW > 1 ? 1 : kPicks); ++s0) {
-                const int s = NW > 1 ? wv / (NW / 2) : s0;
-                if (s >= n) break;
+                const int s = NW > 1 ? wv / (SW > 1 ? SW / 2 : 1) : s0;
+                if (s >= n) break;                     // also the pairs' waves
                 const int p = s ? pick[1] : pick[0];
                 const int tp = __builtin_amdgcn_readfirstlane(t[p]);
                 if (lane < LOGN) {
@@ -367,16 +386,19 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
                     const int q = MAT::kRows ? pos[i] : i;         // kRows: i is the node, so that rows are read in order
                     const int tq = MAT::kRows ? i : t[i];
                     if (q < 0) continue;
-                    int total = 0;
+                    int total = 0, x[LOGN], y[LOGN];
+#pragma unroll
+                    for (int k = 0; k < LOGN; ++k) {
+                        const int tm = t[q ^ (1 << k)];
+                        x[k] = mat.at(scan_a[wv][s0][k].w, tq);
+                        y[k] = MAT::kRows ? rows[s * N + tm] : mat.at(tp, tm);
+                    }
+                    if constexpr (LOGN == 10) in_flight(x, y);
 #pragma unroll
                     for (int k = 0; k < LOGN; ++k) {
                         const int4 w = scan_a[wv][s0][k];
-                        const int v = scan_b[wv][s0][k];
-                        const int tm = t[q ^ (1 << k)];
-                        const int x = mat.at(w.w, tq);
-                        const int y = MAT::kRows ? rows[s * N + tm] : mat.at(tp, tm);
-                        const int up = q | (1 << k);
-                        const int cost = max(up == w.x ? w.z : w.y, max(x, y));
+                        const int v = scan_b[wv][s0][k], up = q | (1 << k);
+                        const int cost = max(up == w.x ? w.z : w.y, max(x[k], y[k]));
                         total += up == (p | (1 << k)) ? v : cost;  // the mate: the link stays, and with it the round
                     }
                     const int move = min(p, q) * N + max(p, q);
@@ -386,82 +408,97 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
                 }
                 __builtin_amdgcn_wave_barrier();
             }
-            block_min(hi, id);
-            best_hi = hi;
-            best_id = id;
-        }
-        // ---- pairs that move two large links at once: an end of a round's largest and one of its second largest link, or
-        // two ends of largest links; pairs with a scanned end are known already
-        const unsigned long long left = __ballot(!seen);
-        if (left) {
-            int hi = best_hi, id = best_id;
-            constexpr int kSameRound = 4 * LOGN, kPairs = kSameRound + kEnds * (kEnds / 2);
+            // ---- pairs that move two large links at once: an end of a round's largest and one of its second largest link, or
+            // two ends of largest links; pairs with an end of the first scan are known already
+            if (left && (PAIRS == 0 || wv >= SW)) {
+                constexpr int kSameRound = 4 * LOGN, kAtOnce = kPairThreads / kPairLanes;
+                const int bound = PAIRS ? hi : wave_min(hi);
+                constexpr int kRounds = (LOGN + kPairLanes - 1) / kPairLanes;
 #pragma unroll 1
-            for (int i0 = 0; i0 < kPairs; i0 += THREADS) {
-                const int i = i0 + tid, u = max(i - kSameRound, 0);
-                int e1 = u % kEnds, e2 = e1 + 1 + u / kEnds;
-                e2 = e2 >= kEnds ? e2 - kEnds : e2;
-                const bool same = i < kSameRound;
-                e1 = same ? ((i >> 2) << 1) | (i & 1) : e1;
-                e2 = same ? kEnds + (((i >> 2) << 1) | ((i >> 1) & 1)) : e2;
-                const int p = __shfl(end_rank, e1), q = __shfl(end_rank, e2);
-                const int reach = __shfl(gain, e1) + __shfl(gain, e2) + min(__shfl(both, e1), __shfl(both, e2));
-                if (i >= kPairs || !((left >> e1) & 1) || (!same && !((left >> e2) & 1)) || p == q || cur - reach > hi ||
-                    reach == 0)
-                    continue;
-                const int tp = t[p], tq = t[q];
-                int total = 0;
+                for (int i0 = 0; i0 < kPairs; i0 += kAtOnce) {
+                    const int at = PAIRS ? tid - SCAN : tid, i = i0 + at / kPairLanes, u = max(i - kSameRound, 0);
+                    int e1 = u % kEnds, e2 = e1 + 1 + u / kEnds;
+                    e2 = e2 >= kEnds ? e2 - kEnds : e2;
+                    const bool same = i < kSameRound;
+                    e1 = same ? ((i >> 2) << 1) | (i & 1) : e1;
+                    e2 = same ? kEnds + (((i >> 2) << 1) | ((i >> 1) & 1)) : e2;
+                    const int p = __shfl(end_rank, e1), q = __shfl(end_rank, e2);
+                    const int reach = __shfl(gain, e1) + __shfl(gain, e2) + min(__shfl(both, e1), __shfl(both, e2));
+                    if (i >= kPairs || !((left >> e1) & 1) || (!same && !((left >> e2) & 1)) || p == q || cur - reach > bound ||
+                        reach == 0)
+                        continue;
+                    const int tp = t[p], tq = t[q];
+                    int total = 0;
 #pragma unroll
-                for (int k = 0; k < LOGN; ++k) {
-                    const int k1 = top[0][k], k2 = top[1][k], k3 = top[2][k], up = p | (1 << k), uq = q | (1 << k);
-                    const bool one = (k1 & 1023) == up || (k1 & 1023) == uq, two = (k2 & 1023) == up || (k2 & 1023) == uq;
-                    const int other = (one ? (two ? k3 : k2) : k1) >> 10;
-                    const int cost = max(other, max(mat.at(tq, t[p ^ (1 << k)]), mat.at(tp, t[q ^ (1 << k)])));
-                    total += up == uq ? k1 >> 10 : cost;
+                    for (int j = 0; j < kRounds; ++j) {
+                        const int k = min(at % kPairLanes * kRounds + j, LOGN - 1);
+                        const int k1 = top[0][k], k2 = top[1][k], k3 = top[2][k], up = p | (1 << k), uq = q | (1 << k);
+                        const bool one = ((k1 & 1023) == up) | ((k1 & 1023) == uq), two = ((k2 & 1023) == up) | ((k2 & 1023) == uq);
+                        const int other = (one ? (two ? k3 : k2) : k1) >> 10;
+                        const int cost = max(other, max(mat.at(tq, t[p ^ (1 << k)]), mat.at(tp, t[q ^ (1 << k)])));
+                        const bool counts = kRounds * kPairLanes == LOGN || at % kPairLanes * kRounds + j < LOGN;
+                        total += counts ? (up == uq ? k1 >> 10 : cost) : 0;
+                    }
+                    if (kPairLanes == 2) total += __builtin_amdgcn_update_dpp(0, total, 0xB1, 0xf, 0xf, true);       // quad_perm 1, 0, 3, 2
+                    const int move = min(p, q) * N + max(p, q);
+                    const bool better = total < hi || (total == hi && move < id);
+                    hi = better ? total : hi;
+                    id = better ? move : id;
                 }
-                const int move = min(p, q) * N + max(p, q);
-                const bool better = total < hi || (total == hi && move < id);
-                hi = better ? total : hi;
-                id = better ? move : id;
             }
             block_min(hi, id);
             best_hi = hi;
             best_id = id;
         }
         if (best_hi >= cur) break;
-        // ---- the swap: the first wave moves the two nodes and renews the 2 LOGN links they touch
-        const int sp = best_id >> LOGN, sq = best_id & (N - 1);
-        if (wv == 0) {
-            const int a = t[sp], b = t[sq];
-            const int k = min(lane >> 1, LOGN - 1), rank = (lane & 1) ? sq : sp, mate = rank ^ (1 << k);
-            const int tr = (lane & 1) ? a : b;
+        // ---- the swap: every wave renews the links of its rounds, the first one moves the two nodes
+        const int sp = best_id >> LOGN, sq = best_id & (N - 1), a = t[sp], b = t[sq];
+        dirty = 0;
+        {
+            const int k0 = wv * kPerWave, k = min(k0 + (lane >> 1), LOGN - 1);
+            const int rank = (lane & 1) ? sq : sp, mate = rank ^ (1 << k), tr = (lane & 1) ? a : b;
             int tm = t[mate];
             tm = mate == sp ? b : (mate == sq ? a : tm);
             bool touched = false;
-            if (lane < kEnds) {
+            if (lane < 2 * min(kPerWave, LOGN - k0)) {
                 const int up = rank | (1 << k), key = (mat.at(tr, tm) << 10) | up, l = link_of(rank, k);
                 const int k3 = top[2][k];
                 touched = key > k3 || links[k * HALF + l] >= k3;
                 links[k * HALF + l] = key;
             }
             const unsigned long long bits = __ballot(touched);
-            unsigned mask = 0;
 #pragma unroll
-            for (int j = 0; j < LOGN; ++j) mask |= ((bits >> (2 * j)) & 3) ? 1u << j : 0u;
-            if (lane == 0) {
-                t[sp] = b;
-                t[sq] = a;
+            for (int j = 0; j < kPerWave; ++j) dirty |= ((bits >> (2 * j)) & 3) ? 1u << (k0 + j) : 0u;
+        }
+        if (wv == 0) {
+            if (lane < 4) {
+                // this swap and the one before, which the other copy has not seen
+                const int x = lane & 2 ? (lane & 1 ? sq : sp) : (lane & 1 ? last_q : last_p);
+                const int node = x == sp ? b : x == sq ? a : t[x];
+                t_next[x] = node;
                 if (MAT::kRows) {
-                    pos[b] = sp;
-                    pos[a] = sq;
+                    const int y = lane & 2 ? (lane & 1 ? b : a) : (lane & 1 ? last_b : last_a);
+                    pos_next[y] = y == a ? sq : y == b ? sp : pos[y];
                 }
-                dirty_rounds = mask;
+            }
+            last_p = sp;
+            last_q = sq;
+            last_a = a;
+            last_b = b;
+        }
+        {
+            int32_t* const was = t;
+            t = t_next;
+            t_next = was;
+            if (MAT::kRows) {
+                int32_t* const were = pos;
+                pos = pos_next;
+                pos_next = were;
             }
         }
         ++applied;
         cur = best_hi;
-        sync();
-        dirty = __builtin_amdgcn_readfirstlane(dirty_rounds);
+        __builtin_amdgcn_wave_barrier();
     }
     for (int p = tid; p < N; p += THREADS) tour[p] = t[p];
     if (tid == 0) {
@@ -470,13 +507,13 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
     }
 }
 
-template <int LOGN, int THREADS>
-__global__ __launch_bounds__(THREADS) void rdswap_pruned_kernel(const int32_t* __restrict__ c,
+template <int LOGN, int SCAN, int PAIRS>
+__global__ __launch_bounds__(SCAN + PAIRS, LOGN <= 6 ? 5 : 1) void rdswap_pruned_kernel(const int32_t* __restrict__ c,
                                                                 const uint16_t* __restrict__ folded,
                                                                 int32_t* __restrict__ tours, int64_t* __restrict__ costs,
                                                                 int32_t* __restrict__ moves,
                                                                 const int32_t* __restrict__ flags) {
-    constexpr int N = 1 << LOGN;
+    constexpr int N = 1 << LOGN, THREADS = SCAN + PAIRS;
     extern __shared__ __attribute__((aligned(16))) int32_t sm[];
     const int tid = threadIdx.x;
     const int64_t r = blockIdx.x;
@@ -499,7 +536,7 @@ __global__ __launch_bounds__(THREADS) void rdswap_pruned_kernel(const int32_t* _
         if constexpr (LOGN == 8) {
             for (int w = 0; w < THREADS / 64; ++w) mx = max(mx, wave_top[w]);
             if (mx >= (1 << 16)) {
-                descend_pruned<LOGN, THREADS>(GlobalWords{c, LOGN}, sm, tour, costs + r, moves + r);
+                descend_pruned<LOGN, SCAN, PAIRS>(GlobalWords{c, LOGN}, sm, tour, costs + r, moves + r);
                 return;
             }
         }
@@ -514,25 +551,25 @@ __global__ __launch_bounds__(THREADS) void rdswap_pruned_kernel(const int32_t* _
             }
         }
         __syncthreads();
-        if constexpr (LOGN <= 7) descend_pruned<LOGN, THREADS>(LdsWords{m, LOGN}, sm, tour, costs + r, moves + r);
-        else descend_pruned<LOGN, THREADS>(LdsHalves{m, LOGN}, sm, tour, costs + r, moves + r);
+        if constexpr (LOGN <= 7) descend_pruned<LOGN, SCAN, PAIRS>(LdsWords{m, LOGN}, sm, tour, costs + r, moves + r);
+        else descend_pruned<LOGN, SCAN, PAIRS>(LdsHalves{m, LOGN}, sm, tour, costs + r, moves + r);
     } else {
-        if (flags[0] < (1 << 16)) descend_pruned<LOGN, THREADS>(GlobalHalves{folded, LOGN}, sm, tour, costs + r, moves + r);
-        else descend_pruned<LOGN, THREADS>(GlobalWords{c, LOGN}, sm, tour, costs + r, moves + r);
+        if (flags[0] < (1 << 16)) descend_pruned<LOGN, SCAN, PAIRS>(GlobalHalves{folded, LOGN}, sm, tour, costs + r, moves + r);
+        else descend_pruned<LOGN, SCAN, PAIRS>(GlobalWords{c, LOGN}, sm, tour, costs + r, moves + r);
     }
 }
 
-template <int LOGN, int THREADS>
+template <int LOGN, int SCAN, int PAIRS = 0>
 hipError_t rdswap_pruned_launch(const int32_t* c, const uint16_t* folded, int restarts, int32_t* tours, int64_t* costs,
                                 int32_t* moves, const int32_t* flags, hipStream_t s) {
     constexpr size_t N = (size_t)1 << LOGN;
     const size_t lds = swap_state_words(LOGN, LOGN >= 8) * 4 + (LOGN <= 7 ? 4 * N * N : LOGN == 8 ? 2 * N * N : 0);
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)rdswap_pruned_kernel<LOGN, THREADS>,
+        hipError_t e = hipFuncSetAttribute((const void*)rdswap_pruned_kernel<LOGN, SCAN, PAIRS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((rdswap_pruned_kernel<LOGN, THREADS>), dim3(restarts), dim3(THREADS), lds, s, c, folded, tours, costs,
+    hipLaunchKernelGGL((rdswap_pruned_kernel<LOGN, SCAN, PAIRS>), dim3(restarts), dim3(SCAN + PAIRS), lds, s, c, folded, tours, costs,
                        moves, flags);
     return hipGetLastError();
 }
@@ -561,21 +598,27 @@ hipError_t launch_rdswap(const int32_t* c, int N, int restarts, uint64_t seed, b
         if (e == hipSuccess) e = launch_fold_to_u16(c, N, mat16, flags, s);
         if (e != hipSuccess) return e;
     }
-    // Threads per restart, from a sweep over 64 .. 1024 at few and at many restarts: a sweep is a chain of latencies, and
-    // wider workgroups shorten its scans until the barriers cost more than they save (N = 64: 128 and 256 the same at 34
-    // restarts, 128 better at 1024; N = 256: 1.28 ms with 512, 1.54 with 256, 2.3 with 1024, 58 restarts).
+    // A sweep is a chain of latencies: more wavefronts per restart, and others for the pairs beside them, shorten it until the compute
+    // units run out of room for restarts.  (Wavefronts that scan + those for the pairs, 0: the same; us.)  N = 8, 1024 restarts
+    // 1+0 28, 2+1 24, 4096 restarts 35 / 41; N = 16, 1024 restarts 1+0 98, 2+2 66, 2+1 73, 2+0 77, 2048 restarts 98 / 82 / 75 / 77, 4096
+    // 105 / 120 / 116 / 107; N = 32, 768 restarts 1+0 177, 2+3 118, 2+2 128, 2+0 137, 2048 restarts 227 / 243 / 186 / 171; N = 64, 256
+    // restarts 2+3 199, 2+2 204, 2+0 238, 1+0 320, 1280 restarts 385 / 286 / 298 / 392, 2048 restarts 559 / 402 / 327 / 398; N = 128,
+    // 256 restarts 4+4 425, 4+2 482, 4+0 501, 2048 restarts 1591 / 1942 / 1799; N = 512, 256 restarts 8+4 3168, 8+0 3550, 4+4
+    // 3862, 512 restarts 5663 / 3999 / 4081; N = 1024, 256 restarts 8+4 3990, 8+0 4546, 512 restarts 7295 / 6358.
+#define CC_SWAP(LOGN, SCAN, PAIRS) rdswap_pruned_launch<LOGN, SCAN, PAIRS>(c, mat16, restarts, tours, costs, moves, flags, s)
     switch (N) {
-        case 2: return rdswap_pruned_launch<1, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 4: return rdswap_pruned_launch<2, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 8: return rdswap_pruned_launch<3, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 16: return rdswap_pruned_launch<4, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 32: return rdswap_pruned_launch<5, 64>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 64: return rdswap_pruned_launch<6, 128>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 128: return rdswap_pruned_launch<7, 256>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 256: return rdswap_pruned_launch<8, 512>(c, mat16, restarts, tours, costs, moves, flags, s);
-        case 512: return rdswap_pruned_launch<9, 512>(c, mat16, restarts, tours, costs, moves, flags, s);
-        default: return rdswap_pruned_launch<10, 512>(c, mat16, restarts, tours, costs, moves, flags, s);
+        case 2: return CC_SWAP(1, 64, 0);
+        case 4: return CC_SWAP(2, 64, 0);
+        case 8: return restarts <= 3072 ? CC_SWAP(3, 128, 64) : CC_SWAP(3, 64, 0);
+        case 16: return restarts <= 1536 ? CC_SWAP(4, 128, 128) : restarts <= 3072 ? CC_SWAP(4, 128, 0) : CC_SWAP(4, 64, 0);
+        case 32: return restarts <= 768 ? CC_SWAP(5, 128, 192) : restarts <= 3072 ? CC_SWAP(5, 128, 0) : CC_SWAP(5, 64, 0);
+        case 64: return restarts <= 768 ? CC_SWAP(6, 128, 192) : restarts <= 1280 ? CC_SWAP(6, 128, 128) : CC_SWAP(6, 128, 0);
+        case 128: return CC_SWAP(7, 256, 256);
+        case 256: return CC_SWAP(8, 512, 320);
+        case 512: return restarts <= 256 ? CC_SWAP(9, 512, 256) : CC_SWAP(9, 512, 0);
+        default: return restarts <= 256 ? CC_SWAP(10, 512, 256) : CC_SWAP(10, 512, 0);
     }
+#undef CC_SWAP
 }
 
 }  // namespace cc
