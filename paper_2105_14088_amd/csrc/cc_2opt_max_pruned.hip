@@ -551,19 +551,27 @@ hipError_t launch(const int32_t* c, int N, bool directed, int restarts, bool wit
 
 hipError_t launch_2opt_max_pruned(const int32_t* c, int N, bool directed, int restarts, bool with_flip, int32_t* tours,
                                   int64_t* costs, int32_t* moves, hipStream_t s) {
-    // Wider workgroups shorten a sweep's phases until their barriers cost more.  The directed searches of the head of this
-    // file: N = 100, 1000 restarts 205 us with 128 threads, 261 with 64; N = 256, 1024 restarts 551 us with 256, 684 with
-    // 128, 1040 with 64.
+    // Wider workgroups shorten a sweep's phases until their barriers cost more, and take room from other restarts.  The directed
+    // searches of the head of this file: N = 100, 1000 restarts 205 us with 128 threads, 261 with 64, 221 with 256; N = 256, 1024
+    // restarts 551 us with 256, 684 with 128, 823 with 512; N = 300, 256 restarts 604 us with 512, 735 with 256, 839 with 1024, 1000 restarts
+    // 961 / 800 / 2163; N = 512, 256 restarts 872 / 1156 / 1147; N = 1024, 32 restarts 2027 / 2992 / 2064.  Undirected: N = 100, 1000
+    // restarts 120 us with 64, 155 with 256; N = 256, 256 restarts 139 us with 256, 150 with 128, 1000 restarts 173 / 190; N = 512, 256
+    // restarts 236 us with 512, 226 with 256; N = 1024, 256 restarts 314 / 330.
+    const bool few = restarts <= 512;
     if (N <= 64) return launch<64, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
     if (N <= 128) {
         if (directed) return launch<128, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
         return launch<64, 2>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
     }
     if (N <= 256) {
-        if (directed) return launch<256, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
+        if (directed || restarts <= 1024) return launch<256, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
         return launch<128, 2>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
     }
-    if (N <= 512) return launch<256, 2>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
+    if (N <= 512) {
+        if (directed && few) return launch<512, 1>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
+        return launch<256, 2>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
+    }
+    if (few) return launch<512, 2>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
     return launch<256, 4>(c, N, directed, restarts, with_flip, tours, costs, moves, s);
 }
 
