@@ -424,137 +424,223 @@ static bool ring_rows_pays(int N, int64_t B) {
 // marks in LDS, one bit per entry (32 KiB at N = 500, 128 KiB at N = 1024), the entries that are T or more; T is chosen
 // from 4096 sampled hops of the batch's orders so that about ln N of an order's N hops carry the bit (where the exact look-ups and the orders
 // without a marked hop, which are looked up whole, cost the same).  Any T gives the right result, only the time depends on
-// it.  Sixteen lanes per order as in ring_batch_rows_kernel; a lane notes its marked hops in a 64-bit mask (at most 64
-// steps) and afterwards looks them up one by one, ranks from the order stream (in cache) and entries through L2.  An order
-// that has reached the matrix maximum is finished, so a matrix of few values ends early.
-// The generic kernels ask L2 for every hop and run at its request rate; here what is left is the marking and the order
-// stream.  Generic -> marked, seeded orders: N = 300, 200000 orders 255 -> 87 us; N = 500, 65000 orders 144 -> 65 us, of two
-// bytes a rank 140 -> 58 us; N = 1000, 65000 orders 335 -> 134 us.  Orders of small hops only: N = 500, 65000 orders
-// 113 -> 57 us (a threshold from the matrix's entries instead was 3 to 7 us cheaper on seeded orders, but marks none of
-// these).
-template <typename RANK>
+// it.  One order per wave, its ranks in a wide load or two, two orders ahead; the marked hops' entries are read together, the others'
+// lanes at one common place.  Where all marked entries are the largest one nothing is read, and an order with many marked hops ends
+// at the first of the largest, so a matrix of few values ends early.
+// The generic kernels ask L2 for every hop and run at its request rate; here what is left is the marking (N = 500: 1 MB read per
+// compute unit, 14 us), sampling (3 us) and the order stream.  Generic -> marked, seeded orders: N = 300, 200000 orders 255 -> 75 us;
+// N = 500, 65000 orders 144 -> 47 us, of two bytes a rank 140 -> 42 us; N = 1000, 65000 orders 335 -> 95 us.  Orders of small hops
+// only: N = 500, 65000 orders 113 -> 46 us.  With sixteen lanes per order, a rank per load, the same 4096 places sampled by every
+// workgroup and a ballot per 64 marked entries: 65, 58, 134 and 57 us.
+// W consecutive ranks of an order, aligned as a rank is
+template <typename RANK, int W>
+struct Ranks;
+template <>
+struct Ranks<uint16_t, 4> {
+    typedef unsigned short type __attribute__((ext_vector_type(4), aligned(2)));
+};
+template <>
+struct Ranks<uint16_t, 8> {
+    typedef unsigned short type __attribute__((ext_vector_type(8), aligned(2)));
+};
+template <>
+struct Ranks<int32_t, 4> {
+    typedef ranks4 type;
+};
+template <>
+struct Ranks<int32_t, 8> {
+    struct type {
+        ranks4 a, b;
+        __device__ __forceinline__ int operator[](int i) const { return i < 4 ? a[i] : b[i - 4]; }
+    };
+};
+
+// A lane takes the R = ceil(N / 64) ranks from R * lane on, W + SECOND of them at most: W from there and W up to their end, of which
+// the last SECOND are looked at (W = 4 up to N = 512, so that 5 .. 8 ranks are 5 .. 8 look-ups; above W = 8).
+template <typename RANK, int W, int SECOND>
 __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32_t* __restrict__ c, int N,
                                                                      const RANK* __restrict__ perms, int64_t B,
                                                                      int64_t* __restrict__ out, int wanted) {
-    constexpr int U = 16;                                        // steps in flight
+    using Part = typename Ranks<RANK, W>::type;
+    constexpr int H = W + SECOND;                                // hops of a lane
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_ring_marks[];
     int* per_wave = (int*)smem_ring_marks;                       // [2][16]: the waves' estimates of T, their maxima
     uint32_t* marks = (uint32_t*)(smem_ring_marks + 128);        // bit e of the flat matrix: bit e & 31 of word e >> 5
-    const int lane = lane_id(), wv = threadIdx.x >> 6, sub = lane & 15;
-    auto node = [&](int r) { return sizeof(RANK) == 4 ? clampi(r, 0, N - 1) : min(r, N - 1); };
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t waves = (int64_t)gridDim.x * 16, first_order = (int64_t)blockIdx.x * 16 + wv;
+    // 4 * node, to be the byte offset of an entry when multiplied
+    auto node = [&](int r) { return (unsigned)(sizeof(RANK) == 4 ? clampi(r, 0, N - 1) : min(r, N - 1)) << 2; };
+    const int R = (N + 63) >> 6, start = min(lane * R, N - R);   // the last lanes have ranks of others again
+    struct Mine {
+        Part a, b;
+    };
+    auto load = [&](int64_t b) {
+        const RANK* pi = perms + b * N + start;
+        Mine m;
+        m.a = *(const Part*)pi;
+        m.b = *(const Part*)(pi + R - W);
+        return m;
+    };
+    Mine next = load(min(first_order, B - 1));
     int v[4];
+    {
+        // hops of 16 of the orders that this workgroup will look at, one per wave, spread over the batch (of orders from all over the
+        // batch, the same in every workgroup: 12 us, now 3)
+        const int64_t turns = (B + waves - 1) / waves;
+        const Mine m = load(min(first_order + wv % turns * waves, B - 1));
+        auto hop = [&](int x, int y) { return max(*(const int32_t*)((const char*)c + (__umul24(node(x), (unsigned)N) + node(y))), 0); };
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint64_t h = splitmix64_at(0, (uint64_t)(threadIdx.x + 1024 * i + 1));
-        const int p = (int)(((h & 0xffffffffu) * (uint64_t)N) >> 32);
-        const RANK* pi = perms + (int64_t)__umul64hi(h, (uint64_t)B) * N;
-        v[i] = max(c[node(pi[p]) * N + node(pi[p ? p - 1 : N - 1])], 0);
+        for (int i = 0; i < 3; ++i) v[i] = hop(m.a[i + 1], m.a[i]);
+        v[3] = hop(m.b[W - 1], m.b[W - 2]);
     }
     const int T = sampled_threshold(v, wanted, per_wave);
-    // 32 runs of 64 entries per wave and pass, all loads in flight; the workgroups start at different places, so that they
+    // 2048 entries per wave and pass, all loads in flight; the workgroups start at different places, so that they
     // do not all ask the same L2 channel at once
     int top = 0;
     const int total = N * N, passes = (total + 16 * 2048 - 1) / (16 * 2048);
     const int first = (int)((int64_t)blockIdx.x * passes / gridDim.x);
     for (int i = 0; i < passes; ++i) {
         const int at = ((first + i < passes ? first + i : first + i - passes) * 16 + wv) * 2048;
-        int e[32];
+        if (at + 2048 <= total) {
+            // a lane's four entries make four bits (the sign of T - 1 - entry), eight lanes' a word
+            ranks4 e[8];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) e[k] = c[min(at + 64 * k + lane, total - 1)];
-        uint32_t word = 0;
+            for (int k = 0; k < 8; ++k) e[k] = *(const ranks4*)(c + at + 256 * k + 4 * lane);
+            uint32_t word = 0;
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const unsigned long long bits = __ballot(e[k] >= T);
-            top = max(top, e[k]);
-            if ((lane >> 1) == k) word = lane & 1 ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+            for (int k = 0; k < 8; ++k) {
+                uint32_t bits = 0;
+#pragma unroll
+                for (int q = 3; q >= 0; --q) bits = __builtin_amdgcn_alignbit(bits, (uint32_t)(T - 1) - (uint32_t)e[k][q], 31);
+                top = max(max(top, e[k][0]), max(max(e[k][1], e[k][2]), e[k][3]));
+                int v = (int)(bits << (4 * (lane & 7)));
+                v |= __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);        // quad_perm 1, 0, 3, 2
+                v |= __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);        // quad_perm 2, 3, 0, 1
+                v |= __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);       // row_half_mirror
+                if ((lane & 7) == k) word = (uint32_t)v;
+            }
+            marks[(at >> 5) + 8 * (lane & 7) + (lane >> 3)] = word;
+        } else if (at < total) {
+            uint32_t word = 0;
+#pragma unroll 4
+            for (int k = 0; k < 32; ++k) {
+                const int e = c[min(at + 64 * k + lane, total - 1)];
+                const unsigned long long bits = __ballot(e >= T);
+                top = max(top, e);
+                if ((lane >> 1) == k) word = lane & 1 ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+            }
+            if (at + 32 * lane < total) marks[(at >> 5) + lane] = word;
         }
-        if (at + 32 * lane < total) marks[(at >> 5) + lane] = word;
     }
     top = wave_max(top);
     if (lane == 0) per_wave[16 + wv] = top;
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 16; ++k) top = max(top, per_wave[16 + k]);
-    auto row_max = [](int a) {
-        a = max(a, __builtin_amdgcn_update_dpp(a, a, 0xB1, 0xf, 0xf, true));
-        a = max(a, __builtin_amdgcn_update_dpp(a, a, 0x4E, 0xf, 0xf, true));
-        a = max(a, __builtin_amdgcn_update_dpp(a, a, 0x141, 0xf, 0xf, true));
-        return max(a, __builtin_amdgcn_update_dpp(a, a, 0x140, 0xf, 0xf, true));
-    };
-    const int64_t waves = (int64_t)gridDim.x * 16;
-    for (int64_t w = (int64_t)blockIdx.x * 16 + wv; w * 4 < B; w += waves) {
-        const int64_t b = w * 4 + (lane >> 4);
-        const RANK* pi = perms + (b < B ? b : B - 1) * N;
-        auto hop = [&](int p) { return c[node(pi[p]) * N + node(pi[p ? p - 1 : N - 1])]; };
-        int before = node(pi[N - 1]);
-        uint64_t hits = 0;                                       // bit t: the hop into rank 16 t + sub
-        for (int p0 = 0; p0 < N; p0 += 16 * U) {
-            int r[U];
+    Mine after = load(min(first_order + waves, B - 1));
+    const bool known = T >= top;                                 // what a marked entry costs
+    const bool whole = lane * R <= N - R;                        // not: the first rank's hop is an earlier lane's
+    const bool own = lane * R < N;                               // not: all of them are
+    auto entry = [&](unsigned at) { return *(const int32_t*)((const char*)c + at); };
+    for (int64_t b = first_order; b < B; b += waves) {
+        const Mine now = next;
+        next = after;
+        after = load(min(b + 2 * waves, B - 1));
+        // hop i leads into x[i] from y[i]
+        unsigned x[H], y[H], at[H];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (p0 + 16 * u < N) r[u] = (int)pi[min(p0 + 16 * u + sub, N - 1)];
-            }
-            uint32_t chunk = 0;
+        for (int i = 0; i < W; ++i) {
+            x[i] = node(now.a[i]);
+            if (i) y[i] = x[i - 1];
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (p0 + 16 * u < N) {
-                    const int x = node(r[u]);
-                    const int rot = __builtin_amdgcn_update_dpp(x, x, 0x121, 0xf, 0xf, true);      // row_ror:1
-                    const int y = sub == 0 ? before : rot;
-                    before = rot;
-                    const unsigned e = (unsigned)(x * N + y);
-                    const uint32_t bit = (marks[e >> 5] >> (e & 31)) & 1u;
-                    if (p0 + 16 * u + sub < N) chunk |= bit << u;
-                }
-            }
-            hits |= (uint64_t)chunk << (p0 >> 4);
+        for (int i = 0; i < SECOND; ++i) {
+            x[W + i] = node(now.b[W - SECOND + i]);
+            if (i) y[W + i] = x[W + i - 1];
+            else if (SECOND < W) y[W] = node(now.b[SECOND < W ? W - SECOND - 1 : 0]);
+            else y[W] = R == 2 * W ? x[W - 1] : x[W - 2];        // its own predecessor, or that of the rank it has again
         }
-        int best = -1;
-        while (__ballot(hits != 0)) {
-            if (hits) {
-                const int t0 = __ffsll((unsigned long long)hits) - 1;       // two at once: their loads overlap
-                hits &= hits - 1;
-                const int t1 = hits ? __ffsll((unsigned long long)hits) - 1 : t0;
-                hits &= hits - 1;
-                best = max(best, max(hop(16 * t0 + sub), hop(16 * t1 + sub)));
-            }
-            if ((__ballot(best >= top) >> (lane & 48)) & 0xffffu) hits = 0;
-        }
-        best = row_max(best);
-        if (__ballot(best < 0)) {                                // an order without a marked hop: all of them
-            if (best < 0) {
-                best = 0;
-                for (int p0 = sub; p0 < N; p0 += 16 * 8) {
+        y[0] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x[H - 1], w64::kDppWaveRor1, 0xf, 0xf, true);
+        int hit[H], any = 0, best = 0;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) best = max(best, hop(min(p0 + 16 * u, N - 1)));
-                }
-            }
-            best = row_max(best);
+        for (int i = 0; i < H; ++i) {
+            at[i] = __umul24(x[i], (unsigned)N) + y[i];
+            const uint32_t word = *(const uint32_t*)((const char*)marks + ((at[i] >> 5) & ~3u));
+            hit[i] = __builtin_amdgcn_sbfe((int)word, at[i] >> 2, 1);                    // -1 where it is marked
         }
-        if (sub == 0 && b < B) out[b] = best;
+        if (!whole) hit[0] = 0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) any |= hit[i];
+        if (!own) any = 0;
+        if (__ballot(any != 0) == 0) {                           // an order without a marked hop: all of them
+            int value[H];
+#pragma unroll
+            for (int i = 0; i < H; ++i) value[i] = entry(at[i]);
+            if (!whole) value[0] = 0;
+#pragma unroll
+            for (int i = 0; i < H; ++i) best = max(best, value[i]);
+            best = wave_max(best);
+        } else if (known) {
+            best = top;
+        } else if (__popcll(__ballot(any != 0)) > 32) {          // a matrix of few values: until one of the largest is met
+#pragma unroll
+            for (int i0 = 0; i0 < H; i0 += 4) {
+                int value[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) value[i] = i0 + i < H ? entry(own ? at[i0 + i] & (unsigned)hit[i0 + i] : 0u) & hit[i0 + i] : 0;
+                best = max(max(best, value[0]), max(max(value[1], value[2]), value[3]));
+                if (!own) best = 0;
+                if (__ballot(best >= top)) break;
+            }
+            best = wave_max(best);
+        } else {
+            int value[H];
+#pragma unroll
+            for (int i = 0; i < H; ++i) value[i] = entry(own ? at[i] & (unsigned)hit[i] : 0u);
+#pragma unroll
+            for (int i = 0; i < H; ++i) best = max(best, value[i] & hit[i]);
+            best = wave_max(own ? best : 0);
+        }
+        if (lane == 0) out[b] = best;
     }
 }
 
-template <typename RANK>
+template <typename RANK, int W, int SECOND>
 static hipError_t ring_max_marked_launch(const int32_t* c, int N, const RANK* perms, int64_t B, int64_t* out,
                                          hipStream_t s) {
     const size_t lds = 128 + sizeof(uint32_t) * (((size_t)N * N + 31) / 32);
-    hipError_t e = hipFuncSetAttribute((const void*)ring_batch_max_marked_kernel<RANK>,
+    hipError_t e = hipFuncSetAttribute((const void*)ring_batch_max_marked_kernel<RANK, W, SECOND>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     int64_t blocks = (B + 63) / 64;
     if (blocks > 256) blocks = 256;                             // one per compute unit: each reads the whole matrix
     const int wanted = (256 * 6 + N / 2) / N;                   // of 256 samples: 6 of N, ln N being 5.6 .. 6.9
-    hipLaunchKernelGGL(ring_batch_max_marked_kernel<RANK>, dim3((int)blocks), dim3(1024), lds, s, c, N, perms, B, out,
+    hipLaunchKernelGGL((ring_batch_max_marked_kernel<RANK, W, SECOND>), dim3((int)blocks), dim3(1024), lds, s, c, N, perms, B, out,
                        wanted);
     return hipGetLastError();
 }
+template <typename RANK>
+static hipError_t ring_max_marked(const int32_t* c, int N, const RANK* perms, int64_t B, int64_t* out, hipStream_t s) {
+    switch ((N + 63) / 64) {
+        case 5: return ring_max_marked_launch<RANK, 4, 1>(c, N, perms, B, out, s);
+        case 6: return ring_max_marked_launch<RANK, 4, 2>(c, N, perms, B, out, s);
+        case 7: return ring_max_marked_launch<RANK, 4, 3>(c, N, perms, B, out, s);
+        case 8: return ring_max_marked_launch<RANK, 4, 4>(c, N, perms, B, out, s);
+        case 9:
+        case 10: return ring_max_marked_launch<RANK, 8, 2>(c, N, perms, B, out, s);
+        case 11:
+        case 12: return ring_max_marked_launch<RANK, 8, 4>(c, N, perms, B, out, s);
+        case 13:
+        case 14: return ring_max_marked_launch<RANK, 8, 6>(c, N, perms, B, out, s);
+        default: return ring_max_marked_launch<RANK, 8, 8>(c, N, perms, B, out, s);
+    }
+}
 
-// The threshold and the marking, once per workgroup, take about as long as the generic kernel takes for 21000 (N = 1000) to
-// 25000 orders (N = 300; generic / marked: N = 300, 20480 orders 26 / 31 us; N = 1000, 20480 orders 106 / 111 us).  Orders that
-// differ in a few ranks ask for the same few entries, which the caches hold: for them the lines meet later (N = 300, 30000
-// orders 26 / 32 us, 100000 orders 88 / 62; N = 1000, 30000 orders 97 / 109; seeded orders there 41 / 34, 130 / 59, 154 / 113).
-constexpr int64_t kRingMaxMarkedMinOrders = 28672;
+// The threshold and the marking, once per workgroup, take about as long as the generic kernel takes for 8000 (N = 500) to
+// 12000 orders (N = 300; generic / marked: N = 300, 20000 orders 26.7 / 17.1 us; N = 1000, 20000 orders 105 / 66 us).  Orders that
+// differ in a few ranks ask for the same few entries, which the caches hold: for them the lines meet later (N = 300, 28000
+// orders 21.2 / 19.2 us, of two bytes a rank 17.1 / 18.7; N = 1000, 20000 orders 60 / 62, 28000 orders 89 / 68).
+constexpr int64_t kRingMaxMarkedMinOrders = 24576;
 static bool ring_max_marked_pays(int N, int64_t B) { return N > kRingRowsMaxN && B >= kRingMaxMarkedMinOrders; }
 
 hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const int32_t* perms, int64_t B,
@@ -577,7 +663,7 @@ hipError_t launch_ring_cost_batch(const int32_t* c, int N, bool is_max, const in
     if (ring_rows_pays(N, B))
         return is_max ? ring_rows_launch<int32_t, true>(c, N, perms, B, out, s)
                       : ring_rows_launch<int32_t, false>(c, N, perms, B, out, s);
-    if (is_max && ring_max_marked_pays(N, B)) return ring_max_marked_launch<int32_t>(c, N, perms, B, out, s);
+    if (is_max && ring_max_marked_pays(N, B)) return ring_max_marked(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_generic_kernel<true>), dim3(grid), dim3(256), 0, s, c, N, perms, B, out);
@@ -631,7 +717,7 @@ hipError_t launch_ring_cost_batch_u16(const int32_t* c, int N, bool is_max, cons
     if (ring_rows_pays(N, B))
         return is_max ? ring_rows_launch<uint16_t, true>(c, N, perms, B, out, s)
                       : ring_rows_launch<uint16_t, false>(c, N, perms, B, out, s);
-    if (is_max && ring_max_marked_pays(N, B)) return ring_max_marked_launch<uint16_t>(c, N, perms, B, out, s);
+    if (is_max && ring_max_marked_pays(N, B)) return ring_max_marked(c, N, perms, B, out, s);
     const int grid = batch_grid(4, B);
     if (is_max)
         hipLaunchKernelGGL((ring_batch_narrow_generic_kernel<uint16_t, true>), dim3(grid), dim3(256), 0, s, c, N, perms,
