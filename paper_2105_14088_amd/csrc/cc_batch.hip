@@ -1171,7 +1171,9 @@ __global__ __launch_bounds__(1024) void links_batch_lds16_kernel(const int32_t* 
 // largest entry seen, for the early end in rd_batch_marked_kernel.
 // Behind the marks (N^2 / 8 bytes) the folded entries themselves, 16 bits each, lower triangle with diagonal by rows
 // (N (N + 1) bytes, both within the workspace's 2 N^2): an exact look-up is then one request; used when all fit 16 bits.
-constexpr int kMarkBlocks = 64;                    // tops: 64 words, the flags part of the workspace
+// Behind those the workgroups' largest entries.  A workgroup per compute unit (64 workgroups: 16.5 us, 256: 15.6).
+constexpr int kMarkBlocks = 256;
+constexpr size_t mark_tops_offset(size_t N) { return N * N / 8 + N * (N + 1); }
 
 template <int LOGN>
 __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restrict__ c, uint32_t* __restrict__ marks,
@@ -1185,8 +1187,10 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
     int v[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint32_t h = (uint32_t)splitmix64_at(0, (uint64_t)(threadIdx.x + 1024 * i + 1));
-        const int x = h & (N - 1), y = (h >> LOGN) & (N - 1);
+        // sixteen lanes a place of 4 x 4 pairs: 32 cache lines for both directions of a wave's instead of 128 (64 places a wave,
+        // read by every workgroup: the kernel 15.6 us at N = 1024, now 9.4)
+        const uint32_t h = (uint32_t)splitmix64_at(0, (uint64_t)((threadIdx.x >> 4) + 64 * i + 1));
+        const int x = (h & (N - 4)) + (lane & 3), y = ((h >> LOGN) & (N - 4)) + ((lane >> 2) & 3);
         v[i] = entry(x, x == y ? y ^ 1 : y);
     }
     // a wave takes 64 consecutive x and kRows consecutive y, so both directions come from few cache lines
@@ -1247,8 +1251,8 @@ __device__ __forceinline__ void lane_links(unsigned a, unsigned b, int lane, uns
 // taking its own one by one, all rounds mixed, their maxima formed in LDS.  A round without a marked link is looked up
 // whole; one that has reached the matrix maximum is finished, so a matrix of few values ends early.
 // Before: the folded 16-bit matrix through L2, bound by its request rate.  Both launches together, seeded orders: N = 1024,
-// 65536 orders 1384 -> 146 us (1.9 TB/s of the order stream), 1000 orders 104 -> 28 us; N = 512, 131072 orders
-// 1136 -> 147 us, 1000 orders 27 -> 17 us.  Orders without any marked link, every link looked up: N = 1024, 65536 orders
+// 65536 orders 1384 -> 138 us (1.9 TB/s of the order stream), 1000 orders 104 -> 23 us; N = 512, 131072 orders
+// 1136 -> 142 us, 1000 orders 27 -> 16 us.  Orders without any marked link, every link looked up: N = 1024, 65536 orders
 // 1213 -> 1227 us, N = 512 458 -> 455 us.  So nothing else serves these sizes.
 template <int LOGN>
 __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kernel(
@@ -1263,7 +1267,9 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     for (int e = threadIdx.x; e < N * N / 128; e += 64 * WAVES) ((int4*)lmarks)[e] = ((const int4*)marks)[e];
     int top = 0;
-    for (int k = 0; k < kMarkBlocks; ++k) top = max(top, tops[k]);
+#pragma unroll
+    for (int k = 0; k < kMarkBlocks; k += 64) top = max(top, tops[k + lane]);
+    top = wave_max(top);
     const long long weight =
         lane < LOGN ? (weights ? (long long)clampi(weights[lane], 0, kMaxRoundWeight) : 1ll) : 0ll;
     __syncthreads();
@@ -1382,9 +1388,10 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
 }
 
 template <int LOGN>
-static hipError_t rd_marked_launch(const int32_t* c, void* room, int32_t* tops, const int32_t* weights,
+static hipError_t rd_marked_launch(const int32_t* c, void* room, const int32_t* weights,
                                    const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
     constexpr int N = 1 << LOGN, WAVES = LOGN == 10 ? 15 : 16;
+    int32_t* tops = (int32_t*)((char*)room + mark_tops_offset(N));
     const size_t lds = N * N / 8 + sizeof(uint16_t) * WAVES * N + sizeof(int) * WAVES * 16;
     hipError_t e = hipFuncSetAttribute((const void*)rd_batch_marked_kernel<LOGN>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1510,8 +1517,8 @@ hipError_t launch_rd_cost_batch(const int32_t* c, int N, const int32_t* weights,
         if (N == 128) return links_lds16_launch<7, false>(c, weights, perms, B, out, s);
         if (N == 256) return links_lds16_launch<8, false>(c, weights, perms, B, out, s);
     }
-    if (flags && folded && N == 512) return rd_marked_launch<9>(c, folded, flags, weights, perms, B, out, s);
-    if (flags && folded && N == 1024) return rd_marked_launch<10>(c, folded, flags, weights, perms, B, out, s);
+    if (flags && folded && N == 512) return rd_marked_launch<9>(c, folded, weights, perms, B, out, s);
+    if (flags && folded && N == 1024) return rd_marked_launch<10>(c, folded, weights, perms, B, out, s);
     const int32_t* skip = nullptr;
     if (flags && folded) {
         // both kernels are enqueued; the matrix maximum, computed on the device, decides which of them works
