@@ -18,7 +18,7 @@
 // compute unit.  Whole searches, against the exhaustive kernels: undirected N = 50, 1197 restarts 587 -> 60 us, N = 256, 1024
 // restarts 1456 -> 160 us, N = 700, 100 restarts 21 -> 0.26 ms; directed, inverse bandwidths that are eight times as small
 // inside a rack, N = 100, 1000 restarts 2272 -> 205 us, N = 256, 1024 restarts 2656 -> 551 us, N = 350, 316 restarts
-// 20.4 -> 0.81 ms, N = 1023, 41 restarts 141 -> 2.8 ms; directed on a symmetric matrix, N = 256, 1024 restarts 2350 -> 252 us
+// 20.4 -> 0.71 ms, N = 1023, 41 restarts 141 -> 1.5 ms; directed on a symmetric matrix, N = 256, 1024 restarts 2350 -> 252 us
 // (fewer sweeps).
 #include "cc_device.h"
 #include "cc_internal.h"
