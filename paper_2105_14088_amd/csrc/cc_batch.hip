@@ -19,15 +19,19 @@ using namespace ccd;
 
 constexpr int kMaxRoundWeight = 1 << 30;   // round weights are clamped to [0, 2^30]: weight * cost stays below 2^51
 
-// A threshold that about `wanted` of 256 entries reach, from 4096 sampled ones, four per thread of a 1024-thread workgroup:
-// every wave takes the wanted-th largest of its 256, the result is the ninth largest of the sixteen values.  `v` are not
-// negative; per_wave: 16 words of LDS.  (A bit-by-bit search over all 4096, a barrier per bit, took 10 us longer.)
-__device__ __forceinline__ int sampled_threshold(int (&v)[4], int wanted, int* per_wave) {
+// A threshold that about `wanted` of 64 U entries reach, from 1024 U sampled ones, U per thread of a 1024-thread workgroup: every
+// wave takes the wanted-th largest of its 64 U, the result is the one of the sixteen values that ABOVE of them exceed.  `v` are
+// not negative; per_wave: 16 words of LDS.  (A bit-by-bit search over all 4096, a barrier per bit, took 10 us longer.)
+template <int ABOVE = 8, int U>
+__device__ __forceinline__ int sampled_threshold(int (&v)[U], int wanted, int* per_wave) {
     int T = 0;
     for (int seen = 0; seen < wanted;) {
-        T = wave_max(max(max(v[0], v[1]), max(v[2], v[3])));
+        int largest = v[0];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 1; i < U; ++i) largest = max(largest, v[i]);
+        T = wave_max(largest);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
             seen += __popcll(__ballot(v[i] == T));
             if (v[i] == T) v[i] = -1;
         }
@@ -38,7 +42,7 @@ __device__ __forceinline__ int sampled_threshold(int (&v)[4], int wanted, int* p
     int above = 0;
 #pragma unroll
     for (int k = 0; k < 16; ++k) above += per_wave[k] > mine || (per_wave[k] == mine && k < sub);
-    return __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)__ballot(above == 8)) - 1);
+    return __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)__ballot(above == ABOVE)) - 1);
 }
 
 // four ranks of an order, aligned as a rank is
@@ -1163,10 +1167,15 @@ __global__ __launch_bounds__(1024) void links_batch_lds16_kernel(const int32_t* 
 
 // N = 512, 1024 with a workspace: a round costs its largest link, so only links among the largest entries have to be
 // looked up exactly.  mark_links_kernel writes one bit per pair of nodes, "the larger direction costs T or more" (128 KiB
-// at N = 1024, which fits LDS; the 16-bit folded matrix, 2 MiB, does not); T is chosen so that about ln(N / 2) of a
-// round's N / 2 links carry the bit, from the same 4096 sampled entries in every workgroup (about where the exact
-// look-ups and the rounds without a marked link, whose links are all looked up, cost the same number of requests).
-// Any T gives the right result, only the time depends on it.  Word (y >> 5) * N + x holds the pairs of x with the
+// at N = 1024, which fits LDS; the 16-bit folded matrix, 2 MiB, does not); T is chosen so that about 5 of a
+// round's N / 2 links carry the bit, from the same 2048 sampled entries in every workgroup: 4 to 7 of them take the same time
+// within 4 %, with fewer the rounds without a marked link, whose links are all looked up, cost more than the exact look-ups
+// saved (N = 512, 65536 orders, 2.6 / 4 / 5 / 8 of 256: 93 / 76 / 75 / 80 us).  Any T gives the right result, only the time
+// depends on it.  The samples lie apart, so that T does not follow how the nodes are numbered: 256 places of 4 x 4 neighbouring
+// pairs held one value sixteen times where the numbers follow the hosts, and five times as many links were marked (pairs that
+// cost what their hosts do, 65536 orders: N = 1024 187 us, now 138; N = 512 89, now 75; numbers in no order 137 and 75 either
+// way); 4096 places of their own mark no better and take 8 us to read at N = 1024.
+// Word (y >> 5) * N + x holds the pairs of x with the
 // nodes y & ~31 .. y | 31 (the folded matrix is symmetric, so a ballot over x gives the words of y).  tops[workgroup] =
 // largest entry seen, for the early end in rd_batch_marked_kernel.
 // Behind the marks (N^2 / 8 bytes) the folded entries themselves, 16 bits each, lower triangle with diagonal by rows
@@ -1178,27 +1187,27 @@ constexpr size_t mark_tops_offset(size_t N) { return N * N / 8 + N * (N + 1); }
 template <int LOGN>
 __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restrict__ c, uint32_t* __restrict__ marks,
                                                           int32_t* __restrict__ tops) {
-    constexpr int N = 1 << LOGN, kWanted = LOGN == 10 ? 3 : 5;                  // of 256 samples: 6 or 5 of N / 2
+    constexpr int N = 1 << LOGN;
+    constexpr int kWanted = LOGN == 10 ? 2 : 3;                                 // of 128 samples: 6 or 5 of N / 2
     constexpr int kRows = N * N / 64 / (16 * kMarkBlocks);                      // rows of 64 entries per wave
     uint16_t* folded = (uint16_t*)(marks + N * N / 32);
     __shared__ int per_wave[16], wave_top[16];
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     auto entry = [&](int x, int y) { return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1); };
-    int v[4];
+    int v[2];
+    {
+        // two lanes share a place: the pairs of x, x ^ 16 with y, y ^ 16, two cache lines for both directions of a lane's two
+        const uint32_t h = (uint32_t)splitmix64_at(0, (uint64_t)((threadIdx.x >> 1) + 1));
+        const int x = (h & (N - 1)) ^ ((lane & 1) << 4), y = (h >> LOGN) & (N - 1);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        // sixteen lanes a place of 4 x 4 pairs: 32 cache lines for both directions of a wave's instead of 128 (64 places a wave,
-        // read by every workgroup: the kernel 15.6 us at N = 1024, now 9.4)
-        const uint32_t h = (uint32_t)splitmix64_at(0, (uint64_t)((threadIdx.x >> 4) + 64 * i + 1));
-        const int x = (h & (N - 4)) + (lane & 3), y = ((h >> LOGN) & (N - 4)) + ((lane >> 2) & 3);
-        v[i] = entry(x, x == y ? y ^ 1 : y);
+        for (int i = 0; i < 2; ++i) v[i] = entry(x, x == (y ^ (i << 4)) ? x ^ 1 : y ^ (i << 4));
     }
     // a wave takes 64 consecutive x and kRows consecutive y, so both directions come from few cache lines
     const int w = blockIdx.x * 16 + wv, x0 = (w & (N / 64 - 1)) * 64, y0 = (w / (N / 64)) * kRows;
     int e[kRows];
 #pragma unroll
     for (int k = 0; k < kRows; ++k) e[k] = entry(x0 + lane, y0 + k);
-    const int T = sampled_threshold(v, kWanted, per_wave);
+    const int T = sampled_threshold<5>(v, kWanted, per_wave);
     int top = 0;
 #pragma unroll
     for (int k = 0; k < kRows; ++k) {

@@ -53,3 +53,28 @@ def test_rd_batch_marked_links_several_passes_weights_and_unaligned_orders(n):
     got = cc.cc_bcube_cost_batch_weighted(dev(c), 2, dev(w), view)
     torch.cuda.synchronize()
     assert np.array_equal(got.cpu().numpy(), oracle.bcube_cost_weighted_batch(c, 2, w, perms[:200]))
+
+
+@pytest.mark.parametrize("n,wanted", [(512, 0.02), (1024, 0.01)])
+@pytest.mark.parametrize("noise", [0.0, 0.05])
+@pytest.mark.parametrize("group", [4, 32])
+def test_rd_batch_marks_do_not_follow_how_nodes_are_numbered(n, wanted, noise, group):
+    """Nodes numbered by host (4) or rack (32) and pairs that cost what these do: about as many links are marked as where the
+    numbers are in no order.  2048 samples in quadruples that may hold one value put the share within a factor of 1.7 of
+    what is wanted (three standard deviations of the third of 32); 16 equal samples put it beyond a factor of 2.3."""
+    say(f"rd batch, share of marked links, N={n}, groups of {group}, noise {noise}")
+    rng = np.random.default_rng(n + group)
+    of = np.arange(n) // group
+    base = rng.integers(800, 2000, size=(n // group, n // group))
+    c = base[of][:, of] * np.exp(noise * rng.standard_normal((n, n)))
+    c = np.triu(np.rint(c), 1).astype(np.int32)
+    c = c + c.T
+    for numbering in (np.arange(n), rng.permutation(n)):
+        m = np.ascontiguousarray(c[numbering][:, numbering])
+        perms = random_perms(n, 16, seed=n)
+        room = torch.zeros(cc.cc_rd_batch_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+        got = cc.cc_rd_cost_batch(dev(m), dev(perms), workspace=room)
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), oracle.rd_cost_batch(m, perms))
+        share = np.unpackbits(room[: n * n // 8].cpu().numpy()).mean()
+        assert wanted / 3 < share < wanted * 1.9, share
