@@ -180,18 +180,21 @@ struct LdsWords {                       // folded int32 in LDS
     int log_n;
     __device__ __forceinline__ int at(int x, int y) const { return m[(x << log_n) | y]; }
     static constexpr bool kRows = false;
+    static constexpr bool kScattered = false;
 };
 struct LdsHalves {                      // folded 16-bit in LDS
     const uint16_t* m;
     int log_n;
     __device__ __forceinline__ int at(int x, int y) const { return m[(x << log_n) | y]; }
     static constexpr bool kRows = false;
+    static constexpr bool kScattered = false;
 };
 struct GlobalHalves {                   // folded 16-bit copy in the workspace
     const uint16_t* m;
     int log_n;
     __device__ __forceinline__ int at(int x, int y) const { return m[(x << log_n) | y]; }
     static constexpr bool kRows = true;
+    static constexpr bool kScattered = false;
 };
 struct GlobalWords {                    // the caller's matrix, folded as it is read
     const int32_t* m;
@@ -200,6 +203,7 @@ struct GlobalWords {                    // the caller's matrix, folded as it is 
         return max(clampi(m[(x << log_n) | y], 0, kCostMax), clampi(m[(y << log_n) | x], 0, kCostMax));
     }
     static constexpr bool kRows = true;
+    static constexpr bool kScattered = true;      // some look-ups take a cache line per lane
 };
 
 // LDS words of a workgroup besides the matrix: order, link values, inverse order (the two orders twice) and rows of two scanned
@@ -233,9 +237,9 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
     __shared__ int4 scan_a[SW][kPicks][LOGN];          // for a scanned end: {largest other link's name, its value, the next value, mate's node}
     __shared__ int scan_b[SW][kPicks][LOGN];           // value 1
     __shared__ unsigned long long red[3];
-    // the order, and what it becomes while every wave still reads the nodes that move; it is a swap behind
-    int32_t *t = state, *t_next = t + N;               // [N]
-    int32_t* links = t_next + N;                       // [LOGN][HALF] keys
+    // the order, and what it becomes while every wave still reads the nodes that move; it is a swap behind (one wave: the same)
+    int32_t *t = state, *t_next = NW > 1 ? t + N : t;  // [N]
+    int32_t* links = t + 2 * N;                        // [LOGN][HALF] keys
     int32_t *pos = links + LOGN * HALF, *pos_next = pos + N;           // [N] (kRows) rank of a node, -1: none
     int32_t* rows = pos_next + N;                      // [kPicks][N] (kRows)
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -244,7 +248,8 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
     auto link_of = [](int p, int k) { return ((p >> (k + 1)) << k) | (p & ((1 << k) - 1)); };
 
     for (int p = tid; p < N; p += THREADS) {
-        t[p] = t_next[p] = clampi(tour[p], 0, N - 1);
+        t[p] = clampi(tour[p], 0, N - 1);
+        if (NW > 1) t_next[p] = t[p];
         if (MAT::kRows) pos[p] = -1;
     }
     if (tid < 3) red[tid] = ~0ull;
@@ -285,6 +290,10 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
     constexpr int kPerWave = (LOGN + NW - 1) / NW;     // rounds whose largest links a wave keeps up to date
     constexpr int kBatch = kPerWave < 3 ? kPerWave : 3;
     unsigned dirty = (1u << LOGN) - 1u;                // of this wave's rounds
+    // Pairs beside the first scan are bounded by less than pairs behind the last one.  Where their look-ups share the caches with those
+    // of many restarts, they come last (entries from 2^16 up, beside / last: N = 1024, 16 restarts 6.93 / 7.17 ms, 64 restarts 8.34 /
+    // 8.12, 256 restarts 13.9 / 12.6; N = 512, 64 restarts 5.2 / 5.8, 256 restarts 7.9 / 7.5, 1024 restarts 23.8 / 22.8).
+    const bool pairs_beside = !MAT::kScattered || LOGN < 9 || gridDim.x <= (LOGN == 9 ? 128 : 32);
     int applied = 0, cur = -1, last_p = 0, last_q = 0, last_a = t[0], last_b = t[0];
     for (;;) {
         // ---- the three largest links of the rounds that may have new ones
@@ -345,7 +354,7 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
         // ---- scans: two ends at a time, in falling order of G, against every rank
         bool seen = lane >= kEnds;
         int best_hi = cur, best_id = 0;                // a winner has a total below cur
-        for (bool first = true;; first = false) {
+        for (bool pairs_left = true;;) {
             int pick[kPicks] = {};
             int n = 0;
             if (__ballot(!seen && gain > 0 && cur - gain <= best_hi))
@@ -359,7 +368,9 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
                     n = s + 1;
                 }
             }
-            const unsigned long long left = first ? __ballot(!seen) : 0;
+            const bool pairs_now = pairs_left && (pairs_beside || n == 0);
+            const unsigned long long left = pairs_now ? __ballot(!seen) : 0;
+            pairs_left = pairs_left && !pairs_now;
             if (n == 0 && !left) break;
             if (MAT::kRows && n) {
                 for (int i = tid; i < n * N; i += THREADS) rows[i] = mat.at(t[i < N ? pick[0] : pick[1]], i & (N - 1));
@@ -409,7 +420,7 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
                 __builtin_amdgcn_wave_barrier();
             }
             // ---- pairs that move two large links at once: an end of a round's largest and one of its second largest link, or
-            // two ends of largest links; pairs with an end of the first scan are known already
+            // two ends of largest links; pairs with an end scanned before or beside them are known already
             if (left && (PAIRS == 0 || wv >= SW)) {
                 constexpr int kSameRound = 4 * LOGN, kAtOnce = kPairThreads / kPairLanes;
                 const int bound = PAIRS ? hi : wave_min(hi);
@@ -470,7 +481,9 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
 #pragma unroll
             for (int j = 0; j < kPerWave; ++j) dirty |= ((bits >> (2 * j)) & 3) ? 1u << (k0 + j) : 0u;
         }
-        if (wv == 0) {
+        if (NW == 1) {
+            if (lane < 2) t[lane ? sq : sp] = lane ? a : b;
+        } else if (wv == 0) {
             if (lane < 4) {
                 // this swap and the one before, which the other copy has not seen
                 const int x = lane & 2 ? (lane & 1 ? sq : sp) : (lane & 1 ? last_q : last_p);
@@ -486,7 +499,7 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
             last_a = a;
             last_b = b;
         }
-        {
+        if (NW > 1) {
             int32_t* const was = t;
             t = t_next;
             t_next = was;

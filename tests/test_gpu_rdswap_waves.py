@@ -28,3 +28,19 @@ def test_every_number_of_wavefronts(n, restarts):
             assert costs[r] == oc[0] and moves[r] == om[0] and np.array_equal(tours[r], ot[0])
         k = int(np.argmin(costs))
         assert int(b.best_restart.item()) == k and int(b.best_cost.item()) == costs[k]
+
+
+@pytest.mark.parametrize("n,restarts", [(512, 128), (512, 129), (512, 257), (1024, 32), (1024, 33), (1024, 257)])
+def test_pairs_beside_and_after_the_scans(n, restarts):
+    """Equal values, and entries from 2^16 up, where the pairs come beside the scans or after them by the number of restarts; above
+    256 restarts no wavefronts are there for them."""
+    ties = random_matrix(n, n, symmetric=True, lo=0, hi=400)
+    for c, tag in [(ties, "ties"), (ties * 4000, "ties beyond 2^16")] + \
+                  ([(random_matrix(n, n, symmetric=False, lo=0, hi=1 << 20), "beyond 2^16")] if n == 512 else []):
+        say(f"pair swaps, pairs beside or after the scans N={n} R={restarts} {tag}")
+        b = cc.cc_rd_swap_search_ex(dev(c), restarts, 9)
+        torch.cuda.synchronize()
+        r = restarts - 1
+        oc, ot, om = oracle.rd_swap_restarts(c, 9, r, r + 1)
+        assert int(b.restart_costs[r].item()) == oc[0] and int(b.restart_moves[r].item()) == om[0]
+        assert np.array_equal(b.restart_tours[r].cpu().numpy(), ot[0])
