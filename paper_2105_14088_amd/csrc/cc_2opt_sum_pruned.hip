@@ -53,7 +53,10 @@ __host__ __device__ constexpr size_t order_bytes(int N) { return ((size_t)N * 8 
 __host__ __device__ constexpr size_t group_order_bytes(int N) { return order_bytes(N) + (((size_t)N * 2 + 15) & ~(size_t)15); }
 constexpr int kGroupAtOnce = 3;         // times 64 candidates
 constexpr int kGroupPassed = 64 * (kGroupAtOnce + 1);
-__host__ __device__ constexpr size_t group_wave_bytes(int room) { return (size_t)room * 2 + kGroupPassed * 8; }
+// entries: a passed candidate is kept with its entry of the list (eight bytes), else by its place in the lists (four)
+__host__ __device__ constexpr size_t group_wave_bytes(int room, bool entries) {
+    return (size_t)room * 2 + kGroupPassed * (entries ? 8 : 4);
+}
 
 // What the waves of one restart tell each other
 template <int WAVES>
@@ -66,7 +69,7 @@ struct GroupWords {
 
 // One descent.  A node's scale (of its buckets) is scale0 (one node per lane) or scales[node].  Wave `wv` of the restart
 // owns the nodes 64 * (wv * K + k) + lane.
-template <int WAVES, int K, int ROOM, typename COUNT, class MAT>
+template <int WAVES, int K, int ROOM, bool ENTRIES, typename COUNT, class MAT>
 __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __restrict__ lists, int M,
                                         const COUNT* __restrict__ counts, int scale0, const uint16_t* scales, unsigned char* order_mem,
                                         unsigned char* wave_mem, GroupWords<WAVES>* group, int wv, int lane,
@@ -82,7 +85,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
     uint16_t* owner = (uint16_t*)wave_mem;                     // [ROOM] stamp << 6 | lane
     // [kPassed] x | place << 10 | sides << 21; place: in the list of x, or M + y for a node scanned against every node
     uint32_t* passed = (uint32_t*)(wave_mem + ROOM * 2);
-    uint2* passed_entries = (uint2*)passed;                    // GROUP: [kGroupPassed] x | sides << 21, cost << 10 | y
+    uint2* passed_entries = (uint2*)passed;                    // ENTRIES: [kGroupPassed] x | sides << 21, cost << 10 | y
     uint16_t* starts = (uint16_t*)(order_mem + order_bytes(N));                    // GROUP: [N] place of a node's first candidate
     const int tid = wv * 64 + lane;
     auto list_entry = [&](unsigned at) { return *(const uint32_t*)((const char*)lists + at * 4u); };
@@ -214,7 +217,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
         auto score = [&](int from, int n) {
             const bool live = lane < n;
             int x, y, sides, cost;
-            if (GROUP) {
+            if (ENTRIES) {
                 const uint2 w = passed_entries[from + (live ? lane : 0)];
                 x = (int)(w.x & 1023u);
                 sides = (int)(w.x >> 21);
@@ -253,7 +256,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             if (__ballot(live && sides == 3)) side(sides != 3);        // the other side of those; of the others, any
         };
         // Notes the pair x, y of cost e >> 10 if a bracket of it passes; the node with the longer removed edge looks at it.  Side bits: 1
-        // the edges behind x and y, 2 those before; place: where the list has y (GROUP: unused).  No branches but the store:
+        // the edges behind x and y, 2 those before; place: where the list has y (ENTRIES: unused).  No branches but the store:
         // with one per condition a candidate took half as many instructions again.
         auto look = [&](bool live, uint2 ix, uint2 iy, uint32_t e, int x, int place) {
             const int ox = hop_out(ix), oy = hop_out(iy), nx = hop_in(ix), ny = hop_in(iy), least = (int)((e >> 9) & ~1u) - D;
@@ -262,7 +265,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             if (out | in) {
                 const unsigned at = (unsigned)(n_passed + lanes_below(mask));
                 const unsigned who = (unsigned)x | (out ? 1u << 21 : 0u) | (in ? 2u << 21 : 0u);
-                if (GROUP) passed_entries[at] = make_uint2(who, e);
+                if (ENTRIES) passed_entries[at] = make_uint2(who, e);
                 else passed[at] = who | ((unsigned)place << 10);
             }
             n_passed += __popcll(mask);
@@ -317,7 +320,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
                 const int nx = x_first + (int)__builtin_ctzll(rest);
                 rest &= rest - 1;
                 const uint2 jx = info[nx];
-                constexpr int U = GROUP ? kGroupAtOnce : 4;
+                constexpr int U = GROUP ? 2 : 4;               // four times 64 nodes of N = 256 (three at a time: N = 225, 300 restarts 1.47 ms, 1.41)
                 for (int y0 = 0; y0 < N; y0 += 64 * U) {
                     int cost[U];
 #pragma unroll
@@ -354,7 +357,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
                     first[u] = 64 * w;
                     live[u] = __builtin_amdgcn_readlane(laid_out, w) - i0;
                     place[u] = i0 + lane;
-                    src[u] = ((const uint16_t*)(wave_mem + (w - wv) * (int)group_wave_bytes(ROOM)))[place[u]];
+                    src[u] = ((const uint16_t*)(wave_mem + (w - wv) * (int)group_wave_bytes(ROOM, ENTRIES)))[place[u]];
                 }
                 // marks of earlier layouts are smaller than this one's, and the first of the 64 is always marked
 #pragma unroll
@@ -369,7 +372,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
 #pragma unroll
                 for (int u = 0; u < U; ++u) jy[u] = info[e[u] & 1023u];
 #pragma unroll
-                for (int u = 0; u < U; ++u) look(lane < live[u], jx[u], jy[u], e[u], (int)src[u], 0);
+                for (int u = 0; u < U; ++u) look(lane < live[u], jx[u], jy[u], e[u], (int)src[u], place[u] - from[u]);
             };
             // one after the other in turn: the candidates of a node that most is scored of lie side by side
             for (int g = wv; g < blocks; g += kGroupAtOnce * WAVES) {
@@ -482,7 +485,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
 
 // N <= 64 K: a workgroup holds the lists in LDS (and the matrix as 16-bit entries when lds_matrix is set and its entries
 // allow) for `waves` restarts of one wavefront each, or (WAVES > 1) for one restart of WAVES wavefronts.
-template <int E, int WAVES>
+template <int E, int WAVES, bool ENTRIES>
 __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* __restrict__ c, int N, int M, int lds_matrix,
                                                                  int waves, int restarts, int32_t* __restrict__ tours,
                                                                  int64_t* __restrict__ costs,
@@ -525,14 +528,14 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
     if (r >= restarts) return;
     const int mine = WAVES > 1 ? 0 : wv, part = WAVES > 1 ? wv : 0;
     unsigned char* order_mem = rest + (size_t)mine * (order_bytes(N) + wave_bytes(kRoom));
-    unsigned char* wave_mem = WAVES > 1 ? order_mem + group_order_bytes(N) + (size_t)part * group_wave_bytes(kRoom)
+    unsigned char* wave_mem = WAVES > 1 ? order_mem + group_order_bytes(N) + (size_t)part * group_wave_bytes(kRoom, ENTRIES)
                                         : order_mem + order_bytes(N);
     const int scale0 = (int)scales[min(64 * part + lane, N - 1)];
     if (in_lds)
-        descend<WAVES, K, kRoom>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
+        descend<WAVES, K, kRoom, ENTRIES>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
                           tours + r * N, costs + r, moves + r);
     else
-        descend<WAVES, K, kRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
+        descend<WAVES, K, kRoom, ENTRIES>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
                           tours + r * N, costs + r, moves + r);
 }
 
@@ -566,19 +569,19 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(80))) vo
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
     const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
-    descend<WAVES, 1, kGroupRoom>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
-                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom), &group, wv, lane, tours + r * N, costs + r,
+    descend<WAVES, 1, kGroupRoom, true>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
+                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom, true), &group, wv, lane, tours + r * N, costs + r,
                                   moves + r);
 }
 
-template <int E, int WAVES>
+template <int E, int WAVES, bool ENTRIES>
 hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, int restarts, int32_t* tours, int64_t* costs,
                       int32_t* moves, const int32_t* skip_if_small, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<E, WAVES>,
+    hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<E, WAVES, ENTRIES>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.bytes);
     if (e != hipSuccess) return e;
     const int grid = WAVES > 1 ? restarts : (restarts + plan.waves - 1) / plan.waves;
-    hipLaunchKernelGGL((twoopt_sum_pruned_kernel<E, WAVES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
+    hipLaunchKernelGGL((twoopt_sum_pruned_kernel<E, WAVES, ENTRIES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
                        s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves, skip_if_small);
     return hipGetLastError();
 }
@@ -590,11 +593,17 @@ hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, i
     // room (4 / 8 / 12 / 16 waves: N = 150, 200 restarts 612 / 579 / 610 / 650 us; N = 256, 200 restarts 1526 / 1335 / 1319 / 1550; two
     // restarts per unit: N = 150, 500 restarts 696 / 723 / 876 / 1230).
     constexpr int kOne = 8, kTwo = 4;
-    auto state = [&](int waves) { return group_order_bytes(N) + waves * group_wave_bytes(kRoom); };
-    const LdsPlan plan = lds_plan(N, restarts, order_bytes(N), Groups{2, false, {kOne, kTwo}, {state(kOne), state(kTwo)}});
-    if (!plan.together) return launch_lds<E, 1>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
-    return plan.waves == kOne ? launch_lds<E, kOne>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s)
-                         : launch_lds<E, kTwo>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    // Two restarts per unit above N = 208: what passes is noted by its place, so that the lists have room for four to six partners more
+    // per node (with the entry / by place: N = 200, 300 restarts 1082 / 1091 us, zones of equal costs 425 / 439; N = 225 1411 / 1354, zones
+    // 484 / 498; N = 250 2048 / 1856; N = 255, whose lists would be too short for two at a time, zones 898 / 580).
+    const bool places = E == 4 && N > 208;
+    auto state = [&](int waves, bool entries) { return group_order_bytes(N) + waves * group_wave_bytes(kRoom, entries); };
+    const LdsPlan plan = lds_plan(N, restarts, order_bytes(N), Groups{2, false, {kOne, kTwo}, {state(kOne, true), state(kTwo, !places)}});
+    if (!plan.together) return launch_lds<E, 1, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    if (plan.waves == kOne) return launch_lds<E, kOne, true>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    if constexpr (E == 4)
+        if (places) return launch_lds<E, kTwo, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    return launch_lds<E, kTwo, true>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
 }
 
 template <int WAVES>
@@ -605,7 +614,7 @@ hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32
     const uint16_t* counts;
     hipError_t e = launch_partner_lists(c, N, room, M, lists, counts, s);
     if (e != hipSuccess) return e;
-    const size_t lds = group_order_bytes(N) + WAVES * group_wave_bytes(kGroupRoom);
+    const size_t lds = group_order_bytes(N) + WAVES * group_wave_bytes(kGroupRoom, true);
     e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

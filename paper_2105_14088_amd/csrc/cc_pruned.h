@@ -180,7 +180,8 @@ inline LdsPlan lds_plan(int N, int restarts, size_t order_bytes, const Groups& g
     };
     if (per_unit <= groups.most_per_unit)
         for (int at_a_time = per_unit > 1 ? 2 : 1; at_a_time >= 1; --at_a_time) {
-            const size_t state = groups.state[at_a_time - 1], all = kLds / at_a_time - 1024, room = all > state ? all - state : 0;
+            // 1024 bytes for a unit's words outside the plan
+            const size_t state = groups.state[at_a_time - 1], all = (kLds - 1024) / at_a_time, room = all > state ? all - state : 0;
             p.together = true;
             p.waves = groups.waves[at_a_time - 1];
             const int forms[3] = {1, groups.triangle ? 2 : 0, 0};

@@ -26,3 +26,9 @@ def test_every_number_of_wavefronts(n, restarts):
             costs, tours, moves = oracle.restarts(c, oracle.SUM, 21, r, r + 1)
             assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0]
             assert np.array_equal(got["tours"][r], tours[0])
+
+
+@pytest.mark.parametrize("n,restarts", [(200, 300), (208, 257), (209, 257), (225, 512), (246, 300), (255, 257), (256, 300)])
+def test_two_restarts_per_unit_with_short_lists(n, restarts):
+    """Passed candidates by entry and by place, lists so short that many nodes are scanned against every node."""
+    test_every_number_of_wavefronts(n, restarts)
