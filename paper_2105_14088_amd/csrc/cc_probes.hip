@@ -67,15 +67,14 @@ __device__ __forceinline__ int bits_of(int x) { return x > 0 ? 32 - __clz(x) : 0
 
 // The pairs a < b of N nodes on a grid of full rows: row y holds the pairs of node y and, in the columns these leave, those of
 // the node as far from the other end.
-__host__ __device__ constexpr int pair_columns(int N) { return N | 1; }
+__host__ __device__ constexpr int pair_columns(int N) { return (N - 1) | 1; }
 __host__ __device__ constexpr int pair_rows(int N) { return N / 2; }
-__device__ __forceinline__ bool pair_of(int x, int y, int N, int& a, int& b) {
-    // N | 1 columns: with N odd the N - 1 - y pairs of node y and the y + 1 of node N - 2 - y; with N even the y
-    // pairs of node N - 1 - y, one column left over
+__device__ __forceinline__ void pair_of(int x, int y, int N, int& a, int& b) {
+    // with N odd N columns, the N - 1 - y pairs of node y and the y + 1 of node N - 2 - y; with N even N - 1, the y pairs of node
+    // N - 1 - y instead; every workgroup has a pair
     const int first = N - 1 - y;
     a = x < first ? y : (N & 1 ? N - 2 - y : N - 1 - y);
     b = x < first ? y + 1 + x : a + 1 + x - first;
-    return b < N;
 }
 
 // Chunk of 256 samples that pilot register i takes its sample from in the lanes whose number is j modulo 16 / PILOT: sixteen
@@ -107,7 +106,7 @@ __global__ __launch_bounds__(128, CH <= 48 ? (CH <= 24 ? 3 : 2) : 1) void probes
     __shared__ unsigned inside_all[2][PILOT ? ROOM + 4 : 1][64];
     const int lane = threadIdx.x & 63, dir = threadIdx.x >> 6;
     int a, b;
-    if (!pair_of(blockIdx.x, blockIdx.y, N, a, b)) return;
+    pair_of(blockIdx.x, blockIdx.y, N, a, b);
     const int from = dir ? b : a, to = dir ? a : b;
     const int32_t* src = samples + ((int64_t)from * N + to) * K;
     int4 v[CH];

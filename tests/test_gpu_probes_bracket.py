@@ -52,8 +52,9 @@ def test_forms_and_sequences_a_pilot_does_not_describe(k):
 def test_every_pair_of_odd_and_even_n_is_written(n):
     say(f"probes bracket N={n} K=1100")
     s = np.random.default_rng(n).integers(1, 30000, size=(n, n, 1100)).astype(np.int32)
-    out = torch.full((n, n), -1, dtype=torch.int32, device="cuda")
-    got = cc.cc_cost_matrix_from_probes(dev(s), 25, False)
-    out.copy_(got)
-    torch.cuda.synchronize()
-    assert np.array_equal(out.cpu().numpy(), oracle.cost_matrix_from_probes(s, 25, False))
+    for symmetrize in (False, True):
+        out = torch.full((n, n), -1, dtype=torch.int32, device="cuda")
+        got = cc.cc_cost_matrix_from_probes(dev(s), 25, symmetrize, out=out)
+        torch.cuda.synchronize()
+        assert got is out
+        assert np.array_equal(out.cpu().numpy(), oracle.cost_matrix_from_probes(s, 25, symmetrize))
