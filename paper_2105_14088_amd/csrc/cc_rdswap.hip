@@ -292,8 +292,9 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
     unsigned dirty = (1u << LOGN) - 1u;                // of this wave's rounds
     // Pairs beside the first scan are bounded by less than pairs behind the last one.  Where their look-ups share the caches with those
     // of many restarts, they come last (entries from 2^16 up, beside / last: N = 1024, 16 restarts 6.93 / 7.17 ms, 64 restarts 8.34 /
-    // 8.12, 256 restarts 13.9 / 12.6; N = 512, 64 restarts 5.2 / 5.8, 256 restarts 7.9 / 7.5, 1024 restarts 23.8 / 22.8).
-    const bool pairs_beside = !MAT::kScattered || LOGN < 9 || gridDim.x <= (LOGN == 9 ? 128 : 32);
+    // 8.12, 256 restarts 13.9 / 12.6; N = 512, 64 restarts 5.2 / 5.8, 256 restarts 7.9 / 7.5, 1024 restarts 23.8 / 22.8).  A wavefront
+    // alone, 4096 restarts: N = 32 237 / 232 us, but N = 16 88 / 96 and N = 8 32.4 / 32.7.
+    const bool pairs_beside = NW == 1 ? LOGN != 5 : !MAT::kScattered || LOGN < 9 || gridDim.x <= (LOGN == 9 ? 128 : 32);
     int applied = 0, cur = -1, last_p = 0, last_q = 0, last_a = t[0], last_b = t[0];
     for (;;) {
         // ---- the three largest links of the rounds that may have new ones
@@ -520,8 +521,9 @@ __device__ __forceinline__ void descend_pruned(const MAT mat, int32_t* state, in
     }
 }
 
-template <int LOGN, int SCAN, int PAIRS>
-__global__ __launch_bounds__(SCAN + PAIRS, LOGN <= 6 ? 5 : 1) void rdswap_pruned_kernel(const int32_t* __restrict__ c,
+// ON_SIMD: wavefronts that find room on a SIMD at least
+template <int LOGN, int SCAN, int PAIRS, int ON_SIMD>
+__global__ __launch_bounds__(SCAN + PAIRS, ON_SIMD) void rdswap_pruned_kernel(const int32_t* __restrict__ c,
                                                                 const uint16_t* __restrict__ folded,
                                                                 int32_t* __restrict__ tours, int64_t* __restrict__ costs,
                                                                 int32_t* __restrict__ moves,
@@ -572,17 +574,17 @@ __global__ __launch_bounds__(SCAN + PAIRS, LOGN <= 6 ? 5 : 1) void rdswap_pruned
     }
 }
 
-template <int LOGN, int SCAN, int PAIRS = 0>
+template <int LOGN, int SCAN, int PAIRS, int ON_SIMD = LOGN <= 6 ? 5 : 1>
 hipError_t rdswap_pruned_launch(const int32_t* c, const uint16_t* folded, int restarts, int32_t* tours, int64_t* costs,
                                 int32_t* moves, const int32_t* flags, hipStream_t s) {
     constexpr size_t N = (size_t)1 << LOGN;
     const size_t lds = swap_state_words(LOGN, LOGN >= 8) * 4 + (LOGN <= 7 ? 4 * N * N : LOGN == 8 ? 2 * N * N : 0);
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void*)rdswap_pruned_kernel<LOGN, SCAN, PAIRS>,
+        hipError_t e = hipFuncSetAttribute((const void*)rdswap_pruned_kernel<LOGN, SCAN, PAIRS, ON_SIMD>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((rdswap_pruned_kernel<LOGN, SCAN, PAIRS>), dim3(restarts), dim3(SCAN + PAIRS), lds, s, c, folded, tours, costs,
+    hipLaunchKernelGGL((rdswap_pruned_kernel<LOGN, SCAN, PAIRS, ON_SIMD>), dim3(restarts), dim3(SCAN + PAIRS), lds, s, c, folded, tours, costs,
                        moves, flags);
     return hipGetLastError();
 }
@@ -618,14 +620,20 @@ hipError_t launch_rdswap(const int32_t* c, int N, int restarts, uint64_t seed, b
     // restarts 2+3 199, 2+2 204, 2+0 238, 1+0 320, 1280 restarts 385 / 286 / 298 / 392, 2048 restarts 559 / 402 / 327 / 398; N = 128,
     // 256 restarts 4+4 425, 4+2 482, 4+0 501, 2048 restarts 1591 / 1942 / 1799; N = 512, 256 restarts 8+4 3168, 8+0 3550, 4+4
     // 3862, 512 restarts 5663 / 3999 / 4081; N = 1024, 256 restarts 8+4 3990, 8+0 4546, 512 restarts 7295 / 6358.
-#define CC_SWAP(LOGN, SCAN, PAIRS) rdswap_pruned_launch<LOGN, SCAN, PAIRS>(c, mat16, restarts, tours, costs, moves, flags, s)
+    // Two or three wavefronts each are the faster as long as all restarts are on the chip at once: 9 of three on a unit at N = 8 (2+1 /
+    // 1+0: 2304 restarts 27.5 / 28.0, 3072 32.9 / 28.5), 10 of two at N = 32 (2+0 / 1+0: 2560 restarts 163 / 199, 3072 229 / 229).
+    // At N = 64 registers for five wavefronts on a SIMD are three to six too few; four, where that is room enough (five / four: 256 restarts
+    // 273 / 258, 512 285 / 270, 768 301 / 395; 2+2 1280 restarts 317 / 393; 2+0 2048 restarts 371 / 368, 4096 643 / 629).
+#define CC_SWAP(LOGN, SCAN, ...) rdswap_pruned_launch<LOGN, SCAN, __VA_ARGS__>(c, mat16, restarts, tours, costs, moves, flags, s)
     switch (N) {
         case 2: return CC_SWAP(1, 64, 0);
         case 4: return CC_SWAP(2, 64, 0);
-        case 8: return restarts <= 3072 ? CC_SWAP(3, 128, 64) : CC_SWAP(3, 64, 0);
+        case 8: return restarts <= 2304 ? CC_SWAP(3, 128, 64) : CC_SWAP(3, 64, 0);
         case 16: return restarts <= 1536 ? CC_SWAP(4, 128, 128) : restarts <= 3072 ? CC_SWAP(4, 128, 0) : CC_SWAP(4, 64, 0);
-        case 32: return restarts <= 768 ? CC_SWAP(5, 128, 192) : restarts <= 3072 ? CC_SWAP(5, 128, 0) : CC_SWAP(5, 64, 0);
-        case 64: return restarts <= 768 ? CC_SWAP(6, 128, 192) : restarts <= 1280 ? CC_SWAP(6, 128, 128) : CC_SWAP(6, 128, 0);
+        case 32: return restarts <= 768 ? CC_SWAP(5, 128, 192) : restarts <= 2560 ? CC_SWAP(5, 128, 0) : CC_SWAP(5, 64, 0);
+        case 64:
+            if (restarts <= 512) return CC_SWAP(6, 128, 192, 4);
+            return restarts <= 768 ? CC_SWAP(6, 128, 192) : restarts <= 1280 ? CC_SWAP(6, 128, 128) : CC_SWAP(6, 128, 0, 4);
         case 128: return CC_SWAP(7, 256, 256);
         case 256: return CC_SWAP(8, 512, 320);
         case 512: return restarts <= 256 ? CC_SWAP(9, 512, 256) : CC_SWAP(9, 512, 0);

@@ -12,7 +12,8 @@ pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
 
 
 @pytest.mark.parametrize("n,restarts", [(8, 3072), (8, 3073), (16, 1536), (16, 1537), (16, 3073), (32, 768), (32, 769), (32, 3073), (64, 768),
-                                        (64, 769), (64, 1281), (128, 257), (256, 257), (512, 2), (512, 257), (1024, 1), (1024, 257)])
+                                        (64, 769), (64, 1281), (128, 257), (256, 257), (512, 2), (512, 257), (1024, 1), (1024, 257),
+                                        (8, 2304), (8, 2305), (32, 2560), (32, 2561), (64, 512), (64, 513)])
 def test_every_number_of_wavefronts(n, restarts):
     matrices = [(hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, False, n), "racks")]
     if n < 512:
