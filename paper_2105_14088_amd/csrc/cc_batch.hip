@@ -1765,15 +1765,13 @@ hipError_t launch_bcube_cost_batch(const int32_t* c, int N, int base, const int3
 // depend on the order: their places in LDS are found once.  (5 + 2^(REST + 1) - 1) look-ups per lane for 2 (N - 1) edges; what
 // bounds it is the rate of scattered requests to the L2 (about 3e11 a second).  Every rank walking its whole path -> this kernel: N = 1000,
 // 65000 orders 851 -> 544 us, 1000 orders 72 -> 13 us; N = 500, 65000 orders 338 -> 244 us; N = 300, 16000 orders 51 -> 38 us.
+// `order`: N + N / 32 + 1 words for this wave, number `wave` of nwaves.
 template <int REST>
-__global__ __launch_bounds__(256) void dbt_batch_kernel(const int32_t* __restrict__ c, int N,
-                                                        const int32_t* __restrict__ perms, int64_t B,
-                                                        int64_t* __restrict__ out) {
+__device__ __forceinline__ void dbt_wave_per_order(const int32_t* __restrict__ c, int N, const int32_t* __restrict__ perms, int64_t B,
+                                                   int64_t* __restrict__ out, int32_t* order, int64_t wave, int64_t nwaves) {
     constexpr int SUB = (2 << REST) - 1;                   // places of a subtree, heap order: 0; 1, 2; 3 .. 6; ..
     constexpr int CHUNKS = REST < 5 ? 1 << REST : 16;      // 64 ranks each
-    extern __shared__ int32_t sm[];
     const int lane = lane_id(), shift = lane >> 5;
-    int32_t* order = sm + (threadIdx.x >> 6) * (N + N / 32 + 1);
     // one word left out behind every 32: the places of a level lie N / 32 ranks apart
     auto place = [](int rank) { return rank + (rank >> 5); };
     auto rank_at = [&](int position) { return position + shift >= N ? position + shift - N : position + shift; };
@@ -1808,8 +1806,6 @@ __global__ __launch_bounds__(256) void dbt_batch_kernel(const int32_t* __restric
             sub[h] = place(rank_at(in_sub[h] ? (first[h] + last[h]) >> 1 : 0));
         }
     }
-    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
     int next[CHUNKS];
     auto request = [&](int64_t b) {
         const int32_t* pi = perms + (b < B ? b : B - 1) * N;
@@ -1853,6 +1849,15 @@ __global__ __launch_bounds__(256) void dbt_batch_kernel(const int32_t* __restric
 }
 
 template <int REST>
+__global__ __launch_bounds__(256) void dbt_batch_kernel(const int32_t* __restrict__ c, int N,
+                                                        const int32_t* __restrict__ perms, int64_t B,
+                                                        int64_t* __restrict__ out) {
+    extern __shared__ int32_t sm[];
+    dbt_wave_per_order<REST>(c, N, perms, B, out, sm + (threadIdx.x >> 6) * (N + N / 32 + 1),
+                             (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), (int64_t)gridDim.x * 4);
+}
+
+template <int REST>
 static hipError_t dbt_launch(const int32_t* c, int N, const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
     const size_t lds = sizeof(int32_t) * 4 * (size_t)(N + N / 32 + 1);
     hipLaunchKernelGGL(dbt_batch_kernel<REST>, dim3(batch_grid(4, B)), dim3(256), lds, s, c, N, perms, B, out);
@@ -1868,8 +1873,10 @@ static hipError_t dbt_launch(const int32_t* c, int N, const int32_t* perms, int6
 // What bounds it: LDS look-ups (two bytes and two entries per rank) and, up to some 100000 orders, the latency of one or two tiles per
 // wave.  Level by level with sixteen lanes per order, top levels nearly empty -> here: N = 100, 100000 orders 33.3 -> 18.5 us, 300000
 // orders 80 -> 38 us; N = 50, 10^6 orders 120 -> 58 us; N = 8, 10^6 orders 78 -> 10 us; N = 255 (few waves beside the
-// matrix), 100000 orders 212 -> 40 us; N = 200, 300000 orders 202 -> 73 us.  Only matrices without an entry below 65535 are slower at
-// N = 193 .. 230 (100000 orders, N = 200 148 -> 187 us: all look-ups through L2, with half the wavefronts).  One wave per tile: N = 255,
+// matrix), 100000 orders 212 -> 40 us; N = 200, 300000 orders 202 -> 73 us.  Matrices with hardly an
+// entry below 65535, N >= 186: through L2 there is nothing to gain from this walk, so such a workgroup's waves take an order each (level
+// by level / this walk / now: N = 200, 8000 orders 22.5 / 23.0 / 18.0 us, 30000 52 / 56 / 49, 100000 148 / 175 / 156; N = 254, 8000 orders
+// 19.7 / 27.7 / 23.2, 100000 261 / 205 / 203).  One wave per tile: N = 255,
 // 100000 orders 127 us; two workgroups of eight waves per unit: N = 100, 50000 orders 11.2 instead of 9.4 us.
 constexpr int kDbtRow = 68;                     // bytes per rank: 64 orders, and a bank further from rank to rank
 
@@ -2007,7 +2014,45 @@ __global__ __launch_bounds__(1024) void dbt_batch_lanes_kernel(const int32_t* __
         }
     };
     if (slot < tiles) request((int64_t)blockIdx.x * tiles + slot);
-    unsigned top = stage_matrix(c, N * N, staged);
+    unsigned top = 0;
+    int done = 0;
+    if constexpr (sizeof(ENTRY) == 2) {
+        // The first 32768 of at least 34596 entries (N >= 186).  Where nearly all of the first half are 65535 or more, most look-ups would go
+        // through L2, and a wave per order is the faster (share of such entries, N = 193, 100000 orders, this walk / a wave per order: 0.9
+        // 156 / 150 us, 1.0 171 / 150; N = 254 187 / 203, 205 / 203); the second half is on its way while the waves agree.
+        constexpr int U = 16, kHalf = U * 1024;
+        unsigned v[2][U];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[h][u] = (unsigned)c[h * kHalf + u * 1024 + (int)threadIdx.x];
+        int* large = (int*)(staged + ((N * N + 7) & ~7));               // [16], where the tiles come
+        int mine = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) mine += __popcll(__ballot(v[0][u] >= 0xffffu));
+        if (lane == 0) large[wv] = mine;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            top = max(top, v[0][u]);
+            staged[u * 1024 + threadIdx.x] = (ENTRY)min(v[0][u], 0xffffu);
+        }
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) all += large[k];
+        if (__builtin_amdgcn_readfirstlane(all) > kHalf / 16 * 15) {
+            dbt_wave_per_order<2>(c, N, perms, B, out, (int32_t*)staged + wv * (N + N / 32 + 1), (int64_t)blockIdx.x * 16 + wv,
+                                  (int64_t)gridDim.x * 16);
+            return;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            top = max(top, v[1][u]);
+            staged[kHalf + u * 1024 + threadIdx.x] = (ENTRY)min(v[1][u], 0xffffu);
+        }
+        done = 2 * kHalf;
+    }
+    top = max(top, stage_matrix(c + done, N * N - done, staged + done));
     top = (unsigned)wave_max((int)min(top, 0x7fffffffu));
     if (lane == 0) wave_top[wv] = top;
     if (PARTS > 1 && part == 0 && slot < tiles) costliest[lane] = 0;

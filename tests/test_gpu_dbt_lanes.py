@@ -61,3 +61,25 @@ def test_ranks_out_of_range_are_clamped():
         same = cc.cc_dbt_cost_batch(dev(c), dev(clamped[:b]))
         torch.cuda.synchronize()
         assert torch.equal(got, same)
+
+
+@pytest.mark.parametrize("n", [186, 191, 192, 193, 255])
+@pytest.mark.parametrize("first", ["large", "mostly large", "small"])
+def test_dbt_where_the_first_entries_decide(n, first):
+    """The first entries of the matrix say whether it is staged: nearly all from 65535 up and the others small, fifteen of sixteen, or
+    small ones before a large half."""
+    c = random_matrix(n, n, symmetric=False, lo=0, hi=60000)
+    large = random_matrix(n, n + 1, symmetric=False, lo=65535, hi=COST_MAX)
+    flat, other = c.reshape(-1), large.reshape(-1)
+    if first == "small":
+        flat[17000:] = other[17000:]
+    else:
+        flat[:16384] = other[:16384]
+    if first == "mostly large":
+        flat[:16384:16] = 5
+    b = 7000
+    perms = random_perms(n, b, seed=n)
+    say(f"tree batch, first entries {first} N={n} B={b}")
+    got = cc.cc_dbt_cost_batch(dev(c), dev(perms))
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.dbt_cost_batch(c, perms))
