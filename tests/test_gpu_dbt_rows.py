@@ -1,5 +1,5 @@
-"""GPU parity, double binary tree batches on the 16-bit matrix in LDS (sixteen lanes per order): the smallest trees, full and
-nearly empty last levels, the largest N served, entries below and above 2^16, batches that end inside a workgroup's pass."""
+"""GPU parity, double binary tree batches around 2^20 ranks and above, one order per lane on the matrix in LDS: the smallest trees,
+full and nearly empty last levels, the largest N served, entries below and above 2^16, batches that end inside a tile of 64 orders."""
 import numpy as np
 import pytest
 import torch
