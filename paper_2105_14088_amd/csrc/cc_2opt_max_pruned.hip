@@ -13,8 +13,8 @@
 // because a part of its value already exceeds the best one seen.
 //
 // One workgroup per restart; order and hops in LDS, carried through the moves; rows of the matrix through L2.  A sweep
-// is a chain of latencies (two or three wave reductions, two LDS round trips, one gather, the move; about 7000 clocks
-// directed at N = 100, of which the pairs around e are 2500): no matrix staging, so any number of workgroups share a
+// is a chain of latencies (two or three wave reductions, two LDS round trips, one gather, the move; about 8000 clocks
+// directed at N = 100): no matrix staging, so any number of workgroups share a
 // compute unit.  Whole searches, against the exhaustive kernels: undirected N = 50, 1197 restarts 587 -> 60 us, N = 256, 1024
 // restarts 1456 -> 160 us, N = 700, 100 restarts 21 -> 0.26 ms; directed, inverse bandwidths that are eight times as small
 // inside a rack, N = 100, 1000 restarts 2272 -> 205 us, N = 256, 1024 restarts 2656 -> 551 us, N = 350, 316 restarts

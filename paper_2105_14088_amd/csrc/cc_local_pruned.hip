@@ -15,11 +15,11 @@
 //
 // What bounds it: a sweep is a chain of phases, each a few LDS look-ups deep, with a barrier behind it.  Up to 512 restarts 4 to 16
 // wavefronts share a restart: its candidates, 64 at a time in turn, and then both halves of the pairs that passed, 32 pairs at a
-// time.  N = 150, 512 restarts (8 wavefronts each, two restarts per compute unit): 13000 clocks a sweep, 3500 of them the scoring of 180
-// to 240 pairs, 2300 the brackets; with a wavefront per 64 nodes, each of which scored what its own nodes had passed, 26000, of which
-// 15000 were scoring (1.58 ms, now 1.08).  There the matrix is in LDS as a triangle; a look-up through the cache costs a line per lane,
-// which bounds N > 256 (N = 700: 12000 clocks of brackets, 20000 of scoring, before only the moves with a bracket of their own were
-// looked up: 16.1 ms, now 11.3).  One wavefront per restart: instruction issue.
+// time.  N = 150, 512 restarts (8 wavefronts each, two restarts per compute unit): 16700 clocks a sweep and 680 vector instructions per
+// wavefront, VALU 57 % and LDS 23 % of the time busy, the wavefronts waiting for half of it (a wavefront per 64 nodes, each of which
+// scored what its own nodes had passed: 1.58 ms, now 1.08).  There the matrix is in LDS as a triangle; a look-up through the cache costs a line
+// per lane, which bounds N > 256 (N = 700, before only the moves with a bracket of their own were looked up: 16.1 ms, now 11.3).  One
+// wavefront per restart: instruction issue.
 // Against the general kernel (cc_local.hip), 2-opt and insertion: N = 32, 1024 restarts 381 -> 165 us; N = 100, 512 restarts
 // 4.9 -> 0.62 ms; N = 150, 512 restarts 13.1 -> 1.1 ms; N = 292, 228 restarts 53 -> 2.3 ms; N = 1000, 20 restarts 1371 -> 23 ms;
 // against the exhaustive multi-rank kernel at N = 256, 250 restarts 9.6 -> 2.0 ms.  Matrices of few values are handed over to
@@ -37,6 +37,7 @@ namespace {
 
 using namespace pruned;
 constexpr int kNoSegment = -(1 << 28);  // R of a segment that does not exist
+constexpr int kNodesLeft = 1 << 16;     // in GroupWords::laid_out: nodes of the wavefront had no room
 
 // LDS of one restart: per node {hop in << 10 | rank, hop out} and {longest hop, largest R}, R of the segments of length
 // 1, 2, 3 by first rank, the nodes of the ranks -1 .. N
@@ -370,24 +371,27 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             if (WITH_2OPT) most = max(most, vx.x + vy.x);
             return (mx > my || (mx == my && x < y)) && twice - most <= D;
         };
-        // ---- how far the threshold of node x (one per lane) reaches; the candidates of 64 nodes end to end.  Returns where they end;
-        // all: x is scanned against every node instead, its partners are beyond the list or the room.
-        auto lay_out = [&](int x, int scale, int& start, bool& all) {
+        // ---- how far the threshold of node x (one per lane) reaches; the candidates of 64 nodes end to end, of those that are left.
+        // Returns where they end, with kNodesLeft if nodes are left; all: x is scanned against every node instead, its partners are beyond
+        // the list; left: not 0, for another time, they are beyond the room (a list is shorter than the room: of the nodes that are
+        // left one fits).
+        auto lay_out = [&](int x, int scale, int& start, bool& all, int& left) {
             const int2 vx = value[min(x, N - 1)];
             const int reach = max(vx.x, vx.y) + (D >> 1);
             const int bucket = bucket_of(max(reach, 0), scale);
             int count = (int)counts[(size_t)min(x, N - 1) * kBuckets + max(0, min(bucket, kBuckets - 2))];
             count = bucket >= kBuckets - 1 ? N - 1 : count;
-            count = x < N && reach >= 0 && bucket >= 0 ? count : 0;
+            count = left && reach >= 0 && bucket >= 0 ? count : 0;
+            left = 0;
             all = count > M;
             count = all ? 0 : count;
             int end = wave_prefix_sum(count);
             int total = __builtin_amdgcn_readlane(end, 63);
             if (total > ROOM) {
                 const bool out = end > ROOM;
-                all = all || (out && count > 0);
+                left = out ? count : 0;
                 count = out ? 0 : count;
-                total = wave_max(out ? 0 : end);
+                total = wave_max(out ? 0 : end) | kNodesLeft;
             }
             start = end - count;
             if (++stamp == 1024) {
@@ -424,98 +428,107 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
             pass(u_const, ok, x, e, place);
         };
         if constexpr (GROUP) {
-            // ---- an equal share of all nodes' candidates for every wave, 64 at a time
-            bool all = false;
-            if (owns) {
-                int start;
-                const int x = 64 * wv + lane, total = lay_out(x, scale0, start, all);
-                if (x < N) starts[x] = (uint16_t)start;
-                if (lane == 0) group->laid_out[wv] = total;
-            } else if (lane == 0) {
-                group->laid_out[wv] = 0;
-            }
-            const unsigned long long scanned_here = __ballot(all);
-            if (lane == 0) group->scanned[wv] = scanned_here;
-            __syncthreads();
-            const int laid_out = lane < WAVES ? group->laid_out[lane] : 0;
-            const int upto = wave_prefix_sum((laid_out + 63) >> 6);          // of the waves up to this lane's
-            const int listed = __builtin_amdgcn_readlane(upto, 63);
-            const int chunks = (N + 63) >> 6, scans_upto = wave_prefix_sum(lane < WAVES ? __popcll(group->scanned[lane]) : 0);
-            const int blocks = listed + __builtin_amdgcn_readlane(scans_upto, 63) * chunks;
-            auto brackets = [&](auto u_const, int g0) {
-                constexpr int U = decltype(u_const)::value;
-                unsigned src[U];
-                int from[U], place[U], first[U], live[U], x[U];
-                int2 jx[U], jy[U];
-                uint32_t e[U];
-                bool ok[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int g = g0 + WAVES * u, w = __popcll(__ballot(upto <= g));         // whose candidates these are
-                    const int i0 = 64 * (g - (w ? __builtin_amdgcn_readlane(upto, w - 1) : 0));
-                    first[u] = 64 * w;
-                    live[u] = __builtin_amdgcn_readlane(laid_out, w) - i0;
-                    place[u] = i0 + lane;
-                    src[u] = owners[w * ROOM + place[u]];
-                }
-                // marks of earlier layouts are smaller than this one's, and the first of the 64 is always marked
-#pragma unroll
-                for (int u = 0; u < U; ++u) src[u] = min((unsigned)first[u] + (wave_prefix_max(src[u]) & 63u), (unsigned)N - 1);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    from[u] = starts[src[u]];
-                    jx[u] = value[src[u]];
-                    x[u] = (int)src[u];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    place[u] -= from[u];                         // in the list of x
-                    e[u] = lists[lane < live[u] ? __umul24(src[u], (unsigned)M) + (unsigned)place[u] : 0u];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) jy[u] = value[e[u] & 1023u];
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    ok[u] = lane < live[u] && worth_scoring(x[u], jx[u], (int)(e[u] & 1023u), jy[u], 2 * (int)(e[u] >> 10));
-                pass(u_const, ok, x, e, place);
-            };
-            auto scan_block = [&](int g) {
-                const int i = (g - listed) / chunks, w = __popcll(__ballot(scans_upto <= i));
-                const unsigned long long nodes = group->scanned[w];
-                const int skip = i - (w ? __builtin_amdgcn_readlane(scans_upto, w - 1) : 0);
-                const unsigned long long at = __ballot((nodes >> lane & 1) && lanes_below(nodes) == skip);
-                scan(std::integral_constant<int, 1>{}, 64 * w + (int)__builtin_ctzll(at), 64 * (g - listed - i * chunks));
-            };
-            // two blocks for each wave at a time; then what passed is scored if it is enough to give every wave 32 pairs, or the last
-            int g = wv;
+            // ---- an equal share of all nodes' candidates for every wave, 64 at a time.  What the room does not hold follows in a turn of
+            // its own: with barriers between them, scans of those nodes against every node took longer than they had within one
+            // wavefront (32 zones of equal costs, N = 1000, 16 restarts 61 -> 91 ms when the candidates came to be shared, now 43; 16
+            // zones 87 -> 123, now 52; hosts and racks without noise 37 -> 34, now 20).
+            int left = 64 * wv + lane < N ? 1 : 0, words;      // in vector registers: the scalar ones are spilled as it is
             do {
-                if (g + WAVES < listed) {
-                    brackets(std::integral_constant<int, 2>{}, g);
-                } else {
-                    if (g < listed) brackets(std::integral_constant<int, 1>{}, g);
-                    else if (g < blocks) scan_block(g);
-                    if (g + WAVES < blocks) scan_block(g + WAVES);
+                bool all = false;
+                if (owns) {
+                    int start;
+                    const int x = 64 * wv + lane, total = lay_out(x, scale0, start, all, left);
+                    if (x < N) starts[x] = (uint16_t)start;
+                    if (lane == 0) group->laid_out[wv] = total;
+                } else if (lane == 0) {
+                    group->laid_out[wv] = 0;
                 }
-                g += 2 * WAVES;
-                const bool more = g - wv < blocks;
+                const unsigned long long scanned_here = __ballot(all);
+                if (lane == 0) group->scanned[wv] = scanned_here;
                 __syncthreads();
-                const int pairs = __builtin_amdgcn_readfirstlane(group->passed[list]);
-                if (more && pairs <= 32 * WAVES) {
+                words = lane < WAVES ? group->laid_out[lane] : 0;
+                const int laid_out = words & (kNodesLeft - 1);
+                asm volatile("" : "+v"(left), "+v"(words));
+                const int upto = wave_prefix_sum((laid_out + 63) >> 6);          // of the waves up to this lane's
+                const int listed = __builtin_amdgcn_readlane(upto, 63);
+                const int chunks = (N + 63) >> 6, scans_upto = wave_prefix_sum(lane < WAVES ? __popcll(group->scanned[lane]) : 0);
+                const int blocks = listed + __builtin_amdgcn_readlane(scans_upto, 63) * chunks;
+                auto brackets = [&](auto u_const, int g0) {
+                    constexpr int U = decltype(u_const)::value;
+                    unsigned src[U];
+                    int from[U], place[U], first[U], live[U], x[U];
+                    int2 jx[U], jy[U];
+                    uint32_t e[U];
+                    bool ok[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int g = g0 + WAVES * u, w = __popcll(__ballot(upto <= g));         // whose candidates these are
+                        const int i0 = 64 * (g - (w ? __builtin_amdgcn_readlane(upto, w - 1) : 0));
+                        first[u] = 64 * w;
+                        live[u] = __builtin_amdgcn_readlane(laid_out, w) - i0;
+                        place[u] = i0 + lane;
+                        src[u] = owners[w * ROOM + place[u]];
+                    }
+                    // marks of earlier layouts are smaller than this one's, and the first of the 64 is always marked
+#pragma unroll
+                    for (int u = 0; u < U; ++u) src[u] = min((unsigned)first[u] + (wave_prefix_max(src[u]) & 63u), (unsigned)N - 1);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        from[u] = starts[src[u]];
+                        jx[u] = value[src[u]];
+                        x[u] = (int)src[u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        place[u] -= from[u];                         // in the list of x
+                        e[u] = lists[lane < live[u] ? __umul24(src[u], (unsigned)M) + (unsigned)place[u] : 0u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) jy[u] = value[e[u] & 1023u];
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        ok[u] = lane < live[u] && worth_scoring(x[u], jx[u], (int)(e[u] & 1023u), jy[u], 2 * (int)(e[u] >> 10));
+                    pass(u_const, ok, x, e, place);
+                };
+                auto scan_block = [&](int g) {
+                    const int i = (g - listed) / chunks, w = __popcll(__ballot(scans_upto <= i));
+                    const unsigned long long nodes = group->scanned[w];
+                    const int skip = i - (w ? __builtin_amdgcn_readlane(scans_upto, w - 1) : 0);
+                    const unsigned long long at = __ballot((nodes >> lane & 1) && lanes_below(nodes) == skip);
+                    scan(std::integral_constant<int, 1>{}, 64 * w + (int)__builtin_ctzll(at), 64 * (g - listed - i * chunks));
+                };
+                // two blocks for each wave at a time; then what passed is scored if it is enough to give every wave 32 pairs, or the last
+                int g = wv;
+                do {
+                    if (g + WAVES < listed) {
+                        brackets(std::integral_constant<int, 2>{}, g);
+                    } else {
+                        if (g < listed) brackets(std::integral_constant<int, 1>{}, g);
+                        else if (g < blocks) scan_block(g);
+                        if (g + WAVES < blocks) scan_block(g + WAVES);
+                    }
+                    g += 2 * WAVES;
+                    const bool more = g - wv < blocks;
                     __syncthreads();
-                    continue;
-                }
-                if (tid == 0) group->passed[list ^ 1] = 0;       // for the next ones
-                list ^= 1;
-                for (int i0 = 32 * wv; i0 < pairs; i0 += 32 * WAVES) score_listed(i0, pairs - i0);
-                if (more) __syncthreads();
-            } while (g - wv < blocks);
+                    const int pairs = __builtin_amdgcn_readfirstlane(group->passed[list]);
+                    if (more && pairs <= 32 * WAVES) {
+                        __syncthreads();
+                        continue;
+                    }
+                    if (tid == 0) group->passed[list ^ 1] = 0;       // for the next ones
+                    list ^= 1;
+                    for (int i0 = 32 * wv; i0 < pairs; i0 += 32 * WAVES) score_listed(i0, pairs - i0);
+                    if (more) __syncthreads();
+                } while (g - wv < blocks);
+            } while (__ballot(words >= kNodesLeft));
         } else {
 #pragma unroll 1
             for (int k = 0; k < K; ++k) {
                 const int x_first = 64 * (wv * K + k), x = x_first + lane;
                 int start;
                 bool all;
-                const int total = lay_out(x, K == 1 ? scale0 : (int)scales[min(x, N - 1)], start, all);
+                int left = x < N ? 1 : 0;
+                const int total = lay_out(x, K == 1 ? scale0 : (int)scales[min(x, N - 1)], start, all, left) & (kNodesLeft - 1);
                 __builtin_amdgcn_wave_barrier();
                 // ---- brackets, U times 64 candidates with their LDS and list reads in flight together
                 auto brackets = [&](auto u_const, int i0) {
@@ -553,7 +566,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
                     else if (total - i0 > 64) brackets(std::integral_constant<int, 2>{}, i0);
                     else brackets(std::integral_constant<int, 1>{}, i0);
                 }
-                unsigned long long rest = __ballot(all);
+                unsigned long long rest = __ballot(all || left != 0);
                 while (rest) {
                     const int nx = x_first + (int)__builtin_ctzll(rest);
                     rest &= rest - 1;

@@ -163,10 +163,11 @@ __global__ __launch_bounds__(256) void fold_to_u16_kernel(const int32_t* __restr
 // The result (value, lowest id) is that of the exhaustive sweep.  Link values live in LDS from sweep to sweep: a swap
 // changes 2 log2 N of them, and a round's three largest are found anew only if one of them changed or was passed.
 //
-// What bounds a sweep is latency: LDS round trips, wave reductions, two barriers.  N = 256, 9000 clocks: the three largest links 900,
-// which ends to scan 1300, the scans 1900 each, 1.6 a sweep, the pairs 2950 beside the first of them, the swap 650; every wave renews
-// the links of the rounds whose largest it keeps, and the order has a second copy for the swap, so that no barrier stands between.
-// (11200 with the pairs behind the scans, one wave for the swap and five barriers: 256 restarts 1.27 ms, now 1.01.)  Against the
+// What bounds a sweep is latency: LDS round trips, wave reductions, two barriers.  N = 256, 256 restarts: 10000 clocks a sweep and 306
+// vector instructions per wavefront, VALU a third and LDS a quarter of the time busy, the wavefronts waiting for more than half of it.
+// So the pairs are looked at beside the first scan, every wave renews the links of the rounds whose largest it keeps, and the order has
+// a second copy for the swap, with no barrier between (pairs behind the scans, one wave for the swap, five barriers: 1.27 ms, now 1.01).
+// Against the
 // exhaustive sweeps before it, matrices of the benchmark's hierarchy: N = 1024, 32 restarts 394 -> 3.3 ms; N = 512, 136 restarts
 // 95.7 -> 3.1 ms; N = 256, 58 restarts 9.4 -> 0.98 ms, 788 restarts 31.7 -> 3.0 ms; N = 128, 600 restarts 4.6 -> 0.75 ms; N = 32, 300
 // restarts 2.4 -> 0.09 ms.

@@ -30,3 +30,11 @@ def test_every_number_of_wavefronts(n, restarts):
         for classes in (BOTH, INSERTION) if n < 512 else (BOTH,):
             say(f"pruned insertion groups N={n} R={restarts} {tag} classes={classes}")
             check(c, classes, restarts, 21, sorted({0, restarts - 1}))
+
+
+@pytest.mark.parametrize("n,k", [(257, 8), (700, 12)])
+def test_candidates_of_several_rooms(n, k):
+    """Nodes whose candidates find no room beside those of their wavefront's other nodes: laid out after them."""
+    for classes in (BOTH, INSERTION) if n < 512 else (BOTH,):
+        say(f"pruned insertion, several rooms N={n} zones={k} classes={classes}")
+        check(zones(n, k), classes, 2, 23, [1])
