@@ -83,11 +83,12 @@ hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, con
                                 hipStream_t s);
 // Segment insertions, with or without 2-opt, any 4 <= N <= 1024 (cc_local_pruned.hip); same conventions.
 // With `flags` set an exhaustive kernel is enqueued behind it, and the matrix decides which of them does the work: the other
-// one when more than `most` of the N (N - 1) costs are about the smallest of their row (and, for to_16bit, all are below
-// 2^16).  flags[0] then lets it run: below 2^16 for to_16bit, otherwise 2^16 or above.
+// one when more than `most` of the N (N - 1) costs are about the smallest of their row or (N <= 256, to_16bit) more than `most_level`
+// are in their row's fullest bucket of cost but for the last one, and, for to_16bit, all are below 2^16.  flags[0] then lets it run:
+// below 2^16 for to_16bit, otherwise 2^16 or above.
 struct TieHandover {
     int32_t* flags;
-    int most;
+    int most, most_level;
     bool to_16bit;
 };
 hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, const TieHandover& ties, int restarts,

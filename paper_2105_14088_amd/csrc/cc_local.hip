@@ -181,14 +181,22 @@ hipError_t launch_insertion_search(const int32_t* c, int N, bool with_2opt, int 
         // alone 9.0 and 8.8, and with 16 zones of equal costs 4.4 and 5.3).  From N = 65 on the matrix has a say: with many partners
         // at a row's smallest cost most pairs pass their brackets, and the other kernel can be the faster.  Where the lines lie, in
         // zones of equal costs, 100 inside and 1000 across, this kernel against the other one.  2-opt and insertion, up to 512
-        // restarts: always this one, two zones, N = 100, 512 restarts 0.74 against 1.54 ms, N = 240 9.1 / 10.5, N = 400 40.1 / 40.8; above
+        // restarts: always this one, two zones, N = 100, 512 restarts 0.77 against 1.59 ms, N = 240 9.7 / 10.5, N = 400 38.8 / 40.2, N = 1024 560 / 825; above
         // as before, N = 240, 1024 restarts 16.9 / 16.2.  Insertion alone, up to 512 restarts: three zones N = 100 0.52 / 1.18 ms, N = 240
         // 6.8 / 6.6, two zones N = 200 5.7 / 4.2.  N = 128, 192, 256: up to 256 restarts 8 zones 0.59 / 0.71, 1.33 / 1.72, 2.97 / 3.88 ms,
         // 4 zones 0.79 / 0.60, 1.64 / 1.41, 3.30 / 3.31; 512 restarts, 12 zones 0.66 / 0.83, 2.02 / 1.9, 5.24 / 4.52.
         const int all = N * (N - 1);
         const int most = multi ? all / (restarts <= 256 ? 7 : N == 128 ? 9 : 12)
                          : with_2opt ? (restarts <= 512 ? all : all / 5 * 2) : restarts <= 512 ? all / 5 * 2 : all / 10 * 3;
-        const TieHandover ties{N > 64 && most < all ? flags : nullptr, most, multi};
+        // Hosts in racks without noise: most pairs pass while the racks' cost is what is moved to.  Partners at that cost, this kernel against
+        // the other one, 2-opt and insertion / insertion alone: N = 128, 64 restarts, 60 partners 0.91 / 0.94, 1.25 / 0.88 ms, 48 partners
+        // 0.84 / 0.71, 0.92 / 0.68, 44 partners 0.74 / 0.95, 0.91 / 0.95; 512 restarts, 60 partners 1.15 / 0.99, 1.52 / 0.93, 44
+        // partners 0.85 / 1.01, 1.05 / 0.97, 38 partners 0.79 / 1.05, 0.98 / 0.98; N = 192, 64 restarts, 88 partners 1.85 / 2.26, 2.40 /
+        // 2.61; 512 restarts, 60 partners 2.95 / 2.67, 4.79 / 3.07, 44 partners 1.83 / 2.66, 2.65 / 3.02; N = 256, 64 restarts, 120 partners
+        // 4.10 / 5.77, 5.75 / 5.16, 81 partners 3.02 / 6.37, 5.07 / 5.59; 512 restarts, 120 partners 8.25 / 5.96, 81 partners 5.85 / 6.54.
+        const bool many = restarts > 256;
+        const int level = N == 128 ? (many && !with_2opt ? 39 : 46) : N == 192 ? (many ? 46 : N) : many == with_2opt ? 96 : N;
+        const TieHandover ties{N > 64 && most < all ? flags : nullptr, most, level * N, multi};
         hipError_t e = launch_local_pruned(c, N, with_2opt, room, ties, restarts, tours, costs, moves, s);
         if (e != hipSuccess || !ties.flags) return e;
         if (multi) return launch_local_multi(c, N, with_2opt, restarts, tours, costs, moves, flags, s);

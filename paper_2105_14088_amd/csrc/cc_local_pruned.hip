@@ -15,7 +15,7 @@
 //
 // What bounds it: a sweep is a chain of phases, each a few LDS look-ups deep, with a barrier behind it.  Up to 512 restarts 4 to 16
 // wavefronts share a restart: its candidates, 64 at a time in turn, and then both halves of the pairs that passed, 32 pairs at a
-// time.  N = 150, 512 restarts (8 wavefronts each, two restarts per compute unit): 16700 clocks a sweep and 680 vector instructions per
+// time.  N = 150, 512 restarts (8 wavefronts each, two restarts per compute unit): 16900 clocks a sweep and 690 vector instructions per
 // wavefront, VALU 57 % and LDS 23 % of the time busy, the wavefronts waiting for half of it (a wavefront per 64 nodes, each of which
 // scored what its own nodes had passed: 1.58 ms, now 1.08).  There the matrix is in LDS as a triangle; a look-up through the cache costs a line
 // per lane, which bounds N > 256 (N = 700, before only the moves with a bracket of their own were looked up: 16.1 ms, now 11.3).  One
@@ -630,9 +630,9 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
 
 // Whether the kernel behind this one does the work (see TieHandover).  Where many partners cost the same, most pairs pass
 // their brackets in one role or another, and scoring them costs more than the exhaustive sweeps.
-__device__ __forceinline__ bool hand_over(const TieHandover& ties, int tied, int highest) {
+__device__ __forceinline__ bool hand_over(const TieHandover& ties, int tied, int level, int highest) {
     if (!ties.flags) return false;
-    const bool hand = tied > ties.most && (!ties.to_16bit || highest < (1 << 16));
+    const bool hand = (tied > ties.most || level > ties.most_level) && (!ties.to_16bit || highest < (1 << 16));
     if (blockIdx.x == 0 && threadIdx.x == 0) ties.flags[0] = hand == ties.to_16bit ? 0 : 1 << 16;
     return hand;
 }
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
                                                             int32_t* __restrict__ moves) {
     constexpr int K = WAVES > 1 ? 1 : E;                       // nodes per lane
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ int largest[16], tied[16];
+    __shared__ int largest[16], tied[16], level[16];
     __shared__ GroupWords<WAVES> group;
     uint32_t* lists = (uint32_t*)smem;                         // [N][M]
     unsigned char* counts = smem + (size_t)N * M * 4;          // [N][kBuckets]
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     {
         int* hist = (int*)rest + kBuckets * wv;                // where the restarts' state comes later
-        int high = 0, tied_here = 0;
+        int high = 0, tied_here = 0, level_here = 0;
         for (int x = wv; x < N; x += nw) {
             int row_max;
             const int scale = make_list<E>(c, N, x, M, lists + (size_t)x * M, counts + (size_t)x * kBuckets, hist, lane, row_max,
@@ -666,21 +666,29 @@ __global__ __launch_bounds__(1024) void local_pruned_kernel(const int32_t* __res
                                            });
             if (lane == 0) scales[x] = (uint16_t)scale;
             high = max(high, row_max);
-            tied_here += counts[(size_t)x * kBuckets];
+            const unsigned char* upto = counts + (size_t)x * kBuckets;
+            tied_here += upto[0];
+            if (ties.to_16bit) {
+                // a move to a cost that many partners have in common ties with many others, the row's largest cost is none to move to
+                const int below = lane ? upto[2 * lane - 1] : 0, first = upto[2 * lane], second = upto[2 * lane + 1];
+                level_here += wave_max(max(first < N - 1 ? first - below : 0, second < N - 1 ? second - first : 0));
+            }
         }
         if (lane == 0) {
             largest[wv] = high;
             tied[wv] = tied_here;
+            level[wv] = level_here;
         }
     }
     __syncthreads();
-    int high = 0, tied_in_all = 0;
+    int high = 0, tied_in_all = 0, level_in_all = 0;
     for (int w = 0; w < nw; ++w) {
         high = max(high, largest[w]);
         tied_in_all += tied[w];
+        level_in_all += level[w];
     }
     high = __builtin_amdgcn_readfirstlane(high);
-    if (hand_over(ties, __builtin_amdgcn_readfirstlane(tied_in_all), high)) return;
+    if (hand_over(ties, __builtin_amdgcn_readfirstlane(tied_in_all), __builtin_amdgcn_readfirstlane(level_in_all), high)) return;
     if (wv >= waves) return;                                   // barriers below wait for the remaining wavefronts only
     const int in_lds = high < (1 << 16) ? lds_matrix : 0;
     const int64_t r = WAVES > 1 ? blockIdx.x : (int64_t)blockIdx.x * waves + wv;
@@ -716,7 +724,7 @@ __global__ __launch_bounds__(64 * WAVES) void local_pruned_group_kernel(const in
         __syncthreads();
         int tied_in_all = 0;
         for (int w = 0; w < WAVES; ++w) tied_in_all += group.word[w];
-        if (hand_over(ties, __builtin_amdgcn_readfirstlane(tied_in_all), 0)) return;
+        if (hand_over(ties, __builtin_amdgcn_readfirstlane(tied_in_all), 0, 0)) return;
         __syncthreads();
     }
     const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];

@@ -38,3 +38,18 @@ def test_candidates_of_several_rooms(n, k):
     for classes in (BOTH, INSERTION) if n < 512 else (BOTH,):
         say(f"pruned insertion, several rooms N={n} zones={k} classes={classes}")
         check(zones(n, k), classes, 2, 23, [1])
+
+
+@pytest.mark.parametrize("n,restarts", [(128, 256), (128, 257), (192, 257), (256, 256), (256, 257)])
+def test_levels_of_equal_costs(n, restarts):
+    """Hosts in racks without noise: more and fewer partners at the racks' cost than the line between the pruned and the exhaustive kernel,
+    and entries that the latter does not take."""
+    node = np.arange(n)
+    for rack in (n // 4, n // 2):
+        c = np.where(node[:, None] // rack == node[None, :] // rack, 300, 1000)
+        c = np.where(node[:, None] // 4 == node[None, :] // 4, 100, c)
+        np.fill_diagonal(c, 0)
+        for factor in (1, 100):
+            for classes in (BOTH, INSERTION):
+                say(f"pruned insertion, levels N={n} R={restarts} racks of {rack} times {factor} classes={classes}")
+                check((c * factor).astype(np.int32), classes, restarts, 25, [0, restarts - 1])
