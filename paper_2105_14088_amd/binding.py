@@ -170,9 +170,11 @@ def _batch(c: torch.Tensor, perms: torch.Tensor):
 
 
 def _costs(out: Optional[torch.Tensor], b: int, cost_matrix: torch.Tensor, stream):
-    """The orders' costs, the caller's tensor or one made here, and where they are."""
+    """The orders' costs, the caller's tensor or one made here as _new does, and where they are."""
     if out is None:
-        out = _new(b, torch.int64, cost_matrix.device, stream)
+        out = torch.empty(b, dtype=torch.int64, device=cost_matrix.device)
+        if stream is not None:
+            out.record_stream(stream)
         return out, out.data_ptr()
     return out, _dev(out, torch.int64, "out")
 

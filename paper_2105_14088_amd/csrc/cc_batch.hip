@@ -1764,7 +1764,8 @@ hipError_t launch_bcube_cost_batch(const int32_t* c, int N, int base, const int3
 // below the fifth level and then that subtree, REST levels below its root (N < 2^(6 + REST)).  Which ranks these are does not
 // depend on the order: their places in LDS are found once.  (5 + 2^(REST + 1) - 1) look-ups per lane for 2 (N - 1) edges; what
 // bounds it is the rate of scattered requests to the L2 (about 3e11 a second).  Every rank walking its whole path -> this kernel: N = 1000,
-// 65000 orders 851 -> 544 us, 1000 orders 72 -> 13 us; N = 500, 65000 orders 338 -> 244 us; N = 300, 16000 orders 51 -> 38 us.
+// 65000 orders 851 -> 544 us, 1000 orders 72 -> 13 us; N = 1024 (242 registers, two waves per SIMD) 909 -> 600 and 76 -> 15 us; N = 500,
+// 65000 orders 338 -> 244 us; N = 300, 16000 orders 51 -> 38 us.
 // `order`: N + N / 32 + 1 words for this wave, number `wave` of nwaves.
 template <int REST>
 __device__ __forceinline__ void dbt_wave_per_order(const int32_t* __restrict__ c, int N, const int32_t* __restrict__ perms, int64_t B,
