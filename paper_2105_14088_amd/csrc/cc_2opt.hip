@@ -385,29 +385,31 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
             e = launch_init_tours(N, 0, restarts, seed, tours, s);
             if (e != hipSuccess) return e;
         }
-        // Ring sum.  Scoring only the moves that can win pays for any entries from N = 257 on (N = 1000 40 times) and at 129 ..
-        // 255 but 192 (1.2 to 5 times against the exhaustive kernels with the matrix as 16-bit entries).  Those have the
-        // shorter sweeps and win up to 96, at 97 .. 127 up to 1536 restarts (below 100 up to 2048; N = 97: 1537 restarts 0.59
-        // against 0.67 ms, 4096 restarts 1.20 against 0.88) and where the nodes fill their lanes: at 128, and at 192 and 256 from
-        // 257 restarts on, where the other's restarts get a single wavefront each, until their own wavefronts crowd each other
-        // (N = 192: 1025 restarts 1.64 against 1.95 ms, 3000 restarts 2.43 against 2.49, 4096 restarts 3.2 against 2.9; N = 256:
-        // 1024 restarts 3.5 against 4.2, 1500 restarts 4.2 against 4.1, 2048 restarts 4.3 against 3.8).
-        const bool full_lanes = N == 192 || N == 256;
-        const bool pruned = N > 256 || (N > 128 && !full_lanes) || (N == 192 && (restarts <= 256 || restarts > 3072)) ||
-                            (N == 256 && (restarts <= 256 || restarts > 1536)) ||
-                            (N > 96 && N < 128 && restarts > (N < 100 ? 2048 : 1536));
-        if (objective == 0 && pruned) {
-            e = launch_2opt_sum_pruned(c, N, mat16, restarts, tours, costs, moves, nullptr, s);
-        } else if (objective == 0 && N >= 4 && N <= 256) {
+        // Ring sum.  From N = 65 on a workgroup per restart that keeps its pairs has the shorter search until the restarts crowd each
+        // other, above N = 256 always (other kernels / kept pairs: N = 65, 512 restarts 184 / 171 us, 1024 restarts 211 / 226; N = 90, 1000
+        // restarts 370 / 318; N = 97, 2048 restarts 656 / 542, 4096 restarts 832 / 910; N = 128, 1000 restarts 597 / 514, 2048 restarts 691 /
+        // 892; N = 200, 2048 restarts 2481 / 1997; N = 192, 1536 restarts 1661 / 1386, 2048 restarts 1729 / 1846; N = 256, 2000 restarts 4085 /
+        // 3078, 3000 restarts 4.4 / 4.5 ms; N = 300, 3000 restarts 7.0 / 4.8 ms).  With more restarts the exhaustive kernels with the matrix as
+        // 16-bit entries win up to 96, at 128 and at 192 up to 3072 restarts (N = 192, 3000 restarts 2.43 against 2.49, 4096 restarts 3.2 against
+        // 2.9), the pruned one with a wavefront per restart elsewhere.
+        const int most_kept = N > 256 ? 1 << 30 : N == 192 ? 1536 : N > 128 ? 2048 : N == 128 ? 1024 : N > 96 ? 2048 : N >= 80 ? 1024 : N > 64 ? 512 : 0;
+        const bool exhaustive = N <= 96 || N == 128 || (N == 192 && restarts <= 3072);
+        if (objective == 0 && restarts <= most_kept) {
+            e = launch_2opt_sum_kept(c, N, mat16, restarts, tours, costs, moves, s);
+            if (e != hipSuccess) return e;
+            if (sum_kept_leaves_restarts(N)) e = launch_2opt_sum_pruned(c, N, mat16, restarts, tours, costs, moves, nullptr, true, s);
+        } else if (objective == 0 && !exhaustive) {
+            e = launch_2opt_sum_pruned(c, N, mat16, restarts, tours, costs, moves, nullptr, false, s);
+        } else if (objective == 0 && N >= 4) {
             // the exhaustive kernel when max(c) < 2^16, else the pruned one or, where its lists do not pay, the general one:
             // both are enqueued and the matrix maximum, computed on the device, decides which does the work (no host
             // round trip)
             e = launch_matrix_max(c, N, flags, s);
             if (e != hipSuccess) return e;
-            e = N == 128 || full_lanes ? launch_2opt_sum_multi(c, N, restarts, tours, costs, moves, flags, s)
-                                       : launch_2opt_sum_flex(c, N, restarts, tours, costs, moves, flags, s);
+            e = N >= 128 ? launch_2opt_sum_multi(c, N, restarts, tours, costs, moves, flags, s)
+                         : launch_2opt_sum_flex(c, N, restarts, tours, costs, moves, flags, s);
             if (e != hipSuccess) return e;
-            e = N > 96 ? launch_2opt_sum_pruned(c, N, mat16, restarts, tours, costs, moves, flags, s)
+            e = N > 96 ? launch_2opt_sum_pruned(c, N, mat16, restarts, tours, costs, moves, flags, false, s)
                        : launch_general_objective(c, N, objective, restarts, tours, costs, moves, flags, false, s);
         } else {
             e = launch_general_objective(c, N, objective, restarts, tours, costs, moves, nullptr, false, s);

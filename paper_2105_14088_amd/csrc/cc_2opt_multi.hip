@@ -1,6 +1,6 @@
-// 2-opt descent for N = 128, 192 and 256, ring-sum objective on a symmetric matrix: one wavefront per
+// 2-opt descent for N = 128 and 192, ring-sum objective on a symmetric matrix: one wavefront per
 // restart, K = N / 64 consecutive ranks per lane, the whole cost matrix staged once per workgroup in
-// LDS as 16-bit entries (128 KiB at N = 256, shared by the 16 restarts of a 1024-thread workgroup).
+// LDS as 16-bit entries (72 KiB at N = 192, shared by the 16 restarts of a 1024-thread workgroup).
 //
 // Same cyclic-diagonal sweep as the N = 64 kernel (cc_2opt_n64.hip): exchanging ring edges a and
 // b = a + d costs  G(a-1, b-1) + G(a, b) - f[a] - f[b]  with G(p, q) = c[t[p]][t[q]], so rank a gathers
@@ -372,8 +372,7 @@ static hipError_t launch_multi(const int32_t* c, int restarts, int32_t* tours, i
 hipError_t launch_2opt_sum_multi(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs,
                                  int32_t* moves, const int32_t* flags, hipStream_t s) {
     if (N == 128) return launch_multi<2>(c, restarts, tours, costs, moves, flags, s);
-    if (N == 192) return launch_multi<3>(c, restarts, tours, costs, moves, flags, s);
-    return launch_multi<4>(c, restarts, tours, costs, moves, flags, s);
+    return launch_multi<3>(c, restarts, tours, costs, moves, flags, s);
 }
 
 template <int K>
@@ -392,7 +391,7 @@ static hipError_t launch_flex_k(const int32_t* c, int N, int restarts, int32_t* 
     return hipGetLastError();
 }
 
-// Any 4 <= N < 128.  Tours must already hold the initial orders, flags[0] the matrix maximum.
+// Any 4 <= N <= 96.  Tours must already hold the initial orders, flags[0] the matrix maximum.
 hipError_t launch_2opt_sum_flex(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                                 const int32_t* flags, hipStream_t s) {
     if (N <= 64) return launch_flex_k<1>(c, N, restarts, tours, costs, moves, flags, s);

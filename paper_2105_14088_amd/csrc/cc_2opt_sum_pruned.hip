@@ -1,4 +1,5 @@
-// Ring-sum 2-opt for 65 <= N <= 1024 and any entries: only the moves that can be the best one are scored.  Move set,
+// Ring-sum 2-opt for 97 <= N <= 1024 and any entries, where restarts are too many, or pairs, for cc_2opt_sum_kept.hip: only the moves
+// that can be the best one are scored.  Move set,
 // value and tie-break rules as stated in cc.h; symmetric matrix, read through its upper triangle.
 //
 // Exchanging the ring edges a and b (edge p joins ranks p-1 and p) changes the cost by
@@ -18,7 +19,7 @@
 // or whose candidates exceed the room for them, is scanned against every node instead.
 //   * N <= 256: lists in LDS, made by the workgroup itself; up to 256 (N <= 192: mostly 512) restarts one workgroup of eight
 //     (four) wavefronts each, beyond that up to 16 restarts of one wavefront each around one copy of the lists.
-//   * N > 256: one workgroup per restart, lists in the workspace (M = (N - 128) / 2), made by a kernel of their own.
+//   * N > 256 (restarts that cc_2opt_sum_kept.hip left): one workgroup per restart, lists in the workspace (M = (N - 128) / 2), made by a kernel of their own.
 // The candidates of 64 nodes are laid out end to end (prefix sum of their counts) and taken 64 at a time, up to four
 // times 64 with their look-ups in flight together; those whose bracket passes are collected in LDS and scored 64 at a
 // time.  The wavefronts of one restart take the 64s of all nodes in turn (the nodes of one wavefront have two or three times the
@@ -72,7 +73,7 @@ struct GroupWords {
 template <int WAVES, int K, int ROOM, bool ENTRIES, typename COUNT, class MAT>
 __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __restrict__ lists, int M,
                                         const COUNT* __restrict__ counts, int scale0, const uint16_t* scales, unsigned char* order_mem,
-                                        unsigned char* wave_mem, GroupWords<WAVES>* group, int wv, int lane,
+                                        unsigned char* wave_mem, GroupWords<WAVES>* group, int wv, int lane, int applied,
                                         int32_t* __restrict__ tour, int64_t* __restrict__ cost_out,
                                         int32_t* __restrict__ moves_out) {
     constexpr int THREADS = 64 * WAVES;
@@ -95,7 +96,7 @@ __device__ __forceinline__ void descend(const MAT mat, int N, const uint32_t* __
     auto rank_of = [](uint2 w) { return (int)(w.x & 1023u); };
 
     // ---- order, hops, ranks
-    int t0[K], applied = 0, turn = 0;
+    int t0[K], turn = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int p = tid + THREADS * k;
@@ -490,10 +491,17 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
                                                                  int waves, int restarts, int32_t* __restrict__ tours,
                                                                  int64_t* __restrict__ costs,
                                                                  int32_t* __restrict__ moves,
-                                                                 const int32_t* __restrict__ skip_if_small) {
+                                                                 const int32_t* __restrict__ skip_if_small, int left_over) {
     constexpr int K = WAVES > 1 ? 1 : E;                        // nodes per lane
     // when the exhaustive 16-bit kernel is launched beside this one, the matrix maximum decides which of them runs
     if (skip_if_small && skip_if_small[0] < (1 << 16)) return;
+    if (left_over) {
+        // behind the kernel that keeps pairs: only restarts that it left
+        bool any = false;
+        const int64_t first = WAVES > 1 ? blockIdx.x : (int64_t)blockIdx.x * waves;
+        for (int i = 0; i < (WAVES > 1 ? 1 : waves); ++i) any = any || costs[min(first + i, (int64_t)restarts - 1)] < 0;
+        if (!any) return;
+    }
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int largest[16];
     __shared__ GroupWords<WAVES> group;
@@ -525,17 +533,18 @@ __global__ __launch_bounds__(1024) void twoopt_sum_pruned_kernel(const int32_t* 
     for (int w = 0; w < nw; ++w) high = max(high, largest[w]);
     const bool in_lds = lds_matrix && __builtin_amdgcn_readfirstlane(high) < (1 << 16);
     const int64_t r = WAVES > 1 ? blockIdx.x : (int64_t)blockIdx.x * waves + wv;
-    if (r >= restarts) return;
+    if (r >= restarts || (left_over && costs[r] >= 0)) return;
+    const int applied = left_over ? moves[r] : 0;
     const int mine = WAVES > 1 ? 0 : wv, part = WAVES > 1 ? wv : 0;
     unsigned char* order_mem = rest + (size_t)mine * (order_bytes(N) + wave_bytes(kRoom));
     unsigned char* wave_mem = WAVES > 1 ? order_mem + group_order_bytes(N) + (size_t)part * group_wave_bytes(kRoom, ENTRIES)
                                         : order_mem + order_bytes(N);
     const int scale0 = (int)scales[min(64 * part + lane, N - 1)];
     if (in_lds)
-        descend<WAVES, K, kRoom, ENTRIES>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
+        descend<WAVES, K, kRoom, ENTRIES>(LdsMatrix{m16, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane, applied,
                           tours + r * N, costs + r, moves + r);
     else
-        descend<WAVES, K, kRoom, ENTRIES>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane,
+        descend<WAVES, K, kRoom, ENTRIES>(CallersMatrix{c, N}, N, lists, M, counts, scale0, scales, order_mem, wave_mem, &group, part, lane, applied,
                           tours + r * N, costs + r, moves + r);
 }
 
@@ -563,32 +572,33 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(80))) vo
                                                                              const uint16_t* __restrict__ counts,
                                                                              int32_t* __restrict__ tours,
                                                                              int64_t* __restrict__ costs,
-                                                                             int32_t* __restrict__ moves) {
+                                                                             int32_t* __restrict__ moves, int left_over) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ GroupWords<WAVES> group;
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
+    if (left_over && costs[r] >= 0) return;                    // only restarts that the kernel that keeps pairs left
     const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
     descend<WAVES, 1, kGroupRoom, true>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
-                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom, true), &group, wv, lane, tours + r * N, costs + r,
-                                  moves + r);
+                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom, true), &group, wv, lane, left_over ? moves[r] : 0,
+                                  tours + r * N, costs + r, moves + r);
 }
 
 template <int E, int WAVES, bool ENTRIES>
 hipError_t launch_lds(const int32_t* c, int N, const LdsPlan& plan, int restarts, int32_t* tours, int64_t* costs,
-                      int32_t* moves, const int32_t* skip_if_small, hipStream_t s) {
+                      int32_t* moves, const int32_t* skip_if_small, bool left_over, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_kernel<E, WAVES, ENTRIES>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.bytes);
     if (e != hipSuccess) return e;
     const int grid = WAVES > 1 ? restarts : (restarts + plan.waves - 1) / plan.waves;
     hipLaunchKernelGGL((twoopt_sum_pruned_kernel<E, WAVES, ENTRIES>), dim3(grid), dim3(64 * (plan.waves > 8 ? plan.waves : 8)), plan.bytes,
-                       s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves, skip_if_small);
+                       s, c, N, plan.M, plan.lds_matrix, plan.waves, restarts, tours, costs, moves, skip_if_small, left_over ? 1 : 0);
     return hipGetLastError();
 }
 
 template <int E>
 hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
-                        const int32_t* skip_if_small, hipStream_t s) {
+                        const int32_t* skip_if_small, bool left_over, hipStream_t s) {
     // A wave's own instructions bound a sweep, so more of them than the 64 nodes each would need are the faster as long as the unit has
     // room (4 / 8 / 12 / 16 waves: N = 150, 200 restarts 612 / 579 / 610 / 650 us; N = 256, 200 restarts 1526 / 1335 / 1319 / 1550; two
     // restarts per unit: N = 150, 500 restarts 696 / 723 / 876 / 1230).
@@ -599,61 +609,66 @@ hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, i
     const bool places = E == 4 && N > 208;
     auto state = [&](int waves, bool entries) { return group_order_bytes(N) + waves * group_wave_bytes(kRoom, entries); };
     const LdsPlan plan = lds_plan(N, restarts, order_bytes(N), Groups{2, false, {kOne, kTwo}, {state(kOne, true), state(kTwo, !places)}});
-    if (!plan.together) return launch_lds<E, 1, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
-    if (plan.waves == kOne) return launch_lds<E, kOne, true>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
-    if constexpr (E == 4)
-        if (places) return launch_lds<E, kTwo, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
-    return launch_lds<E, kTwo, true>(c, N, plan, restarts, tours, costs, moves, skip_if_small, s);
+    if constexpr (E > 2) {                                      // N <= 128 comes here with more than 1024 restarts
+        if (plan.together && plan.waves == kOne)
+            return launch_lds<E, kOne, true>(c, N, plan, restarts, tours, costs, moves, skip_if_small, left_over, s);
+        if constexpr (E == 4)
+            if (plan.together && places)
+                return launch_lds<E, kTwo, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, left_over, s);
+        if (plan.together) return launch_lds<E, kTwo, true>(c, N, plan, restarts, tours, costs, moves, skip_if_small, left_over, s);
+    }
+    return launch_lds<E, 1, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, left_over, s);
 }
 
 template <int WAVES>
 hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
-                        hipStream_t s) {
+                        bool left_over, hipStream_t s) {
     int M;
     const uint32_t* lists;
     const uint16_t* counts;
-    hipError_t e = launch_partner_lists(c, N, room, M, lists, counts, s);
+    hipError_t e = launch_partner_lists(c, N, room, M, lists, counts, s, left_over);
     if (e != hipSuccess) return e;
     const size_t lds = group_order_bytes(N) + WAVES * group_wave_bytes(kGroupRoom, true);
     e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((twoopt_sum_pruned_group_kernel<WAVES>), dim3(restarts), dim3(64 * WAVES), lds, s, c, N, M, lists,
-                       counts, tours, costs, moves);
+                       counts, tours, costs, moves, left_over ? 1 : 0);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
-                                hipStream_t s) {
+                                hipStream_t s, bool there) {
     M = group_list(N);
     lists = (const uint32_t*)room;
     counts = (const uint16_t*)(lists + (size_t)N * M);
+    if (there) return hipSuccess;
     hipLaunchKernelGGL(partner_lists_kernel, dim3((N + 3) / 4), dim3(256), 0, s, c, N, M, (uint32_t*)lists, (uint16_t*)counts);
     return hipGetLastError();
 }
 
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
-                                  int32_t* moves, const int32_t* skip_if_small, hipStream_t s) {
-    if (N <= 128) return launch_waves<2>(c, N, restarts, tours, costs, moves, skip_if_small, s);
-    if (N <= 192) return launch_waves<3>(c, N, restarts, tours, costs, moves, skip_if_small, s);
-    if (N <= 256) return launch_waves<4>(c, N, restarts, tours, costs, moves, skip_if_small, s);
+                                  int32_t* moves, const int32_t* skip_if_small, bool left_over, hipStream_t s) {
+    if (N <= 128) return launch_waves<2>(c, N, restarts, tours, costs, moves, skip_if_small, left_over, s);
+    if (N <= 192) return launch_waves<3>(c, N, restarts, tours, costs, moves, skip_if_small, left_over, s);
+    if (N <= 256) return launch_waves<4>(c, N, restarts, tours, costs, moves, skip_if_small, left_over, s);
     // at least a wave per 64 nodes; more where the compute units have room for them (a wave per 64 nodes / 8 / 12 / 16 waves: N = 300, 250
     // restarts 1782 / 1590 / 1534 / 1620 us, 500 restarts 1982 / 1867 / 2022 / 2300, 1000 restarts 2523 / 3219 / 3786; N = 512, 250
     // restarts 3621 / - / 3340 / 3330, 500 restarts 4431 / - / 4605 / 4900)
     if (restarts <= 256) {
-        if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, s);
+        if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, left_over, s);
     } else if (restarts <= 512) {
-        if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, s);
+        if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, left_over, s);
     }
-    if (N <= 320) return launch_group<5>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 384) return launch_group<6>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 448) return launch_group<7>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 640) return launch_group<10>(c, N, room, restarts, tours, costs, moves, s);
-    if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, s);
-    return launch_group<16>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 320) return launch_group<5>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    if (N <= 384) return launch_group<6>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    if (N <= 448) return launch_group<7>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    if (N <= 640) return launch_group<10>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    return launch_group<16>(c, N, room, restarts, tours, costs, moves, left_over, s);
 }
 
 }  // namespace cc

@@ -73,14 +73,20 @@ hipError_t launch_2opt_max_n64(const int32_t* c, int restarts, uint64_t seed, bo
 hipError_t launch_2opt_dsum_n64(const int32_t* c, int restarts, uint64_t seed, bool generate, bool with_flip, int32_t* tours,
                                 int64_t* costs, int32_t* moves, const int32_t* flags, hipStream_t s);
 
-// Ring-sum objective, 65 <= N <= 1024 and any entries (cc_2opt_sum_pruned.hip).  `tours` must hold the initial tours;
+// Ring-sum objective, 97 <= N <= 1024 and any entries (cc_2opt_sum_pruned.hip).  `tours` must hold the initial tours;
 // `room`: 2 N^2 bytes of device memory when N > 256 (the workspace's mat16).  With skip_if_small (N <= 256) it returns at
 // once if skip_if_small[0], the matrix maximum, is below 2^16.
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
-                                  int32_t* moves, const int32_t* skip_if_small, hipStream_t s);
-// Partner lists of all nodes for N > 256, written into `room` (2 N^2 bytes): M entries per list, where lists and counts lie.
+                                  int32_t* moves, const int32_t* skip_if_small, bool left_over, hipStream_t s);
+// 65 <= N <= 1024, few enough restarts (launch_2opt): a workgroup per restart keeps its pairs (cc_2opt_sum_kept.hip).  A restart whose pairs do not fit is left where
+// it got to, with a cost of -1; launch_2opt_sum_pruned with left_over goes on with those (N > 256: with the lists that this one made).
+hipError_t launch_2opt_sum_kept(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
+                                int32_t* moves, hipStream_t s);
+bool sum_kept_leaves_restarts(int N);          // whether it may leave any
+// Partner lists of all nodes for N > 256, written into `room` (2 N^2 bytes): M entries per list, where lists and counts lie.  there:
+// they have been made, only where they lie is wanted.
 hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
-                                hipStream_t s);
+                                hipStream_t s, bool there = false);
 // Segment insertions, with or without 2-opt, any 4 <= N <= 1024 (cc_local_pruned.hip); same conventions.
 // With `flags` set an exhaustive kernel is enqueued behind it, and the matrix decides which of them does the work: the other
 // one when more than `most` of the N (N - 1) costs are about the smallest of their row or (N <= 256, to_16bit) more than `most_level`
@@ -93,11 +99,11 @@ struct TieHandover {
 };
 hipError_t launch_local_pruned(const int32_t* c, int N, bool with_2opt, void* room, const TieHandover& ties, int restarts,
                                int32_t* tours, int64_t* costs, int32_t* moves, hipStream_t s);
-// N = 128 / 192 / 256, ring-sum objective, max(c) < 2^16: one wavefront per restart, 16-bit matrix in LDS
+// N = 128 / 192, ring-sum objective, max(c) < 2^16: one wavefront per restart, 16-bit matrix in LDS
 // (cc_2opt_multi.hip).  launch_matrix_max writes max(c) to flags[0]; the kernel returns at once if
 // flags[0] >= 2^16.  `tours` must hold the initial tours.
 hipError_t launch_matrix_max(const int32_t* c, int N, int32_t* flags, hipStream_t s);
-// Any 4 <= N < 128, ring-sum objective, max(c) < 2^16: one wavefront per restart, order and partner data in LDS
+// Any 4 <= N <= 96, ring-sum objective, max(c) < 2^16: one wavefront per restart, order and partner data in LDS
 // (cc_2opt_multi.hip).  Same flags convention.
 hipError_t launch_2opt_sum_flex(const int32_t* c, int N, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                                 const int32_t* flags, hipStream_t s);

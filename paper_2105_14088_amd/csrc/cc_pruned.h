@@ -64,6 +64,7 @@ struct CallersMatrix {
     int N;
     __device__ __forceinline__ int operator()(int x, int y) const { return entry(c, N, x, y); }
     __device__ __forceinline__ int row(int x) const { return x; }
+    __device__ __forceinline__ int above(int x, int y) const { return c[__umul24((unsigned)x, (unsigned)N) + (unsigned)y]; }      // raw, x < y
     // for several look-ups at once: what is read, and then the cost
     __device__ __forceinline__ int raw(bool ok, int row, int y) const {
         const unsigned at = __umul24((unsigned)min(row, y), (unsigned)N) + (unsigned)max(row, y);
@@ -77,6 +78,7 @@ struct LdsMatrix {
     int N;
     __device__ __forceinline__ int operator()(int x, int y) const { return m[__umul24((unsigned)x, (unsigned)N) + (unsigned)y]; }
     __device__ __forceinline__ const uint16_t* row(int x) const { return m + __umul24((unsigned)x, (unsigned)N); }
+    __device__ __forceinline__ int above(int x, int y) const { return (*this)(x, y); }
     __device__ __forceinline__ int raw(bool, const uint16_t* row, int y) const { return row[(unsigned)y]; }
     __device__ __forceinline__ int cost(int raw) const { return raw; }
 };

@@ -1,0 +1,49 @@
+"""GPU parity of the ring-sum descents that keep their pairs: every launch the dispatch chooses on both sides of its lines, entries on both
+sides of 2^16, pairs that do not fit, descents that are left to the other kernel, orders that are no permutation."""
+import numpy as np
+import pytest
+
+import oracle
+from gen import hierarchical_matrix, random_matrix
+from gpu_util import gpu_search, say
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
+
+
+def _zones(n, count):
+    zone = np.random.default_rng(n).permutation(n) * count // n
+    c = np.where(zone[:, None] == zone[None, :], 100, 1000)
+    return np.where(np.eye(n, dtype=bool), 0, c).astype(np.int32)
+
+
+def _check(c, restarts, seed, rows, init=None):
+    got = gpu_search(c, oracle.SUM, restarts, seed, init)
+    k = int(np.argmin(got["costs"]))
+    assert got["best_restart"] == k and got["best_cost"] == got["costs"][k]
+    for r in rows:
+        span = (r, r + 1) if init is None else (0, 1)
+        costs, tours, moves = oracle.restarts(c, oracle.SUM, seed, *span, init=None if init is None else init[r:r + 1])
+        assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0]
+        assert np.array_equal(got["tours"][r], tours[0])
+
+
+# both sides of every line of launch_2opt and launch_2opt_sum_kept, the smallest and the largest N of each range
+@pytest.mark.parametrize("n,restarts", [(65, 1), (65, 512), (79, 513), (80, 257), (80, 1024), (97, 1025), (112, 1000), (113, 1000), (127, 2048),
+                                        (128, 256), (128, 257), (128, 1024), (129, 513), (176, 512), (177, 512), (192, 1536), (255, 2048),
+                                        (256, 512), (256, 513), (257, 256), (320, 513), (321, 513), (512, 257), (513, 3), (640, 3), (641, 3),
+                                        (1023, 2)])
+def test_every_launch(n, restarts):
+    for c, tag in ((hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n), "racks"),
+                   (random_matrix(n, n, symmetric=True, lo=0, hi=4), "ties"), (_zones(n, 2), "two zones"), (_zones(n, n // 8), "racks of eight"),
+                   (random_matrix(n, n, symmetric=True, lo=1, hi=1 << 20), "beyond 2^16")):
+        say(f"kept ring sum N={n} R={restarts} {tag}")
+        _check(c, restarts, 21, sorted({0, restarts // 2, restarts - 1}))
+
+
+@pytest.mark.parametrize("n", [65, 66, 100, 128])
+def test_orders_that_are_no_permutation_up_to_128(n):
+    say(f"kept ring sum N={n}: orders that are no permutation")
+    init = np.random.default_rng(5).integers(0, n, size=(4, n)).astype(np.int32)
+    init[3] = np.random.default_rng(6).permutation(n)
+    for c in (random_matrix(n, 18, symmetric=True, lo=0, hi=3000), random_matrix(n, 19, symmetric=True, lo=0, hi=1 << 20)):
+        _check(c, 4, 1, range(4), init)
