@@ -56,7 +56,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
             def compile_one(src: str) -> str:
                 obj = os.path.join(tmp, os.path.basename(src) + ".o")
-                cmd = [hipcc] + HIPCC_FLAGS + os.environ.get("XF","").split() + ["-save-temps", "-c", src, "-o", obj]
+                cmd = [hipcc] + HIPCC_FLAGS + ["-save-temps", "-c", src, "-o", obj]
                 if verbose:
                     print(" ".join(cmd), flush=True)
                 subprocess.check_call(cmd, cwd=tmp)
