@@ -1175,14 +1175,24 @@ __global__ __launch_bounds__(1024) void links_batch_lds16_kernel(const int32_t* 
 // pairs held one value sixteen times where the numbers follow the hosts, and five times as many links were marked (pairs that
 // cost what their hosts do, 65536 orders: N = 1024 187 us, now 138; N = 512 89, now 75; numbers in no order 137 and 75 either
 // way); 4096 places of their own mark no better and take 8 us to read at N = 1024.
-// Word (y >> 5) * N + x holds the pairs of x with the
-// nodes y & ~31 .. y | 31 (the folded matrix is symmetric, so a ballot over x gives the words of y).  tops[workgroup] =
-// largest entry seen, for the early end in rd_batch_marked_kernel.
+// A word holds the pairs of x with the 32 nodes that share their low LOGN - 5 bits with y, the bit of y's high bits h at 31 - h, so that
+// a shift by h puts it at the top.  Its byte address takes bits from x and bits from y, all of which mark_word<LOGN> of either
+// holds in their places: one v_bfi per look-up.  tops[workgroup] = largest entry seen, tops[kMarkBlocks] = T, for the early end in rd_batch_marked_kernel.
 // Behind the marks (N^2 / 8 bytes) the folded entries themselves, 16 bits each, lower triangle with diagonal by rows
 // (N (N + 1) bytes, both within the workspace's 2 N^2): an exact look-up is then one request; used when all fit 16 bits.
 // Behind those the workgroups' largest entries.  A workgroup per compute unit (64 workgroups: 16.5 us, 256: 15.6).
 constexpr int kMarkBlocks = 256;
 constexpr size_t mark_tops_offset(size_t N) { return N * N / 8 + N * (N + 1); }
+
+// Of an address in the marks, what x gives: node << 3 or 4, its low bits in the bank's; the others are y's low bits.  y's high bits,
+// the shift, are bits 8 .. 12 of its own word.
+template <int LOGN>
+constexpr unsigned kMarkX = LOGN == 10 ? 0x1ff8u : 0x1ff0u;
+template <int LOGN>
+__device__ __forceinline__ unsigned mark_word(unsigned node) {
+    if (LOGN == 10) return (__umul24(node, 0x2008u) & 0x1fff8u) | ((node >> 2) & 4u);
+    return (__umul24(node, 0x2010u) & 0x7ff0u) | (node & 12u);
+}
 
 template <int LOGN>
 __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restrict__ c, uint32_t* __restrict__ marks,
@@ -1191,7 +1201,9 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
     constexpr int kWanted = LOGN == 10 ? 2 : 3;                                 // of 128 samples: 6 or 5 of N / 2
     constexpr int kRows = N * N / 64 / (16 * kMarkBlocks);                      // rows of 64 entries per wave
     uint16_t* folded = (uint16_t*)(marks + N * N / 32);
+    constexpr int kGroupRows = kRows * 16 * 64 / N, kLow = LOGN - 5;            // rows of N entries per workgroup
     __shared__ int per_wave[16], wave_top[16];
+    __shared__ uint32_t row_bits[kGroupRows][N / 32];
     const int lane = lane_id(), wv = threadIdx.x >> 6;
     auto entry = [&](int x, int y) { return clampi(max(c[x * N + y], c[y * N + x]), 0, (1 << 21) - 1); };
     int v[2];
@@ -1214,7 +1226,7 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
         const int y = y0 + k;
         const unsigned long long bits = __ballot(e[k] >= T);
         top = max(top, e[k]);
-        if (lane < 2) marks[((x0 >> 5) + lane) * N + y] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+        if (lane < 2) row_bits[y - kGroupRows * blockIdx.x][(x0 >> 5) + lane] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
         if (x0 + lane <= y) folded[y * (y + 1) / 2 + x0 + lane] = (uint16_t)e[k];
     }
     top = wave_max(top);
@@ -1223,62 +1235,99 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
     if (threadIdx.x == 0) {
         for (int k = 1; k < 16; ++k) top = max(top, wave_top[k]);
         tops[blockIdx.x] = top;
+        if (blockIdx.x == 0) tops[kMarkBlocks] = T;
+    }
+    // the rows' bits into words of nodes with the same low bits, half a wave per word
+#pragma unroll
+    for (int i = 0; i < (kGroupRows << kLow) / 32; ++i) {
+        const int o = 32 * i + 2 * wv + (lane >> 5), row = o >> kLow, low = o & ((1 << kLow) - 1);
+        const int x = low | ((31 - (lane & 31)) << kLow);
+        const unsigned long long bits = __ballot((row_bits[row][x >> 5] >> (x & 31)) & 1u);
+        const unsigned at = (mark_word<LOGN>(kGroupRows * blockIdx.x + row) & kMarkX<LOGN>) | (mark_word<LOGN>(low) & ~kMarkX<LOGN>);
+        if ((lane & 31) == 0) marks[at >> 2] = lane ? (uint32_t)(bits >> 32) : (uint32_t)bits;
     }
 }
 
-// Lane l <- lane l xor 2^M of its own `v` (M = 0 .. 3: within a row of 16 lanes).
+// The two ends of the links of ranks that differ in lane bit M < 4, from the registers v[2u] and v[2u + 1]: a lane with the bit clear
+// takes the link of the even register, a lane with the bit set that of the odd one, so the 64 lanes hold 64 different links.  One
+// instruction per end: the lane's own register or, through DPP, its partner's other one.  A DPP operand must have been written
+// two instructions before: one wait for four of them.
+#define CC_LANE_ENDS(dpp_x, dpp_y)                                                                                     \
+    asm("s_mov_b64 vcc, %12\n\ts_nop 0\n\t"                                                                            \
+        "v_cndmask_b32_dpp %0, %5, %4, vcc " dpp_x " row_mask:0xf bank_mask:0xf\n\t"                                   \
+        "v_cndmask_b32_dpp %1, %7, %6, vcc " dpp_x " row_mask:0xf bank_mask:0xf\n\t"                                   \
+        "v_cndmask_b32_dpp %2, %9, %8, vcc " dpp_x " row_mask:0xf bank_mask:0xf\n\t"                                   \
+        "v_cndmask_b32_dpp %3, %11, %10, vcc " dpp_x " row_mask:0xf bank_mask:0xf"                                     \
+        : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3])                                                           \
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "s"(~kUpper) : "vcc"); \
+    asm("s_mov_b64 vcc, %12\n\ts_nop 0\n\t"                                                                            \
+        "v_cndmask_b32_dpp %0, %4, %5, vcc " dpp_y " row_mask:0xf bank_mask:0xf\n\t"                                   \
+        "v_cndmask_b32_dpp %1, %6, %7, vcc " dpp_y " row_mask:0xf bank_mask:0xf\n\t"                                   \
+        "v_cndmask_b32_dpp %2, %8, %9, vcc " dpp_y " row_mask:0xf bank_mask:0xf\n\t"                                   \
+        "v_cndmask_b32_dpp %3, %10, %11, vcc " dpp_y " row_mask:0xf bank_mask:0xf"                                     \
+        : "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])                                                           \
+        : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "s"(kUpper) : "vcc")
 template <int M>
-__device__ __forceinline__ unsigned from_lane_xor(unsigned v) {
-    const int s = (int)v;
-    if (M == 0) return (unsigned)__builtin_amdgcn_update_dpp(s, s, 0xB1, 0xf, 0xf, true);          // quad_perm 1,0,3,2
-    if (M == 1) return (unsigned)__builtin_amdgcn_update_dpp(s, s, 0x4E, 0xf, 0xf, true);          // quad_perm 2,3,0,1
-    if (M == 3) return (unsigned)__builtin_amdgcn_update_dpp(s, s, 0x128, 0xf, 0xf, true);         // row_ror:8
-    const int r = __builtin_amdgcn_update_dpp(s, s, 0x141, 0xf, 0xf, true);                        // row_half_mirror: xor 7
-    return (unsigned)__builtin_amdgcn_update_dpp(r, r, 0x1B, 0xf, 0xf, true);                      // quad_perm 3,2,1,0: xor 3
-}
-
-// The two ends of the links of ranks that differ in lane bit M, from two registers of ranks: a lane with the bit clear
-// takes the link of register a, a lane with the bit set that of register b, so the 64 lanes hold 64 different links.
-template <int M>
-__device__ __forceinline__ void lane_links(unsigned a, unsigned b, int lane, unsigned& x, unsigned& y) {
-    if constexpr (M >= 4) {
-        const auto r = M == 4 ? __builtin_amdgcn_permlane16_swap(a, b, false, false)
-                              : __builtin_amdgcn_permlane32_swap(a, b, false, false);
-        x = r[0];
-        y = r[1];
+__device__ __forceinline__ void lane_links(const unsigned* v, unsigned (&x)[4], unsigned (&y)[4]) {
+    constexpr unsigned long long kUpper = M == 0 ? 0xaaaaaaaaaaaaaaaaull : M == 1 ? 0xccccccccccccccccull : M == 2 ? 0xf0f0f0f0f0f0f0f0ull : 0xff00ff00ff00ff00ull;
+    if constexpr (M == 0) {
+        CC_LANE_ENDS("quad_perm:[1,0,3,2]", "quad_perm:[1,0,3,2]");
+    } else if constexpr (M == 1) {
+        CC_LANE_ENDS("quad_perm:[2,3,0,1]", "quad_perm:[2,3,0,1]");
+    } else if constexpr (M == 2) {
+        CC_LANE_ENDS("row_ror:4", "row_ror:12");
     } else {
-        const bool upper = (lane >> M) & 1;
-        x = upper ? b : a;
-        y = from_lane_xor<M>(upper ? a : b);
+        CC_LANE_ENDS("row_ror:8", "row_ror:8");
     }
 }
+#undef CC_LANE_ENDS
 
 // One order per wave, its ranks in registers: lane l holds ranks 256 q + 4 l + j (register 4 q + j), so rounds 0, 1 and
-// 8, 9 pair registers of a lane and rounds 2 .. 7 pair lanes.  Per link two or three VALU instructions bring the ends
-// together and one LDS look-up (random, which with its bank conflicts is the larger half of the time) tells whether it is
-// marked; the marked ones, about 60 of 5120 at N = 1024, are then looked up exactly in the caller's matrix, each lane
-// taking its own one by one, all rounds mixed, their maxima formed in LDS.  A round without a marked link is looked up
-// whole; one that has reached the matrix maximum is finished, so a matrix of few values ends early.
-// Before: the folded 16-bit matrix through L2, bound by its request rate.  Both launches together, seeded orders: N = 1024,
-// 65536 orders 1384 -> 138 us (1.9 TB/s of the order stream), 1000 orders 104 -> 23 us; N = 512, 131072 orders
-// 1136 -> 142 us, 1000 orders 27 -> 16 us.  Orders without any marked link, every link looked up: N = 1024, 65536 orders
-// 1213 -> 1227 us, N = 512 458 -> 455 us.  So nothing else serves these sizes.
+// 8, 9 pair registers of a lane and rounds 2 .. 7 pair lanes.  A link is at most one VALU instruction per end to bring the ends together,
+// one for the address, one LDS look-up and two to shift its bit into the lane's word of tested links.  The marked ones, about 60 of
+// 5120 at N = 1024, are then looked up exactly, each lane its first and its last one at a time, all rounds mixed, their maxima
+// formed in LDS.  A round without a marked link is looked up whole; one that has reached the matrix maximum is finished, so a
+// matrix of few values ends early, and where T is the maximum nothing is looked up at all.
+// What bounds it: N = 1024, 65536 orders keep the LDS busy for 75 % of the time (6.4 clocks per look-up of 64 random words, two
+// thirds of them bank conflicts) and the VALU for 73 % (620 instructions per order, 880 before the address was one instruction and
+// the bit two); fifteen wavefronts are what fits beside the marks.  Both launches together, seeded orders, before -> now: N = 1024,
+// 65536 orders 137 -> 116 us, 1000 orders 22.0 -> 20.9; N = 512, 131072 orders 142 -> 115 us, 65536 75 -> 62 us, 8000 18.4 -> 17.0;
+// two values, 16384 orders N = 1024 87 -> 39 us, N = 512 56 -> 20; 16384 orders near a search's result as before (102 -> 101, 52.2
+// -> 52.0).  A link's word is asked for twelve links before it is used (eight at a time, waited for together: 121 us).  Through the folded
+// 16-bit matrix, bound by L2 requests: 1384 us and 1136.  Orders without any marked link, every link looked up: N = 1024, 65536
+// orders 1213 -> 1227 us, N = 512 458 -> 455 us.  So nothing else serves these sizes.
 template <int LOGN>
 __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kernel(
     const int32_t* __restrict__ c, const uint32_t* __restrict__ marks, const int32_t* __restrict__ tops,
     const int32_t* __restrict__ weights, const int32_t* __restrict__ perms, int64_t B, int64_t* __restrict__ out) {
     constexpr int N = 1 << LOGN, RK = N / 64, LM = RK / 2, Q = N / 256;         // ranks, links, quads of ranks per lane
-    constexpr int WAVES = LOGN == 10 ? 15 : 16, WORDS = (LM * LOGN + 31) / 32;
+    constexpr int WAVES = LOGN == 10 ? 15 : 16, kLinks = LM * LOGN, WORDS = (kLinks + 31) / 32, kIdle = 32 * WORDS - kLinks;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_marked[];
-    uint32_t* lmarks = (uint32_t*)smem_marked;                                              // [N * N / 32]
+    uint32_t* lmarks = (uint32_t*)smem_marked;                                              // [N * N / 32], at LDS address 0: no other variable is there
     uint16_t* order = (uint16_t*)(smem_marked + N * N / 8) + (threadIdx.x >> 6) * N;        // [WAVES][N]
     int* worst = (int*)(smem_marked + N * N / 8 + sizeof(uint16_t) * WAVES * N) + (threadIdx.x >> 6) * 16;  // [WAVES][16]
+    // by its place in the order of testing: lower rank of the link but for the lane's part << 0, round << 10, lane bit that counts << 16
+    // and whether one does << 24
+    int* links = (int*)(smem_marked + N * N / 8 + (sizeof(uint16_t) * N + sizeof(int) * 16) * WAVES);       // [kLinks]
     const int lane = lane_id(), wv = threadIdx.x >> 6;
+    auto round_of = [](int nth) { return nth < 6 ? nth : LOGN == 10 ? (nth < 8 ? nth + 2 : nth - 2) : nth == 6 ? 8 : nth - 1; };
+    auto round_bits = [](int nth) {                                              // in its word of tested links
+        const int from = nth * LM, in_word = kLinks - (from & ~31) < 32 ? kLinks - (from & ~31) : 32;
+        return ((1u << LM) - 1) << (in_word - (from & 31) - LM);
+    };
+    if ((int)threadIdx.x < kLinks) {
+        const int u = threadIdx.x % LM, k = round_of(threadIdx.x / LM), bit = k < 2 ? k : k - 6;
+        const bool in_lane = k >= 2 && k < 8;
+        const int i = in_lane ? 2 * u : ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));         // register
+        links[threadIdx.x] = (256 * (i >> 2) + (i & 3)) | k << 10 | (in_lane && k != 7 ? (k - 2) << 16 | 1 << 24 : 0);
+    }
+    const int lane_swapped = (lane >> 5) << 6 | (lane & 15) << 2 | (lane >> 4 & 1);
     for (int e = threadIdx.x; e < N * N / 128; e += 64 * WAVES) ((int4*)lmarks)[e] = ((const int4*)marks)[e];
     int top = 0;
 #pragma unroll
     for (int k = 0; k < kMarkBlocks; k += 64) top = max(top, tops[k + lane]);
     top = wave_max(top);
+    const bool marked_is_top = tops[kMarkBlocks] >= top;
     const long long weight =
         lane < LOGN ? (weights ? (long long)clampi(weights[lane], 0, kMaxRoundWeight) : 1ll) : 0ll;
     __syncthreads();
@@ -1305,77 +1354,146 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
     int4 v[Q];
     if (b < B) load(b, v);
     for (; b < B; b += nwaves) {
-        unsigned X[RK];                                                          // 4 * node
+        unsigned X[RK];                                                          // mark_word of the node
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            X[4 * q] = (unsigned)clampi(v[q].x, 0, N - 1) << 2;
-            X[4 * q + 1] = (unsigned)clampi(v[q].y, 0, N - 1) << 2;
-            X[4 * q + 2] = (unsigned)clampi(v[q].z, 0, N - 1) << 2;
-            X[4 * q + 3] = (unsigned)clampi(v[q].w, 0, N - 1) << 2;
-            const uint2 four = make_uint2(X[4 * q] | X[4 * q + 1] << 16, X[4 * q + 2] | X[4 * q + 3] << 16);
+            const unsigned n[4] = {(unsigned)clampi(v[q].x, 0, N - 1), (unsigned)clampi(v[q].y, 0, N - 1), (unsigned)clampi(v[q].z, 0, N - 1),
+                                   (unsigned)clampi(v[q].w, 0, N - 1)};
+            const uint2 four = make_uint2(n[0] | n[1] << 16, n[2] | n[3] << 16);
             __builtin_memcpy(__builtin_assume_aligned(order + 256 * q + 4 * lane, 8), &four, 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) X[4 * q + j] = mark_word<LOGN>(n[j]);
         }
         if (lane < 16) worst[lane] = -1;
         if (b + nwaves < B) load(b + nwaves, v);
+        // a bit per link, LM per round, the first one tested on top: rounds 0 .. 5, 8, 9, 6, 7
         uint32_t hits[WORDS] = {};
-        auto test = [&](int at, unsigned x, unsigned y) {
-            const uint32_t word = *(const uint32_t*)((const char*)lmarks + (((y & ~127u) << (LOGN - 5)) | x));
-            hits[at >> 5] |= ((word >> ((y >> 2) & 31)) & 1u) << (at & 31);
+        // A link's word is asked for kAhead links before its bit is taken.
+        constexpr int kAhead = 12;
+        int asked = 0, taken = 0;                                                // constants at every use
+        uint32_t word[2 * kAhead];
+        unsigned shift[2 * kAhead];
+        auto take = [&] {
+            uint32_t shifted;
+            asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD"
+                : "=v"(shifted) : "v"(shift[taken % (2 * kAhead)]), "v"(word[taken % (2 * kAhead)]));
+            hits[taken >> 5] = __builtin_amdgcn_alignbit(hits[taken >> 5], shifted, 31);
+            ++taken;
         };
+        auto test = [&](unsigned x, unsigned y) {
+            // written out: the compiler masks both ends and adds a base that is 0
+            uint32_t at;
+            asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(at) : "s"(kMarkX<LOGN>), "v"(x), "v"(y));
+            word[asked % (2 * kAhead)] = *(const __attribute__((address_space(3))) uint32_t*)(uintptr_t)at;
+            shift[asked % (2 * kAhead)] = y;
+            if (++asked % 4 == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+                while (taken + kAhead < asked) take();
+            }
+        };
+        auto lane_round = [&](auto m) {
+#pragma unroll
+            for (int u = 0; u < LM; u += 4) {
+                unsigned x[4], y[4];
+                lane_links<decltype(m)::value>(X + 2 * u, x, y);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) test(x[i], y[i]);
+            }
+        };
+        auto register_round = [&](auto m) {
+            constexpr int bit = decltype(m)::value;
+#pragma unroll
+            for (int u = 0; u < LM; ++u) {
+                const int i = ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));
+                test(X[i], X[i | (1 << bit)]);
+            }
+        };
+        register_round(std::integral_constant<int, 0>{});
+        register_round(std::integral_constant<int, 1>{});
+        lane_round(std::integral_constant<int, 0>{});
+        lane_round(std::integral_constant<int, 1>{});
+        lane_round(std::integral_constant<int, 2>{});
+        lane_round(std::integral_constant<int, 3>{});
+        register_round(std::integral_constant<int, 2>{});
+        if constexpr (LOGN == 10) register_round(std::integral_constant<int, 3>{});
+        // Lane bits 4 and 5 change places with the lowest bit of the register's number: a swap per two registers, after which they hold
+        // the two ends (and rank bit 0 is where bit 6 was, then bit 6 where bit 7 was)
 #pragma unroll
         for (int u = 0; u < LM; ++u) {
-            unsigned x, y;
-#pragma unroll
-            for (int k = 0; k < LOGN; ++k) {
-                if (k >= 2 && k < 8) continue;
-                const int bit = k < 2 ? k : k - 6;                               // of the register index
-                const int i = ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));
-                test(k * LM + u, X[i], X[i | (1 << bit)]);
-            }
-            lane_links<0>(X[2 * u], X[2 * u + 1], lane, x, y);
-            test(2 * LM + u, x, y);
-            lane_links<1>(X[2 * u], X[2 * u + 1], lane, x, y);
-            test(3 * LM + u, x, y);
-            lane_links<2>(X[2 * u], X[2 * u + 1], lane, x, y);
-            test(4 * LM + u, x, y);
-            lane_links<3>(X[2 * u], X[2 * u + 1], lane, x, y);
-            test(5 * LM + u, x, y);
-            lane_links<4>(X[2 * u], X[2 * u + 1], lane, x, y);
-            test(6 * LM + u, x, y);
-            lane_links<5>(X[2 * u], X[2 * u + 1], lane, x, y);
-            test(7 * LM + u, x, y);
+            const auto r = __builtin_amdgcn_permlane16_swap(X[2 * u], X[2 * u + 1], false, false);
+            X[2 * u] = r[0];
+            X[2 * u + 1] = r[1];
+            test(r[0], r[1]);
         }
+#pragma unroll
+        for (int u = 0; u < LM; ++u) {
+            const auto r = __builtin_amdgcn_permlane32_swap(X[2 * u], X[2 * u + 1], false, false);
+            test(r[0], r[1]);
+        }
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) take();
         __builtin_amdgcn_wave_barrier();
         uint32_t finished = 0;
+        if (marked_is_top) {
+            // a matrix of few values: a marked link is worth the matrix maximum, which ends its round
+#pragma unroll
+            for (int nth = 0; nth < LOGN; ++nth) finished |= __ballot(hits[nth * LM >> 5] & round_bits(nth)) ? 1u << round_of(nth) : 0u;
+            if (lane < LOGN && (finished >> lane & 1)) worst[lane] = top;
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) hits[w] = 0;
+            __builtin_amdgcn_wave_barrier();
+        }
         for (;;) {
             uint32_t any = 0;
 #pragma unroll
             for (int w = 0; w < WORDS; ++w) any |= hits[w];
             if (__ballot(any != 0) == 0) break;
-            if (any) {
-                int at = 0;
-                bool found = false;
+            // a lane's first and its last link, their look-ups in flight together
+            uint32_t first = hits[WORDS - 1], last = hits[0];
+            int in_first = WORDS - 1, in_last = 0;
 #pragma unroll
-                for (int w = 0; w < WORDS; ++w) {
-                    if (!found && hits[w]) {
-                        at = 32 * w + __builtin_ctz(hits[w]);
-                        hits[w] &= hits[w] - 1;
-                        found = true;
-                    }
+            for (int w = 1; w < WORDS; ++w) {
+                in_first = hits[WORDS - 1 - w] ? WORDS - 1 - w : in_first;
+                first = hits[WORDS - 1 - w] ? hits[WORDS - 1 - w] : first;
+                in_last = hits[w] ? w : in_last;
+                last = hits[w] ? hits[w] : last;
+            }
+            const int from_top = __builtin_clz(first | 1u), from_bottom = __builtin_ctz(last | 0x80000000u);
+            const uint32_t bit_first = any ? 0x80000000u >> from_top : 0u, bit_last = any ? 1u << from_bottom : 0u;
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) hits[w] &= ~((in_first == w ? bit_first : 0u) | (in_last == w ? bit_last : 0u));
+            const int at[2] = {32 * in_first + from_top - (in_first == WORDS - 1 ? kIdle : 0),
+                               32 * in_last + 31 - from_bottom - (in_last == WORDS - 1 ? kIdle : 0)};
+            int k[2], x[2], y[2], value[2];
+            if (any) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int link = links[at[i]];
+                    k[i] = link >> 10 & 15;
+                    const int p = (link & 1023) + (k[i] == 7 ? lane_swapped : 4 * lane) + (int)__builtin_amdgcn_ubfe((unsigned)lane, (unsigned)link >> 16, (unsigned)link >> 24);
+                    x[i] = order[p];
+                    y[i] = order[p ^ (1 << k[i])];
                 }
-                const int k = at / LM, u = at % LM, bit = k < 2 ? k : k - 6;
-                const int i = k >= 2 && k < 8 ? 2 * u + ((lane >> (k - 2)) & 1)
-                                              : ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));
-                const int p = 256 * (i >> 2) + 4 * lane + (i & 3);
-                atomicMax(worst + k, exact(order[p] >> 2, order[p ^ (1 << k)] >> 2));
+                if (halves) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const unsigned hi = (unsigned)max(x[i], y[i]), lo = (unsigned)min(x[i], y[i]);
+                        value[i] = folded[(__umul24(hi, hi + 1) >> 1) + lo];
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) value[i] = exact(x[i], y[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) atomicMax(worst + k[i], value[i]);
             }
             __builtin_amdgcn_wave_barrier();
             const uint32_t full = (uint32_t)__ballot(lane < LOGN && *(volatile int*)(worst + (lane & 15)) >= top);
             if (full != finished) {
                 finished = full;
 #pragma unroll
-                for (int at = 0; at < LM * LOGN; at += LM)
-                    if ((full >> (at / LM)) & 1) hits[at >> 5] &= ~(((1u << LM) - 1) << (at & 31));
+                for (int nth = 0; nth < LOGN; ++nth)
+                    if ((full >> round_of(nth)) & 1) hits[nth * LM >> 5] &= ~round_bits(nth);
             }
         }
         int mine = lane < LOGN ? *(volatile int*)(worst + (lane & 15)) : 0;
@@ -1385,7 +1503,7 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
 #pragma unroll
             for (int u = 0; u < LM; ++u) {
                 const int i = lane + 64 * u, p = ((i >> k) << (k + 1)) | (i & ((1 << k) - 1));
-                t = max(t, exact(order[p] >> 2, order[p | (1 << k)] >> 2));
+                t = max(t, exact(order[p], order[p | (1 << k)]));
             }
             t = wave_max(t);
             if (lane == k) mine = t;
@@ -1401,7 +1519,7 @@ static hipError_t rd_marked_launch(const int32_t* c, void* room, const int32_t* 
                                    const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
     constexpr int N = 1 << LOGN, WAVES = LOGN == 10 ? 15 : 16;
     int32_t* tops = (int32_t*)((char*)room + mark_tops_offset(N));
-    const size_t lds = N * N / 8 + sizeof(uint16_t) * WAVES * N + sizeof(int) * WAVES * 16;
+    const size_t lds = N * N / 8 + sizeof(uint16_t) * WAVES * N + sizeof(int) * WAVES * 16 + sizeof(int) * (N / 128 * LOGN);
     hipError_t e = hipFuncSetAttribute((const void*)rd_batch_marked_kernel<LOGN>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -27,6 +27,8 @@ def _matrices(n):
     half = random_matrix(n, n + 2, symmetric=False, lo=1, hi=500)
     half[: n // 2, n // 2:] += 10000
     yield "two islands", half
+    side = np.arange(n) >= n // 2
+    yield "two islands, two values", np.where(side[:, None] == side[None, :], 3, 9).astype(np.int32)
 
 
 @pytest.mark.parametrize("n", [512, 1024])
