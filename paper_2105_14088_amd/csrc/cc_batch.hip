@@ -432,10 +432,12 @@ static bool ring_rows_pays(int N, int64_t B) {
 // lanes at one common place.  Where all marked entries are the largest one nothing is read, and an order with many marked hops ends
 // at the first of the largest, so a matrix of few values ends early.
 // The generic kernels ask L2 for every hop and run at its request rate; here what is left is the marking (N = 500: 1 MB read per
-// compute unit, 14 us), sampling (3 us) and the order stream.  Generic -> marked, seeded orders: N = 300, 200000 orders 255 -> 75 us;
-// N = 500, 65000 orders 144 -> 47 us, of two bytes a rank 140 -> 42 us; N = 1000, 65000 orders 335 -> 95 us.  Orders of small hops
-// only: N = 500, 65000 orders 113 -> 46 us.  With sixteen lanes per order, a rank per load, the same 4096 places sampled by every
-// workgroup and a ballot per 64 marked entries: 65, 58, 134 and 57 us.
+// compute unit, 14 us), sampling (3 us), the order stream and a chain of LDS and L2 latencies per order, two orders' overlapping.
+// Generic -> marked, seeded orders: N = 500, 65000 orders 144 -> 43 us, of two bytes a rank 140 -> 38 us; N = 1000, 65000 orders
+// 335 -> 102 us.  Orders of small hops only: N = 500, 65000 orders 113 -> 38 us.  An order's entries
+// reduced before the next order was looked at: two bytes a rank, N = 300, 200000 orders 75 us, now 56; N = 400, 50000 31.5, now 28.1;
+// N = 500, 65000 41.0, now 37.9; N = 700, 60000 72, now 70; N = 1000, 65000 81, now 79; slower where every hop of an order is marked and none
+// is the largest (two values and a search's results, N = 500, 65000 orders 92 -> 96, N = 300, 200000 189 -> 202).
 // W consecutive ranks of an order, aligned as a rank is
 template <typename RANK, int W>
 struct Ranks;
@@ -546,12 +548,13 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
     const bool whole = lane * R <= N - R;                        // not: the first rank's hop is an earlier lane's
     const bool own = lane * R < N;                               // not: all of them are
     auto entry = [&](unsigned at) { return *(const int32_t*)((const char*)c + at); };
-    for (int64_t b = first_order; b < B; b += waves) {
+    // the next order's hops: where their entries lie, which of them are marked
+    auto test = [&](int64_t b, unsigned (&at)[H], int (&hit)[H], int& any) {
         const Mine now = next;
         next = after;
         after = load(min(b + 2 * waves, B - 1));
         // hop i leads into x[i] from y[i]
-        unsigned x[H], y[H], at[H];
+        unsigned x[H], y[H];
 #pragma unroll
         for (int i = 0; i < W; ++i) {
             x[i] = node(now.a[i]);
@@ -565,7 +568,7 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
             else y[W] = R == 2 * W ? x[W - 1] : x[W - 2];        // its own predecessor, or that of the rank it has again
         }
         y[0] = (unsigned)__builtin_amdgcn_update_dpp(0, (int)x[H - 1], w64::kDppWaveRor1, 0xf, 0xf, true);
-        int hit[H], any = 0, best = 0;
+        any = 0;
 #pragma unroll
         for (int i = 0; i < H; ++i) {
             at[i] = __umul24(x[i], (unsigned)N) + y[i];
@@ -576,37 +579,68 @@ __global__ __launch_bounds__(1024) void ring_batch_max_marked_kernel(const int32
 #pragma unroll
         for (int i = 0; i < H; ++i) any |= hit[i];
         if (!own) any = 0;
-        if (__ballot(any != 0) == 0) {                           // an order without a marked hop: all of them
-            int value[H];
+    };
+    if (known) {
+        for (int64_t b = first_order; b < B; b += waves) {
+            unsigned at[H];
+            int hit[H], any, best = 0;
+            test(b, at, hit, any);
+            if (__ballot(any != 0)) {
+                best = top;
+            } else {                                             // an order without a marked hop: all of them
+                int value[H];
 #pragma unroll
-            for (int i = 0; i < H; ++i) value[i] = entry(at[i]);
-            if (!whole) value[0] = 0;
+                for (int i = 0; i < H; ++i) value[i] = entry(at[i]);
+                if (!whole) value[0] = 0;
 #pragma unroll
-            for (int i = 0; i < H; ++i) best = max(best, value[i]);
-            best = wave_max(best);
-        } else if (known) {
-            best = top;
-        } else if (__popcll(__ballot(any != 0)) > 32) {          // a matrix of few values: until one of the largest is met
+                for (int i = 0; i < H; ++i) best = max(best, value[i]);
+                best = wave_max(best);
+            }
+            if (lane == 0) out[b] = best;
+        }
+        return;
+    }
+    // An order's entries are reduced when the next order's hops have been tested.  They are asked for in every order and at one place in the
+    // code: waits count the loads behind, over all ways, and a wait for an order's ranks would otherwise be one for the entries of the
+    // order before as well (which costs what reducing them later gains).
+    int value[H], counts[H], more = 0;
+    auto finish = [&](int64_t b) {
+        int best = more;
+#pragma unroll
+        for (int i = 0; i < H; ++i) best = max(best, value[i] & counts[i]);
+        best = wave_max(own ? best : 0);
+        if (lane == 0) out[b] = best;
+    };
+    for (int64_t b = first_order; b < B; b += waves) {
+        unsigned at[H];
+        int hit[H], any, best = 0;
+        test(b, at, hit, any);
+        const int hits = __popcll(__ballot(any != 0));           // lanes with one
+        if (b != first_order) finish(b - waves);
+        if (hits > 32) {                                         // a matrix of few values: until one of the largest is met
 #pragma unroll
             for (int i0 = 0; i0 < H; i0 += 4) {
-                int value[4];
+                int some[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) value[i] = i0 + i < H ? entry(own ? at[i0 + i] & (unsigned)hit[i0 + i] : 0u) & hit[i0 + i] : 0;
-                best = max(max(best, value[0]), max(max(value[1], value[2]), value[3]));
+                for (int i = 0; i < 4; ++i) some[i] = i0 + i < H ? entry(own ? at[i0 + i] & (unsigned)hit[i0 + i] : 0u) & hit[i0 + i] : 0;
+                best = max(max(best, some[0]), max(max(some[1], some[2]), some[3]));
                 if (!own) best = 0;
                 if (__ballot(best >= top)) break;
             }
-            best = wave_max(best);
-        } else {
-            int value[H];
 #pragma unroll
-            for (int i = 0; i < H; ++i) value[i] = entry(own ? at[i] & (unsigned)hit[i] : 0u);
+            for (int i = 0; i < H; ++i) hit[i] = 0;
+        } else if (!hits) {                                      // an order without a marked hop: all of them
 #pragma unroll
-            for (int i = 0; i < H; ++i) best = max(best, value[i] & hit[i]);
-            best = wave_max(own ? best : 0);
+            for (int i = 0; i < H; ++i) hit[i] = i || whole ? -1 : 0;
         }
-        if (lane == 0) out[b] = best;
+        more = best;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            counts[i] = own ? hit[i] : 0;
+            value[i] = entry(at[i] & (unsigned)counts[i]);
+        }
     }
+    if (first_order < B) finish(first_order + (B - 1 - first_order) / waves * waves);
 }
 
 template <typename RANK, int W, int SECOND>
