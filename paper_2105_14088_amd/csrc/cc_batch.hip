@@ -1199,7 +1199,7 @@ __global__ __launch_bounds__(1024) void links_batch_lds16_kernel(const int32_t* 
     }
 }
 
-// N = 512, 1024 with a workspace: a round costs its largest link, so only links among the largest entries have to be
+// N = 512, 1024 with a workspace, halving-doubling and (N = 1024) BCube base 4: a round costs its largest link, so only links among the largest entries have to be
 // looked up exactly.  mark_links_kernel writes one bit per pair of nodes, "the larger direction costs T or more" (128 KiB
 // at N = 1024, which fits LDS; the 16-bit folded matrix, 2 MiB, does not); T is chosen so that about 5 of a
 // round's N / 2 links carry the bit, from the same 2048 sampled entries in every workgroup: 4 to 7 of them take the same time
@@ -1228,11 +1228,10 @@ __device__ __forceinline__ unsigned mark_word(unsigned node) {
     return (__umul24(node, 0x2010u) & 0x7ff0u) | (node & 12u);
 }
 
-template <int LOGN>
+template <int LOGN, int WANTED>
 __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restrict__ c, uint32_t* __restrict__ marks,
                                                           int32_t* __restrict__ tops) {
     constexpr int N = 1 << LOGN;
-    constexpr int kWanted = LOGN == 10 ? 2 : 3;                                 // of 128 samples: 6 or 5 of N / 2
     constexpr int kRows = N * N / 64 / (16 * kMarkBlocks);                      // rows of 64 entries per wave
     uint16_t* folded = (uint16_t*)(marks + N * N / 32);
     constexpr int kGroupRows = kRows * 16 * 64 / N, kLow = LOGN - 5;            // rows of N entries per workgroup
@@ -1253,7 +1252,7 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
     int e[kRows];
 #pragma unroll
     for (int k = 0; k < kRows; ++k) e[k] = entry(x0 + lane, y0 + k);
-    const int T = sampled_threshold<5>(v, kWanted, per_wave);
+    const int T = sampled_threshold<5>(v, WANTED, per_wave);
     int top = 0;
 #pragma unroll
     for (int k = 0; k < kRows; ++k) {
@@ -1282,7 +1281,7 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
     }
 }
 
-// The two ends of the links of ranks that differ in lane bit M < 4, from the registers v[2u] and v[2u + 1]: a lane with the bit clear
+// The two ends of the links of ranks that differ in lane bit M < 4, or (M = 4, 5) in lane bits 0 and 1, 2 and 3 both, from the registers v[2u] and v[2u + 1]: a lane with the bit clear
 // takes the link of the even register, a lane with the bit set that of the odd one, so the 64 lanes hold 64 different links.  One
 // instruction per end: the lane's own register or, through DPP, its partner's other one.  A DPP operand must have been written
 // two instructions before: one wait for four of them.
@@ -1303,13 +1302,17 @@ __global__ __launch_bounds__(1024) void mark_links_kernel(const int32_t* __restr
         : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "s"(kUpper) : "vcc")
 template <int M>
 __device__ __forceinline__ void lane_links(const unsigned* v, unsigned (&x)[4], unsigned (&y)[4]) {
-    constexpr unsigned long long kUpper = M == 0 ? 0xaaaaaaaaaaaaaaaaull : M == 1 ? 0xccccccccccccccccull : M == 2 ? 0xf0f0f0f0f0f0f0f0ull : 0xff00ff00ff00ff00ull;
+    constexpr unsigned long long kUpper = M == 0 || M == 4 ? 0xaaaaaaaaaaaaaaaaull : M == 1 ? 0xccccccccccccccccull : M == 3 ? 0xff00ff00ff00ff00ull : 0xf0f0f0f0f0f0f0f0ull;
     if constexpr (M == 0) {
         CC_LANE_ENDS("quad_perm:[1,0,3,2]", "quad_perm:[1,0,3,2]");
     } else if constexpr (M == 1) {
         CC_LANE_ENDS("quad_perm:[2,3,0,1]", "quad_perm:[2,3,0,1]");
     } else if constexpr (M == 2) {
         CC_LANE_ENDS("row_ror:4", "row_ror:12");
+    } else if constexpr (M == 4) {
+        CC_LANE_ENDS("quad_perm:[3,2,1,0]", "quad_perm:[3,2,1,0]");
+    } else if constexpr (M == 5) {
+        CC_LANE_ENDS("row_ror:12", "row_ror:4");
     } else {
         CC_LANE_ENDS("row_ror:8", "row_ror:8");
     }
@@ -1330,30 +1333,49 @@ __device__ __forceinline__ void lane_links(const unsigned* v, unsigned (&x)[4], 
 // -> 52.0).  A link's word is asked for twelve links before it is used (eight at a time, waited for together: 121 us).  Through the folded
 // 16-bit matrix, bound by L2 requests: 1384 us and 1136.  Orders without any marked link, every link looked up: N = 1024, 65536
 // orders 1213 -> 1227 us, N = 512 458 -> 455 us.  So nothing else serves these sizes.
-template <int LOGN>
+// BCube base 4, N = 1024 (half as many links marked for the rounds are three times as long): 7680 links per order, before from the folded
+// matrix through L2 (bcube_b4_folded_kernel): 65536 seeded orders 1964 -> 150 us, of entries from 2^16 up 4939 -> 153, a search's results
+// 1979 -> 338; 1000 orders 116 -> 23, one order 90 -> 15.
+// BCUBE4: the 4 x 3 / 2 links of a group of four ranks are those of its two rank bits and those of ranks that differ in both.
+template <int LOGN, bool BCUBE4>
 __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kernel(
     const int32_t* __restrict__ c, const uint32_t* __restrict__ marks, const int32_t* __restrict__ tops,
     const int32_t* __restrict__ weights, const int32_t* __restrict__ perms, int64_t B, int64_t* __restrict__ out) {
     constexpr int N = 1 << LOGN, RK = N / 64, LM = RK / 2, Q = N / 256;         // ranks, links, quads of ranks per lane
-    constexpr int WAVES = LOGN == 10 ? 15 : 16, kLinks = LM * LOGN, WORDS = (kLinks + 31) / 32, kIdle = 32 * WORDS - kLinks;
+    constexpr int WAVES = LOGN == 10 ? 15 : 16, ROUNDS = BCUBE4 ? LOGN / 2 : LOGN;
+    constexpr int KINDS = BCUBE4 ? LOGN + LOGN / 2 : LOGN, kLinks = LM * KINDS, WORDS = (kLinks + 31) / 32, kIdle = 32 * WORDS - kLinks;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_marked[];
     uint32_t* lmarks = (uint32_t*)smem_marked;                                              // [N * N / 32], at LDS address 0: no other variable is there
     uint16_t* order = (uint16_t*)(smem_marked + N * N / 8) + (threadIdx.x >> 6) * N;        // [WAVES][N]
     int* worst = (int*)(smem_marked + N * N / 8 + sizeof(uint16_t) * WAVES * N) + (threadIdx.x >> 6) * 16;  // [WAVES][16]
-    // by its place in the order of testing: lower rank of the link but for the lane's part << 0, round << 10, lane bit that counts << 16
-    // and whether one does << 24
+    // by its place in the order of testing: lower rank of the link but for the lane's part << 0, round << 10, lane bit that counts << 14
+    // and whether one does << 19, whether the lanes have changed places << 20, the bits in which the other rank differs << 21
     int* links = (int*)(smem_marked + N * N / 8 + (sizeof(uint16_t) * N + sizeof(int) * 16) * WAVES);       // [kLinks]
     const int lane = lane_id(), wv = threadIdx.x >> 6;
-    auto round_of = [](int nth) { return nth < 6 ? nth : LOGN == 10 ? (nth < 8 ? nth + 2 : nth - 2) : nth == 6 ? 8 : nth - 1; };
+    // links tested nth: of rank bit kind, or of both bits of digit kind - LOGN
+    auto kind_of = [](int nth) {
+        if (BCUBE4) {
+            const int digit = nth < 9 ? nth / 3 : nth < 12 ? 4 : 3;
+            return nth % 3 < 2 ? 2 * digit + nth % 3 : LOGN + digit;
+        }
+        return nth < 6 ? nth : LOGN == 10 ? (nth < 8 ? nth + 2 : nth - 2) : nth == 6 ? 8 : nth - 1;
+    };
+    auto round_of = [=](int nth) {
+        const int kind = kind_of(nth);
+        return !BCUBE4 ? kind : kind < LOGN ? kind >> 1 : kind - LOGN;
+    };
     auto round_bits = [](int nth) {                                              // in its word of tested links
         const int from = nth * LM, in_word = kLinks - (from & ~31) < 32 ? kLinks - (from & ~31) : 32;
         return ((1u << LM) - 1) << (in_word - (from & 31) - LM);
     };
     if ((int)threadIdx.x < kLinks) {
-        const int u = threadIdx.x % LM, k = round_of(threadIdx.x / LM), bit = k < 2 ? k : k - 6;
-        const bool in_lane = k >= 2 && k < 8;
-        const int i = in_lane ? 2 * u : ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));         // register
-        links[threadIdx.x] = (256 * (i >> 2) + (i & 3)) | k << 10 | (in_lane && k != 7 ? (k - 2) << 16 | 1 << 24 : 0);
+        const int u = threadIdx.x % LM, nth = threadIdx.x / LM, kind = kind_of(nth);
+        const int both = kind >= LOGN, bit = both ? 2 * (kind - LOGN) : kind;                       // the lower one
+        const bool in_lane = bit >= 2 && bit < 8, swapped = kind == 7 || (both && bit == 6);
+        const int r = bit < 2 ? bit : bit - 6;                                                      // of the register's number
+        const int i = in_lane ? 2 * u : ((u >> r) << (r + 1)) | (u & ((1 << r) - 1));               // register
+        links[threadIdx.x] = (256 * (i >> 2) + (i & 3)) | round_of(nth) << 10 | (in_lane && !swapped ? (bit - 2) << 14 | 1 << 19 : 0) |
+                             (swapped ? 1 << 20 : 0) | (both ? 3 : 1) << (21 + bit);
     }
     const int lane_swapped = (lane >> 5) << 6 | (lane & 15) << 2 | (lane >> 4 & 1);
     for (int e = threadIdx.x; e < N * N / 128; e += 64 * WAVES) ((int4*)lmarks)[e] = ((const int4*)marks)[e];
@@ -1363,7 +1385,7 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
     top = wave_max(top);
     const bool marked_is_top = tops[kMarkBlocks] >= top;
     const long long weight =
-        lane < LOGN ? (weights ? (long long)clampi(weights[lane], 0, kMaxRoundWeight) : 1ll) : 0ll;
+        lane < ROUNDS ? (weights ? (long long)clampi(weights[lane], 0, kMaxRoundWeight) : 1ll) : 0ll;
     __syncthreads();
     const uint16_t* folded = (const uint16_t*)(marks + N * N / 32);
     const bool halves = top < (1 << 16);
@@ -1400,7 +1422,7 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
         }
         if (lane < 16) worst[lane] = -1;
         if (b + nwaves < B) load(b + nwaves, v);
-        // a bit per link, LM per round, the first one tested on top: rounds 0 .. 5, 8, 9, 6, 7
+        // a bit per link, LM of each kind, the first one tested on top
         uint32_t hits[WORDS] = {};
         // A link's word is asked for kAhead links before its bit is taken.
         constexpr int kAhead = 12;
@@ -1442,14 +1464,27 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
                 test(X[i], X[i | (1 << bit)]);
             }
         };
+        // ranks that differ in both register bits from `bit` on
+        auto both_round = [&](auto m) {
+            constexpr int bit = decltype(m)::value;
+#pragma unroll
+            for (int u = 0; u < LM; ++u) {
+                const int i = ((u >> bit) << (bit + 1)) | (u & ((1 << bit) - 1));
+                test(X[i], X[i ^ (3 << bit)]);
+            }
+        };
         register_round(std::integral_constant<int, 0>{});
         register_round(std::integral_constant<int, 1>{});
+        if constexpr (BCUBE4) both_round(std::integral_constant<int, 0>{});
         lane_round(std::integral_constant<int, 0>{});
         lane_round(std::integral_constant<int, 1>{});
+        if constexpr (BCUBE4) lane_round(std::integral_constant<int, 4>{});
         lane_round(std::integral_constant<int, 2>{});
         lane_round(std::integral_constant<int, 3>{});
+        if constexpr (BCUBE4) lane_round(std::integral_constant<int, 5>{});
         register_round(std::integral_constant<int, 2>{});
         if constexpr (LOGN == 10) register_round(std::integral_constant<int, 3>{});
+        if constexpr (BCUBE4) both_round(std::integral_constant<int, 2>{});
         // Lane bits 4 and 5 change places with the lowest bit of the register's number: a swap per two registers, after which they hold
         // the two ends (and rank bit 0 is where bit 6 was, then bit 6 where bit 7 was)
 #pragma unroll
@@ -1462,7 +1497,16 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
 #pragma unroll
         for (int u = 0; u < LM; ++u) {
             const auto r = __builtin_amdgcn_permlane32_swap(X[2 * u], X[2 * u + 1], false, false);
+            X[2 * u] = r[0];
+            X[2 * u + 1] = r[1];
             test(r[0], r[1]);
+        }
+        if constexpr (BCUBE4) {
+#pragma unroll
+            for (int u = 0; u < LM; ++u) {
+                const auto r = __builtin_amdgcn_permlane32_swap(X[2 * u + 1], X[2 * u + 1], false, false);
+                test(X[2 * u], lane < 32 ? r[1] : r[0]);
+            }
         }
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) take();
@@ -1471,8 +1515,8 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
         if (marked_is_top) {
             // a matrix of few values: a marked link is worth the matrix maximum, which ends its round
 #pragma unroll
-            for (int nth = 0; nth < LOGN; ++nth) finished |= __ballot(hits[nth * LM >> 5] & round_bits(nth)) ? 1u << round_of(nth) : 0u;
-            if (lane < LOGN && (finished >> lane & 1)) worst[lane] = top;
+            for (int nth = 0; nth < KINDS; ++nth) finished |= __ballot(hits[nth * LM >> 5] & round_bits(nth)) ? 1u << round_of(nth) : 0u;
+            if (lane < ROUNDS && (finished >> lane & 1)) worst[lane] = top;
 #pragma unroll
             for (int w = 0; w < WORDS; ++w) hits[w] = 0;
             __builtin_amdgcn_wave_barrier();
@@ -1502,11 +1546,12 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
             if (any) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const int link = links[at[i]];
-                    k[i] = link >> 10 & 15;
-                    const int p = (link & 1023) + (k[i] == 7 ? lane_swapped : 4 * lane) + (int)__builtin_amdgcn_ubfe((unsigned)lane, (unsigned)link >> 16, (unsigned)link >> 24);
+                    const unsigned link = (unsigned)links[at[i]];
+                    k[i] = (int)(link >> 10 & 15);
+                    const int p = (int)(link & 1023) + (link >> 20 & 1 ? lane_swapped : 4 * lane) +
+                                  (int)__builtin_amdgcn_ubfe((unsigned)lane, link >> 14 & 31, link >> 19 & 1);
                     x[i] = order[p];
-                    y[i] = order[p ^ (1 << k[i])];
+                    y[i] = order[p ^ (int)(link >> 21)];
                 }
                 if (halves) {
 #pragma unroll
@@ -1522,22 +1567,25 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
                 for (int i = 0; i < 2; ++i) atomicMax(worst + k[i], value[i]);
             }
             __builtin_amdgcn_wave_barrier();
-            const uint32_t full = (uint32_t)__ballot(lane < LOGN && *(volatile int*)(worst + (lane & 15)) >= top);
+            const uint32_t full = (uint32_t)__ballot(lane < ROUNDS && *(volatile int*)(worst + (lane & 15)) >= top);
             if (full != finished) {
                 finished = full;
 #pragma unroll
-                for (int nth = 0; nth < LOGN; ++nth)
+                for (int nth = 0; nth < KINDS; ++nth)
                     if ((full >> round_of(nth)) & 1) hits[nth * LM >> 5] &= ~round_bits(nth);
             }
         }
-        int mine = lane < LOGN ? *(volatile int*)(worst + (lane & 15)) : 0;
+        int mine = lane < ROUNDS ? *(volatile int*)(worst + (lane & 15)) : 0;
         for (uint32_t missing = (uint32_t)__ballot(mine < 0); missing; missing &= missing - 1) {
             const int k = __builtin_ctz(missing);
             int t = 0;
+            for (int j = 0; j < (BCUBE4 ? 3 : 1); ++j) {
+                const int bit = BCUBE4 ? 2 * k + (j & 1) : k, other = (j == 2 ? 3 : 1) << bit;
 #pragma unroll
-            for (int u = 0; u < LM; ++u) {
-                const int i = lane + 64 * u, p = ((i >> k) << (k + 1)) | (i & ((1 << k) - 1));
-                t = max(t, exact(order[p], order[p | (1 << k)]));
+                for (int u = 0; u < LM; ++u) {
+                    const int i = lane + 64 * u, p = ((i >> bit) << (bit + 1)) | (i & ((1 << bit) - 1));
+                    t = max(t, exact(order[p], order[p ^ other]));
+                }
             }
             t = wave_max(t);
             if (lane == k) mine = t;
@@ -1548,21 +1596,22 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
     }
 }
 
-template <int LOGN>
+template <int LOGN, bool BCUBE4 = false>
 static hipError_t rd_marked_launch(const int32_t* c, void* room, const int32_t* weights,
                                    const int32_t* perms, int64_t B, int64_t* out, hipStream_t s) {
     constexpr int N = 1 << LOGN, WAVES = LOGN == 10 ? 15 : 16;
+    constexpr int kWanted = LOGN == 10 ? BCUBE4 ? 1 : 2 : 3;                    // of 128 samples: 6 or 5 of N / 2, half as many under BCube
     int32_t* tops = (int32_t*)((char*)room + mark_tops_offset(N));
-    const size_t lds = N * N / 8 + sizeof(uint16_t) * WAVES * N + sizeof(int) * WAVES * 16 + sizeof(int) * (N / 128 * LOGN);
-    hipError_t e = hipFuncSetAttribute((const void*)rd_batch_marked_kernel<LOGN>,
+    const size_t lds = N * N / 8 + sizeof(uint16_t) * WAVES * N + sizeof(int) * WAVES * 16 + sizeof(int) * (N / 128 * (BCUBE4 ? LOGN / 2 * 3 : LOGN));
+    hipError_t e = hipFuncSetAttribute((const void*)(rd_batch_marked_kernel<LOGN, BCUBE4>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mark_links_kernel<LOGN>, dim3(kMarkBlocks), dim3(1024), 0, s, c, (uint32_t*)room, tops);
+    hipLaunchKernelGGL((mark_links_kernel<LOGN, kWanted>), dim3(kMarkBlocks), dim3(1024), 0, s, c, (uint32_t*)room, tops);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     int64_t blocks = (B + WAVES - 1) / WAVES;
     if (blocks > 256) blocks = 256;
-    hipLaunchKernelGGL(rd_batch_marked_kernel<LOGN>, dim3((int)blocks), dim3(64 * WAVES), lds, s, c,
+    hipLaunchKernelGGL((rd_batch_marked_kernel<LOGN, BCUBE4>), dim3((int)blocks), dim3(64 * WAVES), lds, s, c,
                        (const uint32_t*)room, tops, weights, perms, B, out);
     return hipGetLastError();
 }
@@ -1814,7 +1863,7 @@ __global__ __launch_bounds__(256) void bcube_batch_b4n64_kernel(const int32_t* _
     }
 }
 
-// Base 4 at N = 256, 1024 on the folded 16-bit copy of the matrix (as rd_batch_folded_kernel): the four ranks that
+// Base 4 at N = 256, small batches, on the folded 16-bit copy of the matrix (as rd_batch_folded_kernel): the four ranks that
 // differ in one base-4 digit exchange pairwise, and both directions of a pair are one folded entry, so a round is the
 // maximum over N / 4 groups of six entries - 1.5 N look-ups instead of 3 N.  A lane takes whole groups: four order
 // look-ups in LDS, six gathers.  Returns at once when flags[0] = max(c) is 2^16 or more.
@@ -1885,17 +1934,15 @@ hipError_t launch_bcube_cost_batch(const int32_t* c, int N, int base, const int3
     if (base == 4 && N == 4) return rounds_small_launch<2, true>(c, weights, perms, B, out, s);
     if (base == 4 && N == 16) return rounds_small_launch<4, true>(c, weights, perms, B, out, s);
     if (base == 4 && N == 256 && B >= kLdsBatchMinOrders) return links_lds16_launch<8, true>(c, weights, perms, B, out, s);
+    if (flags && folded && base == 4 && N == 1024) return rd_marked_launch<10, true>(c, folded, weights, perms, B, out, s);
     const int32_t* skip = nullptr;
-    if (flags && folded && base == 4 && (N == 256 || N == 1024)) {
+    if (flags && folded && base == 4 && N == 256) {
         // both kernels are enqueued; the matrix maximum, computed on the device, decides which of them works
         hipError_t e = launch_matrix_max(c, N, flags, s);
         if (e == hipSuccess) e = launch_fold_to_u16(c, N, folded, flags, s);
         if (e != hipSuccess) return e;
         const int grid = batch_grid(4, B);
-        if (N == 256)
-            hipLaunchKernelGGL(bcube_b4_folded_kernel<4>, dim3(grid), dim3(256), 0, s, folded, weights, perms, B, out, flags);
-        else
-            hipLaunchKernelGGL(bcube_b4_folded_kernel<5>, dim3(grid), dim3(256), 0, s, folded, weights, perms, B, out, flags);
+        hipLaunchKernelGGL(bcube_b4_folded_kernel<4>, dim3(grid), dim3(256), 0, s, folded, weights, perms, B, out, flags);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         skip = flags;

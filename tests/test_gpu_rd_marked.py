@@ -57,6 +57,34 @@ def test_rd_batch_marked_links_several_passes_weights_and_unaligned_orders(n):
     assert np.array_equal(got.cpu().numpy(), oracle.bcube_cost_weighted_batch(c, 2, w, perms[:200]))
 
 
+def test_bcube_base_4_marked_links():
+    n = 1024
+    for name, c in _matrices(n):
+        for b in (1, 16, 241):
+            say(f"bcube base 4, marked links, N={n} B={b}, {name}")
+            perms = random_perms(n, b, seed=n + b)
+            perms[0] = np.arange(n)
+            got = cc.cc_bcube_cost_batch(dev(c), 4, dev(perms))
+            torch.cuda.synchronize()
+            assert np.array_equal(got.cpu().numpy(), oracle.bcube_cost_batch(c, 4, perms))
+
+
+def test_bcube_base_4_marked_links_several_passes_weights_and_unaligned_orders():
+    n = 1024
+    say("bcube base 4, marked links: 4111 orders, weighted rounds, order stream 4 bytes off")
+    c = random_matrix(n, 3 * n, symmetric=False, lo=0, hi=COST_MAX)
+    perms = random_perms(n, 4111, seed=n)
+    got = cc.cc_bcube_cost_batch(dev(c), 4, dev(perms))
+    w = np.array([1 << 30, 0, 3, 4, 5], dtype=np.int32)
+    room = torch.empty(200 * n + 1, dtype=torch.int32, device="cuda")
+    view = room[1:].view(200, n)
+    view.copy_(dev(perms[:200]))
+    weighted = cc.cc_bcube_cost_batch_weighted(dev(c), 4, dev(w), view)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), oracle.bcube_cost_batch(c, 4, perms))
+    assert np.array_equal(weighted.cpu().numpy(), oracle.bcube_cost_weighted_batch(c, 4, w, perms[:200]))
+
+
 @pytest.mark.parametrize("n,wanted", [(512, 0.02), (1024, 0.01)])
 @pytest.mark.parametrize("noise", [0.0, 0.05])
 @pytest.mark.parametrize("group", [4, 32])
