@@ -122,6 +122,11 @@ __host__ __device__ constexpr int dsum_multi_limit(int N) { return (1 << 22) / (
 hipError_t launch_2opt_dsum_multi(const int32_t* c, int N, int restarts, bool with_flip, int32_t* tours, int64_t* costs,
                                   int32_t* moves, const int32_t* flags, hipStream_t s);
 
+// Directed ring sum, any 4 <= N <= 1024 and any entries (cc_2opt_dsum_pruned.hip).  `tours` must hold the initial tours.  With
+// skip_if_small it returns at once if skip_if_small[0], the matrix maximum, is below small_limit.
+hipError_t launch_2opt_dsum_pruned(const int32_t* c, int N, bool with_flip, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
+                                   const int32_t* skip_if_small, int small_limit, hipStream_t s);
+
 // Pair-swap descent under the halving-doubling model for `restarts` tours (cc_rdswap.hip); same tour
 // convention as launch_2opt.  The best-of-restarts step is launch_best_restart.
 // `mat16` has room for N*N 16-bit entries when N > 256 (the folded copy of the matrix).
