@@ -369,7 +369,7 @@ hipError_t launch_2opt(const int32_t* c, int N, int objective, int classes, int 
     } else if ((flip || classes == kMoves2opt) && objective == 2 && (N > kGeneralLdsMatrixMaxN || (N > 64 && restarts <= 512))) {
         // only the moves that can win.  While the general kernel has the matrix in LDS and many restarts hide its latencies it is the
         // faster (general / this one: N = 48, 4000 restarts 0.92 / 1.11 ms, N = 55, 1000 restarts, symmetric, 0.70 / 0.85; N = 80, 300
-        // restarts 1.07 / 0.77; N = 100, 1000 restarts 3.0 / 1.4)
+        // restarts 1.07 / 0.62; N = 100, 1000 restarts 3.0 / 1.1)
         if (!tours_hold_init) {
             e = launch_init_tours(N, 0, restarts, seed, tours, s);
             if (e != hipSuccess) return e;

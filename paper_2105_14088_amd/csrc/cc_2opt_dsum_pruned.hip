@@ -7,16 +7,17 @@
 //     c(t[i-1], t[j]) + c(t[i], t[q]) - b[i] - b[q] - (P[j] - P[i]) + (sum b - sum f).
 // An entry is at least the smallest of its row and of its column, so either is at least U[i] + V[j] with U and V known per rank: a move is
 // one addition and a comparison, and only those that can be worth the threshold T are looked up, 64 at a time through L2.  Along a good
-// order f is below b, so P grows and all but short pieces, or short rests, fall out.  T is 3/4 of the last move's value (the first sweep:
-// any that lowers the cost) and shrinks to the best value found as a sweep goes on; when no move is worth T, T is halved, and no move
+// order f is below b, so P grows and all but short pieces, or short rests, fall out.  T is a quarter of the last move's value (the first sweep:
+// any that lowers the cost) and shrinks to the best value found as a sweep goes on; when no move is worth T, T is an eighth of it, and no move
 // worth -1 ends the descent.
 //
 // What bounds it: a sweep of N^2 / 64 additions over the workgroup's wavefronts, then look-ups, 64 in a chain of LDS, L2 and a wave
 // minimum at a time.  The general kernel, which looks every move up -> this one, inverse bandwidths that are eight times as small inside a
-// rack: N = 100, 1000 restarts 3.0 -> 1.4 ms, 4000 restarts 9.1 -> 3.7; N = 150, 100 restarts 6.7 -> 1.3, 2000 restarts 19.3 -> 6.0; N = 220,
-// 500 restarts 19.8 -> 4.7; N = 256, 1000 restarts (costs beyond the exhaustive kernel's keys) 60.5 -> 9.6; N = 300, 300 restarts 39 ->
-// 8.0; N = 512, 100 restarts 78 -> 13.6.  Symmetric costs, where P is flat and hardly a move falls out by it: N = 100, 1000 restarts 3.9 -> 3.2,
-// N = 512, 100 restarts 134 -> 68.
+// rack: N = 100, 1000 restarts 3.0 -> 1.1 ms, 4000 restarts 9.1 -> 3.0; N = 150, 100 restarts 6.7 -> 1.1, 2000 restarts 19.3 -> 4.9; N = 220,
+// 500 restarts 19.8 -> 3.7; N = 256, 1000 restarts (costs beyond the exhaustive kernel's keys) 60.5 -> 7.8; N = 300, 300 restarts 39 ->
+// 6.3; N = 512, 100 restarts 78 -> 10.2.  Symmetric costs, where P is flat and hardly a move falls out by it: N = 100, 1000 restarts 3.9 -> 2.7,
+// N = 512, 100 restarts 134 -> 61.  T nearer to the last value costs sweeps that find nothing: N = 220, 500 restarts with 15/16 of it 6.8 ms,
+// 3/4 4.7, 1/2 4.0; two values alone are the faster for it (3.9, 3/4 3.3).  The matrix as 16-bit entries in LDS gained nothing.
 #include "cc_device.h"
 #include "cc_internal.h"
 #include "cc_pruned.h"
@@ -209,10 +210,10 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_dsum_pruned_kernel(const in
             hi = __builtin_amdgcn_readfirstlane((int)((unsigned)(k >> 32) ^ 0x80000000u));
             __syncthreads();
             if (lo != kNone || T == -1) break;
-            T = -max(1, -(T / 2));
+            T = -max(1, -(T / 8));
         }
         if (lo == kNone) break;                                  // no move lowers the cost
-        T = min(-1, (int)((long long)hi * 3 / 4));
+        T = min(-1, (int)((long long)hi / 4));
         // ---- apply: new[p] = old[src(p)]
         const int o = lo & 1, move = lo >> 1, mi = move / N, mj = move - mi * N;
         const int p0 = o ? (tid == 0 ? 0 : N - tid) : tid, src = p0 >= mi && p0 <= mj ? mi + mj - p0 : p0;
@@ -241,7 +242,7 @@ hipError_t launch(const int32_t* c, int N, bool with_flip, int restarts, int32_t
 
 hipError_t launch_2opt_dsum_pruned(const int32_t* c, int N, bool with_flip, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                                    const int32_t* skip_if_small, int small_limit, hipStream_t s) {
-    // (4 / 8 / 16 wavefronts: N = 50, 500 restarts 455 / 465 / 778 us, 2000 restarts 667 / 1092 / 2726; N = 70, 500 restarts 797 / 628 / 859; N =
+    // (4 / 8 / 16 wavefronts, with 3/4 of the last move's value as T: N = 50, 500 restarts 455 / 465 / 778 us, 2000 restarts 667 / 1092 / 2726; N = 70, 500 restarts 797 / 628 / 859; N =
     // 100, 100 restarts 1202 / 899 / 692, 1000 restarts 1406 / 1581 / 2360; N = 150, 500 restarts 3.2 / 2.2 / 2.7 ms; N = 256, 1000 restarts
     // 10.1 / 9.4 / 12.4; N = 300, 300 restarts - / 8.8 / 9.7; N = 400, 200 restarts - / 13.6 / 9.1; N = 512, 100 restarts - / 19.2 / 13.5)
     const int per_unit = (restarts + 255) / 256;
