@@ -40,6 +40,9 @@ using namespace pruned;
 // ones, those of the longest hops, do not.
 constexpr int kStaysMaxN = 176, kUnkeptSweeps = 12;
 
+// What becomes of an order that is no permutation: left as it is, taken down rank by rank, or that if no entry needs more than 16 bits.
+enum ByRank { kLeftAlone, kByRank, kByRank16 };
+
 // What each wave's best move is, used in turn: value (kNone: none), id, the new hops into the reversed ranks and behind them; the top bit
 // of the last says that the wave could not keep all its pairs.
 template <int WAVES>
@@ -81,7 +84,7 @@ struct PartnerLists {
 
 // LISTS: pairs come from partner lists (N > 256), else from the whole upper triangle.
 template <int WAVES, bool LISTS, class MAT>
-__device__ __forceinline__ void descend_kept(const MAT mat, int N, const PartnerLists lists, int room, int alpha, unsigned char* state, void* pairs_mem,
+__device__ __forceinline__ void descend_kept(const MAT mat, int N, const PartnerLists lists, int room, int alpha, int by_rank, unsigned char* state, void* pairs_mem,
                                              KeptWords<WAVES>* group, int wv, int lane, int32_t* __restrict__ tour,
                                              int64_t* __restrict__ cost_out, int32_t* __restrict__ moves_out) {
     using Pair = std::conditional_t<MAT::kScattered, WidePair, ShortPair>;
@@ -122,7 +125,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
         }
     }
     __syncthreads();
-    // An order that is no permutation (a data error) is left as it is, or rank by rank taken down below: node-wise hops would not describe it.
+    // An order that is no permutation (a data error) is left as it is, or taken down rank by rank below: node-wise hops would not describe it.
     const bool search = over_waves(__ballot(tid < N && (int)info[t0].w != tid) == 0 ? 1 : 0) != 0;
 
     int applied = 0, turn = 0, n_pairs = 0, unkept = 0;
@@ -457,8 +460,18 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
         __syncthreads();
     }
     if constexpr (!LISTS) {
-        // The exhaustive kernels that serve up to N = 128 where this one does not go by ranks and descend from such an order as from any.
-        while (!search && N <= 128) {
+        // The exhaustive kernels go by ranks and descend from such an order as from any; where one serves N as well, so does this.
+        bool descends = !search && by_rank != kLeftAlone;
+        if (descends && by_rank == kByRank16) {
+            int high = 0;
+            for (int e = tid; e < N * N; e += 64 * WAVES) {
+                const int x = e / N, y = e - x * N;
+                high = max(high, mat(x, y));
+            }
+            __syncthreads();                                   // the words of `search` have been read
+            descends = over_waves(-wave_max(high)) > -(1 << 16);
+        }
+        while (descends) {
             unsigned long long key = ~0ull;
             for (int e = tid; e < N * N; e += 64 * WAVES) {
                 const int i = e / N, j = e - i * N, q = j + 1 == N ? 0 : j + 1;
@@ -503,7 +516,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
 // N <= 64 WAVES.  lds_matrix: the matrix as 16-bit entries in LDS where its entries allow.
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void twoopt_sum_kept_kernel(const int32_t* __restrict__ c, int N, int lds_matrix, int room,
-                                                                     int alpha, int32_t* __restrict__ tours,
+                                                                     int alpha, int by_rank, int32_t* __restrict__ tours,
                                                                      int64_t* __restrict__ costs, int32_t* __restrict__ moves) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ KeptWords<WAVES> group;
@@ -528,13 +541,13 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_sum_kept_kernel(const int32
         for (int w = 0; w < WAVES; ++w) high = max(high, group.word[w]);
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(high) < (1 << 16)) {
-            descend_kept<WAVES, false>(LdsMatrix{m16, N}, N, none, room, alpha, smem, pairs, &group, wv, lane, tours + r * N, costs + r,
+            descend_kept<WAVES, false>(LdsMatrix{m16, N}, N, none, room, alpha, by_rank, smem, pairs, &group, wv, lane, tours + r * N, costs + r,
                                        moves + r);
             return;
         }
     }
     // wider pairs; the matrix's room is theirs
-    descend_kept<WAVES, false>(CallersMatrix{c, N}, N, none, room, alpha, smem, pairs, &group, wv, lane, tours + r * N, costs + r, moves + r);
+    descend_kept<WAVES, false>(CallersMatrix{c, N}, N, none, room, alpha, by_rank, smem, pairs, &group, wv, lane, tours + r * N, costs + r, moves + r);
 }
 
 // N > 256: partner lists in the workspace.
@@ -548,7 +561,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     __shared__ KeptWords<WAVES> group;
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
-    descend_kept<WAVES, true>(CallersMatrix{c, N}, N, PartnerLists{lists, counts, M}, room, alpha, smem,
+    descend_kept<WAVES, true>(CallersMatrix{c, N}, N, PartnerLists{lists, counts, M}, room, alpha, kLeftAlone, smem,
                                (void*)(smem + kept_state_bytes(N)), &group, wv, lane, tours + r * N,
                               costs + r, moves + r);
 }
@@ -561,8 +574,10 @@ hipError_t launch_kept(const int32_t* c, int N, bool lds_matrix, int room, int a
     const size_t lds = kept_state_bytes(N) + (lds_matrix && brief > wide ? brief : wide);
     hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_kept_kernel<WAVES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((twoopt_sum_kept_kernel<WAVES>), dim3(restarts), dim3(64 * WAVES), lds, s, c, N, lds_matrix ? 1 : 0, room, alpha, tours,
-                       costs, moves);
+    // 192 and 256: the restarts that the exhaustive kernels of these sizes are the alternative for
+    const int by_rank = N <= 128 ? kByRank : (N == 192 || N == 256) && restarts > 256 && restarts <= 1536 ? kByRank16 : kLeftAlone;
+    hipLaunchKernelGGL((twoopt_sum_kept_kernel<WAVES>), dim3(restarts), dim3(64 * WAVES), lds, s, c, N, lds_matrix ? 1 : 0, room, alpha, by_rank,
+                       tours, costs, moves);
     return hipGetLastError();
 }
 

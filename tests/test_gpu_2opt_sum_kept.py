@@ -47,3 +47,16 @@ def test_orders_that_are_no_permutation_up_to_128(n):
     init[3] = np.random.default_rng(6).permutation(n)
     for c in (random_matrix(n, 18, symmetric=True, lo=0, hi=3000), random_matrix(n, 19, symmetric=True, lo=0, hi=1 << 20)):
         _check(c, 4, 1, range(4), init)
+
+
+@pytest.mark.parametrize("n,restarts", [(192, 257), (192, 1536), (256, 257), (256, 1536)])
+def test_orders_that_are_no_permutation_at_the_exhaustive_kernels_sizes(n, restarts):
+    """Several restarts per compute unit and entries of 16 bits: descended from like any other, as the exhaustive kernels do."""
+    say(f"kept ring sum N={n} R={restarts}: orders that are no permutation")
+    init = np.stack([np.random.default_rng(r).permutation(n) for r in range(restarts)]).astype(np.int32)
+    init[:3] = np.random.default_rng(7).integers(0, n, size=(3, n))
+    init[restarts - 1, 0] = init[restarts - 1, n - 1]
+    for hi in (3000, 65535):
+        c = random_matrix(n, 18, symmetric=True, lo=0, hi=hi)
+        c[0, n - 1] = c[n - 1, 0] = hi
+        _check(c, restarts, 1, (0, 1, 2, 3, restarts - 1), init)
