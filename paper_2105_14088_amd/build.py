@@ -29,14 +29,35 @@ HIPCC_FLAGS = [
 # so that the rotate stays an instruction of its own (an empty asm statement with the value as in/out operand).
 FORBIDDEN_ISA = re.compile(r"^\s*(v_\w*rev\w*_dpp)\b", re.M)
 
+# Kernels that address their dynamic LDS from 0 on (an addition per look-up saved).  It starts behind whatever LDS the
+# compiler itself places, a __shared__ variable for instance, so a build in which one of them has any is refused.
+DYNAMIC_LDS_AT_0 = ("rd_batch_marked_kernel",)
+KERNEL_LDS = re.compile(r"^\s*\.amdhsa_kernel\s+(\S+)\s+\.amdhsa_group_segment_fixed_size\s+(\d+)", re.M)
+
+
+def device_listings(folder: str) -> list:
+    return sorted(glob.glob(os.path.join(folder, "*-hip-amdgcn-amd-amdhsa-gfx950.s")))
+
 
 def check_device_isa(folder: str) -> None:
-    for path in sorted(glob.glob(os.path.join(folder, "*-hip-amdgcn-amd-amdhsa-gfx950.s"))):
+    for path in device_listings(folder):
         with open(path) as fh:
             hit = FORBIDDEN_ISA.search(fh.read())
         if hit:
             raise RuntimeError(f"{os.path.basename(path)}: the compiler emitted {hit.group(1)}, which does not "
                                "compute what its operands say on gfx950; keep the rotate out of the subtraction")
+
+
+def check_dynamic_lds(folder: str) -> None:
+    placed = {}
+    for path in device_listings(folder):
+        with open(path) as fh:
+            placed.update((name, int(size)) for name, size in KERNEL_LDS.findall(fh.read()))
+    for kernel in DYNAMIC_LDS_AT_0:
+        sizes = [size for name, size in placed.items() if f"{len(kernel)}{kernel}I" in name]
+        if not sizes or any(sizes):
+            raise RuntimeError(f"{kernel}: its dynamic LDS has to start at address 0, but the compiler placed {sizes} bytes "
+                               "of LDS before it (no number: no such kernel was found)")
 
 
 def needs_build() -> bool:
@@ -66,6 +87,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
             with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
                 objects = list(pool.map(compile_one, SOURCES))
             check_device_isa(tmp)
+            check_dynamic_lds(tmp)
             link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC"] + objects + ["-o", out]
             if verbose:
                 print(" ".join(link), flush=True)

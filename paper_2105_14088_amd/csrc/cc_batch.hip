@@ -1345,7 +1345,7 @@ __global__ __launch_bounds__(LOGN == 10 ? 960 : 1024) void rd_batch_marked_kerne
     constexpr int WAVES = LOGN == 10 ? 15 : 16, ROUNDS = BCUBE4 ? LOGN / 2 : LOGN;
     constexpr int KINDS = BCUBE4 ? LOGN + LOGN / 2 : LOGN, kLinks = LM * KINDS, WORDS = (kLinks + 31) / 32, kIdle = 32 * WORDS - kLinks;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_marked[];
-    uint32_t* lmarks = (uint32_t*)smem_marked;                                              // [N * N / 32], at LDS address 0: no other variable is there
+    uint32_t* lmarks = (uint32_t*)smem_marked;                                              // [N * N / 32], at LDS address 0, which the build checks: the kernel has no other LDS
     uint16_t* order = (uint16_t*)(smem_marked + N * N / 8) + (threadIdx.x >> 6) * N;        // [WAVES][N]
     int* worst = (int*)(smem_marked + N * N / 8 + sizeof(uint16_t) * WAVES * N) + (threadIdx.x >> 6) * 16;  // [WAVES][16]
     // by its place in the order of testing: lower rank of the link but for the lane's part << 0, round << 10, lane bit that counts << 14
