@@ -19,6 +19,7 @@
 // N = 512, 100 restarts 134 -> 61.  T nearer to the last value costs sweeps that find nothing: N = 220, 500 restarts with 15/16 of it 6.8 ms,
 // 3/4 4.7, 1/2 4.0; two values alone are the faster for it (3.9, 3/4 3.3).  The matrix as 16-bit entries in LDS gained nothing.
 #include "cc_device.h"
+#include "cc_dsum_bounds.h"
 #include "cc_internal.h"
 #include "cc_pruned.h"
 
@@ -120,9 +121,11 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_dsum_pruned_kernel(const in
         prefix[tid] = upto;
         if (tid < N) {
             const int qn = t[q_own], f_q = f[q_own], b_q = b[q_own];
-            u_of[tid] = make_int2(((col_min[node_before] + col_min[node]) >> 1) - own_f - upto,
-                                  ((row_min[node_before] + row_min[node]) >> 1) - own_b + upto);
-            v_of[tid] = make_int2(((row_min[node] + row_min[qn]) >> 1) - f_q + upto, ((col_min[node] + col_min[qn]) >> 1) - b_q - upto + turned);
+            const dsum::Terms u = dsum::term_of_first((col_min[node_before] + col_min[node]) >> 1, (row_min[node_before] + row_min[node]) >> 1,
+                                                      own_f, own_b, upto);
+            const dsum::Terms v = dsum::term_of_last((row_min[node] + row_min[qn]) >> 1, (col_min[node] + col_min[qn]) >> 1, f_q, b_q, upto, turned);
+            u_of[tid] = make_int2(u.kept, u.other);
+            v_of[tid] = make_int2(v.kept, v.other);
         }
         __syncthreads();
         int hi, lo;
@@ -171,7 +174,8 @@ __global__ __launch_bounds__(64 * WAVES) void twoopt_dsum_pruned_kernel(const in
                         // i < j: from the block's first j on one lane fewer for each i
                         const int over = i - 64 * jb;
                         const unsigned long long open = over < 0 ? real : over > 62 ? 0ull : real & ~((2ull << over) - 1ull);
-                        const unsigned long long kept = __ballot(u.x + v.x <= limit) & open, other = __ballot(u.y + v.y <= limit) & open;
+                        const unsigned long long kept = __ballot(dsum::together(u.x, v.x) <= limit) & open,
+                                                 other = __ballot(dsum::together(u.y, v.y) <= limit) & open;
                         if (kept | other) {
                             if (kept >> lane & 1) items[wv][n_items + lanes_below(kept)] = (uint32_t)(i << 11 | j << 1);
                             n_items += __popcll(kept);

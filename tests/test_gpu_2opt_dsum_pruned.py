@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2105_14088_amd as cc
-from gen import random_matrix
+from gen import COST_MAX, random_matrix
 from gpu_util import dev, gpu_search, say
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("built_library")]
@@ -49,3 +49,22 @@ def test_flip_and_orders_that_are_no_permutation(n, monkeypatch):
                 torch.cuda.synchronize()
                 runs.append([x.cpu().numpy() for x in (b.restart_costs, b.restart_tours, b.restart_moves)])
             assert all(np.array_equal(x, y) for x, y in zip(*runs))
+
+
+def _one_way(n):
+    """Every hop of the ascending order costs the most there is, the descending one hardly anything: prefix sums close to 2^31."""
+    c = np.where(np.arange(n)[:, None] > np.arange(n)[None, :], COST_MAX, np.random.default_rng(n).integers(0, 4, (n, n))).astype(np.int32)
+    c[0, n - 1] = COST_MAX
+    np.fill_diagonal(c, 0)
+    return c
+
+
+@pytest.mark.parametrize("n", [513, 1023, 1024])
+def test_the_largest_costs_one_way(n):
+    init = np.stack([np.arange(n), np.arange(n)[::-1], np.random.default_rng(1).permutation(n)]).astype(np.int32)
+    for c, tag in ((_one_way(n), "as walked"), (np.ascontiguousarray(_one_way(n).T), "the other way"),
+                   (random_matrix(n, n, symmetric=False, lo=0, hi=COST_MAX), "spread")):
+        say(f"directed sum N={n}: the largest costs, {tag}")
+        got = gpu_search(c, oracle.SUM_DIRECTED, 3, 1, init)
+        costs, tours, moves = oracle.restarts(c, oracle.SUM_DIRECTED, 1, 0, 3, init=init)
+        assert np.array_equal(got["costs"], costs) and np.array_equal(got["moves"], moves) and np.array_equal(got["tours"], tours)
