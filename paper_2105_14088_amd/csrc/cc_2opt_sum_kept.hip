@@ -8,21 +8,29 @@
 // The workgroup keeps all pairs for which that holds in LDS (each wavefront its share, with the cost).  A sweep scores the kept
 // pairs on both sides: if the best of them is T or less it is the best move of all, ties included.  A move changes H at four nodes; where
 // one grew beyond what the pairs were made for, that node's row is looked through for the pairs that come in, and pairs that no
-// longer qualify stay until the next making.  When no kept pair gives T or less, no move does, and the pairs are made anew for 3/4 of T,
-// down to T = -1, where the descent ends.  Where the pairs do not fit, a wavefront scores what it has, starts over and the next sweep
-// makes them anew with T = the value just found: slower, the same moves.
+// longer qualify stay until the next making.  When no kept pair gives T or less, no move does, and the pairs are made anew for alpha / 16
+// of T, down to T = -1, where the descent ends; alpha is 8 to 14 by N and restarts (launch_2opt_sum_kept).  Where the pairs do not fit, a
+// wavefront scores what it has, starts over and the next sweep makes them anew with T = the value just found, and alpha is one more
+// from then on, up to 15: slower, the same moves.
 //
-// On hierarchies of hosts and racks with T in steps of 3/4, N = 100 keeps 220 pairs and makes them 28 times in 111 sweeps, N = 256 760 and 27 of
-// 307, N = 1000 4460 and 27 of 1306; every third or fourth move lets a row in.
+// On hierarchies of hosts and racks with 30 % of noise N = 100 keeps some 380 pairs and makes them 12 times in 121 sweeps with alpha 8 (270 and
+// 17 of 126 with 10), N = 256 1100 and 17 of 333 with 10, N = 1000 2900 and 56 of 1400 with 14; every third or fourth move lets a row in
+// (counted in a model of the algorithm on the CPU).
 //
 // What bounds it: a sweep is a chain of LDS round trips (pair, its two nodes, the second new edge, the waves' best, the move) between two
 // barriers, about 3500 clocks up to N = 256 and 7500 at N = 1000, where sixteen wavefronts also share the issue of some 100 vector
 // instructions per 64 pairs; makings are a fifth to a third (5000 clocks at N = 128, 15000 at N = 1000).  Lists of candidates laid out anew on
 // every sweep (cc_2opt_sum_pruned.hip, cc_2opt_multi.hip) -> this one: N = 1000, 128 restarts 10.4 -> 5.2 ms; N = 512, 745 restarts 5.65 ->
 // 3.16; N = 300, 745 restarts 2.23 -> 1.41; N = 256, 200 restarts 1.22 -> 0.89, 1024 restarts 3.5 -> 1.7; N = 128, 256 restarts 0.60 -> 0.33;
-// N = 100, 32 restarts 0.37 -> 0.23.  Matrices of two or three values without noise, whose pairs are mostly equal, are the slower by up to 2
-// times (two zones, N = 256, 1024 restarts 0.86 -> 1.36 ms, N = 1000, 64 restarts 2.8 -> 3.2).  Slower were: rows of the triangle
-// instead of all its entries end to end (N = 128, 256 restarts 0.33 -> 0.40), lists of every node in LDS up to N = 256 (0.39).
+// N = 100, 32 restarts 0.37 -> 0.23.  Slower were: rows of the triangle instead of all its entries end to end (N = 128, 256 restarts 0.33 -> 0.40),
+// lists of every node in LDS up to N = 256 (0.39).
+//
+// Matrices of few values without noise, whose pairs are mostly equal, gain less or lose, by up to 2.8 times where an exhaustive kernel had
+// the matrix in LDS (before -> now, two zones: N = 100, 1000 restarts 0.15 -> 0.22 ms, 2048 restarts 0.23 -> 0.42, N = 150, 2000 restarts 0.46 ->
+// 0.70, N = 192, 1024 restarts 0.35 -> 0.98, N = 256, 1024 restarts 0.86 -> 1.5, N = 1000, 64 restarts 2.4 -> 2.8; three levels: N = 100, 1000
+// restarts 0.29 -> 0.30, N = 256, 1024 restarts 2.3 -> 1.45, 2048 restarts 3.2 -> 4.7; zones of eight: N = 256, 1024 restarts 2.1 -> 1.0).
+// Without the steps over gaps between such values, and handed over above N = 176 only: two zones, N = 100, 1000 restarts 0.26, 2048 restarts
+// 0.87, N = 150, 2000 restarts 2.4.
 #include <type_traits>
 
 #include "cc_device.h"
@@ -36,9 +44,12 @@ namespace {
 
 using namespace pruned;
 
-// Above this N a descent is left to the kernel that keeps no pairs after so many sweeps whose pairs did not fit, or at once if the first
-// ones, those of the longest hops, do not.
-constexpr int kStaysMaxN = 176, kUnkeptSweeps = 12;
+// Above this N a descent is left to the kernel that keeps no pairs: from partner lists after so many sweeps whose pairs did not fit, or at
+// once if the first ones, those of the longest hops, do not; from the triangle, whose makings are cheap, after so many in a row, as costs
+// of few values have them.  In a row / all and at once: racks with 3 % of noise, N = 256, 1024 restarts 1.85 / 5.7 ms, uniform costs, 2048
+// restarts 3.8 / 5.9, but racks of equal costs, 2048 restarts 4.7 / 3.3; lists, N = 300, 1500 restarts, 3 % 6.6 / 5.2, two zones 1.67 / 1.36.
+// Below, the launch that a hand-over needs costs more than it would give.
+constexpr int kStaysMaxN = 128, kMostUnkept = 12, kMostUnkeptInARow = 1;
 
 // What becomes of an order that is no permutation: left as it is, taken down rank by rank, or that if no entry needs more than 16 bits.
 enum ByRank { kLeftAlone, kByRank, kByRank16 };
@@ -128,8 +139,10 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
     // An order that is no permutation (a data error) is left as it is, or taken down rank by rank below: node-wise hops would not describe it.
     const bool search = over_waves(__ballot(tid < N && (int)info[t0].w != tid) == 0 ? 1 : 0) != 0;
 
-    int applied = 0, turn = 0, n_pairs = 0, unkept = 0;
+    constexpr int most_unkept = LISTS ? kMostUnkept : kMostUnkeptInARow;
+    int applied = 0, turn = 0, n_pairs = 0, unkept = 0;        // sweeps whose pairs did not fit, LISTS: all, else the last ones
     int T = 0;                                                 // 0: none chosen yet
+    int had = 0;                                               // pairs of wave lane & 15 when no move was found last
     bool make = true, partial = false;
     int changed = 0, changed_H = 0, changed_before = kNone;    // lanes 0 .. 3: the nodes whose hops the last move changed
     const int units_per_step = 64 * WAVES / (N - 1), rest_per_step = 64 * WAVES - units_per_step * (N - 1);
@@ -386,7 +399,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             partial = true;
         }
         // ---- the best move of all lanes, then of all waves
-        int value, id, h_first, h_after;
+        int value, id, h_first, h_after, have;                 // have: pairs of wave lane & 15, where that found no move
         bool again;
         {
             const int h = wave_min(hi);
@@ -397,7 +410,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             }
             const int holder = (int)__builtin_ctzll(at);
             if (lane == holder)
-                group->best[turn & 1][wv] = make_int4(lo == kNone ? kNone : hi, lo, first_hop, after_hop | (partial ? 1 << 31 : 0));
+                group->best[turn & 1][wv] = make_int4(lo == kNone ? kNone : hi, lo, !LISTS && lo == kNone ? n_pairs : first_hop, after_hop | (partial ? 1 << 31 : 0));
             __syncthreads();
             const int4 b = group->best[turn & 1][min(lane & 15, WAVES - 1)];
             int v = b.x;
@@ -416,13 +429,22 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             h_first = __builtin_amdgcn_readlane(b.z, w);
             h_after = __builtin_amdgcn_readlane(b.w, w) & 0x7fffffff;
             again = __ballot(b.w < 0) != 0;
+            have = b.z;
         }
         ++turn;
         partial = false;
         if (value == kNone && T == -1) break;
-        if (again && N > kStaysMaxN && (unkept += turn == 1 ? kUnkeptSweeps + 1 : 1) > kUnkeptSweeps) break;
+        if constexpr (LISTS) unkept += again ? turn == 1 ? most_unkept + 1 : 1 : 0;
+        else unkept = again ? unkept + 1 : 0;
+        if (N > kStaysMaxN && unkept > most_unkept) break;
         if (value == kNone) {                                   // no move is worth T
             T = looser(T);
+            if constexpr (!LISTS) {
+                // Costs of few values leave gaps: where the last making brought no pair in, T goes on to where some may
+                if (__ballot(have != had) == 0 && __ballot(have * WAVES > N) != 0)
+                    for (int i = 0; i < 4; ++i) T = looser(T);
+                had = have;
+            }
             make = true;
             continue;
         }
@@ -508,7 +530,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
     for (int i = 0; i < WAVES; ++i) sum += group->word[i];
     if (tid < N) tour[tid] = (int)t[tid];
     if (tid == 0) {
-        *cost_out = unkept > kUnkeptSweeps ? -1 : (int64_t)sum;
+        *cost_out = N > kStaysMaxN && unkept > most_unkept ? -1 : (int64_t)sum;
         *moves_out = applied;
     }
 }
