@@ -1,6 +1,6 @@
 // Ring-sum 2-opt for 97 <= N <= 1024 and any entries, where restarts are too many, or pairs, for cc_2opt_sum_kept.hip: only the moves
-// that can be the best one are scored.  Move set,
-// value and tie-break rules as stated in cc.h; symmetric matrix, read through its upper triangle.
+// that can be the best one are scored.  Move set, value and tie-break rules as stated in cc.h; symmetric matrix, read through its upper
+// triangle.
 //
 // Exchanging the ring edges a and b (edge p joins ranks p-1 and p) changes the cost by
 //     delta = [c(t[a-1], t[b-1]) - (f[a] + f[b]) / 2] + [c(t[a], t[b]) - (f[a] + f[b]) / 2],
@@ -17,16 +17,19 @@
 // 2 cost + 1 as a float), with the number of partners up to each bucket: how far a threshold reaches is one look-up, and
 // order inside a bucket does not matter.  A list holds the nearest M partners; a node whose threshold reaches further,
 // or whose candidates exceed the room for them, is scanned against every node instead.
-//   * N <= 256: lists in LDS, made by the workgroup itself; up to 256 (N <= 192: mostly 512) restarts one workgroup of eight
-//     (four) wavefronts each, beyond that up to 16 restarts of one wavefront each around one copy of the lists.
-//   * N > 256 (restarts that cc_2opt_sum_kept.hip left): one workgroup per restart, lists in the workspace (M = (N - 128) / 2), made by a kernel of their own.
+//   * N <= 256: lists in LDS, made by the workgroup itself, up to 16 restarts of one wavefront each around one copy of them.  Up to 256
+//     (N <= 192: mostly 512) restarts, which come here from N = 129 on and only as far as cc_2opt_sum_kept.hip left them, one workgroup of
+//     eight (four) wavefronts each.
+//   * N > 256, only restarts that cc_2opt_sum_kept.hip left: one workgroup per restart, lists in the workspace (M = (N - 128) / 2), which
+//     have been made for that kernel.
 // The candidates of 64 nodes are laid out end to end (prefix sum of their counts) and taken 64 at a time, up to four
 // times 64 with their look-ups in flight together; those whose bracket passes are collected in LDS and scored 64 at a
 // time.  The wavefronts of one restart take the 64s of all nodes in turn (the nodes of one wavefront have two or three times the
 // candidates of another's, and the passed ones lie together), so there may be more wavefronts than nodes / 64.
 //
 // What bounds it: instruction issue (with 16 wavefronts, N = 1000, about 740 vector instructions per wavefront and sweep, 70 % of the
-// SIMDs' rate), and with few wavefronts the latency of each one's own.  Exhaustive kernels -> this one: N = 1000, 128 restarts 494 ->
+// SIMDs' rate), and with few wavefronts the latency of each one's own.  All times here are of whole searches by this kernel, also at the
+// sizes where it now has only what is left.  Exhaustive kernels -> this one: N = 1000, 128 restarts 494 ->
 // 10.6 ms; N = 583, 47 restarts 112 -> 4.4 ms; N = 345, 2140 restarts 239 -> 7.4 ms; N = 1024, 256 restarts 57.9 -> 11.3 ms; N = 512, 768
 // restarts 19.2 -> 5.6 ms; N = 256, 4096 restarts 7.8 -> 5.2 ms.  Every wavefront its own nodes' candidates, one per 64 nodes -> shared,
 // more wavefronts: N = 1000, 128 restarts 11.5 -> 10.6 ms, N = 700, 100 restarts 6.4 -> 5.5, N = 400, 64 restarts 2.77 -> 2.23, N = 300,
@@ -572,15 +575,15 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_num_sgpr(80))) vo
                                                                              const uint16_t* __restrict__ counts,
                                                                              int32_t* __restrict__ tours,
                                                                              int64_t* __restrict__ costs,
-                                                                             int32_t* __restrict__ moves, int left_over) {
+                                                                             int32_t* __restrict__ moves) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ GroupWords<WAVES> group;
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = blockIdx.x;
-    if (left_over && costs[r] >= 0) return;                    // only restarts that the kernel that keeps pairs left
+    if (costs[r] >= 0) return;                                  // only restarts that the kernel that keeps pairs left
     const int scale = (int)counts[(size_t)min(64 * wv + lane, N - 1) * kBuckets + kBuckets - 1];
     descend<WAVES, 1, kGroupRoom, true>(CallersMatrix{c, N}, N, lists, M, counts, scale, nullptr, smem,
-                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom, true), &group, wv, lane, left_over ? moves[r] : 0,
+                                  smem + group_order_bytes(N) + wv * group_wave_bytes(kGroupRoom, true), &group, wv, lane, moves[r],
                                   tours + r * N, costs + r, moves + r);
 }
 
@@ -620,31 +623,34 @@ hipError_t launch_waves(const int32_t* c, int N, int restarts, int32_t* tours, i
     return launch_lds<E, 1, false>(c, N, plan, restarts, tours, costs, moves, skip_if_small, left_over, s);
 }
 
+// Where the lists lie in `room`, and how long they are.
+void partner_lists_at(int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts) {
+    M = group_list(N);
+    lists = (const uint32_t*)room;
+    counts = (const uint16_t*)(lists + (size_t)N * M);
+}
+
 template <int WAVES>
 hipError_t launch_group(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
-                        bool left_over, hipStream_t s) {
+                        hipStream_t s) {
     int M;
     const uint32_t* lists;
     const uint16_t* counts;
-    hipError_t e = launch_partner_lists(c, N, room, M, lists, counts, s, left_over);
-    if (e != hipSuccess) return e;
+    partner_lists_at(N, room, M, lists, counts);
     const size_t lds = group_order_bytes(N) + WAVES * group_wave_bytes(kGroupRoom, true);
-    e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
+    const hipError_t e = hipFuncSetAttribute((const void*)twoopt_sum_pruned_group_kernel<WAVES>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((twoopt_sum_pruned_group_kernel<WAVES>), dim3(restarts), dim3(64 * WAVES), lds, s, c, N, M, lists,
-                       counts, tours, costs, moves, left_over ? 1 : 0);
+                       counts, tours, costs, moves);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
-                                hipStream_t s, bool there) {
-    M = group_list(N);
-    lists = (const uint32_t*)room;
-    counts = (const uint16_t*)(lists + (size_t)N * M);
-    if (there) return hipSuccess;
+                                hipStream_t s) {
+    partner_lists_at(N, room, M, lists, counts);
     hipLaunchKernelGGL(partner_lists_kernel, dim3((N + 3) / 4), dim3(256), 0, s, c, N, M, (uint32_t*)lists, (uint16_t*)counts);
     return hipGetLastError();
 }
@@ -654,21 +660,22 @@ hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int resta
     if (N <= 128) return launch_waves<2>(c, N, restarts, tours, costs, moves, skip_if_small, left_over, s);
     if (N <= 192) return launch_waves<3>(c, N, restarts, tours, costs, moves, skip_if_small, left_over, s);
     if (N <= 256) return launch_waves<4>(c, N, restarts, tours, costs, moves, skip_if_small, left_over, s);
+    if (!left_over) return hipErrorInvalidValue;                // the kernel that keeps pairs is in front of it at any number of restarts
     // at least a wave per 64 nodes; more where the compute units have room for them (a wave per 64 nodes / 8 / 12 / 16 waves: N = 300, 250
     // restarts 1782 / 1590 / 1534 / 1620 us, 500 restarts 1982 / 1867 / 2022 / 2300, 1000 restarts 2523 / 3219 / 3786; N = 512, 250
     // restarts 3621 / - / 3340 / 3330, 500 restarts 4431 / - / 4605 / 4900)
     if (restarts <= 256) {
-        if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, left_over, s);
+        if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, s);
     } else if (restarts <= 512) {
-        if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, left_over, s);
+        if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, s);
     }
-    if (N <= 320) return launch_group<5>(c, N, room, restarts, tours, costs, moves, left_over, s);
-    if (N <= 384) return launch_group<6>(c, N, room, restarts, tours, costs, moves, left_over, s);
-    if (N <= 448) return launch_group<7>(c, N, room, restarts, tours, costs, moves, left_over, s);
-    if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, left_over, s);
-    if (N <= 640) return launch_group<10>(c, N, room, restarts, tours, costs, moves, left_over, s);
-    if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, left_over, s);
-    return launch_group<16>(c, N, room, restarts, tours, costs, moves, left_over, s);
+    if (N <= 320) return launch_group<5>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 384) return launch_group<6>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 448) return launch_group<7>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 512) return launch_group<8>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 640) return launch_group<10>(c, N, room, restarts, tours, costs, moves, s);
+    if (N <= 768) return launch_group<12>(c, N, room, restarts, tours, costs, moves, s);
+    return launch_group<16>(c, N, room, restarts, tours, costs, moves, s);
 }
 
 }  // namespace cc

@@ -75,18 +75,18 @@ hipError_t launch_2opt_dsum_n64(const int32_t* c, int restarts, uint64_t seed, b
 
 // Ring-sum objective, 97 <= N <= 1024 and any entries (cc_2opt_sum_pruned.hip).  `tours` must hold the initial tours;
 // `room`: 2 N^2 bytes of device memory when N > 256 (the workspace's mat16).  With skip_if_small (N <= 256) it returns at
-// once if skip_if_small[0], the matrix maximum, is below 2^16.
+// once if skip_if_small[0], the matrix maximum, is below 2^16.  left_over (N > 256: always): only restarts with a cost of -1.
 hipError_t launch_2opt_sum_pruned(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
                                   int32_t* moves, const int32_t* skip_if_small, bool left_over, hipStream_t s);
-// 65 <= N <= 1024, few enough restarts (launch_2opt): a workgroup per restart keeps its pairs (cc_2opt_sum_kept.hip).  A restart whose pairs do not fit is left where
-// it got to, with a cost of -1; launch_2opt_sum_pruned with left_over goes on with those (N > 256: with the lists that this one made).
+// 65 <= N <= 1024, few enough restarts (launch_2opt): a workgroup per restart keeps its pairs (cc_2opt_sum_kept.hip).  A restart whose
+// pairs do not fit is left where it got to, with a cost of -1; launch_2opt_sum_pruned with left_over goes on with those (N > 256: with the
+// lists that this one made).
 hipError_t launch_2opt_sum_kept(const int32_t* c, int N, void* room, int restarts, int32_t* tours, int64_t* costs,
                                 int32_t* moves, hipStream_t s);
 bool sum_kept_leaves_restarts(int N);          // whether it may leave any
-// Partner lists of all nodes for N > 256, written into `room` (2 N^2 bytes): M entries per list, where lists and counts lie.  there:
-// they have been made, only where they lie is wanted.
+// Partner lists of all nodes for N > 256, written into `room` (2 N^2 bytes): M entries per list, where lists and counts lie.
 hipError_t launch_partner_lists(const int32_t* c, int N, void* room, int& M, const uint32_t*& lists, const uint16_t*& counts,
-                                hipStream_t s, bool there = false);
+                                hipStream_t s);
 // Segment insertions, with or without 2-opt, any 4 <= N <= 1024 (cc_local_pruned.hip); same conventions.
 // With `flags` set an exhaustive kernel is enqueued behind it, and the matrix decides which of them does the work: the other
 // one when more than `most` of the N (N - 1) costs are about the smallest of their row or (N <= 256, to_16bit) more than `most_level`
