@@ -1,5 +1,6 @@
-"""GPU parity of the pruned directed ring-sum descents: every number of wavefronts the launch chooses on both sides of its lines, ties, costs
-that hardly differ by direction, entries beyond 2^16, the orientation flip, orders that are no permutation."""
+"""GPU parity of the pruned directed ring-sum descents: every number of wavefronts the launch chooses on both sides of its lines (48, 64, 65 and 96
+with 513 restarts are beyond them, other kernels'), ties, costs that hardly differ by direction, entries beyond 2^16, a zero in every row and
+column, the orientation flip, orders that are no permutation."""
 import numpy as np
 import pytest
 import torch
@@ -17,9 +18,13 @@ def _matrices(n):
     yield "ties", random_matrix(n, n + 1, symmetric=False, lo=0, hi=4)
     yield "symmetric", random_matrix(n, n + 2, symmetric=True, lo=1, hi=3000)
     yield "beyond 2^16", random_matrix(n, n + 3, symmetric=False, lo=0, hi=(1 << 21) - 1)
+    zero = random_matrix(n, n + 4, symmetric=False, lo=1, hi=5000)
+    ring = np.random.default_rng(n).permutation(n)
+    zero[ring, np.roll(ring, 1)] = 0
+    yield "a zero in every row and column", zero
 
 
-@pytest.mark.parametrize("n,restarts", [(48, 3), (64, 5), (65, 256), (65, 257), (65, 513), (96, 512), (97, 513), (128, 3), (129, 3), (129, 300),
+@pytest.mark.parametrize("n,restarts", [(48, 3), (64, 5), (65, 256), (65, 257), (65, 513), (96, 512), (96, 513), (97, 513), (128, 3), (129, 3), (129, 300),
                                         (192, 2), (255, 257), (256, 2), (257, 2), (257, 257), (512, 1)])
 def test_every_launch(n, restarts):
     for name, c in _matrices(n):

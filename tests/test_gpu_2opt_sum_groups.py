@@ -1,5 +1,5 @@
-"""GPU parity of the pruned ring-sum descents with more wavefronts per restart than their nodes ask for: every number of wavefronts
-per restart the launches choose, entries on both sides of 2^16, ties, costs of two values."""
+"""GPU parity of the ring-sum descents with several wavefronts per restart: every number of wavefronts the launches choose, of the kernel
+that keeps pairs and of the pruned one that goes on with what it leaves, entries on both sides of 2^16, ties, costs of two values."""
 import numpy as np
 import pytest
 
@@ -32,3 +32,21 @@ def test_every_number_of_wavefronts(n, restarts):
 def test_two_restarts_per_unit_with_short_lists(n, restarts):
     """Passed candidates by entry and by place, lists so short that many nodes are scanned against every node."""
     test_every_number_of_wavefronts(n, restarts)
+
+
+@pytest.mark.parametrize("n,restarts", [(300, 513), (320, 600), (384, 513), (448, 513), (449, 513), (512, 257), (512, 513), (513, 2), (640, 257),
+                                        (768, 2), (768, 257), (769, 257), (1024, 2)])
+def test_every_number_of_wavefronts_of_what_is_left(n, restarts):
+    """Two zones of equal costs: about an eighth of all N^2 pairs stand for the first moves, 11000 at N = 300 and 33000 at N = 513, more
+    than there is room for (2000 to 4500 with several restarts per unit, 17000 with one), so every descent is left at once."""
+    say(f"pruned ring sum groups N={n} R={restarts}: descents that are left")
+    zone = np.random.default_rng(n).permutation(n) * 2 // n
+    for near, far in ((100, 1000), (1 << 16, 1 << 20)):
+        c = np.where(zone[:, None] == zone[None, :], near, far).astype(np.int32)
+        np.fill_diagonal(c, 0)
+        got = gpu_search(c, oracle.SUM, restarts, 22)
+        k = int(np.argmin(got["costs"]))
+        assert got["best_restart"] == k and got["best_cost"] == got["costs"][k]
+        for r in (0, restarts - 1):
+            costs, tours, moves = oracle.restarts(c, oracle.SUM, 22, r, r + 1)
+            assert got["costs"][r] == costs[0] and got["moves"][r] == moves[0] and np.array_equal(got["tours"][r], tours[0])

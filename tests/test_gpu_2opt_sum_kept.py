@@ -33,7 +33,8 @@ def _check(c, restarts, seed, rows, init=None):
 @pytest.mark.parametrize("n,restarts", [(65, 1), (65, 512), (79, 513), (80, 257), (80, 1024), (97, 1025), (112, 1000), (113, 1000), (127, 2048),
                                         (128, 256), (128, 257), (128, 1024), (129, 513), (176, 512), (177, 512), (192, 1536), (255, 2048),
                                         (256, 512), (256, 513), (257, 256), (320, 513), (321, 513), (512, 257), (513, 3), (640, 3), (641, 3),
-                                        (1023, 2)])
+                                        (1023, 2), (80, 1025), (97, 2049), (127, 2049), (128, 1025), (129, 2049), (176, 2049), (192, 1537),
+                                        (255, 2049), (256, 2048), (256, 2049)])
 def test_every_launch(n, restarts):
     for c, tag in ((hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n), "racks"),
                    (random_matrix(n, n, symmetric=True, lo=0, hi=4), "ties"), (_zones(n, 2), "two zones"), (_zones(n, n // 8), "racks of eight"),

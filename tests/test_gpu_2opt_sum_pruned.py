@@ -1,5 +1,6 @@
-"""GPU parity of the pruned ring-sum descents: both launch forms at the edges of their sizes, entries on both sides of
-2^16 (16-bit matrix in LDS or not), ties, rows whose partners outgrow the lists, and orders that are no permutation."""
+"""GPU parity of the ring-sum descents above N = 96: with many restarts the exhaustive kernels and the pruned one with a wavefront per
+restart; with fewer the kernel that keeps pairs and, for what that leaves, the pruned one with several.  Edges of their sizes, entries on
+both sides of 2^16 (16-bit matrix in LDS or not), ties, rows whose partners outgrow the lists, and orders that are no permutation."""
 import numpy as np
 import pytest
 import torch
@@ -21,8 +22,10 @@ def test_pruned_ring_sum_equals_the_exhaustive_sweep(n):
         assert_search_equal(gpu_search(c, oracle.SUM, restarts, n), oracle.search(c, oracle.SUM, restarts, n))
 
 
-@pytest.mark.parametrize("n,restarts", [(98, 1600), (127, 1601), (130, 700), (192, 1100)])
+@pytest.mark.parametrize("n,restarts", [(98, 1600), (127, 1601), (130, 700), (192, 1100), (98, 2050), (127, 2049), (130, 2049), (192, 3080),
+                                        (200, 2100), (255, 2049), (256, 2050)])
 def test_one_wavefront_per_restart(n, restarts):
+    """From 2049 restarts on (192: 3073); the first four sizes are below the line, a workgroup per restart."""
     for c, tag in ((random_matrix(n, n, symmetric=True, lo=1, hi=70000), "uniform, beyond 2^16"),
                    (hierarchical_matrix(n, (4, 8), ((50, 100), (200, 400), (800, 2000)), 0.3, True, n), "racks")):
         say(f"pruned ring sum N={n} R={restarts} {tag} (every 50th restart and the winner compared)")
@@ -133,10 +136,13 @@ def test_ties_do_not_bring_all_moves_back():
     assert _seconds(zones, restarts, buffers) < 1.5 * _seconds(plain, restarts, buffers)
 
 
-@pytest.mark.parametrize("n,restarts", [(97, 3), (99, 2047), (100, 1537), (128, 2), (128, 300), (192, 257), (192, 3073), (256, 257), (256, 1537)])
+@pytest.mark.parametrize("n,restarts", [(97, 3), (99, 2047), (100, 1537), (128, 2), (128, 300), (192, 257), (192, 3073), (256, 257), (256, 1537),
+                                        (65, 513), (79, 520), (96, 1025), (97, 2049), (127, 2049), (128, 1025), (128, 1500), (192, 1537),
+                                        (192, 3072), (256, 2049)])
 @pytest.mark.parametrize("hi", [65535, 65536])
 def test_sizes_with_an_exhaustive_kernel_of_16_bit_entries(n, restarts, hi):
-    """Either side of 2^16, where the two kernels that are enqueued take turns, and of the lines between them."""
+    """Either side of 2^16 and of the lines between the kernels.  The two that are enqueued take turns at 65 .. 79 from 513 restarts on, at
+    80 .. 96 and 128 from 1025 on and at 192 with 1537 to 3072; fewer are the kernel's that keeps pairs, more the pruned one's."""
     say(f"ring sum N={n} R={restarts} entries<={hi}")
     c = random_matrix(n, n, symmetric=True, lo=0, hi=hi)
     c[0, n - 1] = c[n - 1, 0] = hi
