@@ -120,8 +120,9 @@ int cc_rd_cost_batch(const int32_t* cost_matrix, int32_t N, const int32_t* perms
  * cc_rd_cost_batch with caller-provided workspace: the same costs, faster for N >= 128.  A link of round k, the two
  * ranks i and i xor 2^k, contributes max(c[x][y], c[y][x]) of its two nodes to the round's maximum; with every entry
  * below 2^16 (decided on the device) the call first writes that larger value for every pair of nodes into the
- * workspace as 16-bit entries, and then scores a link by one look-up instead of one per end.  Other matrices, and
- * N < 128, are scored as by cc_rd_cost_batch.
+ * workspace as 16-bit entries, and then scores a link by one look-up instead of one per end; at N = 512 and 1024, for
+ * any entries, it looks up only the links among the largest ones.  Other matrices, and N < 128, are scored as by
+ * cc_rd_cost_batch.
  *   workspace  device memory, 256-byte aligned, at least cc_rd_batch_workspace_bytes(N) bytes (else
  *              CC_ERR_WORKSPACE); owned by the caller, contents undefined afterwards; calls that overlap in time
  *              need workspaces of their own.
@@ -157,10 +158,10 @@ int cc_bcube_cost_batch_weighted(const int32_t* cost_matrix, int32_t N, int32_t 
 
 /*
  * cc_bcube_cost_batch / cc_bcube_cost_batch_weighted with caller-provided workspace: the same costs.  round_weights
- * may be NULL (every round weighs 1).  For base 2 with N >= 128, and for base 4 with N = 256 or 1024, the call
- * scores on a folded 16-bit copy of the matrix as cc_rd_cost_batch_ex does (an exchange between two ranks costs the
- * larger of the two directed entries, so each pair of a round needs one look-up); other cases are scored as by
- * cc_bcube_cost_batch.  workspace: as for cc_rd_cost_batch_ex, at least cc_rd_batch_workspace_bytes(N) bytes.
+ * may be NULL (every round weighs 1).  For base 2 with N >= 128, and for base 4 with N = 256, the call scores on a
+ * folded 16-bit copy of the matrix as cc_rd_cost_batch_ex does (an exchange between two ranks costs the larger of the
+ * two directed entries, so each pair of a round needs one look-up); at N = 512 and 1024 with base 2 and N = 1024 with
+ * base 4 it looks up only the exchanges among the largest entries; other cases are scored as by cc_bcube_cost_batch.  workspace: as for cc_rd_cost_batch_ex, at least cc_rd_batch_workspace_bytes(N) bytes.
  * Enqueues kernels only.
  */
 int cc_bcube_cost_batch_ex(const int32_t* cost_matrix, int32_t N, int32_t base, const int32_t* round_weights,

@@ -13,10 +13,12 @@
 //
 // What bounds it: a sweep of N^2 / 64 additions over the workgroup's wavefronts, then look-ups, 64 in a chain of LDS, L2 and a wave
 // minimum at a time.  The general kernel, which looks every move up -> this one, inverse bandwidths that are eight times as small inside a
-// rack: N = 100, 1000 restarts 3.0 -> 1.1 ms, 4000 restarts 9.1 -> 3.0; N = 150, 100 restarts 6.7 -> 1.1, 2000 restarts 19.3 -> 4.9; N = 220,
-// 500 restarts 19.8 -> 3.7; N = 256, 1000 restarts (costs beyond the exhaustive kernel's keys) 60.5 -> 7.8; N = 300, 300 restarts 39 ->
-// 6.3; N = 512, 100 restarts 78 -> 10.2.  Symmetric costs, where P is flat and hardly a move falls out by it: N = 100, 1000 restarts 3.9 -> 2.7,
-// N = 512, 100 restarts 134 -> 61.  T nearer to the last value costs sweeps that find nothing: N = 220, 500 restarts with 15/16 of it 6.8 ms,
+// rack: N = 70, 300 restarts 0.77 -> 0.39 ms; N = 100, 1000 restarts 2.7 -> 1.0, 4000 restarts 7.8 -> 2.5; N = 150, 500 restarts 6.6 -> 1.4, 2000
+// restarts 15.9 -> 4.0; N = 220, 500 restarts 16.0 -> 2.7; N = 300, 300 restarts 27 -> 4.2; N = 512, 100 restarts 54 -> 7.0; N = 1000, 16 restarts
+// 286 -> 33; N = 256, 1000 restarts (costs beyond the exhaustive kernel's keys) 60 -> 5.4.  A zero in every row and column, where the smallest
+// entries say nothing: N = 100, 1000 restarts 2.7 -> 0.95, N = 512, 100 restarts 53 -> 6.8.  Symmetric costs, where P is flat and hardly a
+// move falls out by it: N = 100, 1000 restarts 3.9 -> 2.9, N = 512, 100 restarts 134 -> 64.  Two values or two zones of equal costs: 1.3 to 9 times as
+// fast.  T nearer to the last value costs sweeps that find nothing: N = 220, 500 restarts with 15/16 of it 6.8 ms,
 // 3/4 4.7, 1/2 4.0; two values alone are the faster for it (3.9, 3/4 3.3).  The matrix as 16-bit entries in LDS gained nothing.
 #include "cc_device.h"
 #include "cc_dsum_bounds.h"
@@ -246,9 +248,10 @@ hipError_t launch(const int32_t* c, int N, bool with_flip, int restarts, int32_t
 
 hipError_t launch_2opt_dsum_pruned(const int32_t* c, int N, bool with_flip, int restarts, int32_t* tours, int64_t* costs, int32_t* moves,
                                    const int32_t* skip_if_small, int small_limit, hipStream_t s) {
-    // (4 / 8 / 16 wavefronts, with 3/4 of the last move's value as T: N = 50, 500 restarts 455 / 465 / 778 us, 2000 restarts 667 / 1092 / 2726; N = 70, 500 restarts 797 / 628 / 859; N =
-    // 100, 100 restarts 1202 / 899 / 692, 1000 restarts 1406 / 1581 / 2360; N = 150, 500 restarts 3.2 / 2.2 / 2.7 ms; N = 256, 1000 restarts
-    // 10.1 / 9.4 / 12.4; N = 300, 300 restarts - / 8.8 / 9.7; N = 400, 200 restarts - / 13.6 / 9.1; N = 512, 100 restarts - / 19.2 / 13.5)
+    // (4 / 8 / 16 wavefronts: N = 70, 100 restarts 434 / 349 / 289 us, 500 restarts 492 / 398 / 546; N = 100, 100 restarts 772 / 608 / 492, 500 restarts
+    // 808 / 677 / 912, 1000 restarts 992 / 1132 / 1697; N = 150, 100 restarts 2.0 / 1.3 / 1.0 ms, 500 restarts 2.0 / 1.4 / 1.8, 2000 restarts 3.8 / 4.0 /
+    // 6.3; N = 220, 500 restarts 4.1 / 2.7 / 3.3; N = 256, 1000 restarts 6.0 / 5.4 / 7.2; N = 300, 300 restarts - / 4.2 / 4.8; N = 400, 200
+    // restarts - / 6.4 / 4.5; N = 512, 100 restarts - / 9.8 / 7.0, 600 restarts - / 16.7 / 19.2)
     const int per_unit = (restarts + 255) / 256;
     if (N > 512 || (N > 64 && per_unit == 1)) return launch<16>(c, N, with_flip, restarts, tours, costs, moves, skip_if_small, small_limit, s);
     if (N > 128 || (N > 64 && per_unit == 2)) return launch<8>(c, N, with_flip, restarts, tours, costs, moves, skip_if_small, small_limit, s);

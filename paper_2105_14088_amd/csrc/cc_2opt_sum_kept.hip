@@ -18,8 +18,9 @@
 // (counted in a model of the algorithm on the CPU).
 //
 // What bounds it: a sweep is a chain of LDS round trips (pair, its two nodes, the second new edge, the waves' best, the move) between two
-// barriers, about 3500 clocks up to N = 256 and 7500 at N = 1000, where sixteen wavefronts also share the issue of some 100 vector
-// instructions per 64 pairs; makings are a fifth to a third (5000 clocks at N = 128, 15000 at N = 1000).  Lists of candidates laid out anew on
+// barriers: 3700 clocks at N = 100, 4000 at 128, 4900 at 256, 6000 at 512 and 7800 at 1000 with one restart per unit (4400, 4800, 6300 with four at
+// 100, 128, 256).  A sweep that makes the pairs anew takes 8200, 10100, 29900, 22900 and 32300, 15 to 27 % of the time (29 to 39 % with four restarts per unit).
+// N = 1000: 271 vector instructions per wavefront and sweep, VALU 49 % busy, wavefronts waiting for 55 % of their time.  Lists of candidates laid out anew on
 // every sweep (cc_2opt_sum_pruned.hip, cc_2opt_multi.hip) -> this one: N = 1000, 128 restarts 10.4 -> 5.2 ms; N = 512, 745 restarts 5.65 ->
 // 3.16; N = 300, 745 restarts 2.23 -> 1.41; N = 256, 200 restarts 1.22 -> 0.89, 1024 restarts 3.5 -> 1.7; N = 128, 256 restarts 0.60 -> 0.33;
 // N = 100, 32 restarts 0.37 -> 0.23.  Slower were: rows of the triangle instead of all its entries end to end (N = 128, 256 restarts 0.33 -> 0.40),

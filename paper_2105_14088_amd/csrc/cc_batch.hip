@@ -437,7 +437,8 @@ static bool ring_rows_pays(int N, int64_t B) {
 // 335 -> 102 us.  Orders of small hops only: N = 500, 65000 orders 113 -> 38 us.  An order's entries
 // reduced before the next order was looked at: two bytes a rank, N = 300, 200000 orders 75 us, now 56; N = 400, 50000 31.5, now 28.1;
 // N = 500, 65000 41.0, now 37.9; N = 700, 60000 72, now 70; N = 1000, 65000 81, now 79; slower where every hop of an order is marked and none
-// is the largest (two values and a search's results, N = 500, 65000 orders 92 -> 96, N = 300, 200000 189 -> 202).
+// is the largest (two values and a search's results, N = 500, 65000 orders 92 -> 96, N = 300, 200000 189 -> 202).  All in repeated passes over
+// the same orders; a first pass over new ones waits for the stream and gained nothing (N = 500, 65000 orders 65, now 66).
 // W consecutive ranks of an order, aligned as a rank is
 template <typename RANK, int W>
 struct Ranks;
@@ -1325,8 +1326,8 @@ __device__ __forceinline__ void lane_links(const unsigned* v, unsigned (&x)[4], 
 // 5120 at N = 1024, are then looked up exactly, each lane its first and its last one at a time, all rounds mixed, their maxima
 // formed in LDS.  A round without a marked link is looked up whole; one that has reached the matrix maximum is finished, so a
 // matrix of few values ends early, and where T is the maximum nothing is looked up at all.
-// What bounds it: N = 1024, 65536 orders keep the LDS busy for 75 % of the time (6.4 clocks per look-up of 64 random words, two
-// thirds of them bank conflicts) and the VALU for 73 % (620 instructions per order, 880 before the address was one instruction and
+// What bounds it: N = 1024, 65536 orders keep LDS (6.4 clocks per look-up of 64 random words, two thirds of them bank conflicts) and VALU
+// busy for 60 % of the time each at 2.4 GHz, 75 % in a run at 2.0 GHz that took as long (620 instructions per order, 880 before the address was one instruction and
 // the bit two); fifteen wavefronts are what fits beside the marks.  Both launches together, seeded orders, before -> now: N = 1024,
 // 65536 orders 137 -> 116 us, 1000 orders 22.0 -> 20.9; N = 512, 131072 orders 142 -> 115 us, 65536 75 -> 62 us, 8000 18.4 -> 17.0;
 // two values, 16384 orders N = 1024 87 -> 39 us, N = 512 56 -> 20; 16384 orders near a search's result as before (102 -> 101, 52.2
