@@ -26,11 +26,11 @@
 // N = 100, 32 restarts 0.37 -> 0.23.  Slower were: rows of the triangle instead of all its entries end to end (N = 128, 256 restarts 0.33 -> 0.40),
 // lists of every node in LDS up to N = 256 (0.39).
 //
-// Matrices of few values without noise, whose pairs are mostly equal, gain less or lose, by up to 2.8 times where an exhaustive kernel had
-// the matrix in LDS (before -> now, two zones: N = 100, 1000 restarts 0.15 -> 0.22 ms, 2048 restarts 0.23 -> 0.42, N = 150, 2000 restarts 0.46 ->
-// 0.70, N = 192, 1024 restarts 0.35 -> 0.98, N = 256, 1024 restarts 0.86 -> 1.5, N = 1000, 64 restarts 2.4 -> 2.8; three levels: N = 100, 1000
-// restarts 0.29 -> 0.30, N = 256, 1024 restarts 2.3 -> 1.45, 2048 restarts 3.2 -> 4.7; zones of eight: N = 256, 1024 restarts 2.1 -> 1.0).
-// Without the steps over gaps between such values, and handed over above N = 176 only: two zones, N = 100, 1000 restarts 0.26, 2048 restarts
+// Matrices of few values without noise, whose pairs are mostly equal, gain less or lose, by up to 2.7 times where an exhaustive kernel had
+// the matrix in LDS (before -> now, two zones: N = 100, 1000 restarts 0.15 -> 0.21 ms, 2048 restarts 0.23 -> 0.35, N = 150, 2000 restarts 0.46 ->
+// 0.67, N = 192, 1024 restarts 0.35 -> 0.94, N = 256, 1024 restarts 0.86 -> 1.5, N = 1000, 64 restarts 2.4 -> 2.8; three levels: N = 100, 1000
+// restarts 0.29 -> 0.28, N = 256, 1024 restarts 2.3 -> 1.2, 2048 restarts 3.2 -> 4.3; zones of eight: N = 256, 1024 restarts 2.1 -> 0.94).
+// Without the large steps over gaps between such values (N <= 256), and handed over above N = 176 only: two zones, N = 100, 1000 restarts 0.26, 2048 restarts
 // 0.87, N = 150, 2000 restarts 2.4.
 #include <type_traits>
 
@@ -46,11 +46,11 @@ namespace {
 using namespace pruned;
 
 // Above this N a descent is left to the kernel that keeps no pairs: from partner lists after so many sweeps whose pairs did not fit, or at
-// once if the first ones, those of the longest hops, do not; from the triangle, whose makings are cheap, after so many in a row, as costs
+// once if the first ones, those of the longest hops, do not; from the triangle, whose makings are cheap, after two in a row, as costs
 // of few values have them.  In a row / all and at once: racks with 3 % of noise, N = 256, 1024 restarts 1.85 / 5.7 ms, uniform costs, 2048
-// restarts 3.8 / 5.9, but racks of equal costs, 2048 restarts 4.7 / 3.3; lists, N = 300, 1500 restarts, 3 % 6.6 / 5.2, two zones 1.67 / 1.36.
+// restarts 3.8 / 5.9, but racks of equal costs, 2048 restarts 4.3 / 3.3; lists, N = 300, 1500 restarts, 3 % 6.6 / 5.2, two zones 1.67 / 1.36.
 // Below, the launch that a hand-over needs costs more than it would give.
-constexpr int kStaysMaxN = 128, kMostUnkept = 12, kMostUnkeptInARow = 1;
+constexpr int kStaysMaxN = 128, kMostUnkept = 12, kLeft = -1;
 
 // What becomes of an order that is no permutation: left as it is, taken down rank by rank, or that if no entry needs more than 16 bits.
 enum ByRank { kLeftAlone, kByRank, kByRank16 };
@@ -128,6 +128,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
     if (tid < N) t[tid] = (uint16_t)t0;
     __syncthreads();
     int sum = 0;
+    bool few = !LISTS;                                         // 24 of the first 64 ranks' hops cost the same
     {
         const int u = t[p_before], v = t[p_behind];
         const int in = mat(t0, u), out = mat(t0, v);
@@ -135,15 +136,19 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             info[t0] = make_uint4((unsigned)in, (unsigned)out, (unsigned)(u | v << 16), (unsigned)tid);
             sum = in;
         }
+        if (!LISTS && wv == 0) {
+            few = false;
+#pragma unroll
+            for (int l = 0; l < 8; ++l) few = few || __popcll(__ballot(in == __builtin_amdgcn_readlane(in, l))) >= 24;
+        }
     }
     __syncthreads();
     // An order that is no permutation (a data error) is left as it is, or taken down rank by rank below: node-wise hops would not describe it.
-    const bool search = over_waves(__ballot(tid < N && (int)info[t0].w != tid) == 0 ? 1 : 0) != 0;
+    const int start = over_waves(__ballot(tid < N && (int)info[t0].w != tid) == 0 ? few ? 2 : 1 : 0);
+    const bool search = start != 0;
 
-    constexpr int most_unkept = LISTS ? kMostUnkept : kMostUnkeptInARow;
-    int applied = 0, turn = 0, n_pairs = 0, unkept = 0;        // sweeps whose pairs did not fit, LISTS: all, else the last ones
-    int T = 0;                                                 // 0: none chosen yet
-    int had = 0;                                               // pairs of wave lane & 15 when no move was found last
+    int applied = 0, turn = 0, n_pairs = 0, unkept = 0;        // LISTS: sweeps whose pairs did not fit, else the last of them
+    int T = !LISTS && start == 2 ? 1 : 0;                      // none chosen yet; 1: costs of few values
     bool make = true, partial = false;
     int changed = 0, changed_H = 0, changed_before = kNone;    // lanes 0 .. 3: the nodes whose hops the last move changed
     const int units_per_step = 64 * WAVES / (N - 1), rest_per_step = 64 * WAVES - units_per_step * (N - 1);
@@ -230,7 +235,13 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
                 listed = listed > lists.M ? 0 : listed;
                 more = __ballot(listed > 16);
             } else {
-                if (T == 0) hi = T = looser(over_waves(-2 * wave_max(H_own)));
+                if (T >= 0) {
+                    // Costs of few values leave gaps in which no pair comes in: T takes them in large steps.  (Said by T and alpha, which are
+                    // there anyway; a word of its own, or the pairs that came in counted, took 1 to 2 % at N <= 150 with other matrices.)
+                    const int later = T == 1 ? 2 : alpha;
+                    hi = T = looser(over_waves(-2 * wave_max(H_own)));
+                    alpha = later;
+                }
                 unit = tid / (N - 1);
                 entry_in = tid - unit * (N - 1);
             }
@@ -400,7 +411,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             partial = true;
         }
         // ---- the best move of all lanes, then of all waves
-        int value, id, h_first, h_after, have;                 // have: pairs of wave lane & 15, where that found no move
+        int value, id, h_first, h_after;
         bool again;
         {
             const int h = wave_min(hi);
@@ -411,7 +422,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             }
             const int holder = (int)__builtin_ctzll(at);
             if (lane == holder)
-                group->best[turn & 1][wv] = make_int4(lo == kNone ? kNone : hi, lo, !LISTS && lo == kNone ? n_pairs : first_hop, after_hop | (partial ? 1 << 31 : 0));
+                group->best[turn & 1][wv] = make_int4(lo == kNone ? kNone : hi, lo, first_hop, after_hop | (partial ? 1 << 31 : 0));
             __syncthreads();
             const int4 b = group->best[turn & 1][min(lane & 15, WAVES - 1)];
             int v = b.x;
@@ -430,25 +441,19 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
             h_first = __builtin_amdgcn_readlane(b.z, w);
             h_after = __builtin_amdgcn_readlane(b.w, w) & 0x7fffffff;
             again = __ballot(b.w < 0) != 0;
-            have = b.z;
         }
         ++turn;
         partial = false;
         if (value == kNone && T == -1) break;
         if constexpr (LISTS) {                                  // (N is above it; without the comparison N = 1000 takes 1 % longer)
-            if (again && N > kStaysMaxN && (unkept += turn == 1 ? most_unkept + 1 : 1) > most_unkept) break;
-        } else {
-            unkept = again ? unkept + 1 : 0;
-            if (N > kStaysMaxN && unkept > most_unkept) break;
+            if (again && N > kStaysMaxN && (unkept += turn == 1 ? kMostUnkept + 1 : 1) > kMostUnkept) break;
+        } else if (again && N > kStaysMaxN) {
+            const bool in_a_row = unkept == turn - 1 && turn > 1;
+            unkept = in_a_row ? kLeft : turn;
+            if (in_a_row) break;
         }
         if (value == kNone) {                                   // no move is worth T
             T = looser(T);
-            if constexpr (!LISTS) {
-                // Costs of few values leave gaps: where the last making brought no pair in, T goes on to where some may
-                if (__ballot(have != had) == 0 && __ballot(have * WAVES > N) != 0)
-                    for (int i = 0; i < 4; ++i) T = looser(T);
-                had = have;
-            }
             make = true;
             continue;
         }
@@ -534,7 +539,7 @@ __device__ __forceinline__ void descend_kept(const MAT mat, int N, const Partner
     for (int i = 0; i < WAVES; ++i) sum += group->word[i];
     if (tid < N) tour[tid] = (int)t[tid];
     if (tid == 0) {
-        *cost_out = unkept > most_unkept && (LISTS || N > kStaysMaxN) ? -1 : (int64_t)sum;
+        *cost_out = (LISTS ? unkept > kMostUnkept : unkept == kLeft) ? -1 : (int64_t)sum;
         *moves_out = applied;
     }
 }

@@ -78,7 +78,7 @@ def _racks(n, noise):
 
 @pytest.mark.parametrize("n,restarts", [(65, 512), (100, 2048), (128, 1024), (129, 2048), (150, 2000), (176, 512), (200, 1000), (256, 2048), (300, 700)])
 def test_few_values_and_little_noise(n, restarts):
-    """Gaps that T is taken over, pairs that do not fit now and then or sweep after sweep, descents handed over with moves applied."""
+    """Gaps that T is taken over in large steps, pairs that do not fit now and then or sweep after sweep, descents handed over with moves applied."""
     for c, tag in ((_levels(n), "three levels"), (_racks(n, 0.03), "3 % of noise"), (random_matrix(n, n, symmetric=True, lo=0, hi=1), "0 and 1"),
                    (_zones(n, 2), "two zones")):
         say(f"kept ring sum N={n} R={restarts} {tag}")
